@@ -2,7 +2,8 @@
 
 torch is used for device memory and streams; every arithmetic step runs in the
 HIP kernels behind the C ABI.  There is no CPU fallback: if the library is not
-built, loading raises.
+built, loading raises.  The calls a program makes per batch go through the
+extension module _sig_torch (csrc/sig_torch.cpp), the others through ctypes.
 """
 import ctypes
 import os
@@ -109,6 +110,27 @@ def load():
     return lib
 
 
+_torch_lib = None
+
+
+def torch_lib():
+    """The native marshalling module, with the default context set in it (built first only if it does not exist)."""
+    global _torch_lib
+    if _torch_lib is None:
+        load()
+        try:
+            from . import _sig_torch
+        except ImportError:
+            if os.path.exists(os.path.join(HERE, "_sig_torch.so")):
+                raise
+            from . import build as _build
+            _build.build()
+            from . import _sig_torch
+        _sig_torch.set_default_ctx(default_ctx())
+        _torch_lib = _sig_torch
+    return _torch_lib
+
+
 # ---------------------------------------------------------------- thin wrappers, one per C entry point
 def sig_size(d, depth):
     return int(load().sig_size(int(d), int(depth)))
@@ -184,11 +206,11 @@ def _stream_handle(stream):
 
 def sig_compute(ctx, path, depth, stream_flag, out, stream=None, plan=None):
     """Raw call: `path` [B, L, d] and `out` are contiguous float32 torch tensors on the GPU.  Returns the status."""
+    if plan is None:
+        return (_torch_lib or torch_lib()).compute(ctx, path, depth, stream_flag, out, stream)
     B, L, d = path.shape
     args = [ctx, ctypes.c_void_p(path.data_ptr()), B, L, d, int(depth), int(stream_flag),
             ctypes.c_void_p(out.data_ptr())]
-    if plan is None:
-        return load().sig_compute(*args, _stream_handle(stream))
     return load().sig_compute_planned(*args, ctypes.byref(plan), _stream_handle(stream))
 
 
@@ -221,17 +243,12 @@ def bind_compute(ctx, path, depth, stream_flag, out, stream=None, plan=None):
 
 
 def sig_combine(ctx, a, b, d, depth, out, stream=None):
-    return load().sig_combine(ctx, ctypes.c_void_p(a.data_ptr()), ctypes.c_void_p(b.data_ptr()),
-                              a.shape[0], int(d), int(depth), ctypes.c_void_p(out.data_ptr()),
-                              _stream_handle(stream))
+    return (_torch_lib or torch_lib()).combine(ctx, a, b, d, depth, out, stream)
 
 
 def sig_backward(ctx, path, depth, stream_flag, out, grad_out, grad_path, stream=None):
     """Raw call: gradient with respect to `path` given the forward result `out` and d(loss)/d(out)."""
-    B, L, d = path.shape
-    return load().sig_backward(ctx, ctypes.c_void_p(path.data_ptr()), B, L, d, int(depth), int(stream_flag),
-                               ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(grad_out.data_ptr()),
-                               ctypes.c_void_p(grad_path.data_ptr()), _stream_handle(stream))
+    return (_torch_lib or torch_lib()).backward(ctx, path, depth, stream_flag, out, grad_out, grad_path, stream)
 
 
 def bind_backward(ctx, path, depth, stream_flag, out, grad_out, grad_path, stream=None):
@@ -294,6 +311,8 @@ def default_ctx():
 
 def signature(path, depth, stream=False, plan=None, ctx=None, out=None):
     """Depth-`depth` signatures of `path` (float32 CUDA tensor [B, L, d]); allocates the output with torch."""
+    if plan is None and ctx is None and out is None:
+        return (_torch_lib or torch_lib()).signature(path, depth, stream)
     import torch
     if not path.is_cuda or path.dtype != torch.float32:
         raise ValueError("path must be a float32 tensor on the GPU")

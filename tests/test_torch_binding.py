@@ -1,0 +1,68 @@
+"""The native torch binding (csrc/sig_torch.cpp): what it refuses, and the autograd node's bookkeeping.
+
+Results of the layer are checked against the oracle elsewhere (test_gpu_training_step.py, test_gpu_backward.py); here the
+gradient only has to be the one sig_backward gives, bit for bit: the node calls the same kernels on the same values.
+"""
+import pytest
+import torch
+
+from paper_2501_08455_amd import autograd, binding
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("make", [lambda: torch.zeros(2, 5, 3), lambda: torch.zeros(2, 5, 3, dtype=torch.float64, device="cuda"),
+                                  lambda: torch.zeros(5, 3, device="cuda")])
+@pytest.mark.parametrize("call", [binding.signature, autograd.signature])
+def test_signature_refuses_what_it_cannot_read(make, call):
+    with pytest.raises(ValueError):
+        call(make(), 2)
+
+
+@pytest.mark.gpu
+def test_library_errors_keep_their_type():
+    with pytest.raises(binding.SigError) as e:
+        binding.signature(torch.zeros(2, 1, 3, device="cuda"), 2)   # one point has no increment
+    assert e.value.status == binding.SIG_ERR_INVALID
+    with pytest.raises(binding.SigError) as e:
+        binding.signature(torch.zeros(2, 4, 3, device="cuda"), 64)
+    assert e.value.status == binding.SIG_ERR_TOO_LARGE
+    path = torch.zeros(1, 2, 257, device="cuda", requires_grad=True)   # the gradient takes up to 256 channels
+    out = autograd.signature(path, 1)
+    with pytest.raises(binding.SigError) as e:
+        out.sum().backward()
+    assert e.value.status == binding.SIG_ERR_UNSUPPORTED
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("stream", [False, True])
+@pytest.mark.parametrize("layout", ["plain", "transposed", "expanded gradient"])
+def test_gradient_is_the_librarys(stream, layout):
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    base = torch.randn(7, 33, 3, device="cuda", generator=gen).cumsum(1) * 0.1
+    path = base.transpose(1, 2).contiguous().transpose(1, 2) if layout == "transposed" else base.clone()
+    path.requires_grad_(True)
+    out = autograd.signature(path, 3, stream=stream)
+    assert out.grad_fn is not None and torch.equal(out.detach(), binding.signature(base, 3, stream=stream))
+    g = torch.full((), 0.5, device="cuda").expand(out.shape) if layout == "expanded gradient" else torch.randn(
+        out.shape, device="cuda", generator=gen)
+    (grad,) = torch.autograd.grad(out, path, g, retain_graph=True)
+    want = torch.empty_like(base)
+    assert binding.sig_backward(binding.default_ctx(), base, 3, int(stream), out.detach(), g.contiguous(), want) == binding.SIG_OK
+    assert torch.equal(grad, want)
+    torch.autograd.grad(out, path, g)   # the graph was kept once; now it is freed
+    with pytest.raises(RuntimeError):
+        torch.autograd.grad(out, path, g)
+
+
+@pytest.mark.gpu
+def test_saved_tensors_are_watched_and_untracked_calls_keep_no_graph():
+    path = torch.randn(4, 9, 2, device="cuda").cumsum(1)
+    assert not autograd.signature(path, 3).requires_grad
+    path.requires_grad_(True)
+    with torch.no_grad():
+        assert not autograd.signature(path, 3).requires_grad
+    out = autograd.signature(path, 3)
+    with torch.no_grad():
+        path.add_(1.0)
+    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+        out.sum().backward()
