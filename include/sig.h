@@ -221,20 +221,23 @@ int sig_combine(sig_ctx *ctx, const float *a, const float *b, int64_t B, int d, 
  *                read only (the sweep starts from the final signature and undoes one increment at a time)
  *   grad_out     DEVICE, float32, d(loss)/d(out), same shape as out, read only
  *   grad_path    DEVICE, float32 [B][L][d], fully overwritten; must not overlap the inputs
- * Same conventions and status codes as sig_compute (B == 0 returns SIG_OK and launches nothing).  Shapes with a
- * compiled register kernel (see sig_backward_available) whose paths fit its LDS staging take it.
- * Few long paths (fewer workgroups than compute units, from 128 increments on; from 512, and mostly up to 32
- * paths, for shapes with at most 32 lanes per path) and paths too long for that staging are cut into up to 32
- * time segments that are swept by different workgroups: by Eq. 3 a segment can start from the signature of the
- * path up to its end and the gradient with respect to it, which a scan over the segments' own signatures provides.
- * Stream mode is cut the same way at smaller batches (two sweeps per segment and a scan over the segments between
+ * Same conventions and status codes as sig_compute (B == 0 returns SIG_OK and launches nothing).
+ * Final mode: two to twenty channels at depth 2, to 16 at depth 3, 10 at depth 4, 6 at depth 5 and 4 at depth 6 are swept
+ * on Lie brackets (one launch, no scratch, any length): several paths per wavefront, or one path per workgroup with its
+ * steps cut into chunks, or (few long paths) into up to 32 stretches swept by different workgroups.  Paths of a dozen
+ * points or so at depth 4 and above (up to 70 at (4,6)) and every other shape are swept on the signature itself, as below.
+ * The other sweeps start from the signature at the end and undo one increment at a time.  Shapes with a compiled register
+ * kernel (see sig_backward_available) whose paths fit its LDS staging take it.  Few long paths and paths too long for that
+ * staging are cut into up to 32 time segments that are swept by different workgroups: by Eq. 3 a segment can start from the
+ * signature of the path up to its end and the gradient with respect to it, which a scan over the segments' own
+ * signatures provides.  Stream mode is cut the same way (two sweeps per segment and a scan over the segments between
  * them; the upstream gradient is read twice); paths too long for the staging in a batch that fills the chip, or too
  * long even for 32 segments, are walked in tiles of 256 increments by one workgroup; so are, in a batch that fills
  * the chip, paths that fit the staging only a few at a time (kernels with 16 lanes per path or more; those with fewer
  * are cut in time inside the workgroup there, as for few paths, unless the plain sweep still keeps enough lanes busy).
- * Which sweep a call takes never changes its result beyond the rounding order.  Every shape
- * without a register kernel, d <= 256, takes a general sweep, one workgroup per path with its state in LDS or
- * device scratch (much slower); SIG_ERR_UNSUPPORTED only for d > 256.
+ * Which sweep a call takes never changes its result beyond the rounding order.  Every shape without any of these
+ * kernels, d <= 256, takes a general sweep, one workgroup per path with its state in LDS or device scratch (much
+ * slower); SIG_ERR_UNSUPPORTED only for d > 256.
  * Context scratch (allocated on first use, SIG_ERR_ALLOC if that fails): shapes whose index space is cut into more
  * sub-trees than one workgroup has threads, and paths walked in tiles, keep per-workgroup sums
  * (B * ceil(d^p / 256) * (L-1) * d floats); the
@@ -245,13 +248,14 @@ int sig_combine(sig_ctx *ctx, const float *a, const float *b, int64_t B, int d, 
 int sig_backward(sig_ctx *ctx, const float *path, int64_t B, int64_t L, int d, int depth, int stream_flag,
                  const float *out, const float *grad_out, float *grad_path, void *hip_stream);
 
-/* 1 if sig_backward has a compiled register kernel for (d, depth), 0 if it would take the general sweep.  Host only. */
+/* 1 if sig_backward has a compiled register kernel for (d, depth), 0 if stream mode would take the general sweep (final
+ * mode has its own compiled shapes, see sig_backward).  Host only. */
 int sig_backward_available(int d, int depth);
 
 /*
  * How sig_backward would sweep this shape.  Host only; ctx may be NULL (a device with 256 compute units is assumed).
- * Returns the number of time segments the sweep is cut into across workgroups (2 .. 32), 1 for the uncut register
- * sweep, 0 for the general sweep, or minus the SIG_ERR_* status with which sig_backward would reject the arguments.
+ * Returns the number of time segments the sweep may be cut into across workgroups (2 .. 32; final-mode sweeps on brackets
+ * pack whole paths instead where that is faster), 1 for an uncut sweep, 0 for shapes without a register kernel, or minus the SIG_ERR_* status with which sig_backward would reject the arguments.
  */
 int sig_backward_segments(const sig_ctx *ctx, int64_t B, int64_t L, int d, int depth, int stream_flag);
 

@@ -1091,6 +1091,11 @@ int sig_backward(sig_ctx *ctx, const float *path, int64_t B, int64_t L, int d, i
     if (rc != SIG_OK) return rc;
     if (B == 0) return SIG_OK;
     if (!path || !out || !grad_out || !grad_path) return SIG_ERR_INVALID;
+    if (!stream_flag && bracket_wanted(d, depth, L)) {
+        const int segs = bracket_segments(d, depth, B, L, ctx->num_cu);
+        hipError_t eb = launch_bracket(path, out, grad_out, grad_path, B, L, d, depth, segs, ctx->num_cu, (hipStream_t)hip_stream);
+        return eb == hipSuccess ? SIG_OK : SIG_ERR_HIP;
+    }
     const bool fits = backward_available(d, depth) && backward_fits(d, depth, L);
     if (backward_available(d, depth)) {
         // few long paths (or paths too long for the LDS of the uncut sweep): the sweep cut in time across workgroups
@@ -1132,6 +1137,7 @@ int sig_backward_segments(const sig_ctx *ctx, int64_t B, int64_t L, int d, int d
     const int rc = check_shape(B, L, d, depth, stream_flag, &rs);
     if (rc != SIG_OK) return -rc;
     if (!backward_available(d, depth)) return backward_general_available(d) ? 0 : -SIG_ERR_UNSUPPORTED;
+    if (!stream_flag && bracket_wanted(d, depth, L)) return bracket_segments(d, depth, B, L, ctx ? ctx->num_cu : kDefaultCUs);
     const bool fits = backward_fits(d, depth, L);
     if (B > 0) {
         const int segs = backward_segments(d, depth, B, L, ctx ? ctx->num_cu : kDefaultCUs, fits, stream_flag);

@@ -224,13 +224,12 @@ extern __shared__ float sig_backward_smem[];
 constexpr int kTiledSteps = 256;
 
 // Register sweep: the d^P lanes of a path fit a workgroup, which takes `groups` paths side by side.
-// SEG (final mode): the sweep is cut in time and the workgroup takes `groups` (path, segment) pieces instead, piece
+// SEG (stream mode): the sweep is cut in time and the workgroup takes `groups` (path, segment) pieces instead, piece
 // = b * segs + s; every piece is swept as seg_steps increments (the last segment of a path is filled up with zero
-// increments behind its end, which leave the signature and the adjoint as they are), starts from the rows
-// seg_sig / seg_grad (see BackwardArgs) and leaves its sums over the increments in seg_part.
-// SEG in stream mode: a piece starts from the output row at its end (row k of a stream output is the signature of
+// increments behind its end, which leave the signature and the adjoint as they are) and leaves its sums over the
+// increments in seg_part.  It starts from the output row at its end (row k of a stream output is the signature of
 // the path up to increment k) and from the gradient seg_grad that the later pieces leave there, and adds the
-// upstream gradients of its own rows as it goes.  EMIT = false is the first of the two sweeps that provide seg_grad:
+// upstream gradients of its own rows as it goes.  (Final mode comes here with short paths only, see bracket_min_points.)  EMIT = false is the first of the two sweeps that provide seg_grad:
 // from a zero adjoint, without sums over the increments; it writes what the piece's own rows leave at its start to
 // seg_adj_out (the lanes' partial adjoints of a prefix word are added up there).
 // TSV: steps whose partial sums are parked before they are added up; 0 = reduce_steps, the most that is useful.
@@ -242,7 +241,8 @@ template <int d, int N, int P, bool STREAM, bool SEG = false, bool EMIT = true, 
 __global__ __launch_bounds__(256) void sig_backward_kernel(BackwardArgs A)
 {
     static_assert(!PIPE || (STREAM && !SEG), "the pipelined fetch belongs to the uncut stream sweep");
-    static_assert(EMIT || (STREAM && SEG), "the sweep without output belongs to the stream-mode cut");
+    static_assert(STREAM || !SEG, "final mode is not cut here");
+    static_assert(EMIT || SEG, "the sweep without output belongs to the cut");
     using Sh = Shape<d, N, P>;
     constexpr int Q = Sh::Q;
     constexpr int D = Sh::D;
@@ -300,15 +300,13 @@ __global__ __launch_bounds__(256) void sig_backward_kernel(BackwardArgs A)
     identity_state<d, N, P>(ad);
     if (P == 0) ad.s[0] = 0.0f;
     if (active) {
-        const bool inner = SEG && seg < W - 1;   // a segment that ends inside the path
-        if constexpr (STREAM && SEG) {
+        if constexpr (SEG) {
             const int64_t last = k0 + K < Kall ? k0 + K - 1 : Kall - 1;   // last increment of the piece
             load_state<d, N, P>(A.sig + (b * Kall + last) * D, u, ln);
             if constexpr (EMIT) load_adjoint<d, N, P, false>(A.seg_grad + piece * D, u, ad);
         } else {
-            const float *srow = STREAM ? A.sig + (b * K + (K - 1)) * D : inner ? A.seg_sig + piece * D : A.sig + b * D;
-            load_state<d, N, P>(srow, u, ln);
-            if constexpr (!STREAM) load_adjoint<d, N, P, false>(inner ? A.seg_grad + piece * D : A.grad_out + b * D, u, ad);
+            load_state<d, N, P>(STREAM ? A.sig + (b * K + (K - 1)) * D : A.sig + b * D, u, ln);
+            if constexpr (!STREAM) load_adjoint<d, N, P, false>(A.grad_out + b * D, u, ad);
         }
     }
     __syncthreads();
@@ -508,12 +506,11 @@ __global__ __launch_bounds__(256) void sig_backward_kernel(BackwardArgs A)
     }
 }
 
-// Register sweep over paths whose increments do not fit LDS at once: the workgroup walks the A.segs tiles of
+// Register sweep (stream mode) over paths whose increments do not fit LDS at once: the workgroup walks the A.segs tiles of
 // A.seg_steps increments of its `groups` paths one after the other, last first, with the lane states in registers,
 // and leaves the sums over the increments in seg_part ([B][L-1][d]); another launch forms d(loss)/dX.  Sequential in
-// time like the plain sweep (no chunks), but any length fits.  Stream mode fetches a row's upstream gradient one
-// step ahead.
-template <int d, int N, int P, bool STREAM>
+// time like the plain sweep (no chunks), but any length fits.
+template <int d, int N, int P>
 __global__ __launch_bounds__(256) void sig_backward_tiled_kernel(BackwardArgs A)
 {
     using Sh = Shape<d, N, P>;
@@ -547,9 +544,9 @@ __global__ __launch_bounds__(256) void sig_backward_tiled_kernel(BackwardArgs A)
     float *mypark = park + (size_t)gi * TS * Pk::kStepFloats;
     float *myrow = tile + gi * row_stride;
 
-    // Stream mode: the upstream rows of a tile are fetched PD steps ahead into registers, as in the plain sweep; every
+    // The upstream rows of a tile are fetched PD steps ahead into registers, as in the plain sweep; every
     // tile starts with its first PD rows, asked for before its increments are staged.
-    constexpr int PD = !STREAM ? 1 : Sh::SZ <= 24 ? 4 : Sh::SZ <= 48 ? 2 : 1;
+    constexpr int PD = Sh::SZ <= 24 ? 4 : Sh::SZ <= 48 ? 2 : 1;
     Lane<d, N, P> ln, ad, up[PD];
     identity_state<d, N, P>(ln);
     identity_state<d, N, P>(ad);
@@ -558,22 +555,17 @@ __global__ __launch_bounds__(256) void sig_backward_tiled_kernel(BackwardArgs A)
         if (P == 0) up[decltype(jc)::value].s[0] = 0.0f;
     });
     if (P == 0) ad.s[0] = 0.0f;
-    if (active) {
-        load_state<d, N, P>(STREAM ? A.sig + (b * Kall + (Kall - 1)) * D : A.sig + b * D, u, ln);
-        if constexpr (!STREAM) load_adjoint<d, N, P, false>(A.grad_out + b * D, u, ad);
-    }
+    if (active) load_state<d, N, P>(A.sig + (b * Kall + (Kall - 1)) * D, u, ln);
 
     for (int tl = A.segs - 1; tl >= 0; --tl) {
         const int64_t k0 = (int64_t)tl * T;
         const int64_t K = Kall - k0 < T ? Kall - k0 : T;
         const int row_floats = (int)K * d;
-        if constexpr (STREAM) {
-            static_for<0, PD>([&](auto jc) __attribute__((always_inline)) {
-                constexpr int j = decltype(jc)::value;
-                if (active && K - 1 - j >= 0)
-                    load_adjoint<d, N, P, false, false>(A.grad_out + (b * Kall + (k0 + K - 1 - j)) * D, u, up[j]);
-            });
-        }
+        static_for<0, PD>([&](auto jc) __attribute__((always_inline)) {
+            constexpr int j = decltype(jc)::value;
+            if (active && K - 1 - j >= 0)
+                load_adjoint<d, N, P, false, false>(A.grad_out + (b * Kall + (k0 + K - 1 - j)) * D, u, up[j]);
+        });
         if (tl != A.segs - 1) __syncthreads();   // the previous tile's sums have been written out
         for (int i = tid; i < G * row_floats; i += nthr) {
             const int g2 = i / row_floats;
@@ -592,11 +584,9 @@ __global__ __launch_bounds__(256) void sig_backward_tiled_kernel(BackwardArgs A)
             const int64_t k = kk - j;
             if (k < 0) return;
             const int ts = (int)((K - 1 - k) % TS);
-            if constexpr (STREAM) {
-                add_row<d, N, P>(ad, up[j], owner);
-                if (active && k - PD >= 0)
-                    load_adjoint<d, N, P, false, false>(A.grad_out + (b * Kall + (k0 + k - PD)) * D, u, up[j]);
-            }
+            add_row<d, N, P>(ad, up[j], owner);
+            if (active && k - PD >= 0)
+                load_adjoint<d, N, P, false, false>(A.grad_out + (b * Kall + (k0 + k - PD)) * D, u, up[j]);
             Inc<d, P> inc, neg;
             load_inc<d, P>(inc, myrow + k * d, letter);
 #pragma unroll
@@ -664,17 +654,16 @@ constexpr int chunk_row_floats()  // one chunk's row in either LDS buffer of the
 }
 
 template <int d, int N, int P>
-int64_t backward_chunked_lds_bytes(int64_t L, int chunks, int stream_flag)
+int64_t backward_chunked_lds_bytes(int64_t L, int chunks)
 {
     const int64_t tile = ((L - 1) * d + 3) / 4 * 4;
-    int64_t per_chunk = 2 * (int64_t)chunk_row_floats<d, N, P>();
-    if (stream_flag) per_chunk += private_floats<d, N, P>();
+    const int64_t per_chunk = 2 * (int64_t)chunk_row_floats<d, N, P>() + private_floats<d, N, P>();
     return (tile + chunks * per_chunk) * (int64_t)sizeof(float);
 }
 
 // chunks of at least eight increments that one workgroup of `threads` threads sweeps side by side (1: it does not cut)
 template <int d, int N, int P>
-int backward_chunks(int64_t L, int stream_flag, int threads)
+int backward_chunks(int64_t L, int threads)
 {
     int C = threads / Shape<d, N, P>::Q;
     if (C > (L - 1) / 8) C = (int)((L - 1) / 8);
@@ -684,7 +673,7 @@ int backward_chunks(int64_t L, int stream_flag, int threads)
     int cap = 8;
     while ((int64_t)(cap + 1) * (cap + 1) <= L - 1) ++cap;
     if (C > cap) C = cap;
-    while (C > 1 && backward_chunked_lds_bytes<d, N, P>(L, C, stream_flag) > kMaxLdsBytes) --C;
+    while (C > 1 && backward_chunked_lds_bytes<d, N, P>(L, C) > kMaxLdsBytes) --C;
     return C < 1 ? 1 : C;
 }
 

@@ -100,21 +100,17 @@ __device__ __forceinline__ void load_private(const float *buf, unsigned u, Lane<
     for (int i = 0; i < Sh::NPRE; ++i) x.pre[i] = buf[(Sh::SZ + i) * Sh::Q + u];
 }
 
-// The sweep cut in time: one workgroup per path, C chunks of T increments side by side.
+// The sweep cut in time (stream mode): one workgroup per path, C chunks of T increments side by side.
 //   1. every chunk folds its increments from the identity: its own signature E_c                (T steps)
 //   2. a scan from the left gives every prefix S_end(c) = E_0 (x) ... (x) E_c; the workgroup shares each product
-//   3. the adjoint A_end(c) at the end of every chunk:
-//      final mode  - a scan from the right gives X_c = E_{c+1} (x) ... (x) E_{C-1}, and every chunk pulls the
-//                    upstream gradient back through X_c on its own                               (C products)
-//      stream mode - a first sweep of every chunk from a zero adjoint gives what its own rows leave at its
-//                    start; the lanes of chunk 0 then walk the chunks from the last to the first   (T steps, C products)
+//   3. the adjoint A_end(c) at the end of every chunk: a first sweep of every chunk from a zero adjoint gives what its own
+//      rows leave at its start; the lanes of chunk 0 then walk the chunks from the last to the first  (T steps, C products)
 //   4. every chunk runs the reverse sweep over its own increments from (S_end(c), A_end(c))       (T steps)
-// so the critical path is about 2 T (stream: 3 T) steps and 2 C short products instead of C T steps.
-// PIPE (stream mode): the fetch of the upstream rows as a software pipeline, see sig_backward_kernel.
-template <int d, int N, int P, bool STREAM, bool PIPE = false>
+// so the critical path is about 3 T steps and 2 C short products instead of C T steps.
+// PIPE: the fetch of the upstream rows as a software pipeline, see sig_backward_kernel.
+template <int d, int N, int P, bool PIPE = false>
 __global__ __launch_bounds__(256) void sig_backward_chunked_kernel(BackwardArgs A)
 {
-    static_assert(!PIPE || STREAM, "the pipelined fetch belongs to stream mode");
     using Sh = Shape<d, N, P>;
     constexpr int Q = Sh::Q;
     constexpr int D = Sh::D;
@@ -143,8 +139,8 @@ __global__ __launch_bounds__(256) void sig_backward_chunked_kernel(BackwardArgs 
 
     float *tile = sig_backward_smem;                 // [K][d] increments, later their gradients
     float *rowsE = tile + (K * d + 3) / 4 * 4;       // [C][ROW] chunk signatures, later the parked partial sums
-    float *rowsS = rowsE + C * ROW;                  // [C][ROW] prefixes S_end(c), then (final mode) the X_c
-    float *rowsA = rowsS + C * ROW;                  // stream mode: [C][private_floats] adjoints, lane layout
+    float *rowsS = rowsE + C * ROW;                  // [C][ROW] prefixes S_end(c)
+    float *rowsA = rowsS + C * ROW;                  // [C][private_floats] adjoints, lane layout
     for (int i = tid; i < K * d; i += nthr) {
         const float *x = A.path + b * A.L * d + i;
         tile[i] = x[d] - x[0];
@@ -175,16 +171,16 @@ __global__ __launch_bounds__(256) void sig_backward_chunked_kernel(BackwardArgs 
     __syncthreads();
     // The sweep of this lane's chunk from (ln, ad) = (S_end(c), A_end(c)), t = T-1 .. 0 for every chunk alike
     // (chunks with fewer increments idle in the surplus iterations).  EMIT: the partial sums of d(loss)/d(dX) are
-    // parked in rowsE, added up and written over the increments.  Stream mode adds row k's upstream gradient
+    // parked in rowsE, added up and written over the increments.  Row k's upstream gradient is added
     // before step k; the rows are fetched PD steps ahead (see the unchunked kernel).
     float *mypark = rowsE + c * ROW;
     using Pk = Park<d, P>;
-    constexpr int PD = !STREAM ? 1 : Sh::SZ <= 24 ? 4 : Sh::SZ <= 48 ? 2 : 1;
+    constexpr int PD = Sh::SZ <= 24 ? 4 : Sh::SZ <= 48 ? 2 : 1;
     const PrefixOwner<d, N, P> owner(u);
     auto sweep = [&](auto emit_tag) __attribute__((always_inline)) {
         constexpr bool EMIT = decltype(emit_tag)::value;
         Lane<d, N, P> up[PD];
-        // Stream mode: the upstream rows of the chunk, one fetch per step in the order of the sweep, PD steps
+        // The upstream rows of the chunk, one fetch per step in the order of the sweep, PD steps
         // ahead and without conditions (see the PIPE sweep of sig_backward_kernel): row min(c T + max(t, 0), K - 1)
         // for t = T - 1, T - 2, ...; rows of steps that the chunk does not have are fetched and not used.
         const int top = c * T + T - 1 < K - 1 ? c * T + T - 1 : K - 1;
@@ -195,19 +191,17 @@ __global__ __launch_bounds__(256) void sig_backward_chunked_kernel(BackwardArgs 
             next_row -= (tn > 0 && c * T + tn <= K - 1) ? D : 0;
             --tn;
         };
-        if constexpr (STREAM) {
-            static_for<0, PD>([&](auto jc) __attribute__((always_inline)) {
-                constexpr int j = decltype(jc)::value;
-                identity_state<d, N, P>(up[j]);
-                if constexpr (PIPE) {
-                    fetch(up[j]);
-                } else {
-                    const int t = T - 1 - j;
-                    if (t >= 0 && t < steps)
-                        load_adjoint<d, N, P, false, false>(A.grad_out + (b * K + (c * T + t)) * D, u, up[j]);
-                }
-            });
-        }
+        static_for<0, PD>([&](auto jc) __attribute__((always_inline)) {
+            constexpr int j = decltype(jc)::value;
+            identity_state<d, N, P>(up[j]);
+            if constexpr (PIPE) {
+                fetch(up[j]);
+            } else {
+                const int t = T - 1 - j;
+                if (t >= 0 && t < steps)
+                    load_adjoint<d, N, P, false, false>(A.grad_out + (b * K + (c * T + t)) * D, u, up[j]);
+            }
+        });
         // one step of the sweep; `refill` runs between the arithmetic and the parked sums (the plain fetch of the
         // row that replaces `row`)
         auto one = [&](int t, const Lane<d, N, P> &row, auto refill) __attribute__((always_inline)) {
@@ -217,7 +211,7 @@ __global__ __launch_bounds__(256) void sig_backward_chunked_kernel(BackwardArgs 
             for (int a = 0; a < d; ++a) dbar[a] = 0.0f;
             if (t < steps) {
                 const int k = c * T + t;
-                if constexpr (STREAM) add_row<d, N, P>(ad, row, owner);
+                add_row<d, N, P>(ad, row, owner);
                 Inc<d, P> inc, neg;
                 load_inc<d, P>(inc, tile + k * d, letter);
 #pragma unroll
@@ -274,11 +268,9 @@ __global__ __launch_bounds__(256) void sig_backward_chunked_kernel(BackwardArgs 
                     const int t = t0 - j;
                     if (t >= 0) {
                         one(t, up[j], [&]() __attribute__((always_inline)) {
-                            if constexpr (STREAM) {
-                                const int tnext = t - PD;
-                                if (tnext >= 0 && tnext < steps)
-                                    load_adjoint<d, N, P, false, false>(A.grad_out + (b * K + (c * T + tnext)) * D, u, up[j]);
-                            }
+                            const int tnext = t - PD;
+                            if (tnext >= 0 && tnext < steps)
+                                load_adjoint<d, N, P, false, false>(A.grad_out + (b * K + (c * T + tnext)) * D, u, up[j]);
                         });
                     }
                 });
@@ -288,60 +280,39 @@ __global__ __launch_bounds__(256) void sig_backward_chunked_kernel(BackwardArgs 
 
     identity_state<d, N, P>(ad);
     if (P == 0) ad.s[0] = 0.0f;
-    if constexpr (!STREAM) {
-        // 3. the adjoint at the end of chunk c is the upstream gradient pulled back through everything after
-        //    the chunk: A_end(c) = transpose of (. (x) X_c) applied to d(loss)/d(out), X_c = E_{c+1} (x) ... (x)
-        //    E_{C-1}.  The X_c are a scan from the right (X_{C-1} is the identity: a row of zeros); then every
-        //    chunk pulls the gradient back on its own.
-        for (int x = tid; x < D; x += nthr) rowsS[(C - 1) * ROW + x] = 0.0f;
-        __syncthreads();
+    // Every row has its own upstream gradient, so what reaches the end of chunk c from the later
+    // chunks is r_{c+1} + transpose of (. (x) E_{c+1}) applied to A_end(c+1), where r_c is what chunk c's own
+    // rows leave at its start.
+    // 3a. a first sweep from a zero adjoint, without output, gives r_c
+    sweep(std::false_type{});
+    if (active) store_private<d, N, P>(rowsA + c * private_floats<d, N, P>(), u, ad);
+    __syncthreads();
+    // 3b. the lanes of chunk 0 walk the chunks from the last to the first: A_end(c-1) = r_c + pull-back of
+    //     A_end(c) through E_c; A_end(c) takes r_c's place in LDS
+    if (active && c == 0) {
+        Lane<d, N, P> run, r;
+        identity_state<d, N, P>(run);
+        if (P == 0) run.s[0] = 0.0f;
         for (int c2 = C - 1; c2 >= 1; --c2) {
-            for (int x = tid; x < RP::ITEMS; x += nthr)
-                RP::item(rowsE + c2 * ROW, rowsS + c2 * ROW, rowsS + (c2 - 1) * ROW, x);
-            __syncthreads();
-        }
-        if (active) {
-            load_adjoint<d, N, P, false>(A.grad_out + b * D, u, ad);
-            if (c < C - 1) reg_adjoint_product<d, N, P>(ad, rowsS + c * ROW, u);
-        }
-        __syncthreads();
-        // 4. the sweep of every chunk; rowsE now parks the partial sums
-        sweep(std::true_type{});
-    } else {
-        // Stream mode: every row has its own upstream gradient, so what reaches the end of chunk c from the later
-        // chunks is r_{c+1} + transpose of (. (x) E_{c+1}) applied to A_end(c+1), where r_c is what chunk c's own
-        // rows leave at its start.
-        // 3a. a first sweep from a zero adjoint, without output, gives r_c
-        sweep(std::false_type{});
-        if (active) store_private<d, N, P>(rowsA + c * private_floats<d, N, P>(), u, ad);
-        __syncthreads();
-        // 3b. the lanes of chunk 0 walk the chunks from the last to the first: A_end(c-1) = r_c + pull-back of
-        //     A_end(c) through E_c; A_end(c) takes r_c's place in LDS
-        if (active && c == 0) {
-            Lane<d, N, P> run, r;
-            identity_state<d, N, P>(run);
-            if (P == 0) run.s[0] = 0.0f;
-            for (int c2 = C - 1; c2 >= 1; --c2) {
-                float *slot = rowsA + c2 * private_floats<d, N, P>();
-                load_private<d, N, P>(slot, u, r);
-                store_private<d, N, P>(slot, u, run);
-                reg_adjoint_product<d, N, P>(run, rowsE + c2 * ROW, u);
+            float *slot = rowsA + c2 * private_floats<d, N, P>();
+            load_private<d, N, P>(slot, u, r);
+            store_private<d, N, P>(slot, u, run);
+            reg_adjoint_product<d, N, P>(run, rowsE + c2 * ROW, u);
 #pragma unroll
-                for (int i = 0; i < Sh::SZ; ++i) run.s[i] += r.s[i];
+            for (int i = 0; i < Sh::SZ; ++i) run.s[i] += r.s[i];
 #pragma unroll
-                for (int i = 0; i < Sh::NPRE; ++i) run.pre[i] += r.pre[i];
-            }
-            store_private<d, N, P>(rowsA, u, run);
+            for (int i = 0; i < Sh::NPRE; ++i) run.pre[i] += r.pre[i];
         }
-        __syncthreads();
-        // 4. the second sweep, from the true adjoint, with output (rowsE parks the partial sums from here on)
-        if (active) {
-            load_state<d, N, P>(rowsS + c * ROW, u, ln);
-            load_private<d, N, P>(rowsA + c * private_floats<d, N, P>(), u, ad);
-        }
-        __syncthreads();
-        sweep(std::true_type{});
+        store_private<d, N, P>(rowsA, u, run);
     }
+    __syncthreads();
+    // 4. the second sweep, from the true adjoint, with output (rowsE parks the partial sums from here on)
+    if (active) {
+        load_state<d, N, P>(rowsS + c * ROW, u, ln);
+        load_private<d, N, P>(rowsA + c * private_floats<d, N, P>(), u, ad);
+    }
+    __syncthreads();
+    sweep(std::true_type{});
 
     const int out_row = (int)A.L * d;
     for (int i = tid; i < out_row; i += nthr) {
@@ -425,7 +396,6 @@ hipError_t backward_sliced_launch(const BackwardArgs &A0, float *scratch, int, i
     return launch_backward_finish(scratch, A.grad_path, A.B, A.L, d, slices, st);
 }
 
-// the register sweep needs device scratch only for paths it has to walk in tiles: the sums over the increments
 // The increments of a path fit LDS, but so few paths' worth of them that at most half of the lanes of 256 threads
 // would hold a path (long paths: (5,4) with 2,000 points takes 40 KB, one path and 25 lanes per workgroup).  On a batch
 // that fills the chip the plain sweep then runs 1.4-5.7 times slower than either alternative: the sweep cut in time
@@ -445,10 +415,9 @@ bool backward_starved(int64_t L)
 
 // Kernels with fewer than 16 lanes per path whose LDS holds fewer paths than a workgroup has lanes for (the
 // increments of a path take L d floats for a handful of lanes): on a batch that needs the plain sweep's resident
-// workgroups more than one and a half times over (final mode), the paths are walked in short tiles instead, sized so that a full
-// workgroup's tiles take 32 KB and two or more workgroups stay on a CU.  Measured: (5,3), 100 points, 65,536 paths
-// 461 -> 303 us; stream mode, 256 points, 16,384 paths 1,001 -> 685; (6,3), (7,3), (3,4), (2,6) at 100 points
-// 1.25-1.35x; on a chip that the plain sweep fills about once it loses 20-40 %.  Returns the tile length, 0 if the
+// workgroups several times over, the paths are walked in short tiles instead, sized so that a full workgroup's tiles take
+// 32 KB and two or more workgroups stay on a CU.  Measured: (5,3), 256 points, 16,384 paths 1,001 -> 685 us; on a chip that
+// the plain sweep fills about once it loses 20-40 %.  Returns the tile length, 0 if the
 // shape is not of this kind.
 template <int d, int N, int P>
 int backward_short_tile(int64_t L, int threads)
@@ -464,6 +433,7 @@ int backward_short_tile(int64_t L, int threads)
     return T < L - 1 ? T : 0;
 }
 
+// the register sweep needs device scratch only for paths it walks in tiles: the sums over the increments
 template <int d, int N, int P>
 int64_t backward_tiled_scratch_floats(int64_t B, int64_t L)
 {
@@ -489,14 +459,76 @@ int waves_by_registers(Kernel kernel)
 
 // Workgroups of the register sweep that stay resident on a CU: what its LDS holds (the increments of the
 // workgroup's paths plus the parked sums), then what the registers allow.
-template <int d, int N, int P>
-int64_t resident_sweep_workgroups(int64_t L, int stream_flag, int threads, int groups, int park_steps)
+template <int d, int N, int P, bool STREAM = true>
+int64_t resident_sweep_workgroups(int64_t L, int threads, int groups, int park_steps)
 {
-    static const int regs_final = waves_by_registers(&sig_backward_kernel<d, N, P, false>);
-    static const int regs_stream = waves_by_registers(&sig_backward_kernel<d, N, P, true>);
-    const int64_t by_regs = (stream_flag ? regs_stream : regs_final) * 4 / ((threads + kWave - 1) / kWave);
+    static const int regs = waves_by_registers(&sig_backward_kernel<d, N, P, STREAM>);
+    const int64_t by_regs = regs * 4 / ((threads + kWave - 1) / kWave);
     const int64_t by_lds = kCuLdsBytes / backward_lds_bytes<d, N, P>(L, groups, park_steps);
     return by_lds < by_regs ? by_lds : by_regs;
+}
+
+// paths per workgroup: as many as the threads hold, spread over the CUs first, fewer if their LDS does not fit
+template <int d, int N, int P>
+int sweep_groups(int64_t B, int64_t L, int threads, int cus)
+{
+    int G = threads / Shape<d, N, P>::Q;
+    const int64_t per_cu = (B + cus - 1) / (cus > 0 ? cus : 1);
+    if ((int64_t)G > per_cu) G = per_cu > 1 ? (int)per_cu : 1;
+    while (G > 1 && backward_lds_bytes<d, N, P>(L, G) > kMaxLdsBytes) --G;
+    // ... and the same number of paths on every CU: with 16 paths per CU and room for 12 per workgroup, workgroups of 8
+    // put two on every CU where workgroups of 12 put two on a third of the CUs and one on the rest
+    if (per_cu > G) {
+        const int64_t rounds = (per_cu + G - 1) / G;
+        G = (int)((per_cu + rounds - 1) / rounds);
+    }
+    return G;
+}
+
+// Parked steps: the most that is useful (0), unless fewer (kShortPark) keep more workgroups resident on a batch that fills
+// the chip.  Measured at kShortPark against the most, final mode at 65,536 paths of 100 points: (5,4) 749 -> 698 us, (6,4)
+// 352 -> 333, (8,3) 895 -> 657; where the residency is the same (stream mode, whose registers allow two or three
+// wavefronts per SIMD) the shorter park only adds barriers (1-3 % slower).
+// (Smaller workgroups for shapes whose 64 KiB hold fewer paths than 256 threads, and fewer paths per workgroup, were
+// measured too: between 11 % faster and 10 % slower with no rule that told the two apart.)
+template <int d, int N, int P, bool STREAM>
+int sweep_park_steps(int64_t B, int64_t L, int threads, int groups, int cus)
+{
+    if constexpr (reduce_steps<d, P>() > kShortPark) {
+        if (backward_lds_bytes<d, N, P>(L, groups) <= kMaxLdsBytes) {
+            const int64_t per_cu = (B + cus - 1) / (cus > 0 ? cus : 1);
+            const int64_t longest = resident_sweep_workgroups<d, N, P, STREAM>(L, threads, groups, 0);
+            if (per_cu > groups * longest && resident_sweep_workgroups<d, N, P, STREAM>(L, threads, groups, kShortPark) > longest)
+                return kShortPark;
+        }
+    }
+    return 0;
+}
+
+// Final mode: short paths only (see bracket_min_points), the plain sweep
+template <int d, int N, int P>
+hipError_t backward_short_launch(const BackwardArgs &A0, int threads, int cus, hipStream_t st)
+{
+    if constexpr (!bracket_compiled(d, N) || bracket_min_points(d, N) <= 2) {
+        static_assert(bracket_compiled(d, N), "long paths of the register shapes are swept on brackets");
+        return hipErrorInvalidValue;
+    } else {
+        BackwardArgs A = A0;
+        const int G = sweep_groups<d, N, P>(A.B, A.L, threads, cus);
+        const int park_steps = sweep_park_steps<d, N, P, false>(A.B, A.L, threads, G, cus);
+        const int64_t lds = backward_lds_bytes<d, N, P>(A.L, G, park_steps);
+        const int64_t grid = (A.B + G - 1) / G;
+        if (lds > kMaxLdsBytes || grid <= 0 || grid > INT32_MAX) return hipErrorInvalidValue;
+        A.groups = G;
+        if constexpr (reduce_steps<d, P>() > kShortPark) {
+            if (park_steps) {
+                hipLaunchKernelGGL((sig_backward_kernel<d, N, P, false, false, true, kShortPark>), dim3((unsigned)grid), dim3(threads), (size_t)lds, st, A);
+                return hipGetLastError();
+            }
+        }
+        hipLaunchKernelGGL((sig_backward_kernel<d, N, P, false>), dim3((unsigned)grid), dim3(threads), (size_t)lds, st, A);
+        return hipGetLastError();
+    }
 }
 
 template <int d, int N, int P>
@@ -504,54 +536,46 @@ hipError_t backward_launch(const BackwardArgs &A0, float *scratch, int threads, 
 {
     constexpr int Q = Shape<d, N, P>::Q;
     if (threads < Q || threads > 256 || threads % kWave) return hipErrorInvalidValue;
+    if (!A0.stream_flag) return backward_short_launch<d, N, P>(A0, threads, cus, st);
     BackwardArgs A = A0;
-    // Lanes below which the sweep is cut in time inside the workgroup (one path per workgroup).  The cut sweeps every
-    // increment twice (three times in stream mode) and multiplies rows between the chunks, so it pays only while the
-    // plain sweep would leave the chip nearly empty: final mode below one wavefront per SIMD, half of one for paths of
-    // up to 128 increments of kernels with fewer than 64 lanes per path (14 shapes x 32 ... 500 points x 128 ... 8,192 paths against a limit of two: (5,4), 100 points,
-    // 4,096 paths 208 -> 80 us, (3,5), 32 points, 8,192 paths 120 -> 31; long paths between half a wavefront and one
-    // lose 10-45 % with the lower limit); stream mode below a wavefront per CU.
-    const int64_t full_lanes = (int64_t)cus * 4 * kWave * 2;
-    const int64_t few_lanes = A.stream_flag ? (int64_t)cus * kWave
-                              : (A.L - 1 <= 128 && Q < kWave) ? (int64_t)cus * 4 * kWave / 2 : (int64_t)cus * 4 * kWave;
+    // Lanes below which the sweep is cut in time inside the workgroup (one path per workgroup): a wavefront per CU.  The cut
+    // sweeps every increment three times and multiplies rows between the chunks, so it pays only while the plain sweep would
+    // leave the chip nearly empty.
+    const int64_t few_lanes = (int64_t)cus * kWave;
     // A shape that fills at most half of a workgroup's lanes (see backward_starved) ...
     bool half_empty = backward_starved<d, N, P>(A.L);
     if (half_empty && Q < kStarvedChunkedMaxLanes && N >= 3) {
         // ... unless, for the kernels with few lanes per path, the plain sweep still keeps enough lanes on a CU.  The
-        // cut in time sweeps every increment three times (stream mode; twice in final mode) and multiplies whole rows
-        // between the chunks, which costs more the deeper the signature: measured on 14 shapes x 64 ... 2,000 points x
-        // 2,048 ... 32,768 paths, the plain sweep is 1.1-7x faster above these lane counts (stream mode, 256 points,
-        // 8,192 paths: (2,6) 2,504 -> 501 us, (3,4) 843 -> 261, (5,3) 636 -> 426) and up to 5x slower below them; at
-        // depth 2 the cut always wins.
+        // cut in time sweeps every increment three times and multiplies whole rows between the chunks, which costs more
+        // the deeper the signature: measured on 14 shapes x 64 ... 2,000 points x 2,048 ... 32,768 paths, the plain sweep
+        // is 1.1-7x faster above these lane counts (256 points, 8,192 paths: (2,6) 2,504 -> 501 us, (3,4) 843 -> 261, (5,3)
+        // 636 -> 426) and up to 5x slower below them; at depth 2 the cut always wins.
         int G = threads / Q;
         while (G > 1 && backward_lds_bytes<d, N, P>(A.L, G) > kMaxLdsBytes) --G;
-        const int64_t lanes = resident_sweep_workgroups<d, N, P>(A.L, A.stream_flag, threads, G, 0) * G * Q;
-        const int64_t enough = !A.stream_flag ? 224 : N >= 4 ? 56 : 112;
-        if (lanes >= enough) half_empty = false;
+        const int64_t lanes = resident_sweep_workgroups<d, N, P>(A.L, threads, G, 0) * G * Q;
+        if (lanes >= (N >= 4 ? 56 : 112)) half_empty = false;
     }
-    // ... keeps the cut further: final mode up to two wavefronts per SIMD; stream mode, where the row products between
-    // the chunks are cheap (depth up to 3, or rows of up to 400 floats), up to two wavefronts per CU, four for kernels
-    // with 64 lanes per path or more ((4,4), 500 points, 1,024 paths 381 -> 269 us; (8,3), 256 points, 512 paths 176
-    // -> 111; (10,3), 512 paths 239 -> 141; (5,4), (6,4), (4,5) lose 15-35 % there).  From there on it is walked in
-    // tiles, or cut anyway if it has fewer than 16 lanes per path.
+    // ... keeps the cut further: where the row products between the chunks are cheap (depth up to 3, or rows of up to 400
+    // floats), up to two wavefronts per CU, four for kernels with 64 lanes per path or more ((4,4), 500 points, 1,024 paths
+    // 381 -> 269 us; (8,3), 256 points, 512 paths 176 -> 111; (10,3), 512 paths 239 -> 141; (5,4), (6,4), (4,5) lose 15-35 %
+    // there).  From there on it is walked in tiles, or cut anyway if it has fewer than 16 lanes per path.
     constexpr bool cheap_products = N <= 3 || Shape<d, N, P>::D <= 400;
-    const int64_t half_empty_lanes = !A.stream_flag ? full_lanes
-                                     : cheap_products ? few_lanes * (Q >= kWave ? 4 : 2) : few_lanes;
+    const int64_t half_empty_lanes = cheap_products ? few_lanes * (Q >= kWave ? 4 : 2) : few_lanes;
     const bool starved = half_empty && A.B * Q >= half_empty_lanes;
     const bool starved_tiles = starved && Q >= kStarvedChunkedMaxLanes && scratch;
     const bool starved_chunks = starved && Q < kStarvedChunkedMaxLanes;
     // few-lane kernels that LDS keeps from filling their workgroups, on a batch that needs the plain sweep's resident
-    // workgroups more than one and a half times over: short tiles (see backward_short_tile)
+    // workgroups several times over: short tiles (see backward_short_tile)
     int short_tile = 0;
     if (scratch && !half_empty && A.B * Q >= few_lanes) {
         short_tile = backward_short_tile<d, N, P>(A.L, threads);
         if (short_tile) {
             int fit = threads / Q;
             while (fit > 1 && backward_lds_bytes<d, N, P>(A.L, fit) > kMaxLdsBytes) --fit;
-            const int64_t resident = resident_sweep_workgroups<d, N, P>(A.L, A.stream_flag, threads, fit, 0) * fit * Q * cus;
-            // (stream mode: from two and a half times over, unless the lane state is large; at twice over (2,3),
-            // (2,4), (3,4) and (6,3) with 256 points lose 15-25 % to the plain sweep, (2,6) gains 2x)
-            const int64_t times2 = !A.stream_flag || Shape<d, N, P>::SZ >= 48 ? 3 : 5;
+            const int64_t resident = resident_sweep_workgroups<d, N, P>(A.L, threads, fit, 0) * fit * Q * cus;
+            // (from two and a half times over, one and a half where the lane state is large; at twice over (2,3), (2,4),
+            // (3,4) and (6,3) with 256 points lose 15-25 % to the plain sweep, (2,6) gains 2x)
+            const int64_t times2 = Shape<d, N, P>::SZ >= 48 ? 3 : 5;
             if (A.B * Q * 2 < resident * times2) short_tile = 0;
         }
     }
@@ -563,100 +587,57 @@ hipError_t backward_launch(const BackwardArgs &A0, float *scratch, int threads, 
         A.seg_steps = tile;
         A.segs = (int32_t)((A.L - 1 + tile - 1) / tile);
         A.seg_part = scratch;
-        int G = threads / Q;
-        const int64_t per_cu = (A.B + cus - 1) / (cus > 0 ? cus : 1);
-        if ((int64_t)G > per_cu) G = per_cu > 1 ? (int)per_cu : 1;
-        while (G > 1 && backward_lds_bytes<d, N, P>(tile + 1, G) > kMaxLdsBytes) --G;
-        if (per_cu > G) {   // the same number of paths on every CU, see below
-            const int64_t rounds = (per_cu + G - 1) / G;
-            G = (int)((per_cu + rounds - 1) / rounds);
-        }
+        const int G = sweep_groups<d, N, P>(A.B, tile + 1, threads, cus);
         const size_t lds = (size_t)backward_lds_bytes<d, N, P>(tile + 1, G);
         const int64_t grid = (A.B + G - 1) / G;
         if (lds > (size_t)kMaxLdsBytes || grid <= 0 || grid > INT32_MAX) return hipErrorInvalidValue;
         A.groups = G;
-        if (A.stream_flag)
-            hipLaunchKernelGGL((sig_backward_tiled_kernel<d, N, P, true>), dim3((unsigned)grid), dim3(threads), lds, st, A);
-        else
-            hipLaunchKernelGGL((sig_backward_tiled_kernel<d, N, P, false>), dim3((unsigned)grid), dim3(threads), lds, st, A);
+        hipLaunchKernelGGL((sig_backward_tiled_kernel<d, N, P>), dim3((unsigned)grid), dim3(threads), lds, st, A);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         return launch_backward_finish(scratch, A.grad_path, A.B, A.L, d, 1, st);
     }
-    // Few paths (fewer lanes than two wavefronts per SIMD): cut the sweep in time, one workgroup per path with
-    // as many chunks as its threads and LDS hold, at least eight increments each.
-    // (stream mode reads the upstream gradient twice when cut, so only far below one wavefront per SIMD)
+    // Few paths: cut the sweep in time, one workgroup per path with as many chunks as its threads and LDS hold, at least
+    // eight increments each (the upstream gradient is read twice then, so only far below one wavefront per SIMD).
     if ((A.B * Q < few_lanes || (half_empty && A.B * Q < half_empty_lanes) || starved_chunks) && A.B <= INT32_MAX) {
-        const int C = backward_chunks<d, N, P>(A.L, A.stream_flag, threads);
+        const int C = backward_chunks<d, N, P>(A.L, threads);
         if (C > 1) {
             A.groups = C;
-            const size_t lds = (size_t)backward_chunked_lds_bytes<d, N, P>(A.L, C, A.stream_flag);
-            // (stream mode fetches the upstream rows as a pipeline where four rows fit the registers and the launch
-            // leaves the SIMDs a wavefront each or less: (4,4), 256 points, 128 paths 45 -> 37 us; with two rows,
-            // or on fuller chips, the plain fetch is up to a quarter faster)
+            const size_t lds = (size_t)backward_chunked_lds_bytes<d, N, P>(A.L, C);
+            // (the upstream rows are fetched as a pipeline where four rows fit the registers and the launch leaves the SIMDs
+            // a wavefront each or less: (4,4), 256 points, 128 paths 45 -> 37 us; with two rows, or on fuller chips, the
+            // plain fetch is up to a quarter faster)
             constexpr bool kFourRows = Shape<d, N, P>::SZ <= 24;
             const int64_t busy_wavefronts = A.B * (((int64_t)C * Q + kWave - 1) / kWave);
-            if (A.stream_flag && kFourRows && busy_wavefronts <= (int64_t)cus * 4)
-                hipLaunchKernelGGL((sig_backward_chunked_kernel<d, N, P, true, kFourRows>), dim3((unsigned)A.B), dim3(threads), lds, st, A);
-            else if (A.stream_flag)
-                hipLaunchKernelGGL((sig_backward_chunked_kernel<d, N, P, true>), dim3((unsigned)A.B), dim3(threads), lds, st, A);
+            if (kFourRows && busy_wavefronts <= (int64_t)cus * 4)
+                hipLaunchKernelGGL((sig_backward_chunked_kernel<d, N, P, kFourRows>), dim3((unsigned)A.B), dim3(threads), lds, st, A);
             else
-                hipLaunchKernelGGL((sig_backward_chunked_kernel<d, N, P, false>), dim3((unsigned)A.B), dim3(threads), lds, st, A);
+                hipLaunchKernelGGL((sig_backward_chunked_kernel<d, N, P>), dim3((unsigned)A.B), dim3(threads), lds, st, A);
             return hipGetLastError();
         }
     }
-    // paths per workgroup: as many as the threads hold, fewer if their LDS does not fit, spread over the CUs first
-    int G = threads / Q;
-    const int64_t per_cu = (A.B + cus - 1) / (cus > 0 ? cus : 1);
-    if ((int64_t)G > per_cu) G = per_cu > 1 ? (int)per_cu : 1;
-    while (G > 1 && backward_lds_bytes<d, N, P>(A.L, G) > kMaxLdsBytes) --G;
-    // ... and the same number of paths on every CU: with 16 paths per CU and room for 12 per workgroup, workgroups of 8
-    // put two on every CU where workgroups of 12 put two on a third of the CUs and one on the rest
-    if (per_cu > G) {
-        const int64_t rounds = (per_cu + G - 1) / G;
-        G = (int)((per_cu + rounds - 1) / rounds);
-    }
-    // Parked steps: the most that is useful, unless fewer keep more workgroups resident on a batch that fills
-    // the chip.  Measured at kShortPark against the most: (5,4) at 65,536 paths 749 -> 698 us, (6,4) 352 -> 333,
-    // (8,3) 895 -> 657, (5,4) of 300 points 1199 -> 950; where the residency is the same (stream mode, whose
-    // registers allow two or three wavefronts per SIMD) the shorter park only adds barriers (1-3 % slower).
-    // (Smaller workgroups for shapes whose 64 KiB hold fewer paths than 256 threads, and fewer paths per workgroup,
-    // were measured too: between 11 % faster and 10 % slower with no rule that told the two apart.)
-    int short_park = 0;
-    if constexpr (reduce_steps<d, P>() > kShortPark) {
-        if (backward_lds_bytes<d, N, P>(A.L, G) <= kMaxLdsBytes) {
-            const int64_t longest = resident_sweep_workgroups<d, N, P>(A.L, A.stream_flag, threads, G, 0);
-            if (per_cu > G * longest &&
-                resident_sweep_workgroups<d, N, P>(A.L, A.stream_flag, threads, G, kShortPark) > longest)
-                short_park = 1;
-        }
-    }
-    const int park_steps = short_park ? kShortPark : 0;
+    const int G = sweep_groups<d, N, P>(A.B, A.L, threads, cus);
+    const int park_steps = sweep_park_steps<d, N, P, true>(A.B, A.L, threads, G, cus);
     if (backward_lds_bytes<d, N, P>(A.L, G, park_steps) > kMaxLdsBytes) return hipErrorInvalidValue;
     A.groups = G;
     const int64_t grid = (A.B + G - 1) / G;
     if (grid <= 0 || grid > INT32_MAX) return hipErrorInvalidValue;
     const size_t lds = (size_t)backward_lds_bytes<d, N, P>(A.L, G, park_steps);
     if constexpr (reduce_steps<d, P>() > kShortPark) {
-        if (short_park) {
-            if (A.stream_flag)
-                hipLaunchKernelGGL((sig_backward_kernel<d, N, P, true, false, true, kShortPark>), dim3((unsigned)grid), dim3(threads), lds, st, A);
-            else
-                hipLaunchKernelGGL((sig_backward_kernel<d, N, P, false, false, true, kShortPark>), dim3((unsigned)grid), dim3(threads), lds, st, A);
+        if (park_steps) {
+            hipLaunchKernelGGL((sig_backward_kernel<d, N, P, true, false, true, kShortPark>), dim3((unsigned)grid), dim3(threads), lds, st, A);
             return hipGetLastError();
         }
     }
-    // Stream mode on a launch that leaves the SIMDs a wavefront each or less: the upstream rows as a software pipeline
-    // (measured against the plain fetch: (4,4), 256 points, 1,024 paths 156 -> 114 us; (3,5), 100 points, 4,096
-    // paths 162 -> 134; with more wavefronts than SIMDs it loses 3-10 %: its rows in flight evict each other's
-    // lines from the vector cache, whose requests to L2 rise by a fifth).
+    // A launch that leaves the SIMDs a wavefront each or less: the upstream rows as a software pipeline (measured against
+    // the plain fetch: (4,4), 256 points, 1,024 paths 156 -> 114 us; (3,5), 100 points, 4,096 paths 162 -> 134; with more
+    // wavefronts than SIMDs it loses 3-10 %: its rows in flight evict each other's lines from the vector cache, whose
+    // requests to L2 rise by a fifth).
     const int64_t busy_wavefronts = grid * (((int64_t)G * Q + kWave - 1) / kWave);
-    if (A.stream_flag && busy_wavefronts <= (int64_t)cus * 4)
+    if (busy_wavefronts <= (int64_t)cus * 4)
         hipLaunchKernelGGL((sig_backward_kernel<d, N, P, true, false, true, 0, true>), dim3((unsigned)grid), dim3(threads), lds, st, A);
-    else if (A.stream_flag)
-        hipLaunchKernelGGL((sig_backward_kernel<d, N, P, true>), dim3((unsigned)grid), dim3(threads), lds, st, A);
     else
-        hipLaunchKernelGGL((sig_backward_kernel<d, N, P, false>), dim3((unsigned)grid), dim3(threads), lds, st, A);
+        hipLaunchKernelGGL((sig_backward_kernel<d, N, P, true>), dim3((unsigned)grid), dim3(threads), lds, st, A);
     return hipGetLastError();
 }
 

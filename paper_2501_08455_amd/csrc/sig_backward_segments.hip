@@ -1,5 +1,5 @@
-// Gradient of the signature with respect to the path, cut in time across workgroups: few long paths (final mode;
-// stream mode further down, at sig_backward_segment_affine_kernel).
+// Gradient of the signature with respect to the path, cut in time across workgroups: few long paths (final mode of the
+// shapes that have no sweep on brackets, sig_bracket.h; stream mode further down, at sig_backward_segment_affine_kernel).
 //
 // The reverse sweep (see sig_backward.hip) walks the K increments of a path one after the other, and a workgroup
 // per path (and slice of its lanes) leaves most of the chip idle when there are few paths.  Chen's relation (paper
@@ -15,8 +15,8 @@
 //   3. every segment pulls the upstream gradient back through Y_{s+1}: A_end(s)
 //   4. every piece runs the reverse sweep over its own increments                                 (T steps)
 //   5. the sums of d(loss)/d(increment) are added up over the slices and differenced into d(loss)/dX.
-// Launch 4 is the sliced sweep on (path, segment, slice of lanes) for shapes with more than 128 lanes per path, and
-// the register sweep with several (path, segment) pieces per workgroup for the others (both in sig_backward.h).
+// Launch 4 is the sliced sweep on (path, segment, slice of lanes) for shapes with more than 128 lanes per path, and (stream
+// mode) the register sweep with several (path, segment) pieces per workgroup for the others (both in sig_backward.h).
 #include "sig_backward.h"
 
 namespace sig {
@@ -318,58 +318,46 @@ hipError_t backward_segmented_launch(const BackwardArgs &A0, float *scratch, int
         }
     }
 
-    const int fold_threads = Sh::Q >= kSliceLanes ? kSliceLanes : (Sh::Q + kWave - 1) / kWave * kWave;
-    hipLaunchKernelGGL((sig_backward_segment_fold_kernel<d, N, P>), dim3((unsigned)(pieces * slices)), dim3(fold_threads),
-                       (size_t)(T * d) * sizeof(float), st, A0.path, E, A0.L, W, (int)T, 0);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const float *Sin = E, *Yin = E;
-    float *Sout = S0, *Yout = Y0;
-    for (int off = 1; off < W; off *= 2) {
-        hipLaunchKernelGGL((sig_backward_segment_scan_kernel<d, N>), dim3((unsigned)pieces, 2, row_workgroups<d, N>()), dim3(256),
-                           0, st, Sin, Sout, Yin, Yout, W, off);
+    if constexpr (packed || bracket_compiled(d, N)) {
+        return hipErrorInvalidValue;   // final mode of these shapes is swept on brackets (and its short paths are not cut)
+    } else {
+        const int fold_threads = Sh::Q >= kSliceLanes ? kSliceLanes : (Sh::Q + kWave - 1) / kWave * kWave;
+        hipLaunchKernelGGL((sig_backward_segment_fold_kernel<d, N, P>), dim3((unsigned)(pieces * slices)), dim3(fold_threads),
+                           (size_t)(T * d) * sizeof(float), st, A0.path, E, A0.L, W, (int)T, 0);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        const float *Sin = E, *Yin = E;
+        float *Sout = S0, *Yout = Y0;
+        for (int off = 1; off < W; off *= 2) {
+            hipLaunchKernelGGL((sig_backward_segment_scan_kernel<d, N>), dim3((unsigned)pieces, 2, row_workgroups<d, N>()), dim3(256),
+                               0, st, Sin, Sout, Yin, Yout, W, off);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            Sin = Sout;
+            Yin = Yout;
+            Sout = Sout == S0 ? S1 : S0;
+            Yout = Yout == Y0 ? Y1 : Y0;
+        }
+        // the scan's last input buffer of the suffix products is free now: it takes the pulled-back gradients
+        float *Aend = Yout;
+        hipLaunchKernelGGL((sig_backward_segment_adjoint_kernel<d, N>), dim3((unsigned)pieces, 1, row_workgroups<d, N>()), dim3(256),
+                           0, st, A0.grad_out, Yin, Aend, W);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        Sin = Sout;
-        Yin = Yout;
-        Sout = Sout == S0 ? S1 : S0;
-        Yout = Yout == Y0 ? Y1 : Y0;
-    }
-    // the scan's last input buffer of the suffix products is free now: it takes the pulled-back gradients
-    float *Aend = Yout;
-    hipLaunchKernelGGL((sig_backward_segment_adjoint_kernel<d, N>), dim3((unsigned)pieces, 1, row_workgroups<d, N>()), dim3(256),
-                       0, st, A0.grad_out, Yin, Aend, W);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    BackwardArgs A = A0;
-    A.segs = W;
-    A.seg_steps = (int32_t)T;
-    A.seg_sig = Sin;
-    A.seg_grad = Aend;
-    A.seg_part = part;
-    if constexpr (packed) {
-        // pieces per workgroup: as many as the threads hold, spread over the compute units first, fewer if LDS is short
-        int G = 256 / Sh::Q;
-        const int64_t per_cu = (pieces + cus - 1) / cus;
-        if ((int64_t)G > per_cu) G = (int)per_cu;
-        while (G > 1 && backward_lds_bytes<d, N, P>(T + 1, G) > kMaxLdsBytes) --G;
-        if (per_cu > G) {   // the same number of pieces on every compute unit (see backward_launch)
-            const int64_t rounds = (per_cu + G - 1) / G;
-            G = (int)((per_cu + rounds - 1) / rounds);
-        }
-        A.groups = G;
-        const size_t lds = (size_t)backward_lds_bytes<d, N, P>(T + 1, G);
-        hipLaunchKernelGGL((sig_backward_kernel<d, N, P, false, true>), dim3((unsigned)((pieces + G - 1) / G)), dim3(256), lds,
-                           st, A);
-    } else {
+        BackwardArgs A = A0;
+        A.segs = W;
+        A.seg_steps = (int32_t)T;
+        A.seg_sig = Sin;
+        A.seg_grad = Aend;
+        A.seg_part = part;
         const int ts = backward_sliced_steps<d>(T + 1);
         const size_t lds = (size_t)backward_sliced_bytes_with<d>(T + 1, ts);
         hipLaunchKernelGGL((sig_backward_sliced_kernel<d, N, P, false>), dim3((unsigned)(pieces * slices)), dim3(kSliceLanes),
                            lds, st, A, part, ts);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        return launch_backward_finish(part, A.grad_path, A.B, A.L, d, slices, st);
     }
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_backward_finish(part, A.grad_path, A.B, A.L, d, slices, st);
 }
 
 }  // namespace onchip
@@ -377,9 +365,9 @@ hipError_t backward_segmented_launch(const BackwardArgs &A0, float *scratch, int
 namespace {
 
 template <int d, int N, int P>
-int uncut_chunks(int64_t L, int stream_flag)
+int uncut_chunks(int64_t L)
 {
-    if constexpr (onchip::Shape<d, N, P>::Q <= 256) return onchip::backward_chunks<d, N, P>(L, stream_flag, 256);
+    if constexpr (onchip::Shape<d, N, P>::Q <= 256) return onchip::backward_chunks<d, N, P>(L, 256);
     else return 1;
 }
 
@@ -389,7 +377,7 @@ struct SegmentedEntry {
     int64_t row;      // D
     hipError_t (*launch)(const onchip::BackwardArgs &, float *, int, int, hipStream_t);
     bool (*fits)(int64_t);             // does a segment of T increments fit the LDS of its sweep?
-    int (*uncut_chunks)(int64_t L, int stream_flag);   // chunks the uncut sweep holds side by side in a workgroup
+    int (*uncut_chunks)(int64_t L);    // chunks the uncut sweep holds side by side in a workgroup
 };
 #define SIG_SEGMENTED_ENTRY(d, N, P) \
     {d, N, onchip::Shape<d, N, P>::Q, onchip::Shape<d, N, P>::D, &onchip::backward_segmented_launch<d, N, P>, &onchip::segment_fits<d, N, P>, \
@@ -412,18 +400,17 @@ constexpr int64_t kMaxSegmentRow = 1 << 17;   // one workgroup forms a product o
 
 }  // namespace
 
-// Time segments for the final-mode sweep of B paths of L points (<= 1: do not cut).  Cutting pays when the uncut
-// launch leaves most of the chip idle and the path is long: the sequential part drops from K steps (2 K / C for a
-// shape whose plain sweep holds C chunks of a path side by side in its workgroup) to about K / W, for
-// ceil(log2 W) + 3 more launches of 3-6 us each.  Rules, from a measured grid (15 shapes, B = 1 .. 1,024,
-// L = 100 .. 2,000):
+// Time segments for the sweep of B paths of L points (<= 1: do not cut).  Cutting pays when the uncut launch leaves most of
+// the chip idle and the path is long: the sequential part drops from K steps (2 K / C for a shape whose plain sweep
+// holds C chunks of a path side by side in its workgroup) to about K / W, for ceil(log2 W) + 3 more launches of 3-6 us
+// each.  Final mode: only the shapes without a sweep on brackets ask (sig_bracket.h); they are sliced ones.  Rules, from
+// a measured grid (15 shapes, B = 1 .. 1,024, L = 100 .. 2,000):
 //   * from 128 increments on, while the uncut launch has fewer than two workgroups per compute unit (between one
-//     and two, a few segments still pay: d = 8, depth 4, 128 paths of 500 points, 292 -> 187 us with four);
+//     and two, a few segments still pay);
 //   * shapes whose plain sweep holds eight or more chunks: only from 512 increments on; with six or more chunks:
 //     only up to 32 paths (cutting wins or ties at every measured point up to there; beyond, the plain sweep's
 //     workgroups fill enough of the chip).  Long paths leave the plain sweep fewer chunks (their increments take
-//     the LDS), so they are cut at larger batches as well (d = 5, depth 4, 128 paths of 2,000 points: three chunks,
-//     328 -> 173 us);
+//     the LDS), so they are cut at larger batches as well;
 //   * W = K / 24, at most 32, at most two workgroups per compute unit (two wavefronts per SIMD for the shapes that
 //     pack several pieces into a workgroup), one set of rows within 8 MB (beyond, the scan's traffic costs more
 //     than the shorter sweeps save); a launch that has a workgroup per compute unit already: at most 4 segments,
@@ -444,7 +431,7 @@ int backward_segments(int d, int depth, int64_t B, int64_t L, int cus, bool uncu
     if (stream_flag && !packed) busy = B * slices >= (K < 512 ? cus / 2 : cus);
     int64_t min_steps = 128;
     if (packed && uncut_fits) {
-        const int chunks = e->uncut_chunks(L, stream_flag);
+        const int chunks = e->uncut_chunks(L);
         if (chunks >= 8) min_steps = 512;
         if (B > 32 && chunks >= 6) busy = true;
         // stream mode, rows of a few dozen floats (d = 2 at depth 3, d = 5 at depth 2): the plain sweep with its

@@ -78,6 +78,32 @@ hipError_t launch_backward_segmented(const float *path, const float *sig, const 
                                      float *scratch, int64_t B, int64_t L, int d, int depth, int stream_flag, int segs,
                                      int cus, hipStream_t st);
 
+// ---------------------------------------------------------------- gradient of the final signature on Lie brackets
+// (sig_bracket.h; any length).  Compiled shapes:
+constexpr bool bracket_compiled(int d, int depth)
+{
+    return d >= 2 && (depth == 2 ? d <= 20 : depth == 3 ? d <= 16 : depth == 4 ? d <= 10 : depth == 5 ? d <= 6 : depth == 6 && d <= 4);
+}
+// The sweep on brackets pays for the bracket values of a path once (2^{depth-1} words each) and then next to nothing per
+// step; the sweep on signatures (sig_backward.hip) has no such start, and stays for paths of fewer points than this: some
+// 12 + D / 150, twice the second term at depth 6, and D 2^{depth-1} / 2500 where the rows are too long for the packed kernel at
+// depth 5 and 6.  Measured on batches that fill the chip, points per path where the two meet: (4,4) 14, (5,4) 15, (6,4) 16,
+// (7,4) 33, (8,4) 12, (10,4) 9, (3,5) 17, (4,5) 16, (5,5) 25, (6,5) 45, (3,6) 32, (4,6) 80; up to depth 3 it wins or ties
+// from 8 points on.
+constexpr int64_t bracket_min_points(int d, int depth)
+{
+    if (depth < 4) return 2;
+    if (depth == 4 && d > 7) return 12;
+    int64_t D = 0, p = 1;
+    for (int n = 1; n <= depth; ++n) D += p *= d;
+    return D > 3000 ? (D << (depth - 1)) / 2500 : 12 + (depth >= 6 ? 2 : 1) * D / 150;
+}
+inline bool bracket_wanted(int d, int depth, int64_t L) { return bracket_compiled(d, depth) && L >= bracket_min_points(d, depth); }
+// workgroups a path's steps are cut across (1: not cut)
+int bracket_segments(int d, int depth, int64_t B, int64_t L, int cus);
+hipError_t launch_bracket(const float *path, const float *sig, const float *grad_out, float *grad_path, int64_t B, int64_t L,
+                          int d, int depth, int segs, int cus, hipStream_t st);
+
 // ---------------------------------------------------------------- gradient, any (d <= 256, depth): one workgroup per path
 bool backward_general_available(int d);
 int64_t backward_general_scratch_floats(int64_t B, int64_t L, const RowShape &rs);

@@ -1,0 +1,58 @@
+"""The final-mode gradient swept on Lie brackets (csrc/sig_bracket.h) at the edges of its launches, against the fp64 oracle
+with the gates of test_gpu_backward.py: several paths per wavefront with a ragged last one and a ragged last tile, chunks
+side by side (chunk lengths with remainders, fewest steps, steps beyond the end), paths cut across workgroups, the
+depth-2 kernel around its 256- and 512-point stretches, and the shortest paths that still come here."""
+import numpy as np
+import pytest
+
+from paper_2501_08455_amd import workloads
+from test_gpu_backward import check, gpu, sampled_backward, say  # noqa: F401  (gpu is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+# d, depth, B, L: batches that are packed (the oracle on the first, the last and a few in between)
+PACKED = [(5, 4, 8197, 37), (5, 4, 20001, 18), (4, 4, 8200, 101), (2, 6, 16387, 33), (2, 3, 65541, 9), (3, 3, 20011, 64),
+          (7, 4, 8195, 40), (8, 3, 8193, 13), (10, 3, 8193, 12), (3, 6, 9001, 35), (4, 5, 8191, 25)]
+
+
+@pytest.mark.parametrize("case", PACKED, ids=lambda c: "-".join(str(v) for v in c))
+def test_several_paths_per_wavefront(gpu, oracle, case):
+    d, depth, B, L = case
+    x = workloads.brownian_paths(B, L, d, seed=9000 + d + L)
+    say("bracket gradient, packed: %s" % (case,))
+    sampled_backward(gpu, oracle, x, depth, False, [0, 1, 7, B // 2, B - 3, B - 2, B - 1], seed=d + L)
+
+
+# few paths: one workgroup per path and stretch of its steps
+CUT = [(5, 4, 3, 101), (5, 4, 2, 102), (5, 4, 1, 17), (4, 4, 2, 500), (9, 4, 2, 12), (10, 4, 1, 43), (8, 4, 2, 12), (2, 4, 3, 14),
+       (2, 4, 2, 259), (2, 3, 2, 2), (3, 3, 5, 5), (16, 3, 2, 50), (12, 3, 3, 401), (11, 3, 2, 3), (6, 5, 2, 500), (5, 5, 2, 26),
+       (4, 6, 1, 90), (3, 6, 2, 700), (2, 6, 2, 1000), (2, 5, 3, 13), (6, 4, 1, 3001)]
+
+
+@pytest.mark.parametrize("case", CUT, ids=lambda c: "-".join(str(v) for v in c))
+def test_chunks_side_by_side(gpu, oracle, case):
+    d, depth, B, L = case
+    check(gpu, oracle, workloads.brownian_paths(B, L, d, seed=9100 + d + L), depth, False, seed=L, label="bracket, cut in time")
+
+
+DEPTH2 = [(2, 3, 2), (2, 300, 3), (3, 700, 100), (5, 2, 255), (5, 2, 256), (5, 3, 257), (20, 2, 513), (17, 1, 300), (13, 5, 3), (11, 90, 40)]
+
+
+@pytest.mark.parametrize("d,B,L", DEPTH2)
+def test_depth_two(gpu, oracle, d, B, L):
+    check(gpu, oracle, workloads.brownian_paths(B, L, d, seed=9200 + d + L), 2, False, seed=L, label="bracket, depth 2")
+
+
+def test_the_gradient_of_a_translation_vanishes(gpu):
+    """The signature does not see where a path starts: the gradients of a path's points add up to zero, up to the rounding
+    of 2,000 sums of float32 values (the sum of their magnitudes times 2^-23)."""
+    import torch
+    x = torch.from_numpy(workloads.brownian_paths(64, 2000, 5, seed=9300)).cuda()
+    out = gpu.signature(x, 4)
+    g = torch.randn_like(out)
+    gx = torch.full_like(x, float("nan"))
+    assert gpu.sig_backward(gpu.default_ctx(), x, 4, 0, out, g, gx) == gpu.SIG_OK
+    total, size = gx.double().sum(1), gx.double().abs().sum(1)
+    worst = float((total.abs() / size).max())
+    say("sum of a path's gradients over the sum of their magnitudes: %.1e" % worst)
+    assert np.isfinite(worst) and worst <= 2.0 ** -18
