@@ -41,6 +41,10 @@ hipError_t launch_combine_rows(const float *a, int64_t a_stride, const float *b,
                                float *out, int64_t out_stride, int64_t B, const RowShape &rs,
                                hipStream_t st);
 
+// The same for rows that follow each other without a gap, compiled (d, depth) only (sig_combine.hip).
+bool combine_tree_compiled(int d, int depth);
+hipError_t launch_combine_tree(const float *a, const float *b, float *out, int64_t B, int d, int depth, hipStream_t st);
+
 // ---------------------------------------------------------------- level-scan family (d <= 256, depth <= 8)
 // The level-by-level formulation of the paper's Section 3.2: one launch per level, each a cumulative sum over time
 // of per-step terms built from the lower levels of every prefix, which live in `scratch` (level_scan_scratch_floats
