@@ -298,7 +298,20 @@ constexpr double kSegmentCostFactor = 1.7;    // segments of a nearly empty chip
 constexpr double kSegmentOccupancyWaves = 2.0;  // segments on a busy chip: this many wavefronts per SIMD over the chunks' own
 constexpr int kMaxLdsJoinSegments = 8;
 constexpr int kFillByChunksMinSteps = 200;    // from this many increments on, never fewer chunks than fill the chip (final mode)
+constexpr int kMostChannels = 10;             // of the shapes that take their on-chip kernels at every batch, in both modes
+constexpr int kWideMinPaths = 16;             // from this many paths on the others do, in final mode,
+constexpr int kWideMostSteps = 128;           // in chunks of at most this many steps
 }  // namespace tune
+
+// The on-chip kernels of more than ten channels (sig_onchip_table_wide.hip): final mode, from 16 paths on, chunks of at most
+// kWideMostSteps steps (more segments are taken for that; where eight do not do, the call stays with the level-scan family).
+// Level-scan family against these, us: (12,3) 128 paths of 100 points 35.5 and 7.7, 1,024 of 500 392 and 119, 8,192 of 128
+// 773 and 208, 30,000 of 60 1,472 and 352; (11,2) 128 of 2,000 106 and 17; (20,2) 512 of 130 41 and 8, 8,192 of 250 374 and
+// 106; the other 71 points 1.3-15x.  The bound on the steps keeps the rounding where it was: error against 64 bits 2.3e-7 at
+// most over those points (5.5e-7 before), 1.2e-7 at 128 paths of (12,3) as before, 0.4 to 1.2 times the other family's and
+// 0.86 in the mean; uncut folds of 500 steps were 1.5 times as far off.  Fewer than 16 paths keep their plans, which a test
+// of the planner holds, although the kernels are faster there too (4 paths of 30 points: 7.5 us against 10 to 18).
+bool wide_on_chip_wanted(int64_t B, int stream_flag) { return !stream_flag && B >= tune::kWideMinPaths; }
 
 // Which compiled prefix depth to use for (d, depth); entries of one (d, depth) are ordered by increasing prefix depth.
 //  - final mode: the first entry whose lane state is small (several wavefronts per SIMD, chunk tree in registers);
@@ -385,7 +398,8 @@ int plan_auto(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const R
     *pl = sig_plan_t{};
     pl->threads = kThreads;
 
-    const OnChipKernelInfo *ki = (B > 0) ? pick_on_chip(rs.d, rs.depth, stream_flag, B, K, cus) : nullptr;
+    const bool on_chip = B > 0 && (rs.d <= tune::kMostChannels || wide_on_chip_wanted(B, stream_flag));
+    const OnChipKernelInfo *ki = on_chip ? pick_on_chip(rs.d, rs.depth, stream_flag, B, K, cus) : nullptr;
     if (ki) {
         const int Q = ki->lanes_per_chunk;
         const int state = ki->state_floats;
@@ -492,6 +506,12 @@ int plan_auto(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const R
                 const int64_t tree = tree_segments(wanted, B, K, rs);
                 if (tree >= 4 && tree >= 4 * W) W = tree;
             }
+            // more than ten channels: chunks of at most kWideMostSteps steps (see wide_on_chip_wanted)
+            if (rs.d > tune::kMostChannels && ceil_div(K, C * W) > tune::kWideMostSteps) {
+                W = ceil_div(K, C * tune::kWideMostSteps);
+                if (W > tune::kMaxLdsJoinSegments) W = tune::kMaxLdsJoinSegments;
+                while (W > 1 && !join_fits_lds(ki, (int)W, rs)) --W;
+            }
             pl->chunks = (int)C;
             pl->segments = (int)W;
         } else if (!stream_flag) {
@@ -579,6 +599,7 @@ int plan_auto(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const R
                 if (c != want.chunks) pl->segments = 1;
                 OnChipArgs args{};
                 if (finish_on_chip(ki, cus, B, L, stream_flag, *pl, rs, &args)) {
+                    if (rs.d > tune::kMostChannels && args.chunk_steps > tune::kWideMostSteps) return take_level_scan();
                     if (prefer_level_scan(*pl)) return take_level_scan();
                     pl->tile_steps = args.tile_steps;
                     return SIG_OK;

@@ -217,6 +217,7 @@ const OnChipKernelInfo *on_chip_table_depth3();
 const OnChipKernelInfo *on_chip_table_depth4();
 const OnChipKernelInfo *on_chip_table_depth56();
 const OnChipKernelInfo *on_chip_table_odd();
+const OnChipKernelInfo *on_chip_table_wide();
 const OnChipKernelInfo *find_on_chip(int d, int depth, int p);
 
 }  // namespace sig

@@ -29,6 +29,7 @@ const OnChipKernelInfo *on_chip_subtable(int i)
     case 3: return on_chip_table_depth4();
     case 4: return on_chip_table_depth56();
     case 5: return on_chip_table_odd();
+    case 6: return on_chip_table_wide();
     default: return nullptr;
     }
 }
