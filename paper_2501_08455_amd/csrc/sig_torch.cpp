@@ -191,14 +191,9 @@ PyObject *guarded(F f)
         return raise(e);
     } catch (const std::invalid_argument &e) {
         PyErr_SetString(PyExc_ValueError, e.what());
-    } catch (const c10::NotImplementedError &e) {
-        PyErr_SetString(PyExc_NotImplementedError, e.what_without_backtrace());
-    } catch (const c10::OutOfMemoryError &e) {
-        raise_named("torch", "OutOfMemoryError", Py_BuildValue("(s)", e.what_without_backtrace()));
-    } catch (const c10::Error &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
-    } catch (const std::exception &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (...) {
+        // torch's own, and what Python code raised in between (python_error: a saved-tensor hook, a dispatch mode)
+        torch::translate_exception_to_python(std::current_exception());
     }
     return nullptr;
 }

@@ -1,10 +1,13 @@
-"""The native torch binding (csrc/sig_torch.cpp): what it refuses, and the autograd node's bookkeeping.
+"""The native torch binding (csrc/sig_torch.cpp): what it refuses, the autograd node's bookkeeping, and torch's own machinery
+around it (checkpointing, saved-tensor hooks, dispatch modes).
 
 Results of the layer are checked against the oracle elsewhere (test_gpu_training_step.py, test_gpu_backward.py); here the
 gradient only has to be the one sig_backward gives, bit for bit: the node calls the same kernels on the same values.
 """
 import pytest
 import torch
+from torch.utils._python_dispatch import TorchDispatchMode
+from torch.utils.checkpoint import checkpoint
 
 from paper_2501_08455_amd import autograd, binding
 
@@ -66,3 +69,57 @@ def test_saved_tensors_are_watched_and_untracked_calls_keep_no_graph():
         path.add_(1.0)
     with pytest.raises(RuntimeError, match="modified by an inplace operation"):
         out.sum().backward()
+
+
+class Raised(Exception):
+    pass
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("stream", [False, True])
+@pytest.mark.parametrize("after", [lambda s: s, lambda s: 3.0 * s], ids=["layer last", "layer not last"])
+def test_checkpointed_regions(after, stream):
+    """torch ends the recomputation of a region with an exception from its own pack hook, as soon as it has what it needs: with
+    the layer last, that is while the node saves its tensors."""
+    base = torch.randn(3, 17, 3, device="cuda", generator=torch.Generator(device="cuda").manual_seed(5)).cumsum(1) * 0.1
+    grads = []
+    for run in (lambda f, a: f(a), lambda f, a: checkpoint(f, a, use_reentrant=False), lambda f, a: checkpoint(f, a, use_reentrant=True)):
+        path = base.clone().requires_grad_(True)
+        run(lambda a: after(autograd.signature(2.0 * a, 3, stream=stream)), path).square().sum().backward()
+        grads.append(path.grad)
+    assert torch.equal(grads[0], grads[1]) and torch.equal(grads[0], grads[2])
+
+
+@pytest.mark.gpu
+def test_exceptions_of_saved_tensor_hooks_keep_type_and_text():
+    def refuse(_):
+        raise Raised("not this one")
+    path = torch.randn(2, 5, 3, device="cuda", requires_grad=True)
+    with torch.autograd.graph.saved_tensors_hooks(refuse, lambda t: t), pytest.raises(Raised, match="not this one"):
+        autograd.signature(path, 2)
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t, refuse):
+        out = autograd.signature(path, 2)
+    with pytest.raises(Raised, match="not this one"):
+        out.sum().backward()
+
+
+@pytest.mark.gpu
+def test_saved_tensors_go_through_the_hooks():
+    path = torch.randn(2, 9, 3, device="cuda").cumsum(1).requires_grad_(True)
+    packed = []
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: packed.append(tuple(t.shape)) or t.cpu(), lambda t: t.cuda()):
+        out = autograd.signature(path, 2)
+    (got,) = torch.autograd.grad(out.sum(), path)
+    (want,) = torch.autograd.grad(autograd.signature(path, 2).sum(), path)
+    assert packed == [(2, 9, 3), (2, 12)] and torch.equal(got, want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("call", [binding.signature, autograd.signature])
+def test_exceptions_of_dispatch_modes_keep_type_and_text(call):
+    class Refuse(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            raise Raised(str(func))
+    path = torch.randn(2, 5, 3, device="cuda")
+    with Refuse(), pytest.raises(Raised, match="aten.empty"):
+        call(path, 2)
