@@ -1,5 +1,5 @@
 """The native torch binding (csrc/sig_torch.cpp): what it refuses, the autograd node's bookkeeping, and torch's own machinery
-around it (checkpointing, saved-tensor hooks, dispatch modes).
+around it (checkpointing, saved-tensor hooks, dispatch modes, compiled autograd, transforms that it has to refuse).
 
 Results of the layer are checked against the oracle elsewhere (test_gpu_training_step.py, test_gpu_backward.py); here the
 gradient only has to be the one sig_backward gives, bit for bit: the node calls the same kernels on the same values.
@@ -123,3 +123,44 @@ def test_exceptions_of_dispatch_modes_keep_type_and_text(call):
     path = torch.randn(2, 5, 3, device="cuda")
     with Refuse(), pytest.raises(Raised, match="aten.empty"):
         call(path, 2)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("stream", [False, True])
+def test_compiled_autograd(stream):
+    """One compiled backward serves other inputs and other depths; a failing call keeps its error."""
+    torch._dynamo.reset()
+    for depth, B in ((2, 3), (3, 3), (3, 5)):
+        base = torch.randn(B, 12, 3, device="cuda").cumsum(1) * 0.1
+        grads = []
+        for compiled in (False, True):
+            path = base.clone().requires_grad_(True)
+            loss = (autograd.signature(2.0 * path, depth, stream=stream) * 1.5).square().sum()
+            if compiled:
+                with torch._dynamo.compiled_autograd._enable(torch.compile(backend="eager")):
+                    loss.backward()
+            else:
+                loss.backward()
+            grads.append(path.grad)
+        assert torch.equal(grads[0], grads[1]), (depth, B)
+    path = torch.zeros(1, 2, 257, device="cuda", requires_grad=True)   # the gradient takes up to 256 channels
+    out = autograd.signature(path, 1)
+    with torch._dynamo.compiled_autograd._enable(torch.compile(backend="eager")), pytest.raises(Exception, match="status 6"):
+        out.sum().backward()
+    torch._dynamo.reset()
+
+
+@pytest.mark.gpu
+def test_transforms_without_a_rule_are_refused():
+    path = torch.randn(2, 5, 3, device="cuda")
+    layer = lambda p: autograd.signature(p, 2)   # noqa: E731
+    for call in (lambda: torch.vmap(layer)(torch.stack([path, path])), lambda: torch.func.grad(lambda p: layer(p).sum())(path),
+                 lambda: torch.func.jvp(layer, (path,), (path,))):
+        with pytest.raises(RuntimeError):
+            call()
+    with torch.autograd.forward_ad.dual_level(), pytest.raises(NotImplementedError):
+        layer(torch.autograd.forward_ad.make_dual(path, path))
+    path.requires_grad_(True)
+    out = layer(path)
+    with pytest.raises(RuntimeError):
+        torch.autograd.grad(out, path, torch.ones((3,) + out.shape, device="cuda"), is_grads_batched=True)
