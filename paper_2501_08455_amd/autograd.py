@@ -9,9 +9,33 @@ import torch
 from . import binding
 
 
+class _Traced(torch.autograd.Function):
+    """The layer while torch.jit.trace is recording: the tracer keeps a Function as one operation of the graph, but sees nothing
+    of a native call except the allocation of its result."""
+
+    @staticmethod
+    def forward(ctx, path, depth, stream):
+        path = path.contiguous()
+        out = binding.signature(path, depth, stream=stream)
+        ctx.save_for_backward(path, out)
+        ctx.depth, ctx.stream = int(depth), bool(stream)
+        return out
+
+    @staticmethod
+    def backward(ctx, grad_out):
+        path, out = ctx.saved_tensors
+        grad_path = torch.empty_like(path)
+        rc = binding.sig_backward(binding.default_ctx(), path, ctx.depth, int(ctx.stream), out, grad_out.contiguous(), grad_path)
+        if rc != binding.SIG_OK:
+            raise binding.SigError(rc, "sig_backward")
+        return grad_path, None, None
+
+
 def signature(path, depth, stream=False):
     """Depth-`depth` signatures of `path` (float32 CUDA tensor [B, L, d]) with gradient support:
     [B, D], or [B, L-1, D] with stream=True."""
+    if torch.jit.is_tracing():
+        return _Traced.apply(path, depth, stream)
     return (binding._torch_lib or binding.torch_lib()).autograd_signature(path, depth, stream)
 
 

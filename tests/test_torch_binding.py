@@ -1,5 +1,6 @@
 """The native torch binding (csrc/sig_torch.cpp): what it refuses, the autograd node's bookkeeping, and torch's own machinery
-around it (checkpointing, saved-tensor hooks, dispatch modes, compiled autograd, transforms that it has to refuse).
+around it (checkpointing, saved-tensor hooks, dispatch modes, compiled autograd, jit.trace,
+transforms that it has to refuse).
 
 Results of the layer are checked against the oracle elsewhere (test_gpu_training_step.py, test_gpu_backward.py); here the
 gradient only has to be the one sig_backward gives, bit for bit: the node calls the same kernels on the same values.
@@ -164,3 +165,18 @@ def test_transforms_without_a_rule_are_refused():
     out = layer(path)
     with pytest.raises(RuntimeError):
         torch.autograd.grad(out, path, torch.ones((3,) + out.shape, device="cuda"), is_grads_batched=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("stream", [False, True])
+def test_traced_modules_compute_the_signature_of_their_own_input(stream):
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    first, other = (torch.randn(3, 21, 4, device="cuda", generator=gen).cumsum(1) * 0.1 for _ in range(2))
+    traced = torch.jit.trace(lambda p: 2.0 * autograd.signature(p, 3, stream=stream), (first,), check_trace=False)
+    for base in (first, other):
+        path, plain = base.clone().requires_grad_(True), base.clone().requires_grad_(True)
+        got, want = traced(path), 2.0 * autograd.signature(plain, 3, stream=stream)
+        assert torch.equal(got, want)
+        got.square().sum().backward()
+        want.square().sum().backward()
+        assert torch.equal(path.grad, plain.grad)
