@@ -19,15 +19,20 @@
  *     it alive until the HIP stream has passed the call;
  *   - `hip_stream` is a hipStream_t passed as void* (NULL = the default
  *     stream), so that this header needs no HIP include.  All work is enqueued
- *     on it and the call returns without synchronising -- with one exception:
- *     a call that needs more context scratch than any earlier call on the
- *     context waits for the device, frees the old buffer and allocates a larger
- *     one (callers that must not allocate or wait size the scratch with one
+ *     on it and the call returns without synchronising -- with two exceptions:
+ *     the first call that uses context scratch on a second stream (see below),
+ *     and a call that needs more context scratch than any earlier call on the
+ *     context, which waits for the device, frees the old buffer and allocates a
+ *     larger one (callers that must not allocate or wait size the scratch with one
  *     eager call of the largest shape first, or use sig_compute_noalloc);
  *   - nothing is thrown, printed or aborted across this boundary: every
  *     failure is a return code (enum below) and leaves `out` unspecified;
- *   - a context owns reusable device scratch, so one context serves one stream
- *     at a time; calls on the same stream are ordered by the stream.
+ *   - a context owns reusable device scratch.  Host threads may share it, and so
+ *     may streams: a call that uses the scratch on another stream than the last
+ *     such call is ordered behind that one on the device (the first time with a
+ *     wait for the device).  Calls that a HIP graph has captured use the scratch
+ *     whenever the graph runs: ordering its replays with other calls on the
+ *     context that use scratch is the caller's part;
  *   - results are deterministic for a fixed plan (no atomics, fixed combine order).
  */
 #ifndef SIG_H

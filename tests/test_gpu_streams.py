@@ -1,7 +1,11 @@
 """Stream semantics of the C ABI on the GPU: every entry point enqueues on the stream it is given and returns
-without synchronising, multi-launch plans stay ordered on that stream, and a call whose scratch is already
-sized can be captured into a HIP graph and replayed (results compared with eager calls and with the oracle).
+without synchronising, multi-launch plans stay ordered on that stream, streams and host threads may share a context,
+and a call whose scratch is already sized can be captured into a HIP graph and replayed (results compared with eager
+calls and with the oracle).
 """
+import ctypes
+import threading
+
 import numpy as np
 import pytest
 
@@ -203,3 +207,126 @@ def test_pointers_that_are_only_float_aligned(gpu, oracle):
         err = np.linalg.norm(gx.cpu().numpy() - want) / np.linalg.norm(want)
         say("  shifted pointers, gradient (%d, %d): %.2e" % (d, depth, err))
         assert err <= TOL
+
+
+# calls that keep something in context scratch: forward segments joined by a second launch, the level-scan family, the
+# gradient cut into time segments, the general gradient
+SCRATCH = [(128, 2000, 5, 4, 0, False), (48, 200, 12, 3, 1, False), (3, 300, 7, 5, 0, True), (40, 60, 12, 3, 1, True)]
+
+
+def scratch_call(gpu, ctx, i, seed):
+    """Input of call number i and the call itself, as out = call(stream)."""
+    import torch
+    B, L, d, depth, stream_flag, backward = SCRATCH[i % len(SCRATCH)]
+    gen = torch.Generator(device="cuda").manual_seed(seed + i)
+    x = (torch.randn(B, L, d, device="cuda", generator=gen) * L ** -0.5).cumsum(1)
+    D = gpu.sig_size(d, depth)
+    rows = (B, L - 1, D) if stream_flag else (B, D)
+    if not backward:
+        def forward(stream):
+            out = torch.full(rows, float("nan"), device="cuda")
+            assert gpu.sig_compute(ctx, x, depth, stream_flag, out, stream=stream) == gpu.SIG_OK
+            return out
+        return forward
+    out, g = torch.empty(rows, device="cuda"), torch.randn(rows, device="cuda", generator=gen)
+    assert gpu.sig_compute(ctx, x, depth, stream_flag, out) == gpu.SIG_OK
+    torch.cuda.synchronize()
+
+    def gradient(stream):
+        gx = torch.full(x.shape, float("nan"), device="cuda")
+        assert gpu.sig_backward(ctx, x, depth, stream_flag, out, g, gx, stream=stream) == gpu.SIG_OK
+        return gx
+    return gradient
+
+
+def serial(calls):
+    import torch
+    want = []
+    for call in calls:
+        want.append(call(torch.cuda.current_stream()))
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(want[-1]).all())
+    return want
+
+
+def test_two_streams_share_a_context(gpu):
+    """Calls that use the scratch on two streams with nothing to order them but the context: the same bits as one after the
+    other.  The streams alternate, then one of them has the context to itself for a while, then they alternate again."""
+    import torch
+    ctx = gpu.sig_create()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    turns = [0, 1] * 12 + [0] * 70 + [1, 0] * 8
+    try:
+        for first in range(len(SCRATCH)):
+            some = [scratch_call(gpu, ctx, first + i, 200) for i in range(8)]
+            calls = [some[i % 8] for i in range(len(turns))]
+            torch.cuda.synchronize()
+            got = []
+            for call, turn in zip(calls, turns):
+                with torch.cuda.stream(streams[turn]):
+                    got.append(call(streams[turn]))
+            torch.cuda.synchronize()
+            for i, (a, b) in enumerate(zip(got, serial(calls))):
+                assert torch.equal(a, b), (first, i, SCRATCH[(first + i) % len(SCRATCH)])
+    finally:
+        torch.cuda.synchronize()
+        gpu.sig_destroy(ctx)
+
+
+def test_host_threads_share_a_context(gpu):
+    """Four threads, each with a stream of its own, on a context whose scratch has to grow under way."""
+    import torch
+    calls_ctx, ctx = gpu.sig_create(), gpu.sig_create()
+    try:
+        n, each = 4, 12
+        calls = [[scratch_call(gpu, ctx, t + i, 300 + 50 * t) for i in range(each)] for t in range(n)]
+        want = [serial([scratch_call(gpu, calls_ctx, t + i, 300 + 50 * t) for i in range(each)]) for t in range(n)]
+        got, failed = [[None] * each for _ in range(n)], []
+        torch.cuda.synchronize()
+        start = threading.Barrier(n)
+
+        def work(t):
+            try:
+                stream = torch.cuda.Stream()
+                start.wait(30)
+                with torch.cuda.stream(stream):
+                    for i, call in enumerate(calls[t]):
+                        got[t][i] = call(stream)
+                stream.synchronize()
+            except BaseException as e:   # reported by the test's own thread
+                failed.append(e)
+        threads = [threading.Thread(target=work, args=(t,)) for t in range(n)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join(60)
+        assert not failed, failed
+        for t in range(n):
+            for i in range(each):
+                assert torch.equal(got[t][i], want[t][i]), (t, i)
+    finally:
+        torch.cuda.synchronize()
+        gpu.sig_destroy(ctx)
+        gpu.sig_destroy(calls_ctx)
+
+
+def test_a_stream_that_is_gone_does_not_hold_the_context(gpu):
+    """The last stream that used the scratch has been destroyed: the next call, on another one, still runs."""
+    import torch
+    hip = gpu.load()   # its dependencies resolve HIP's own entry points
+    ctx = gpu.sig_create()
+    try:
+        calls = [scratch_call(gpu, ctx, i, 400) for i in range(2)]
+        want = serial(calls)
+        for i, call in enumerate(calls):
+            handle = ctypes.c_void_p()
+            assert hip.hipStreamCreate(ctypes.byref(handle)) == 0
+            torch.cuda.synchronize()
+            kept = call(handle.value)
+            assert hip.hipStreamSynchronize(handle) == 0 and hip.hipStreamDestroy(handle) == 0
+            got = call(torch.cuda.current_stream())
+            torch.cuda.synchronize()
+            assert torch.equal(got, want[i]) and torch.equal(kept, want[i])
+    finally:
+        torch.cuda.synchronize()
+        gpu.sig_destroy(ctx)
