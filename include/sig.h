@@ -22,7 +22,8 @@
  *     on it and the call returns without synchronising -- with two exceptions:
  *     the first call that uses context scratch on a second stream (see below),
  *     and a call that needs more context scratch than any earlier call on the
- *     context, which waits for the device, frees the old buffer and allocates a
+ *     context, which waits for the device, frees the old buffer (unless a HIP
+ *     graph has captured its use: then it stays until sig_destroy) and allocates a
  *     larger one (callers that must not allocate or wait size the scratch with one
  *     eager call of the largest shape first, or use sig_compute_noalloc);
  *   - nothing is thrown, printed or aborted across this boundary: every
@@ -32,7 +33,8 @@
  *     such call is ordered behind that one on the device (the first time with a
  *     wait for the device).  Calls that a HIP graph has captured use the scratch
  *     whenever the graph runs: ordering its replays with other calls on the
- *     context that use scratch is the caller's part;
+ *     context that use scratch is the caller's part (and so is destroying the
+ *     context only when the graph has run for the last time);
  *   - results are deterministic for a fixed plan (no atomics, fixed combine order).
  */
 #ifndef SIG_H

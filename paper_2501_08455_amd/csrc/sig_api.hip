@@ -15,6 +15,12 @@ struct TunedPlan {
     sig_plan_t plan;
 };
 
+// scratch that a captured graph still uses
+struct KeptScratch {
+    float *scratch;
+    KeptScratch *next;
+};
+
 struct sig_ctx {
     int device;
     int num_cu;
@@ -22,6 +28,8 @@ struct sig_ctx {
     mutable std::mutex lock;       // over everything below
     float *scratch;        // partial signatures of time segments, [B][segments][D]
     size_t scratch_bytes;
+    bool scratch_captured;         // a graph holds its address: it stays until the context goes
+    KeptScratch *kept;             // ... outgrown buffers of this kind
     hipStream_t scratch_stream;    // of the last call that used the scratch
     bool scratch_used;             // ... since it was allocated
     bool scratch_shared;           // several streams use it: scratch_event marks the end of the last call (see Scratch)
@@ -693,8 +701,14 @@ public:
     int get(sig_ctx *ctx, size_t bytes, hipStream_t st, float **p)
     {
         hold_ = std::unique_lock<std::mutex>(ctx->lock);
-        int rc = grow(ctx, bytes);
-        if (rc == SIG_OK) rc = order(ctx, st);
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        int rc = hipStreamIsCapturing(st, &capture) == hipSuccess ? grow(ctx, bytes) : SIG_ERR_HIP;
+        // Launches that are being captured run when their graph does, and a capture takes no event from outside it: the
+        // order of a graph's replays and other calls is the caller's (sig.h).
+        if (rc == SIG_OK) {
+            if (capture != hipStreamCaptureStatusNone) ctx->scratch_captured = true;
+            else rc = order(ctx, st);
+        }
         if (rc == SIG_ERR_HIP) (void)hipGetLastError();
         *p = ctx->scratch;
         return rc;
@@ -706,13 +720,18 @@ private:
     static int grow(sig_ctx *ctx, size_t bytes)
     {
         if (bytes <= ctx->scratch_bytes) return SIG_OK;
-        if (ctx->scratch) {
+        if (ctx->scratch && ctx->scratch_captured) {
+            KeptScratch *k = new (std::nothrow) KeptScratch{ctx->scratch, ctx->kept};
+            if (!k) return SIG_ERR_ALLOC;
+            ctx->kept = k;
+        } else if (ctx->scratch) {
             // earlier launches may still read the old buffer
             if (hipDeviceSynchronize() != hipSuccess) return SIG_ERR_HIP;
             (void)hipFree(ctx->scratch);
-            ctx->scratch = nullptr;
-            ctx->scratch_bytes = 0;
         }
+        ctx->scratch = nullptr;
+        ctx->scratch_bytes = 0;
+        ctx->scratch_captured = false;
         void *p = nullptr;
         if (hipMalloc(&p, bytes) != hipSuccess) {
             (void)hipGetLastError();
@@ -729,11 +748,6 @@ private:
         // (hipStreamPerThread is another stream in every thread)
         const bool same = ctx->scratch_used && ctx->scratch_stream == st && st != hipStreamPerThread;
         if (same && !ctx->scratch_shared) return SIG_OK;
-        // Launches that are being captured run when their graph does, and a capture takes no event from outside it: the
-        // order of a graph's replays and other calls is the caller's (sig.h).
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(st, &capture) != hipSuccess) return SIG_ERR_HIP;
-        if (capture != hipStreamCaptureStatusNone) return SIG_OK;
         if (same) {
             if (++ctx->scratch_calls >= kAloneCalls) ctx->scratch_shared = false;
         } else if (ctx->scratch_used) {
@@ -872,6 +886,8 @@ int sig_create(sig_ctx **ctx)
     c->num_cu = cus;
     c->scratch = nullptr;
     c->scratch_bytes = 0;
+    c->scratch_captured = false;
+    c->kept = nullptr;
     c->scratch_stream = nullptr;
     c->scratch_used = false;
     c->scratch_shared = false;
@@ -894,9 +910,12 @@ int sig_create(sig_ctx **ctx)
 void sig_destroy(sig_ctx *ctx)
 {
     if (!ctx) return;
-    if (ctx->scratch) {
-        (void)hipDeviceSynchronize();
-        (void)hipFree(ctx->scratch);
+    if (ctx->scratch || ctx->kept) (void)hipDeviceSynchronize();
+    if (ctx->scratch) (void)hipFree(ctx->scratch);
+    while (KeptScratch *k = ctx->kept) {
+        ctx->kept = k->next;
+        (void)hipFree(k->scratch);
+        delete k;
     }
     if (ctx->scratch_event) (void)hipEventDestroy(ctx->scratch_event);
     delete ctx;

@@ -330,3 +330,31 @@ def test_a_stream_that_is_gone_does_not_hold_the_context(gpu):
     finally:
         torch.cuda.synchronize()
         gpu.sig_destroy(ctx)
+
+
+def test_a_captured_call_survives_a_larger_one(gpu):
+    """A graph keeps the address of the scratch it was captured with: an eager call that outgrows it leaves it in place."""
+    import torch
+    ctx = gpu.sig_create()
+    try:
+        x = torch.randn(4, 400, 5, device="cuda").cumsum(1) * 0.05
+        large = torch.randn(512, 2000, 5, device="cuda").cumsum(1) * 0.02
+        plan = gpu.make_plan(gpu.SIG_VARIANT_ON_CHIP, prefix_depth=2, chunks=4, segments=4)   # partial rows in scratch
+        out = torch.empty((4, gpu.sig_size(5, 4)), device="cuda")
+        assert gpu.sig_compute(ctx, x, 4, 0, out, plan=plan) == gpu.SIG_OK
+        want = out.clone()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            assert gpu.sig_compute(ctx, x, 4, 0, out, plan=plan) == gpu.SIG_OK
+        first = torch.empty((512, out.shape[1]), device="cuda")
+        for _ in range(2):
+            assert gpu.sig_compute(ctx, large, 4, 0, first, plan=plan) == gpu.SIG_OK   # 128 times the scratch
+            taken = torch.full((1 << 20,), 7.0, device="cuda")
+            out.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want) and bool((taken == 7.0).all())
+    finally:
+        torch.cuda.synchronize()
+        gpu.sig_destroy(ctx)
