@@ -66,7 +66,8 @@ enum sig_variant {
     SIG_VARIANT_HBM_STREAMING = 1,
     /* state lives in registers: each lane owns the words below one prefix of length `prefix_depth`
      * and runs the fused multiply-by-exponential of Eq. 3 over its time chunk; chunks of one path
-     * are joined by Eq. 4 products; only for the compiled (d, depth, prefix_depth) combinations */
+     * are joined by Eq. 4 products; only for the compiled (d, depth, prefix_depth) combinations (those of more than ten
+     * channels in final mode only) */
     SIG_VARIANT_ON_CHIP = 2,
     /* the level-by-level formulation of the paper's Section 3.2 (Eqs. 6-10): one launch per level, each a
      * cumulative sum over time of per-step terms built from the lower levels of every prefix; those live in
@@ -266,7 +267,7 @@ int sig_backward_available(int d, int depth);
  */
 int sig_backward_segments(const sig_ctx *ctx, int64_t B, int64_t L, int d, int depth, int stream_flag);
 
-/* 1 if an on-chip kernel is compiled for (d, depth, prefix_depth), else 0.  Host only. */
+/* 1 if an on-chip kernel is compiled for (d, depth, prefix_depth) (more than ten channels: for final mode), else 0.  Host only. */
 int sig_on_chip_available(int d, int depth, int prefix_depth);
 
 /* Static, NUL-terminated description of a status code. */

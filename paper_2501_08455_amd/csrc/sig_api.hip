@@ -125,6 +125,7 @@ bool finish_on_chip(const OnChipKernelInfo *ki, int cus, int64_t B, int64_t L, i
                           : (stream_flag && Q <= kWave) ? (int64_t)(pl.threads / kWave) * (kWave / Q)
                                                         : pl.threads / Q;
     if (Q <= pl.threads && pl.chunks > slots) return false;
+    if (stream_flag && ki->final_only) return false;
     if (stream_flag && pl.segments != 1) return false;       // carries across workgroups are not implemented
     // rows of the segments that do not fit the LDS of a join kernel are joined in device memory by a pairwise
     // tree of batched row products: a power of two of them
@@ -313,8 +314,7 @@ constexpr double kSegmentCostFactor = 1.7;    // segments of a nearly empty chip
 constexpr double kSegmentOccupancyWaves = 2.0;  // segments on a busy chip: this many wavefronts per SIMD over the chunks' own
 constexpr int kMaxLdsJoinSegments = 8;
 constexpr int kFillByChunksMinSteps = 200;    // from this many increments on, never fewer chunks than fill the chip (final mode)
-constexpr int kMostChannels = 10;             // of the shapes that take their on-chip kernels at every batch, in both modes
-constexpr int kWideMinPaths = 16;             // from this many paths on the others do, in final mode,
+constexpr int kWideMinPaths = 16;             // on-chip kernels of more than ten channels: from this many paths on,
 constexpr int kWideMostSteps = 128;           // in chunks of at most this many steps
 }  // namespace tune
 
@@ -413,8 +413,8 @@ int plan_auto(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const R
     *pl = sig_plan_t{};
     pl->threads = kThreads;
 
-    const bool on_chip = B > 0 && (rs.d <= tune::kMostChannels || wide_on_chip_wanted(B, stream_flag));
-    const OnChipKernelInfo *ki = on_chip ? pick_on_chip(rs.d, rs.depth, stream_flag, B, K, cus) : nullptr;
+    const OnChipKernelInfo *ki = (B > 0) ? pick_on_chip(rs.d, rs.depth, stream_flag, B, K, cus) : nullptr;
+    if (ki && ki->final_only && !wide_on_chip_wanted(B, stream_flag)) ki = nullptr;
     if (ki) {
         const int Q = ki->lanes_per_chunk;
         const int state = ki->state_floats;
@@ -522,7 +522,7 @@ int plan_auto(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const R
                 if (tree >= 4 && tree >= 4 * W) W = tree;
             }
             // more than ten channels: chunks of at most kWideMostSteps steps (see wide_on_chip_wanted)
-            if (rs.d > tune::kMostChannels && ceil_div(K, C * W) > tune::kWideMostSteps) {
+            if (ki->final_only && ceil_div(K, C * W) > tune::kWideMostSteps) {
                 W = ceil_div(K, C * tune::kWideMostSteps);
                 if (W > tune::kMaxLdsJoinSegments) W = tune::kMaxLdsJoinSegments;
                 while (W > 1 && !join_fits_lds(ki, (int)W, rs)) --W;
@@ -614,7 +614,7 @@ int plan_auto(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const R
                 if (c != want.chunks) pl->segments = 1;
                 OnChipArgs args{};
                 if (finish_on_chip(ki, cus, B, L, stream_flag, *pl, rs, &args)) {
-                    if (rs.d > tune::kMostChannels && args.chunk_steps > tune::kWideMostSteps) return take_level_scan();
+                    if (ki->final_only && args.chunk_steps > tune::kWideMostSteps) return take_level_scan();
                     if (prefer_level_scan(*pl)) return take_level_scan();
                     pl->tile_steps = args.tile_steps;
                     return SIG_OK;

@@ -1425,10 +1425,12 @@ void on_chip_launch_pipe(const OnChipArgs &A, dim3 g, dim3 blk, size_t lds, hipS
     hipLaunchKernelGGL((sig_on_chip_kernel<d, N, P, CHUNKED, STREAM, false>), g, blk, lds, st, A);
 }
 
-template <int d, int N, int P>
+// FINAL_ONLY: compiled without the kernels of stream mode
+template <int d, int N, int P, bool FINAL_ONLY = false>
 hipError_t on_chip_launch(const OnChipArgs &A, hipStream_t st)
 {
     using Sh = Shape<d, N, P>;
+    if (FINAL_ONLY && A.stream_flag) return hipErrorInvalidValue;
     const int64_t ngroups = A.B * A.segments;
     if (Sh::Q <= A.threads) {
         if (A.groups < 1) return hipErrorInvalidValue;
@@ -1459,20 +1461,19 @@ hipError_t on_chip_launch(const OnChipArgs &A, hipStream_t st)
             return hipErrorInvalidValue;
         }
     }
-    if (A.chunks > 1) {
-        const dim3 g((unsigned)grid);
-        if (A.stream_flag) on_chip_launch_pipe<d, N, P, true, true>(A, g, blk, (size_t)lds, st);
-        else on_chip_launch_pipe<d, N, P, true, false>(A, g, blk, (size_t)lds, st);
-    } else if (A.cooperative) {
-        const dim3 g((unsigned)grid);
-        if (A.stream_flag) on_chip_launch_pipe<d, N, P, false, true>(A, g, blk, (size_t)lds, st);
-        else on_chip_launch_pipe<d, N, P, false, false>(A, g, blk, (size_t)lds, st);
-    } else {
-        // persistent: no more workgroups than stay resident, each walking the same number of work items
-        const dim3 g((unsigned)grid);
-        if (A.stream_flag) hipLaunchKernelGGL((sig_fold_kernel<d, N, P, true>), g, blk, (size_t)lds, st, A);
-        else hipLaunchKernelGGL((sig_fold_kernel<d, N, P, false>), g, blk, (size_t)lds, st, A);
+    const dim3 g((unsigned)grid);
+    if constexpr (!FINAL_ONLY) {
+        if (A.stream_flag) {
+            if (A.chunks > 1) on_chip_launch_pipe<d, N, P, true, true>(A, g, blk, (size_t)lds, st);
+            else if (A.cooperative) on_chip_launch_pipe<d, N, P, false, true>(A, g, blk, (size_t)lds, st);
+            else hipLaunchKernelGGL((sig_fold_kernel<d, N, P, true>), g, blk, (size_t)lds, st, A);
+            return hipGetLastError();
+        }
     }
+    if (A.chunks > 1) on_chip_launch_pipe<d, N, P, true, false>(A, g, blk, (size_t)lds, st);
+    else if (A.cooperative) on_chip_launch_pipe<d, N, P, false, false>(A, g, blk, (size_t)lds, st);
+    // (persistent: no more workgroups than stay resident, each walking the same number of work items)
+    else hipLaunchKernelGGL((sig_fold_kernel<d, N, P, false>), g, blk, (size_t)lds, st, A);
     return hipGetLastError();
 }
 
@@ -1573,12 +1574,14 @@ hipError_t on_chip_join_any(const float *partial, float *out, int64_t B, int W, 
     else return on_chip_join<d, N>(partial, out, B, W, st);
 }
 
-#define SIG_ON_CHIP_ENTRY(d, N, P)                                                              \
+#define SIG_ON_CHIP_ENTRY_IN(d, N, P, FINAL_ONLY)                                               \
     {                                                                                           \
         d, N, P, ::sig::onchip::Shape<d, N, P>::Q, ::sig::onchip::Shape<d, N, P>::SZ,           \
-            d, &::sig::onchip::on_chip_launch<d, N, P>,         \
-            &::sig::onchip::on_chip_lds_bytes<d, N, P>, &::sig::onchip::on_chip_join_any<d, N, P> \
+            d, &::sig::onchip::on_chip_launch<d, N, P, FINAL_ONLY>,                             \
+            &::sig::onchip::on_chip_lds_bytes<d, N, P>, &::sig::onchip::on_chip_join_any<d, N, P>, FINAL_ONLY \
     }
+#define SIG_ON_CHIP_ENTRY(d, N, P) SIG_ON_CHIP_ENTRY_IN(d, N, P, false)
+#define SIG_ON_CHIP_FINAL_ENTRY(d, N, P) SIG_ON_CHIP_ENTRY_IN(d, N, P, true)
 
 }  // namespace onchip
 }  // namespace sig

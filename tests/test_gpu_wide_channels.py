@@ -1,6 +1,7 @@
 """The on-chip kernels of more than ten channels (csrc/sig_onchip_table_wide.hip), every compiled shape in final mode against
 the fp64 oracle: whole paths side by side with a ragged last workgroup, chunks of a path side by side, and paths cut
-across workgroups, with lengths that leave remainders.  The gate is the library's 1e-4 per level."""
+across workgroups, with lengths that leave remainders; then every form of a plan that sig_compute_planned accepts for them.
+The gate is the library's 1e-4 per level."""
 import numpy as np
 import pytest
 
@@ -17,6 +18,19 @@ def test_planner_takes_the_compiled_kernel(d, depth):
         assert binding.sig_plan_validate(B, L, d, depth, 0, pl) == binding.SIG_OK
 
 
+@pytest.mark.parametrize("d,depth", SHAPES, ids=lambda v: str(v))
+def test_stream_mode_refuses_the_compiled_kernel(d, depth):
+    """As the planner does not take it there, no explicit plan may ask for it."""
+    for B, L in [(1, 2), (17, 40), (4096, 100)]:
+        rc, pl = binding.sig_plan(None, B, L, d, depth, 1)
+        assert rc == binding.SIG_OK and pl.variant == binding.SIG_VARIANT_LEVEL_SCAN
+        for chunks in (1, 2, 4):
+            for waves in (0, 1):
+                plan = binding.make_plan(binding.SIG_VARIANT_ON_CHIP, prefix_depth=depth - 1, chunks=chunks, independent_waves=waves)
+                assert binding.sig_plan_validate(B, L, d, depth, 1, plan) == binding.SIG_ERR_INVALID
+                assert binding.sig_plan_footprint(B, L, d, depth, 1, plan)[0] == binding.SIG_ERR_INVALID
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("d,depth", SHAPES, ids=lambda v: str(v))
 def test_against_the_oracle(oracle, d, depth):
@@ -29,11 +43,69 @@ def test_against_the_oracle(oracle, d, depth):
         out = torch.full((B, binding.sig_size(d, depth)), float("nan"), device="cuda")
         assert binding.sig_compute(binding.default_ctx(), torch.from_numpy(x).cuda(), depth, 0, out) == binding.SIG_OK
         assert bool(torch.isfinite(out).all())
-        rows = sorted({0, 1, 7, B // 2, B - 2, B - 1})
-        got, want = out[rows].cpu().numpy().astype(np.float64), oracle.signature(x[rows], depth)
-        start = 0
-        for n in range(1, depth + 1):
-            sl = slice(start, start + d ** n)
-            err = np.linalg.norm(got[:, sl] - want[:, sl], axis=1) / np.linalg.norm(want[:, sl], axis=1)
-            assert float(err.max()) <= 1e-4, (B, L, n, float(err.max()))
-            start += d ** n
+        check_rows(oracle, x, out, d, depth, (B, L))
+
+
+def check_rows(oracle, x, out, d, depth, label):
+    B = x.shape[0]
+    rows = sorted({0, 1, 7, B // 2, B - 2, B - 1} & set(range(B)))
+    got, want = out[rows].cpu().numpy().astype(np.float64), oracle.signature(x[rows], depth)
+    start = 0
+    for n in range(1, depth + 1):
+        sl = slice(start, start + d ** n)
+        err = np.linalg.norm(got[:, sl] - want[:, sl], axis=1) / np.linalg.norm(want[:, sl], axis=1)
+        assert float(err.max()) <= 1e-4, (label, n, float(err.max()))
+        start += d ** n
+
+
+# fields of a plan; the ones a shape cannot hold (more chunks than its lanes leave room for) are refused by the host checks
+FORMS = [dict(), dict(independent_waves=1), dict(independent_waves=1, tile_steps=5), dict(tile_steps=7, tile_loader=1),
+         dict(tile_steps=7, tile_loader=2), dict(chunks=2, threads=512), dict(chunks=3, tile_steps=4, tile_loader=1),
+         dict(chunks=3, tile_steps=4, tile_loader=2), dict(segments=2), dict(segments=3, chunks=2, threads=512), dict(segments=4),
+         dict(segments=16), dict(threads=192), dict(stagger_ticks=50)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,depth", SHAPES, ids=lambda v: str(v))
+def test_explicit_plans_against_the_oracle(oracle, d, depth):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    ctx, ran = binding.default_ctx(), 0
+    for B, L in [(3, 70), (131, 41)]:
+        x = workloads.brownian_paths(B, L, d, seed=9700 + d + L)
+        path = torch.from_numpy(x).cuda()
+        for form in FORMS:
+            plan = binding.make_plan(binding.SIG_VARIANT_ON_CHIP, prefix_depth=depth - 1, **form)
+            out = torch.full((B, binding.sig_size(d, depth)), float("nan"), device="cuda")
+            if binding.sig_plan_validate(B, L, d, depth, 0, plan) != binding.SIG_OK:
+                assert binding.sig_compute(ctx, path, depth, 0, out, plan=plan) == binding.SIG_ERR_INVALID, form
+                continue
+            print("explicit plan: %d paths of %d points, (%d,%d), %s" % (B, L, d, depth, form), flush=True)
+            assert binding.sig_compute(ctx, path, depth, 0, out, plan=plan) == binding.SIG_OK, form
+            assert bool(torch.isfinite(out).all()), form
+            check_rows(oracle, x, out, d, depth, (B, L, form))
+            ran += 1
+    assert ran >= 12
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,depth,B,L,stream", [(12, 3, 4, 30, 0), (20, 2, 9, 200, 0), (11, 3, 9, 40, 1), (16, 2, 5, 60, 1)])
+def test_tuned_plans(oracle, d, depth, B, L, stream):
+    """What sig_autotune settles on, with fewer paths than the planner asks for and in stream mode."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    ctx = binding.sig_create()
+    try:
+        x = workloads.brownian_paths(B, L, d, seed=9800 + d)
+        rc, plan, _ = binding.sig_autotune(ctx, B, L, d, depth, stream)
+        assert rc == binding.SIG_OK and (not stream or plan.variant != binding.SIG_VARIANT_ON_CHIP)
+        D = binding.sig_size(d, depth)
+        out = torch.full((B, L - 1, D) if stream else (B, D), float("nan"), device="cuda")
+        assert binding.sig_compute(ctx, torch.from_numpy(x).cuda(), depth, stream, out) == binding.SIG_OK
+        got, want = out.cpu().numpy().astype(np.float64), oracle.signature(x, depth, stream=bool(stream))
+        assert np.linalg.norm(got - want) <= 1e-4 * np.linalg.norm(want)
+    finally:
+        torch.cuda.synchronize()
+        binding.sig_destroy(ctx)
