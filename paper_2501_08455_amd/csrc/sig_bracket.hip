@@ -81,32 +81,52 @@ hipError_t launch(const Args &A0, int cus, hipStream_t st)
     return hipGetLastError();
 }
 
+// How a depth-2 launch is cut: a point per thread, twice over where the batch fills the chip anyway; whole short paths side
+// by side, as far as 16 KB of LDS hold their matrices.  A launch holds fewer than 2^32 threads: beyond, more points each.
+template <int d>
+bool cut_depth2(Args &A, int cus, int64_t *grid)
+{
+    constexpr int64_t kMostWorkgroups = ((int64_t)1 << 32) / kDepth2Threads - 1;
+    int64_t want = A.B * A.L >= (int64_t)cus * 8 * kDepth2Threads * 4 ? 2 * kDepth2Threads : kDepth2Threads;
+    for (; want <= (int64_t)1 << 24; want *= 2) {
+        A.segs = 1;
+        A.groups = 1;
+        if (A.L >= want) {
+            const int64_t segs = (A.L + want - 1) / want;
+            if (segs > kMostWorkgroups / A.B) continue;
+            A.steps = (int32_t)want;
+            A.segs = (int32_t)segs;
+            *grid = A.B * segs;
+        } else {
+            int64_t paths = want / A.L;
+            const int64_t by_lds = 16384 / (depth2_floats<d>(1) * (int64_t)sizeof(float));
+            if (paths > by_lds) paths = by_lds;
+            if (paths < 1) paths = 1;
+            A.groups = (int32_t)paths;
+            *grid = (A.B + paths - 1) / paths;
+        }
+        if (*grid <= kMostWorkgroups) return true;
+    }
+    return false;
+}
+
 template <int d>
 hipError_t launch_depth2(const Args &A0, int cus, hipStream_t st)
 {
     Args A = A0;
-    if (A.B <= 0 || A.L < 2 || A.L / kDepth2Threads > INT32_MAX - 1) return hipErrorInvalidValue;
-    // a point per thread, twice over where the batch fills the chip anyway; whole short paths side by side
-    const int64_t want = A.B * A.L >= (int64_t)cus * 8 * kDepth2Threads * 4 ? 2 * kDepth2Threads : kDepth2Threads;
-    A.segs = 1;
-    A.groups = 1;
-    int64_t grid;
-    if (A.L >= want) {
-        A.steps = (int32_t)want;
-        A.segs = (int32_t)((A.L + want - 1) / want);
-        grid = A.B * A.segs;
-    } else {
-        int64_t paths = want / A.L;
-        const int64_t by_lds = 16384 / (depth2_floats<d>(1) * (int64_t)sizeof(float));
-        if (paths > by_lds) paths = by_lds;
-        if (paths < 1) paths = 1;
-        A.groups = (int32_t)paths;
-        grid = (A.B + paths - 1) / paths;
-    }
-    if (grid > INT32_MAX) return hipErrorInvalidValue;
+    int64_t grid = 0;
+    if (A.B <= 0 || A.L < 2 || !cut_depth2<d>(A, cus, &grid)) return hipErrorInvalidValue;
     const size_t lds = (size_t)depth2_floats<d>(A.groups) * sizeof(float);
     hipLaunchKernelGGL((sig_bracket_depth2_kernel<d>), dim3((unsigned)grid), dim3(kDepth2Threads), lds, st, A);
     return hipGetLastError();
+}
+
+template <int d>
+bool depth2_geometry(Args &A, int cus, int64_t *grid, int64_t *lds_bytes)
+{
+    if (!cut_depth2<d>(A, cus, grid)) return false;
+    *lds_bytes = depth2_floats<d>(A.groups) * (int64_t)sizeof(float);
+    return true;
 }
 
 struct Entry {
@@ -123,7 +143,16 @@ struct Entry {
 #define SIG_BRACKET_ENTRY(d, N, P) {d, N, most_chunks<Geo<d, N, P>>(), Geo<d, N, P>::D, &launch<d, N, P>},
 #define SIG_BRACKET_DEPTH2(X) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16) X(17) X(18) X(19) X(20)
 #define SIG_BRACKET_DEPTH2_ENTRY(d) {d, 2, 0, d + d * d, &launch_depth2<d>},
+#define SIG_BRACKET_DEPTH2_GEOMETRY(d_) case d_: return depth2_geometry<d_>(A, cus, grid, lds_bytes);
 const Entry kEntries[] = {SIG_BRACKET_DEPTH2(SIG_BRACKET_DEPTH2_ENTRY) SIG_BRACKET_SHAPES(SIG_BRACKET_ENTRY){0, 0, 0, 0, nullptr}};
+
+bool depth2_geometry_of(int d, Args &A, int cus, int64_t *grid, int64_t *lds_bytes)
+{
+    switch (d) {
+        SIG_BRACKET_DEPTH2(SIG_BRACKET_DEPTH2_GEOMETRY)
+    default: return false;
+    }
+}
 
 const Entry *find(int d, int depth)
 {
@@ -148,6 +177,20 @@ int bracket_segments(int d, int depth, int64_t B, int64_t L, int cus)
     if (W > 4 * (int64_t)cus / B) W = 4 * (int64_t)cus / B;
     if (W > 32) W = 32;
     return W < 2 ? 1 : (int)W;
+}
+
+// the launch of the depth-2 gradient, for tests of the host side: workgroups, stretches and paths of each, bytes of LDS
+bool bracket_depth2_geometry(int d, int64_t B, int64_t L, int cus, int64_t *grid, int64_t *segs, int64_t *steps, int64_t *groups,
+                             int64_t *lds_bytes)
+{
+    bracket::Args A{};
+    A.B = B;
+    A.L = L;
+    const bool ok = B > 0 && L >= 2 && bracket::depth2_geometry_of(d, A, cus, grid, lds_bytes);
+    *segs = A.segs;
+    *steps = A.steps;
+    *groups = A.groups;
+    return ok;
 }
 
 hipError_t launch_bracket(const float *path, const float *sig, const float *grad_out, float *grad_path, int64_t B, int64_t L,

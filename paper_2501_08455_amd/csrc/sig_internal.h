@@ -105,6 +105,8 @@ constexpr int64_t bracket_min_points(int d, int depth)
 inline bool bracket_wanted(int d, int depth, int64_t L) { return bracket_compiled(d, depth) && L >= bracket_min_points(d, depth); }
 // workgroups a path's steps are cut across (1: not cut)
 int bracket_segments(int d, int depth, int64_t B, int64_t L, int cus);
+bool bracket_depth2_geometry(int d, int64_t B, int64_t L, int cus, int64_t *grid, int64_t *segs, int64_t *steps, int64_t *groups,
+                             int64_t *lds_bytes);
 hipError_t launch_bracket(const float *path, const float *sig, const float *grad_out, float *grad_path, int64_t B, int64_t L,
                           int d, int depth, int segs, int cus, hipStream_t st);
 

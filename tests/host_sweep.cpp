@@ -9,6 +9,11 @@
 
 #include "sig.h"
 
+namespace sig {   // csrc/sig_internal.h
+bool bracket_depth2_geometry(int d, int64_t B, int64_t L, int cus, int64_t *grid, int64_t *segs, int64_t *steps, int64_t *groups,
+                             int64_t *lds_bytes);
+}
+
 static uint64_t state = 0x9E3779B97F4A7C15ull;
 static uint64_t rnd()
 {
@@ -85,6 +90,24 @@ int main()
             for (int64_t B : {(int64_t)1, (int64_t)100, (int64_t)1 << 45})
                 for (int64_t L : {(int64_t)2, (int64_t)1000, (int64_t)1 << 50})
                     for (int stream = 0; stream < 2; ++stream) one_shape(B, L, d, depth, stream);
+
+    // ---- the launch of the depth-2 gradient: every point has its workgroup, and a launch holds fewer than 2^32 threads,
+    // for every batch that a GPU of 288 GB could hold (path and its gradient, the rows and theirs)
+    for (int it = 0; it < 20000; ++it) {
+        const int d = 2 + (int)(rnd() % 19);
+        const int64_t L = it & 1 ? pick(Ls, sizeof Ls / sizeof *Ls) : 2 + (int64_t)(rnd() % 3000);
+        if (L < 2) continue;
+        int64_t B = it & 2 ? (int64_t)1 << (rnd() % 33) : 1 + (int64_t)(rnd() % ((uint64_t)1 << (1 + rnd() % 33)));
+        const int64_t most = ((int64_t)288 << 30) / (8 * (L * d + d + d * d));
+        if (B > most) B = most;
+        if (B < 1) continue;
+        int64_t grid = 0, segs = 0, steps = 0, groups = 0, lds = 0;
+        const bool ok = sig::bracket_depth2_geometry(d, B, L, 256, &grid, &segs, &steps, &groups, &lds);
+        EXPECT(ok && grid >= 1 && grid * 256 < (int64_t)1 << 32 && lds <= 64 * 1024, "depth 2, d=%d B=%lld L=%lld: %d grid %lld lds %lld", d, (long long)B, (long long)L, ok, (long long)grid, (long long)lds);
+        if (segs > 1) EXPECT(grid == B * segs && groups == 1 && segs * steps >= L && (segs - 1) * steps < L, "stretches: d=%d B=%lld L=%lld %lld x %lld", d, (long long)B, (long long)L, (long long)segs, (long long)steps);
+        else EXPECT(grid * groups >= B && (grid - 1) * groups < B, "paths: d=%d B=%lld L=%lld grid %lld x %lld", d, (long long)B, (long long)L, (long long)grid, (long long)groups);
+        ++checked;
+    }
 
     // ---- arbitrary plans through the checks: they may be refused, they must not misbehave
     for (int it = 0; it < 20000; ++it) {
