@@ -291,7 +291,8 @@ bool finish_on_chip(const OnChipKernelInfo *ki, int cus, int64_t B, int64_t L, i
             }
         }
     }
-    return true;
+    // a launch holds fewer than 2^32 threads
+    return on_chip_workgroups(Q, *args) < ((int64_t)1 << 32) / pl.threads;
 }
 
 // Constants of the planner, each fitted to timings on an MI355X (256 compute units, 2.4 GHz).  They decide between

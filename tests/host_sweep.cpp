@@ -49,6 +49,7 @@ static void one_shape(int64_t B, int64_t L, int d, int depth, int stream)
         EXPECT(lds <= 64 * 1024, "LDS %lld bytes: B=%lld L=%lld d=%d depth=%d stream=%d", (long long)lds, (long long)B, (long long)L, d, depth, stream);
         EXPECT(wgs <= INT32_MAX && (wgs >= 1 || wgs == -1 || B == 0), "workgroups %lld", (long long)wgs);
         EXPECT(scratch >= 0, "scratch %lld", (long long)scratch);
+        if (pl.variant == SIG_VARIANT_ON_CHIP) EXPECT(wgs * pl.threads < (int64_t)1 << 32, "%lld workgroups of %d threads: B=%lld L=%lld d=%d depth=%d stream=%d", (long long)wgs, pl.threads, (long long)B, (long long)L, d, depth, stream);
     }
     if (pl.variant == SIG_VARIANT_ON_CHIP) {
         EXPECT(pl.threads >= 64 && pl.threads <= 512 && pl.threads % 64 == 0, "threads %d", pl.threads);
