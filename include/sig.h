@@ -89,7 +89,8 @@ enum sig_variant {
  *   chunks        time chunks of one path folded concurrently inside one workgroup (>= 1)
  *   segments      workgroups per path along time (>= 1); partial signatures of segments are joined by a second
  *                 launch when all rows of a path fit the LDS of a join kernel, else (a power of two of at most 32
- *                 segments) by a pairwise tree of batched Eq. 4 products in device memory, one launch per round
+ *                 segments) by a pairwise tree of batched Eq. 4 products in device memory, one launch per round; a
+ *                 batch whose partial rows exceed 8 GiB is taken in equal slices of paths that share the scratch
  *   threads       workgroup size (multiple of 64)
  *   tile_steps    increments staged through LDS per tile by the loader (0: chosen by the library)
  *   independent_waves  with chunks == 1: 0 = workgroup-wide tiles of increments (the default, faster in every

@@ -375,19 +375,36 @@ const OnChipKernelInfo *pick_on_chip(int d, int depth, int stream_flag, int64_t 
     return best;
 }
 
-// The level-scan family keeps the levels below the top one of every prefix in scratch: a batch whose tensors would
-// exceed 8 GiB is taken in equal slices of paths, one after the other on the caller's stream, which share the
-// buffer (a slice of that size fills the chip many times over, so nothing is lost but the memory).
-constexpr int64_t kLevelScanSliceFloats = (int64_t)1 << 31;
+// A batch whose scratch would exceed 8 GiB is taken in equal slices of paths, one after the other on the caller's stream,
+// which share the buffer (a slice of that size fills the chip many times over, so nothing is lost but the memory).
+constexpr int64_t kSliceFloats = (int64_t)1 << 31;
 
-int64_t level_scan_slice_paths(int64_t B, int64_t L, const RowShape &rs, int stream_flag)
+int64_t slice_paths(int64_t B, int64_t floats_per_path)
 {
-    const int64_t per_path = level_scan_scratch_floats(1, L, rs, stream_flag);
-    if (B <= 1 || per_path <= 0 || per_path <= kLevelScanSliceFloats / B) return B;
-    int64_t paths = kLevelScanSliceFloats / per_path;
+    if (B <= 1 || floats_per_path <= 0 || floats_per_path <= kSliceFloats / B) return B;
+    int64_t paths = kSliceFloats / floats_per_path;
     if (paths < 1) paths = 1;
     const int64_t slices = ceil_div(B, paths);
     return ceil_div(B, slices);
+}
+
+// the level-scan family keeps the levels below the top one of every prefix in scratch
+int64_t level_scan_slice_paths(int64_t B, int64_t L, const RowShape &rs, int stream_flag)
+{
+    return slice_paths(B, level_scan_scratch_floats(1, L, rs, stream_flag));
+}
+
+// Scratch of B paths whose time segments another launch joins: their partial rows, and for the join in device memory two more
+// buffers of half and a quarter of the rows.
+int64_t segment_floats(const OnChipKernelInfo *ki, int64_t B, int segments, const RowShape &rs)
+{
+    if (segments <= 1) return 0;
+    const int64_t rows = B * segments * rs.D;
+    return join_fits_lds(ki, segments, rs) ? rows : rows + rows / 2 + rows / 4 + 4;
+}
+int64_t segment_slice_paths(const OnChipKernelInfo *ki, int64_t B, int segments, const RowShape &rs)
+{
+    return slice_paths(B, segment_floats(ki, 1, segments, rs));
 }
 
 // the level-scan family takes chunks >= 0 and ignores the other mapping fields
@@ -637,7 +654,7 @@ int plan_auto(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const R
         ls.threads = kThreads;
         ls.segments = 1;
         if (check_level_scan(B, L, rs, stream_flag, ls) == SIG_OK &&
-            level_scan_scratch_floats(1, L, rs, stream_flag) <= kLevelScanSliceFloats) {
+            level_scan_scratch_floats(1, L, rs, stream_flag) <= kSliceFloats) {
             *pl = ls;
             return SIG_OK;
         }
@@ -817,34 +834,41 @@ int run_plan(sig_ctx *ctx, const float *path, int64_t B, int64_t L, const RowSha
     if (!ki) return SIG_ERR_INVALID;
     OnChipArgs args{};
     if (!finish_on_chip(ki, ctx->num_cu, B, L, stream_flag, pl, rs, &args)) return SIG_ERR_INVALID;
-    args.path = path;
-    args.out = out;
-    args.partial = nullptr;
     const bool lds_join = pl.segments > 1 && join_fits_lds(ki, pl.segments, rs);
-    const size_t rows = (size_t)B * pl.segments * rs.D;   // floats of the partial rows
+    const int64_t S = segment_slice_paths(ki, B, pl.segments, rs);
     float *work = nullptr;
     if (pl.segments > 1) {
-        // (the tree in device memory ping-pongs between two more buffers of half and a quarter of the rows)
-        int rc = get_scratch(ctx, scratch, fixed, (lds_join ? rows : rows + rows / 2 + rows / 4 + 4) * sizeof(float), st, &work);
+        int rc = get_scratch(ctx, scratch, fixed, (size_t)segment_floats(ki, S, pl.segments, rs) * sizeof(float), st, &work);
         if (rc != SIG_OK) return rc;
-        args.partial = work;
     }
-    hipError_t e = ki->launch(args, st);
-    if (e != hipSuccess) return SIG_ERR_HIP;
-    if (lds_join) {
-        e = ki->join(work, out, B, pl.segments, st);
+    for (int64_t b0 = 0; b0 < B; b0 += S) {   // (one slice, but for batches whose partial rows exceed 8 GiB)
+        const int64_t nb = B - b0 < S ? B - b0 : S;
+        if (nb != B) {
+            args = OnChipArgs{};
+            if (!finish_on_chip(ki, ctx->num_cu, nb, L, stream_flag, pl, rs, &args)) return SIG_ERR_INVALID;
+        }
+        float *const slice_out = out + b0 * rs.D;   // (S < B only in final mode: stream mode has one segment)
+        args.path = path + b0 * L * rs.d;
+        args.out = slice_out;
+        args.partial = work;
+        hipError_t e = ki->launch(args, st);
         if (e != hipSuccess) return SIG_ERR_HIP;
-    } else if (pl.segments > 1) {
-        // round r joins neighbours: row 2 i (x) row 2 i + 1 of the previous round's rows, the last round into `out`
-        const float *in = work;
-        float *buf[2] = {work + rows, work + rows + rows / 2};
-        int which = 0;
-        for (int64_t n = pl.segments; n > 1; n /= 2) {
-            float *dst = n == 2 ? out : buf[which];
-            e = launch_combine_rows(in, 2 * rs.D, in + rs.D, 2 * rs.D, dst, rs.D, B * (n / 2), rs, st);
+        if (lds_join) {
+            e = ki->join(work, slice_out, nb, pl.segments, st);
             if (e != hipSuccess) return SIG_ERR_HIP;
-            in = dst;
-            which ^= 1;
+        } else if (pl.segments > 1) {
+            // round r joins neighbours: row 2 i (x) row 2 i + 1 of the previous round's rows, the last round into `out`
+            const size_t rows = (size_t)nb * pl.segments * rs.D;   // floats of the partial rows
+            const float *in = work;
+            float *buf[2] = {work + rows, work + rows + rows / 2};
+            int which = 0;
+            for (int64_t n = pl.segments; n > 1; n /= 2) {
+                float *dst = n == 2 ? slice_out : buf[which];
+                e = launch_combine_rows(in, 2 * rs.D, in + rs.D, 2 * rs.D, dst, rs.D, nb * (n / 2), rs, st);
+                if (e != hipSuccess) return SIG_ERR_HIP;
+                in = dst;
+                which ^= 1;
+            }
         }
     }
     return SIG_OK;
@@ -983,10 +1007,7 @@ int sig_plan_footprint(int64_t B, int64_t L, int d, int depth, int stream_flag, 
         if (!ki || !finish_on_chip(ki, kDefaultCUs, B, L, stream_flag, *plan, rs, &args)) return SIG_ERR_INVALID;
         lds = ki->lds_bytes(args);
         wgs = B > 0 ? on_chip_workgroups(ki->lanes_per_chunk, args) : 0;
-        if (plan->segments > 1) {
-            const int64_t rows = B * plan->segments * rs.D;
-            scratch = (join_fits_lds(ki, plan->segments, rs) ? rows : rows + rows / 2 + rows / 4 + 4) * (int64_t)sizeof(float);
-        }
+        if (B > 0) scratch = segment_floats(ki, segment_slice_paths(ki, B, plan->segments, rs), plan->segments, rs) * (int64_t)sizeof(float);
     } else {
         return SIG_ERR_INVALID;
     }
@@ -1062,7 +1083,7 @@ int sig_autotune(sig_ctx *ctx, int64_t B, int64_t L, int d, int depth, int strea
         ls.threads = kThreads;
         ls.segments = 1;
         if (base.variant != SIG_VARIANT_LEVEL_SCAN && check_level_scan(B, L, rs, stream_flag, ls) == SIG_OK &&
-            level_scan_scratch_floats(1, L, rs, stream_flag) <= kLevelScanSliceFloats)
+            level_scan_scratch_floats(1, L, rs, stream_flag) <= kSliceFloats)
             cand[n++] = ls;
     }
     for (int p = 0; p < depth && n < 20; ++p) {

@@ -48,7 +48,7 @@ static void one_shape(int64_t B, int64_t L, int d, int depth, int stream)
     if (f == SIG_OK) {
         EXPECT(lds <= 64 * 1024, "LDS %lld bytes: B=%lld L=%lld d=%d depth=%d stream=%d", (long long)lds, (long long)B, (long long)L, d, depth, stream);
         EXPECT(wgs <= INT32_MAX && (wgs >= 1 || wgs == -1 || B == 0), "workgroups %lld", (long long)wgs);
-        EXPECT(scratch >= 0, "scratch %lld", (long long)scratch);
+        EXPECT(scratch >= 0 && scratch <= (int64_t)8 << 30, "scratch %lld: B=%lld L=%lld d=%d depth=%d stream=%d segments=%d", (long long)scratch, (long long)B, (long long)L, d, depth, stream, pl.segments);
         if (pl.variant == SIG_VARIANT_ON_CHIP) EXPECT(wgs * pl.threads < (int64_t)1 << 32, "%lld workgroups of %d threads: B=%lld L=%lld d=%d depth=%d stream=%d", (long long)wgs, pl.threads, (long long)B, (long long)L, d, depth, stream);
     }
     if (pl.variant == SIG_VARIANT_ON_CHIP) {
@@ -83,6 +83,10 @@ int main()
         const int64_t B = (int64_t)(rnd() % 3000), L = (int64_t)(rnd() % 5000);
         const int d = (int)(rnd() % 300), depth = (int)(rnd() % 12), stream = (int)(rnd() % 3) - (int)(rnd() % 2);
         one_shape(B, L, d, depth, stream);
+    }
+    for (int it = 0; it < 4000; ++it) {   // more than ten channels: large batches and long paths
+        const int d = 11 + (int)(rnd() % 10), depth = d <= 12 && (rnd() & 1) ? 3 : 2;
+        one_shape((int64_t)1 << (rnd() % 25), 2 + (int64_t)(rnd() % ((uint64_t)1 << (1 + rnd() % 14))), d, depth, (int)(rnd() % 2));
     }
     const int ds[] = {1, 2, 10, 255, 256, 257, 8192, 8193, 100000};
     const int depths[] = {1, 2, 8, 9, 29, 30, 31, 64};

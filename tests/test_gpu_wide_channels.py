@@ -109,3 +109,35 @@ def test_tuned_plans(oracle, d, depth, B, L, stream):
     finally:
         torch.cuda.synchronize()
         binding.sig_destroy(ctx)
+
+
+@pytest.mark.gpu
+def test_batches_whose_partial_rows_exceed_the_scratch_limit_go_in_slices(oracle):
+    """150,001 paths of 900 points, (12,3): eight segments, 9.0 GB of partial rows, two slices.  Every path gives the bits that
+    it gives in a batch of its own slice's neighbours under the same plan."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    B, L, d, depth = 150001, 900, 12, 3
+    rc, plan = binding.sig_plan(None, B, L, d, depth, 0)
+    assert rc == binding.SIG_OK and plan.variant == binding.SIG_VARIANT_ON_CHIP and plan.segments == 8
+    D = binding.sig_size(d, depth)
+    rc, _, _, scratch = binding.sig_plan_footprint(B, L, d, depth, 0, plan)
+    S = scratch // (4 * plan.segments * D)
+    assert rc == binding.SIG_OK and scratch <= 8 << 30 and S == 75001
+    ctx = binding.sig_create()
+    try:
+        gen = torch.Generator(device="cuda").manual_seed(9900)
+        path = torch.randn((B, L, d), device="cuda", generator=gen).mul_(L ** -0.5)
+        torch.cumsum(path, 1, out=path)
+        out = torch.full((B, D), float("nan"), device="cuda")
+        assert binding.sig_compute(ctx, path, depth, 0, out) == binding.SIG_OK
+        assert bool(torch.isfinite(out).all())
+        for lo in (0, S - 40, B - 80):   # the ends, and across the border of the slices
+            part = torch.empty((80, D), device="cuda")
+            assert binding.sig_compute(ctx, path[lo:lo + 80], depth, 0, part, plan=plan) == binding.SIG_OK
+            assert torch.equal(part, out[lo:lo + 80]), lo
+            check_rows(oracle, path[lo:lo + 80].cpu().numpy(), part, d, depth, lo)
+    finally:
+        torch.cuda.synchronize()
+        binding.sig_destroy(ctx)
