@@ -10,6 +10,7 @@ source, undoing one increment at a time in fp32, stays far below it for these pa
   single entries of the gradient at the first points of a path do not: measured 1.35e-4 on (d, depth) = (2, 10)).
 grad_path is poisoned with NaN before every call.
 """
+import ctypes
 import sys
 
 import numpy as np
@@ -108,7 +109,8 @@ BACKWARD_GRID = [(2, 2), (3, 2), (4, 2), (5, 2), (6, 2), (8, 2), (10, 2), (2, 3)
 
 @pytest.mark.parametrize("shape", BACKWARD_GRID, ids=lambda c: "-".join(str(v) for v in c))
 def test_backward_shape_grid(gpu, oracle, shape):
-    """Every (d, depth) with a gradient kernel: a few long paths (sweep cut in time), many short ones, stream mode."""
+    """Every (d, depth) with a register kernel: a few long paths (on brackets, but for the depths where 41 points are short),
+    many short ones, stream mode."""
     d, depth = shape
     assert gpu.sig_backward_available(d, depth) == 1
     for B, L, stream in [(3, 41, False), (300, 7, False), (4, 19, True)]:
@@ -116,7 +118,8 @@ def test_backward_shape_grid(gpu, oracle, shape):
         check(gpu, oracle, x, depth, stream, seed=d + depth + L, label="grid")
 
 
-# shapes whose lanes per path exceed one workgroup (or whose parked sums would not fit): the sliced sweep
+# shapes whose lanes per path exceed one workgroup (or whose parked sums would not fit): the sliced sweep in stream mode, and in
+# final mode where no sweep on brackets is compiled ((7,5), (8,5), (9,5), (10,5), (5,6), (10,6)) or the path is too short for it
 SLICED_GRID = [(8, 4), (10, 4), (6, 5), (4, 6), (5, 6), (10, 6), (9, 4), (7, 5), (8, 5), (9, 5), (10, 5)]
 
 
@@ -133,17 +136,17 @@ def test_backward_sliced_shapes(gpu, oracle, shape):
 
 
 def test_backward_sliced_long_paths(gpu, oracle):
-    """Long paths leave the sliced sweep less LDS for its parked sums: it parks fewer steps (down to one) before it
-    hands the shape to the general sweep."""
+    """Long paths of the sliced shapes in final mode: these three are swept on brackets (the sliced sweep itself, which long paths
+    leave less LDS for its parked sums: test_backward_sliced_parks_fewer_steps_on_long_paths)."""
     for d, depth, B, L in [(10, 4, 2, 1000), (8, 4, 1, 1600), (10, 4, 1, 1300)]:
         x = workloads.brownian_paths(B, L, d, seed=8400 + L)
-        check(gpu, oracle, x, depth, False, seed=L, label="sliced, long path")
+        check(gpu, oracle, x, depth, False, seed=L, label="sliced shape, long path")
 
 
 SEGMENTED_CASES = [
-    # d, depth, B, L: few long paths in final mode, which the library cuts in time across workgroups (segment
-    # signatures, their running products and pulled-back gradients, then one sweep per segment); lengths that leave
-    # a ragged last segment, both kernel families, one and several paths
+    # d, depth, B, L: few long paths in final mode, cut in time across workgroups: on brackets, but for (10,5), whose
+    # segments keep signatures, running products and pulled-back gradients (more of these: ON_SIGNATURES); lengths that
+    # leave a ragged last segment, one and several paths
     (5, 4, 1, 1000), (5, 4, 3, 777), (2, 3, 2, 4001), (4, 4, 5, 500), (3, 5, 2, 600), (5, 5, 1, 300), (9, 3, 2, 450),
     (6, 4, 1, 130), (7, 4, 2, 513), (8, 4, 1, 400), (10, 4, 3, 333), (6, 5, 1, 200), (4, 6, 2, 260), (9, 4, 1, 129),
     (10, 5, 1, 150), (2, 6, 4, 2000),
@@ -158,7 +161,8 @@ def test_backward_few_long_paths_cut_in_time(gpu, oracle, case):
 
 
 def test_backward_cut_in_time_reproducible_and_next_to_uncut_calls(gpu, oracle):
-    """The segment rows live in context scratch: the same bits twice, with an uncut call and a stream call between."""
+    """Final mode on brackets, which keeps nothing in context scratch: the same bits twice, with an uncut call and a stream call
+    between."""
     x = workloads.brownian_paths(2, 900, 5, seed=78)
     a = check(gpu, oracle, x, 4, False, seed=5, label="cut in time, first")
     check(gpu, oracle, x[:, :40], 4, False, seed=6, label="uncut call")
@@ -168,7 +172,8 @@ def test_backward_cut_in_time_reproducible_and_next_to_uncut_calls(gpu, oracle):
 
 
 def test_backward_sliced_reproducible_and_after_a_larger_call(gpu, oracle):
-    """The per-slice sums live in context scratch: a smaller call after a larger one, and the same bits twice."""
+    """A shape that stream mode sweeps in slices, with per-slice sums in context scratch: a smaller call after a larger one in
+    final mode (on brackets), and the same bits twice."""
     x = workloads.brownian_paths(6, 30, 10, seed=77)
     a = check(gpu, oracle, x, 4, False, seed=3, label="sliced, first")
     check(gpu, oracle, x[:2, :9], 4, True, seed=4, label="sliced, smaller call")
@@ -177,7 +182,7 @@ def test_backward_sliced_reproducible_and_after_a_larger_call(gpu, oracle):
 
 
 # shapes without a compiled register kernel: the general sweep (state of a path in LDS, or in device scratch for the
-# last three), one channel, depth 1, more channels than coefficients per level allow to vectorise, deep and narrow
+# last three; the final mode of (11,2), (11,3), (12,3) and (20,2) is swept on brackets), one channel, depth 1, more channels than coefficients per level allow to vectorise, deep and narrow
 GENERAL_SHAPES = [(11, 2), (11, 3), (7, 6), (1, 5), (12, 1), (12, 3), (3, 8), (2, 10), (20, 2), (64, 2), (3, 7), (6, 6),
                   (12, 4)]
 
@@ -193,9 +198,9 @@ def test_backward_general_sweep(gpu, oracle, shape):
 
 def test_backward_paths_too_long_for_one_workgroup(gpu, oracle):
     """Paths whose increments exceed the LDS staging of the register kernels (here 3,500 to 20,000 points in five
-    channels): final mode cuts them into time segments (also when the batch alone would fill the chip: 300 paths),
-    stream mode walks them in tiles within one workgroup.  The sweep undoes one increment at a time in fp32, so its
-    error grows with the length: measured against the same 1e-4 gate."""
+    channels): final mode sweeps them on brackets, at any length, stream mode walks them in tiles within one workgroup.
+    That one undoes one increment at a time in fp32, so its error grows with the length: measured against the same 1e-4
+    gate."""
     for B, L, stream in [(2, 5000, False), (1, 20000, False), (300, 3500, False), (1, 4000, True)]:
         x = workloads.brownian_paths(B, L, 5, seed=8300 + L)
         check(gpu, oracle, x, 4, stream, seed=L, label="long path")
@@ -205,8 +210,9 @@ def test_backward_paths_too_long_for_one_workgroup(gpu, oracle):
                                   (10, 2, 2, 60000, False), (10, 3, 3, 40001, True), (5, 2, 600, 3500, True)], ids=lambda c: "-".join(str(v) for v in c))
 def test_backward_walks_long_paths_in_tiles(gpu, oracle, case):
     """Paths too long for LDS where the sweep is not cut across workgroups — stream mode of the sliced shapes at a
-    batch that fills the chip (checked on its first paths), and paths too long even for 32 segments in either mode:
-    one workgroup walks tiles of 256 increments (ragged last tile, several paths per workgroup)."""
+    batch that fills the chip (checked on its first paths), and paths too long even for 32 segments: one workgroup
+    walks tiles of 256 increments (ragged last tile, several paths per workgroup).  (Final mode: the depth-2 kernel on
+    brackets, at the same length.)"""
     d, depth, B, L, stream = case
     assert gpu.sig_backward_segments(None, B, L, d, depth, int(stream)) == 1
     if B <= 8:
@@ -246,6 +252,58 @@ def test_backward_stream_mode_cut_in_time(gpu, oracle, case):
     assert gpu.sig_backward_segments(None, B, L, d, depth, 1) > 1
     x = workloads.brownian_paths(B, L, d, seed=8700 + 3 * L + d)
     check(gpu, oracle, x, depth, True, seed=L + depth, label="stream, cut in time")
+
+
+def launches(gpu, call):
+    """Kernels that `call` launches: the nodes of a graph that captures it (its scratch has to be sized before)."""
+    import torch
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    count = ctypes.c_size_t(0)
+    status = gpu.load().hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count))
+    assert status == 0
+    return count.value
+
+
+# d, depth, B, L, fewest launches: final mode on signatures, of shapes that have no sweep on brackets.  The sliced sweep is two
+# launches (sums per slice, then d(loss)/dX); cut into W time segments it is the fold, one launch per round of the scan
+# (log2 W rounds), the pulled-back gradients, the sweep and the sums.
+ON_SIGNATURES = [(10, 5, 3, 20, 2), (7, 5, 40, 30, 2), (5, 6, 5, 41, 2), (8, 5, 60, 9, 2), (9, 5, 2, 12, 2),
+                 (7, 5, 2, 300, 6), (7, 5, 1, 1000, 6), (8, 5, 3, 260, 6), (5, 6, 1, 200, 6), (9, 5, 1, 140, 6), (10, 5, 1, 150, 6)]
+
+
+@pytest.mark.parametrize("case", ON_SIGNATURES, ids=lambda c: "-".join(str(v) for v in c))
+def test_backward_final_mode_on_signatures(gpu, oracle, case):
+    """The sliced sweep and its cut into time segments, which keep their sums and rows in context scratch: parity, the same bits
+    again after other calls have used the scratch, and the number of launches that says which of the two it was."""
+    import torch
+    d, depth, B, L, fewest = case
+    x = workloads.brownian_paths(B, L, d, seed=8900 + 3 * L + d)
+    first = check(gpu, oracle, x, depth, False, seed=L, label="on signatures")
+    check(gpu, oracle, workloads.brownian_paths(1, 300, 5, seed=7), 4, True, seed=7, label="stream call between")
+    check(gpu, oracle, x[:1, :4], depth, False, seed=8, label="smaller call between")
+    np.testing.assert_array_equal(first, check(gpu, oracle, x, depth, False, seed=L, label="on signatures, again"))
+    assert (gpu.sig_backward_segments(None, B, L, d, depth, 0) > 1) == (fewest > 2)
+    xt = torch.from_numpy(x).cuda()
+    out = gpu.signature(xt, depth)
+    g, gx = torch.ones_like(out), torch.empty_like(xt)
+    call = lambda: gpu.sig_backward(gpu.default_ctx(), xt, depth, 0, out, g, gx)   # noqa: E731
+    assert call() == gpu.SIG_OK
+    n = launches(gpu, call)
+    say("  %d launches" % n)
+    assert n == 2 if fewest == 2 else n >= fewest
+
+
+def test_backward_sliced_parks_fewer_steps_on_long_paths(gpu, oracle):
+    """Long paths leave the sliced sweep less LDS for its parked sums: it parks fewer steps (down to one) before it hands the
+    shape to the general sweep.  Enough paths that they are not cut into segments; the oracle on three of them."""
+    for d, depth, B, L in [(7, 5, 600, 400), (7, 5, 520, 900), (8, 5, 300, 700)]:
+        assert gpu.sig_backward_segments(None, B, L, d, depth, 0) == 1
+        x = workloads.brownian_paths(B, L, d, seed=8400 + L)
+        say("backward case sliced, long path, d=%d depth=%d B=%d L=%d" % (d, depth, B, L))
+        sampled_backward(gpu, oracle, x, depth, False, [0, B // 2, B - 1], seed=L)
 
 
 def test_backward_on_the_configurations(gpu, oracle):
@@ -352,15 +410,15 @@ def test_backward_saturated_variants_sampled(gpu, oracle, name, B):
 
 
 @pytest.mark.parametrize("d,depth,L,B,stream", [
-    (5, 4, 700, 5400, False),     # 25 lanes per path, four paths' increments per workgroup: walked in tiles
-    (4, 4, 1200, 8300, False),    # 16 lanes per path: walked in tiles
-    (4, 3, 500, 33000, False),    # four lanes per path: cut in time inside the workgroup
+    (5, 4, 700, 5400, False),     # final mode, here and below: on brackets
+    (4, 4, 1200, 8300, False),
+    (4, 3, 500, 33000, False),
     (10, 2, 500, 1700, True),     # ten lanes per path, stream mode: cut in time inside the workgroup
     (5, 4, 700, 700, True),       # stream mode, 25 lanes per path: walked in tiles
     # the same kind of shape with paths short enough for the plain sweep to keep enough lanes on a CU: not cut
     (2, 6, 128, 8200, True),      # two lanes per path, stream mode (pipelined fetch would not apply: the chip is full)
     (3, 4, 256, 8200, True),      # three lanes per path, stream mode
-    (5, 3, 128, 33000, False),    # five lanes per path, final mode
+    (5, 3, 128, 33000, False),
     (3, 3, 500, 8200, True),      # stream mode, depth 3 with too few lanes left: still cut in time
     # few-lane kernels whose LDS holds fewer paths than a workgroup has lanes for, on batches that need the plain sweep's
     # resident workgroups several times over: walked in short tiles

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from paper_2501_08455_amd import workloads
-from test_gpu_backward import check, gpu, sampled_backward, say  # noqa: F401  (gpu is a fixture)
+from test_gpu_backward import check, gpu, launches, sampled_backward, say  # noqa: F401  (gpu is a fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +56,19 @@ def test_the_gradient_of_a_translation_vanishes(gpu):
     worst = float((total.abs() / size).max())
     say("sum of a path's gradients over the sum of their magnitudes: %.1e" % worst)
     assert np.isfinite(worst) and worst <= 2.0 ** -18
+
+
+@pytest.mark.parametrize("d,depth,B,L", [(5, 4, 128, 100), (5, 4, 8200, 40), (10, 4, 2, 900), (12, 3, 93, 50), (20, 2, 7, 600),
+                                         (4, 6, 2, 90), (6, 5, 128, 500)])
+def test_one_launch_and_no_scratch(gpu, d, depth, B, L):
+    """What tells the sweep on brackets from the others: a context that has no scratch gets none, under capture too."""
+    import torch
+    x = torch.from_numpy(workloads.brownian_paths(B, L, d, seed=9400 + L)).cuda()
+    out = gpu.signature(x, depth)
+    g, gx = torch.randn_like(out), torch.empty_like(x)
+    ctx = gpu.sig_create()
+    try:
+        assert launches(gpu, lambda: gpu.sig_backward(ctx, x, depth, 0, out, g, gx)) == 1
+    finally:
+        torch.cuda.synchronize()
+        gpu.sig_destroy(ctx)

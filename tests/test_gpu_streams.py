@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 
 from paper_2501_08455_amd import workloads
+from test_gpu_backward import launches
 from test_gpu_parity import TOL, gpu, level_errors, say  # noqa: F401  (gpu is a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -54,8 +55,9 @@ def test_backward_on_a_side_stream(gpu, oracle):
     side = torch.cuda.Stream()
     ctx = gpu.sig_create()
     try:
-        # the second shape takes the two-launch sliced sweep, the third the sweep cut into time segments (nine launches)
-        for d, depth, B, L in [(5, 4, 9, 60), (10, 4, 3, 20), (8, 4, 2, 300)]:
+        # on brackets (one launch; the third cut across workgroups), then the two-launch sliced sweep and the sweep cut into time
+        # segments (eight launches)
+        for d, depth, B, L in [(5, 4, 9, 60), (10, 4, 3, 20), (8, 4, 2, 300), (10, 5, 3, 20), (7, 5, 2, 300)]:
             x = workloads.brownian_paths(B, L, d, seed=92 + d)
             g = np.random.default_rng(d).normal(size=(B, gpu.sig_size(d, depth))).astype(np.float32)
             want = oracle.signature_backward(x, depth, g)
@@ -113,11 +115,11 @@ def test_graph_capture_and_replay(gpu, oracle):
         gpu.sig_destroy(ctx)
 
 
-def test_graph_capture_of_the_paths_cut_in_time(gpu, oracle):
-    """The multi-launch paths for few long paths — forward segments joined in device memory (six launches here) and
-    the gradient cut into time segments (nine) — captured together and replayed with new inputs."""
+@pytest.mark.parametrize("B,L,d,depth,gradient_launches", [(2, 900, 10, 4, 1), (2, 600, 7, 5, 6)])
+def test_graph_capture_of_the_paths_cut_in_time(gpu, oracle, B, L, d, depth, gradient_launches):
+    """The paths for few long paths — forward segments joined in device memory by several launches, and the gradient cut in
+    time, on brackets in one launch and on signatures in six or more — captured together and replayed with new inputs."""
     import torch
-    B, L, d, depth = 2, 900, 10, 4
     D = gpu.sig_size(d, depth)
     ctx = gpu.sig_create()
     try:
@@ -134,6 +136,9 @@ def test_graph_capture_of_the_paths_cut_in_time(gpu, oracle):
             assert gpu.sig_backward(ctx, xt, depth, 0, out, gt, gx) == gpu.SIG_OK
 
         both()   # sizes the scratch
+        assert launches(gpu, lambda: gpu.sig_compute(ctx, xt, depth, 0, out)) >= 4
+        n = launches(gpu, lambda: gpu.sig_backward(ctx, xt, depth, 0, out, gt, gx))
+        assert n == 1 if gradient_launches == 1 else n >= gradient_launches
         torch.cuda.synchronize()
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph):
@@ -191,9 +196,11 @@ def test_pointers_that_are_only_float_aligned(gpu, oracle):
         say("  shifted pointers, %s, %s: %s" % (name, "auto" if plan is None else "variant %d" % plan.variant,
                                                 " ".join("%.2e" % e for e in errs)))
         assert max(errs) <= TOL
-    # gradient: register kernel (5, 4), sliced sweep (10, 4), general sweep (11, 2), sweep cut into time segments
+    # gradient: on brackets, also cut across workgroups; register kernel (4, 4) and general sweep (11, 2) in stream mode; on
+    # signatures the sliced sweep (10, 5) and the sweep cut into time segments (7, 5), in stream mode (10, 4)
     for d, depth, B, L, stream in [(5, 4, 9, 60, False), (4, 4, 5, 40, True), (10, 4, 3, 20, False), (11, 2, 4, 15, True),
-                                   (10, 4, 1, 200, False), (6, 4, 2, 301, False)]:
+                                   (10, 4, 1, 200, False), (6, 4, 2, 301, False), (10, 5, 2, 20, False), (7, 5, 1, 200, False),
+                                   (10, 4, 1, 600, True)]:
         x = workloads.brownian_paths(B, L, d, seed=95 + d)
         D = gpu.sig_size(d, depth)
         rows = (B, L - 1, D) if stream else (B, D)
