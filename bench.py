@@ -135,17 +135,35 @@ def bench_config(binding, workloads, ctx, cfg, B, steps, warmup, plan=None, labe
     return res
 
 
+def swept_on_brackets(d, depth):
+    """The shapes whose final-mode gradient is swept on Lie brackets (include/sig.h, sig_backward; the workloads here are
+    longer than the paths it leaves to the sweep on signatures)."""
+    return 2 <= d <= {2: 20, 3: 16, 4: 10, 5: 6, 6: 4}.get(depth, 0)
+
+
 def backward_work(cfg, B, workloads):
-    """(flops, bytes) of one sig_backward call.  Per increment and path: undoing the increment is one fused
-    step (2 F flops); the transposed step spends 2 FMAs per top-of-chain coefficient (sum_n d^n of them) and
-    3 FMAs + 1 add per inner chain coefficient (F - sum_n d^n of them).  Bytes: path, final signature and
-    upstream gradient read once, gradient written once."""
+    """(flops, bytes) of one sig_backward call, of the sweep that the shape takes.
+
+    On signatures, per increment and path: undoing the increment is one fused step (2 F flops); the transposed step spends
+    2 FMAs per top-of-chain coefficient (sum_n d^n of them) and 3 FMAs + 1 add per inner chain coefficient (F - sum_n d^n
+    of them).  Bytes: path, final signature and upstream gradient read once, gradient written once.
+
+    On brackets, per increment and path: level n has d^(n-2) words in front of each of the d (d-1) / 2 pairs, each contracted
+    N - n times (d FMAs) and added once per contraction; two numbers per pair of N - 1 terms, and four FMAs per pair for the two
+    points they reach.  Per path: the functional on the levels 2 .. N-1 and on level 1 at both ends, and 2^(n-1) signed words
+    for every bracket value.  Bytes: as above, without the top level of the signature."""
     K = cfg.L - 1
     d, N = cfg.d, cfg.depth
     D = workloads.sig_size(d, N)
+    rows = K if cfg.stream else 1
+    if not cfg.stream and swept_on_brackets(d, N):
+        pairs = d * (d - 1) // 2
+        step = 2.0 * pairs * (sum(d ** (n - 2) * (N - n) * (d + 1) for n in range(2, N + 1)) + 2 * (N - 1) + 4)
+        start = 2.0 * sum(d ** (n + i) for n in range(2, N) for i in range(1, N - n + 1))
+        start += 4.0 * d * sum(d ** i for i in range(1, N)) + sum(pairs * d ** (n - 2) * 2 ** (n - 1) for n in range(2, N + 1))
+        return B * (K * step + start), 4.0 * B * (2 * cfg.L * d + (D - d ** N) + D)
     F = workloads.fused_fma_per_step(d, N)
     flops = (2.0 * F + 4.0 * D + 7.0 * (F - D)) * B * K
-    rows = K if cfg.stream else 1
     nbytes = 4.0 * (2 * B * cfg.L * d + B * D + B * rows * D)
     return flops, nbytes
 
