@@ -325,8 +325,9 @@ constexpr int kWideMostSteps = 128;           // in chunks of at most this many 
 // 773 and 208, 30,000 of 60 1,472 and 352; (11,2) 128 of 2,000 106 and 17; (20,2) 512 of 130 41 and 8, 8,192 of 250 374 and
 // 106; the other 71 points 1.3-15x.  The bound on the steps keeps the rounding where it was: error against 64 bits 2.3e-7 at
 // most over those points (5.5e-7 before), 1.2e-7 at 128 paths of (12,3) as before, 0.4 to 1.2 times the other family's and
-// 0.86 in the mean; uncut folds of 500 steps were 1.5 times as far off.  Fewer than 16 paths keep their plans, which a test
-// of the planner holds, although the kernels are faster there too (4 paths of 30 points: 7.5 us against 10 to 18).
+// 0.86 in the mean; uncut folds of 500 steps were 1.5 times as far off.  16 paths are the fewest of those points, not where the
+// two meet: the kernels were faster below as well (4 paths of 30 points: 7.5 us against 10 to 18), but over the lengths only
+// the range from 16 on has been measured, and fewer paths stay with the level-scan family until it has.
 bool wide_on_chip_wanted(int64_t B, int stream_flag) { return !stream_flag && B >= tune::kWideMinPaths; }
 
 // Which compiled prefix depth to use for (d, depth); entries of one (d, depth) are ordered by increasing prefix depth.

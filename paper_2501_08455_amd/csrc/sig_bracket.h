@@ -20,9 +20,11 @@
 //
 // Work per step and path for (5,4): 10 pairs x (25 + 2 x 5) multiply-adds, against 25 lanes x some 200 instructions
 // for undoing the step on the whole signature and transposing it on its adjoint (sig_backward.hip).  Measured, sweep on the
-// signature against this one: (5,4), 100 points, 128 paths 24.7 -> 9.7 us, 65,536 paths 697 -> 188 (reading and writing what
-// it must takes 106); (4,4), 500 points, 65,536 paths 3,226 -> 420; (10,4), 100 points, 8,192 paths 2,990 -> 480;
-// (12,3), 100 points, 128 paths, against the general sweep 678 -> 13.5.
+// signature against this one: (5,4), 100 points, 128 paths 24.7 -> 9.9 us, 65,536 paths 697 -> 189 to 230 (by the card and what
+// ran before; reading and writing what it must takes 92 at the rate of a copy); (4,4), 500 points, 65,536 paths 3,226 -> 407;
+// (10,4), 100 points, 8,192 paths 2,990 -> 490; (12,3), 100 points, 128 paths, against the general sweep 678 -> 13.9.
+// Rounding, over 522 settings of 29 shapes against 64 bits: 1.5e-7 (depth 2) to 1.6e-6 (depth 6) of the gradient's norm at
+// most, 0.02 to 1.01 times the sweep on signatures' and 0.15 in the mean.
 //
 // Lanes.  A lane owns the words that end in its suffix of P letters: pre (P - 2 letters) and a pair a < b, so
 // LQ = d^{P-2} d (d-1) / 2 lanes per path, each with the levels P .. N of its words in registers
@@ -545,10 +547,13 @@ extern __shared__ __align__(16) float sig_bracket_smem[];
 
 // ------------------------------------------------------------------------------------------
 // Several whole paths per wavefront (one wavefront per workgroup, so no barrier costs anything), each walked uncut.
-// Bound by the vector instructions: per step and wavefront some 50 for the walk, 20 for the outputs and 8 for the loads
-// ((5,4): 1.1 us per step of 65,536 paths), after some 700 per path for the bracket values.  Registers decide the residency
-// (three to five wavefronts per SIMD); keeping the paths' bracket values in registers as they are formed, instead of all
-// paths' in LDS, and having the next path's rows in flight took (5,4) at 65,536 paths of 100 points from 246 to 188 us.
+// Per step and wavefront some 50 vector instructions for the walk, 20 for the outputs and 8 for the loads, after some 700 per
+// path for the bracket values.  Bound by waiting, mostly for LDS: (5,4), 100 points, 65,536 paths issue 81,000 vector
+// instructions per SIMD in 414,000 cycles (5.1 cycles each, against 2.2 where the pipe is full), the LDS is busy 70 % of
+// the time (28 % of that bank conflicts), and 531 MB move where 507 must (205 us under the counters).  Registers decide
+// the residency (135 there: three wavefronts per SIMD; two to seven over the shapes); keeping the paths' bracket values in
+// registers as they are formed, instead of all paths' in LDS, and having the next path's rows in flight took a quarter
+// off (246 -> 188 us on one card).
 template <class G>
 constexpr int packed_lds_floats()
 {

@@ -166,8 +166,9 @@ const Entry *find(int d, int depth)
 
 // Cutting a path across workgroups shortens the walk of its chunks, but every workgroup forms the bracket values again and
 // folds everything behind it: from two dozen steps a chunk on while there are few paths, twice that for more than 32, at
-// most four workgroups per compute unit, and not where the rows that are read again exceed a few megabytes.  ((9,3), five
-// paths of 1,221 points: 45 to 16 us; (6,5), 128 paths of 500 points: 149 to 89.)
+// most four workgroups per compute unit, and not where the rows that are read again exceed four megabytes.  Uncut and cut:
+// (9,3), five paths of 1,221 points 32.5 and 6.4 us; (10,4), one path of 1,000 points 123 and 47; (5,4), 128 paths of 2,000
+// points 45 and 36; (6,5), 112 paths of 500 points 153 and 144.
 int bracket_segments(int d, int depth, int64_t B, int64_t L, int cus)
 {
     const bracket::Entry *e = bracket::find(d, depth);

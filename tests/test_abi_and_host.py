@@ -78,7 +78,10 @@ def test_plan_falls_back_for_uncompiled_shapes():
         rc, pl = binding.sig_plan(None, 7, 30, 9, 6, stream)
         assert rc == binding.SIG_OK and pl.variant == binding.SIG_VARIANT_LEVEL_SCAN
         assert binding.sig_plan_validate(7, 30, 9, 6, stream, pl) == binding.SIG_OK
-        rc, pl = binding.sig_plan(None, 7, 30, 12, 3, stream)      # more than 10 channels: run-time d
+        rc, pl = binding.sig_plan(None, 7, 30, 13, 3, stream)      # more than 10 channels: run-time d
+        assert rc == binding.SIG_OK and pl.variant == binding.SIG_VARIANT_LEVEL_SCAN
+        # compiled for final mode, which takes it from 16 paths on
+        rc, pl = binding.sig_plan(None, 7, 30, 12, 3, stream)
         assert rc == binding.SIG_OK and pl.variant == binding.SIG_VARIANT_LEVEL_SCAN
         rc, pl = binding.sig_plan(None, 7, 30, 300, 2, stream)     # more channels than a workgroup has threads
         assert rc == binding.SIG_OK and pl.variant == binding.SIG_VARIANT_HBM_STREAMING

@@ -43,7 +43,7 @@ def test_depth_two(gpu, oracle, d, B, L):
     check(gpu, oracle, workloads.brownian_paths(B, L, d, seed=9200 + d + L), 2, False, seed=L, label="bracket, depth 2")
 
 
-# ||gpu - oracle||_F / ||oracle||_F of a batch: four times the largest of 522 settings (34 shapes, 16 to 2,000 points; Brownian,
+# ||gpu - oracle||_F / ||oracle||_F of a batch: four times the largest of 522 settings (29 shapes, 16 to 2,000 points; Brownian,
 # drifting, uniform, unscaled and zigzag paths) per depth: 1.5e-7, 2.0e-7, 5.7e-7, 1.1e-6, 1.6e-6.  The sweep on signatures
 # was at 1.0 to 50 times these errors, so that a sum held too short or a bracket value lost would show.
 ROUNDING = {2: 6e-7, 3: 8e-7, 4: 2.3e-6, 5: 4.4e-6, 6: 6.4e-6}
