@@ -234,7 +234,8 @@ int sig_combine(sig_ctx *ctx, const float *a, const float *b, int64_t B, int d, 
  * Final mode: two to twenty channels at depth 2, to 16 at depth 3, 10 at depth 4, 6 at depth 5 and 4 at depth 6 are swept
  * on Lie brackets (one launch, no scratch, any length): several paths per wavefront, or one path per workgroup with its
  * steps cut into chunks, or (few long paths) into up to 32 stretches swept by different workgroups.  Paths of a dozen
- * points or so at depth 4 and above (up to 70 at (4,6)) and every other shape are swept on the signature itself, as below.
+ * points or so (fewer than d at depth 2, up to 78 at (4,6); the batch moves this), few long paths of (6,5), (4,6) and
+ * (10,4), and every other shape are swept on the signature itself, as below.
  * The other sweeps start from the signature at the end and undo one increment at a time.  Shapes with a compiled register
  * kernel (see sig_backward_available) whose paths fit its LDS staging take it.  Few long paths and paths too long for that
  * staging are cut into up to 32 time segments that are swept by different workgroups: by Eq. 3 a segment can start from the
@@ -247,7 +248,8 @@ int sig_combine(sig_ctx *ctx, const float *a, const float *b, int64_t B, int d, 
  * Which sweep a call takes never changes its result beyond the rounding order.  Every shape without any of these
  * kernels, d <= 256, takes a general sweep, one workgroup per path with its state in LDS or device scratch (much
  * slower); SIG_ERR_UNSUPPORTED only for d > 256.
- * Context scratch (allocated on first use, SIG_ERR_ALLOC if that fails): shapes whose index space is cut into more
+ * Context scratch (allocated on first use, SIG_ERR_ALLOC if that fails; a shape that has a sweep on brackets takes that one
+ * where scratch would have to grow while the stream is being captured): shapes whose index space is cut into more
  * sub-trees than one workgroup has threads, and paths walked in tiles, keep per-workgroup sums
  * (B * ceil(d^p / 256) * (L-1) * d floats); the
  * sweep cut into W segments keeps those sums and 5 * B * W * D floats of segment rows; the general sweep keeps

@@ -509,26 +509,22 @@ int sweep_park_steps(int64_t B, int64_t L, int threads, int groups, int cus)
 template <int d, int N, int P>
 hipError_t backward_short_launch(const BackwardArgs &A0, int threads, int cus, hipStream_t st)
 {
-    if constexpr (!bracket_compiled(d, N) || bracket_min_points(d, N) <= 2) {
-        static_assert(bracket_compiled(d, N), "long paths of the register shapes are swept on brackets");
-        return hipErrorInvalidValue;
-    } else {
-        BackwardArgs A = A0;
-        const int G = sweep_groups<d, N, P>(A.B, A.L, threads, cus);
-        const int park_steps = sweep_park_steps<d, N, P, false>(A.B, A.L, threads, G, cus);
-        const int64_t lds = backward_lds_bytes<d, N, P>(A.L, G, park_steps);
-        const int64_t grid = (A.B + G - 1) / G;
-        if (lds > kMaxLdsBytes || grid <= 0 || grid > INT32_MAX) return hipErrorInvalidValue;
-        A.groups = G;
-        if constexpr (reduce_steps<d, P>() > kShortPark) {
-            if (park_steps) {
-                hipLaunchKernelGGL((sig_backward_kernel<d, N, P, false, false, true, kShortPark>), dim3((unsigned)grid), dim3(threads), (size_t)lds, st, A);
-                return hipGetLastError();
-            }
+    static_assert(bracket_compiled(d, N), "long paths of the register shapes are swept on brackets");
+    BackwardArgs A = A0;
+    const int G = sweep_groups<d, N, P>(A.B, A.L, threads, cus);
+    const int park_steps = sweep_park_steps<d, N, P, false>(A.B, A.L, threads, G, cus);
+    const int64_t lds = backward_lds_bytes<d, N, P>(A.L, G, park_steps);
+    const int64_t grid = (A.B + G - 1) / G;
+    if (lds > kMaxLdsBytes || grid <= 0 || grid > INT32_MAX) return hipErrorInvalidValue;
+    A.groups = G;
+    if constexpr (reduce_steps<d, P>() > kShortPark) {
+        if (park_steps) {
+            hipLaunchKernelGGL((sig_backward_kernel<d, N, P, false, false, true, kShortPark>), dim3((unsigned)grid), dim3(threads), (size_t)lds, st, A);
+            return hipGetLastError();
         }
-        hipLaunchKernelGGL((sig_backward_kernel<d, N, P, false>), dim3((unsigned)grid), dim3(threads), (size_t)lds, st, A);
-        return hipGetLastError();
     }
+    hipLaunchKernelGGL((sig_backward_kernel<d, N, P, false>), dim3((unsigned)grid), dim3(threads), (size_t)lds, st, A);
+    return hipGetLastError();
 }
 
 template <int d, int N, int P>

@@ -89,20 +89,55 @@ constexpr bool bracket_compiled(int d, int depth)
     return d >= 2 && (depth == 2 ? d <= 20 : depth == 3 ? d <= 16 : depth == 4 ? d <= 10 : depth == 5 ? d <= 6 : depth == 6 && d <= 4);
 }
 // The sweep on brackets pays for the bracket values of a path once (2^{depth-1} words each) and then next to nothing per
-// step; the sweep on signatures (sig_backward.hip) has no such start, and stays for paths of fewer points than this: some
-// 12 + D / 150, twice the second term at depth 6, and D 2^{depth-1} / 2500 where the rows are too long for the packed kernel at
-// depth 5 and 6.  Measured on batches that fill the chip, points per path where the two meet: (4,4) 14, (5,4) 15, (6,4) 16,
-// (7,4) 33, (8,4) 12, (10,4) 9, (3,5) 17, (4,5) 16, (5,5) 25, (6,5) 45, (3,6) 32, (4,6) 80; up to depth 3 it wins or ties
-// from 8 points on.
-constexpr int64_t bracket_min_points(int d, int depth)
+// step; the sweep on signatures (sig_backward.hip) has no such start, and stays for paths of fewer points than this.  From
+// depth 4 on some 12 + D / 150, twice the second term at depth 6, and D 2^{depth-1} / 2500 where the rows are too long for the
+// packed kernel at depth 5 and 6.  Measured on batches that fill the chip, points per path where the two meet: (4,4) 14, (5,4)
+// 15, (6,4) 16, (7,4) 33, (8,4) 12, (10,4) 9, (3,5) 17, (4,5) 16, (5,5) 25, (6,5) 45, (3,6) 32, (4,6) 80.  The other terms:
+// where the batch moves that point (a grid of all compiled shapes x 2 ... 70 points x 1 ... 100,000 paths).  Some hundred to
+// ten thousand paths leave a wavefront of the packed kernel few of them, and its start is not shared ((2,3), 10 points,
+// 1,600 paths 4.3 us on signatures and 6.8 on brackets; (3,5), 14 points, 8,000 paths 13.5 and 18.0); tens of thousands of
+// short paths are bound by reading their rows, which the packed kernel stages a few at a time ((7,3), 8 points, 100,000
+// paths 50 and 87 us); up to some hundred of 8 to 10 channels pay for the chunked kernel's phases ((8,3), 8 points 4.5 and 6.0).
+constexpr int64_t bracket_min_points(int d, int depth, int64_t B)
 {
-    if (depth < 4) return 2;
-    if (depth == 4 && d > 7) return 12;
+    const bool some = B >= 512, many = B >= 4096, full = B >= 16384, flood = B >= 65536;
+    const bool lone = B >= 1024 && B < 2048;   // a wavefront of the packed kernel for every path
+    if (d > 10) return 2;
+    if (depth == 2) return B < 64 ? 2 : flood ? (d > 8 ? 8 : d) : many && (!full || d > 8) ? d - 2 : full ? d - 1 : d;
+    if (depth == 3) {
+        if (d == 2) return full ? 7 : lone ? 21 : some ? 17 : 13;
+        if (d <= 4) return many ? (flood && d == 4 ? 9 : 8) : some ? 12 : 8;
+        if (d <= 7) return d == 5 ? (flood ? 9 : some ? 8 : 5) : flood ? 17 : full ? 13 : some ? 8 : 5;
+        if (d == 8) return many ? 8 : 12;
+        return B < 1024 ? 10 : 6;
+    }
+    if (depth == 4 && d > 7) return d > 8 && B < 128 ? 3 * d - 14 : 12;
+    if (depth == 4 && d == 2) return full ? 12 : lone ? 25 : some ? 17 : 13;
+    if (depth == 4 && d == 4 && many) return 17;
+    if (depth == 5 && d == 3 && B >= 1024) return many && !full ? 20 : 17;
     int64_t D = 0, p = 1;
     for (int n = 1; n <= depth; ++n) D += p *= d;
-    return D > 3000 ? (D << (depth - 1)) / 2500 : 12 + (depth >= 6 ? 2 : 1) * D / 150;
+    if (D > 3000) return (D << (depth - 1)) / 2500 + (B < 1024 ? 0 : depth == 6 ? 9 : 1);
+    return 12 + (depth >= 6 ? 2 : 1) * D / 150;
 }
-inline bool bracket_wanted(int d, int depth, int64_t L) { return bracket_compiled(d, depth) && L >= bracket_min_points(d, depth); }
+// Few long paths of shapes that leave a workgroup few chunks (or pay much for every workgroup's own bracket values): every
+// workgroup folds all that lies behind its stretch, up to K / 2 steps one after the other for (6,5), where the sweep on
+// signatures cut into segments (sig_backward_segments.hip) scans rows.  On brackets and on signatures, us: (6,5) one path of
+// 600 points 95 and 66, of 2,000 281 and 102, of 10,000 1,329 and 324, 10 paths of 800 104 and 134, of 2,000 242 and 184, 20 of
+// 600 73 and 132, of 800 167 and 151, of 2,000 408 and 251, 40 of 1,200 230 and 271; (4,6) one path of 600 65 and 53, of 2,000 109 and 88, 10 of 600 67 and 88; (10,4) one path of 2,000 75 and 90, of
+// 5,000 167 and 159, of 30,000 945 and 771.
+constexpr bool segments_instead_of_brackets(int d, int depth, int64_t B, int64_t L)
+{
+    if (d == 6 && depth == 5) return B <= 12 ? L > 250 + 100 * B : B <= 32 && L > 700;
+    if (d == 4 && depth == 6) return B <= 4 && L > 260;
+    if (d == 10 && depth == 4) return B <= 4 && L > 1000 + 3500 * B;
+    return false;
+}
+constexpr bool segments_compiled_beside_brackets(int d, int depth)
+{
+    return (d == 6 && depth == 5) || (d == 4 && depth == 6) || (d == 10 && depth == 4);
+}
+constexpr bool bracket_wanted(int d, int depth, int64_t B, int64_t L) { return bracket_compiled(d, depth) && L >= bracket_min_points(d, depth, B); }
 // workgroups a path's steps are cut across (1: not cut)
 int bracket_segments(int d, int depth, int64_t B, int64_t L, int cus);
 bool bracket_depth2_geometry(int d, int64_t B, int64_t L, int cus, int64_t *grid, int64_t *segs, int64_t *steps, int64_t *groups,

@@ -70,6 +70,61 @@ def test_errors_stay_at_the_rounding_of_float32(gpu, oracle, d, depth, B, L, sca
     assert err <= ROUNDING[depth]
 
 
+# d, depth, paths, points: the last length on signatures and the first on brackets, where the batch moves that point
+BORDERS = [(3, 2, 64, 3), (5, 2, 300, 5), (10, 2, 64, 10), (10, 2, 63, 3), (8, 2, 5000, 6), (8, 2, 17000, 7), (5, 2, 66000, 5), (2, 3, 600, 17), (2, 3, 1500, 21),
+           (2, 3, 100, 13), (2, 3, 16400, 7), (3, 3, 700, 12), (4, 3, 66000, 9), (4, 3, 40, 8), (5, 3, 600, 8), (5, 3, 66000, 9),
+           (6, 3, 16500, 13), (7, 3, 16500, 13), (7, 3, 66000, 17), (7, 3, 30, 5), (8, 3, 100, 12), (8, 3, 4100, 8), (9, 3, 100, 10),
+           (10, 3, 1100, 6), (2, 4, 600, 17), (2, 4, 1100, 25), (2, 4, 9, 13), (4, 4, 4200, 17), (3, 5, 1100, 17), (3, 5, 5000, 20),
+           (9, 4, 20, 13), (10, 4, 20, 16), (5, 5, 1100, 25)]
+
+
+@pytest.mark.parametrize("d,depth,B,L", BORDERS)
+def test_both_sides_of_the_shortest_path_on_brackets(gpu, oracle, d, depth, B, L):
+    import torch
+    for points in (L - 1, L):
+        x = workloads.brownian_paths(B, points, d, seed=9600 + d + points)
+        say("short paths: (%d,%d) %d paths of %d points" % (d, depth, B, points))
+        sampled_backward(gpu, oracle, x, depth, False, sorted({0, 1, B // 2, B - 2, B - 1}), seed=d + points)
+        path = torch.from_numpy(x).cuda()   # a fresh context: the sweeps that need no scratch, brackets in place of the others
+        out, ctx = gpu.signature(path, depth), gpu.sig_create()
+        g, gx = torch.ones_like(out), torch.empty_like(path)
+        try:
+            assert launches(gpu, lambda: gpu.sig_backward(ctx, path, depth, 0, out, g, gx)) == 1
+        finally:
+            torch.cuda.synchronize()
+            gpu.sig_destroy(ctx)
+
+
+@pytest.mark.parametrize("d,depth,B,L,on_signatures", [(6, 5, 1, 351, True), (6, 5, 1, 350, False), (6, 5, 4, 800, True), (6, 5, 14, 701, True), (6, 5, 33, 800, False),
+                                                       (4, 6, 3, 300, True), (4, 6, 5, 300, False), (10, 4, 1, 4600, True)])
+def test_few_long_paths_that_signatures_take(gpu, oracle, d, depth, B, L, on_signatures):
+    """Cut into segments with rows in context scratch; a context whose scratch cannot grow, under capture, takes brackets."""
+    import torch
+    x = workloads.brownian_paths(B, L, d, seed=9650 + L)
+    check(gpu, oracle, x[:2], depth, False, seed=L, label="few long paths")
+    path = torch.from_numpy(x).cuda()
+    out = gpu.signature(path, depth)
+    g, gx = torch.randn_like(out), torch.full_like(path, float("nan"))
+    eager, ctx = torch.empty_like(path), gpu.sig_create()
+    try:
+        call = lambda: gpu.sig_backward(ctx, path, depth, 0, out, g, gx)   # noqa: E731
+        assert launches(gpu, call) == 1
+        assert gpu.sig_backward(ctx, path, depth, 0, out, g, eager) == gpu.SIG_OK
+        n = launches(gpu, call)
+        assert n >= 6 if on_signatures else n == 1
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            assert call() == gpu.SIG_OK
+        for _ in range(3):
+            gx.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(gx, eager)
+    finally:
+        torch.cuda.synchronize()
+        gpu.sig_destroy(ctx)
+
+
 def test_the_gradient_of_a_translation_vanishes(gpu):
     """The signature does not see where a path starts: the gradients of a path's points add up to zero, up to the rounding
     of 2,000 sums of float32 values (the sum of their magnitudes times 2^-23)."""
