@@ -1,5 +1,6 @@
 // Host side of libsig: argument checking, the planner that maps a shape onto the GPU, scratch
 // management and kernel dispatch.  The C ABI is declared and documented in include/sig.h.
+#include <atomic>
 #include <cmath>
 #include <mutex>
 #include <new>
@@ -36,7 +37,7 @@ struct sig_ctx {
     int scratch_calls;             // calls in a row on scratch_stream since it began to be shared
     hipEvent_t scratch_event;
     TunedPlan tuned[64];   // filled by sig_autotune, consulted by sig_compute and sig_plan (oldest overwritten)
-    int tuned_count;
+    std::atomic<int> tuned_count;   // (calls on a context without tuned plans do not lock for them)
     int tuned_next;
 };
 
@@ -678,7 +679,7 @@ int plan_auto(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const R
 
 bool find_tuned(const sig_ctx *ctx, int64_t B, int64_t L, int d, int depth, int stream_flag, sig_plan_t *pl)
 {
-    if (!ctx) return false;
+    if (!ctx || ctx->tuned_count.load(std::memory_order_relaxed) == 0) return false;
     std::lock_guard<std::mutex> hold(ctx->lock);
     for (int i = 0; i < ctx->tuned_count; ++i) {
         const TunedPlan &t = ctx->tuned[i];
