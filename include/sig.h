@@ -234,8 +234,8 @@ int sig_combine(sig_ctx *ctx, const float *a, const float *b, int64_t B, int d, 
  * Final mode: two to twenty channels at depth 2, to 16 at depth 3, 10 at depth 4, 6 at depth 5 and 4 at depth 6 are swept
  * on Lie brackets (one launch, no scratch, any length): several paths per wavefront, or one path per workgroup with its
  * steps cut into chunks, or (few long paths) into up to 32 stretches swept by different workgroups.  Paths of a dozen
- * points or so (fewer than d at depth 2, up to 78 at (4,6); the batch moves this), few long paths of (6,5), (4,6) and
- * (10,4), and every other shape are swept on the signature itself, as below.
+ * points or so (fewer than d at depth 2, up to 78 at (4,6); the batch moves this) and every other shape are swept on the
+ * signature itself, as below.
  * The other sweeps start from the signature at the end and undo one increment at a time.  Shapes with a compiled register
  * kernel (see sig_backward_available) whose paths fit its LDS staging take it.  Few long paths and paths too long for that
  * staging are cut into up to 32 time segments that are swept by different workgroups: by Eq. 3 a segment can start from the

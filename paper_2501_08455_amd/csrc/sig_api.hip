@@ -885,13 +885,6 @@ int run_plan(sig_ctx *ctx, const float *path, int64_t B, int64_t L, const RowSha
     return SIG_OK;
 }
 
-// Time segments of the final-mode sweep on signatures where it takes a call of a shape that has brackets (0: it does not)
-int segments_beside_brackets(int d, int depth, int64_t B, int64_t L, int cus)
-{
-    if (B < 1 || !segments_instead_of_brackets(d, depth, B, L)) return 0;
-    return backward_segments(d, depth, B, L, cus, backward_fits(d, depth, L), 0);
-}
-
 }  // namespace
 
 extern "C" {
@@ -1256,16 +1249,6 @@ int sig_backward(sig_ctx *ctx, const float *path, int64_t B, int64_t L, int d, i
     const int64_t short_floats = !stream_flag && bracket_compiled(d, depth) ? backward_scratch_floats(d, depth, B, L) : 0;
     if (!stream_flag && (bracket_wanted(d, depth, B, L) ||
                          (short_floats > 0 && !Scratch::within_reach(ctx, (size_t)short_floats * sizeof(float), st)))) {
-        const int cuts = segments_beside_brackets(d, depth, B, L, ctx->num_cu);
-        const int64_t need = cuts > 1 ? backward_segmented_scratch_floats(d, depth, B, L, cuts) : 0;
-        if (need > 0 && Scratch::within_reach(ctx, (size_t)need * sizeof(float), st)) {
-            rc = scratch.get(ctx, (size_t)need * sizeof(float), st, &work);
-            if (rc == SIG_OK) {
-                hipError_t es = launch_backward_segmented(path, out, grad_out, grad_path, work, B, L, d, depth, 0, cuts, ctx->num_cu, st);
-                return es == hipSuccess ? SIG_OK : SIG_ERR_HIP;
-            }
-            if (rc != SIG_ERR_ALLOC) return rc;
-        }
         const int segs = bracket_segments(d, depth, B, L, ctx->num_cu);
         hipError_t eb = launch_bracket(path, out, grad_out, grad_path, B, L, d, depth, segs, ctx->num_cu, st);
         return eb == hipSuccess ? SIG_OK : SIG_ERR_HIP;
@@ -1309,10 +1292,7 @@ int sig_backward_segments(const sig_ctx *ctx, int64_t B, int64_t L, int d, int d
     const int rc = check_shape(B, L, d, depth, stream_flag, &rs);
     if (rc != SIG_OK) return -rc;
     if (!backward_available(d, depth)) return backward_general_available(d) ? 0 : -SIG_ERR_UNSUPPORTED;
-    if (!stream_flag && bracket_wanted(d, depth, B, L)) {
-        const int cus = ctx ? ctx->num_cu : kDefaultCUs, cuts = segments_beside_brackets(d, depth, B, L, cus);
-        return cuts > 1 ? cuts : bracket_segments(d, depth, B, L, cus);
-    }
+    if (!stream_flag && bracket_wanted(d, depth, B, L)) return bracket_segments(d, depth, B, L, ctx ? ctx->num_cu : kDefaultCUs);
     const bool fits = backward_fits(d, depth, L);
     if (B > 0) {
         const int segs = backward_segments(d, depth, B, L, ctx ? ctx->num_cu : kDefaultCUs, fits, stream_flag);

@@ -1,5 +1,5 @@
 // Gradient of the signature with respect to the path, cut in time across workgroups: few long paths (final mode of the
-// shapes that have no sweep on brackets, sig_bracket.h, or where it is the slower one; stream mode further down, at sig_backward_segment_affine_kernel).
+// shapes that have no sweep on brackets, sig_bracket.h; stream mode further down, at sig_backward_segment_affine_kernel).
 //
 // The reverse sweep (see sig_backward.hip) walks the K increments of a path one after the other, and a workgroup
 // per path (and slice of its lanes) leaves most of the chip idle when there are few paths.  Chen's relation (paper
@@ -318,7 +318,7 @@ hipError_t backward_segmented_launch(const BackwardArgs &A0, float *scratch, int
         }
     }
 
-    if constexpr (packed || (bracket_compiled(d, N) && !segments_compiled_beside_brackets(d, N))) {
+    if constexpr (packed || bracket_compiled(d, N)) {
         return hipErrorInvalidValue;   // final mode of these shapes is swept on brackets (and its short paths are not cut)
     } else {
         const int fold_threads = Sh::Q >= kSliceLanes ? kSliceLanes : (Sh::Q + kWave - 1) / kWave * kWave;
@@ -403,8 +403,7 @@ constexpr int64_t kMaxSegmentRow = 1 << 17;   // one workgroup forms a product o
 // Time segments for the sweep of B paths of L points (<= 1: do not cut).  Cutting pays when the uncut launch leaves most of
 // the chip idle and the path is long: the sequential part drops from K steps (2 K / C for a shape whose plain sweep
 // holds C chunks of a path side by side in its workgroup) to about K / W, for ceil(log2 W) + 3 more launches of 3-6 us
-// each.  Final mode: only the shapes without a sweep on brackets ask, and three that have one (segments_instead_of_brackets);
-// they are sliced ones.  Rules, from
+// each.  Final mode: only the shapes without a sweep on brackets ask (sig_bracket.h); they are sliced ones.  Rules, from
 // a measured grid (15 shapes, B = 1 .. 1,024, L = 100 .. 2,000):
 //   * from 128 increments on, while the uncut launch has fewer than two workgroups per compute unit (between one
 //     and two, a few segments still pay);

@@ -58,6 +58,7 @@ struct Args {
     int32_t chunks;         // C: chunks of a workgroup
     int32_t segs;           // W: workgroups of a path
     int32_t steps;          // T: steps of a chunk; W * C * T >= L - 1
+    int32_t fold_slots;     // slots of QF lanes that fold what lies behind the workgroup (>= C; levels 3 and up of R only)
     int32_t groups;         // paths per workgroup (sig_bracket_packed_kernel, sig_bracket_depth2_kernel)
 };
 
@@ -703,13 +704,18 @@ constexpr int kFoldTile = 16;    // steps of every chunk per tile of the fold of
 
 // LDS: pair table, f_1, R rows; then the rows of G and S with, behind them, first the fold's buffers and later F, summands and
 // bracket values; the walk's tile takes the place of all of these
+// What lies behind the workgroup's stretch is folded by more slots than its chunks, as many as the threads and the LDS hold: a
+// chunk of the walk takes LQ lanes, a slot of this fold QF of them ((6,5): 2 chunks of 90 lanes, 13 slots of 6).
+template <class G>
+constexpr int64_t behind_floats(int slots) { return 2 * (int64_t)(slots + 1) * G::DR + (int64_t)slots * kFoldTile * G::d; }
 template <class G>
 constexpr int chunked_rows_at(int C) { return (G::PAIRS + 2 * G::d + (C + 1) * G::DR + 3) / 4 * 4; }
 template <class G>
-int64_t chunked_lds_floats(int C)
+int64_t chunked_lds_floats(int C, int fold_slots = 0)
 {
     const int64_t init = work_floats<G>(G::CT, 1) + G::FST;
-    const int64_t fold = G::FN >= 2 ? (int64_t)(C + 1) * G::DR + (int64_t)C * kFoldTile * G::d : 0;
+    int64_t fold = G::FN >= 2 ? (int64_t)(C + 1) * G::DR + (int64_t)C * kFoldTile * G::d : 0;
+    if (fold_slots > C && behind_floats<G>(fold_slots) > fold) fold = behind_floats<G>(fold_slots);
     const int64_t rows = rows_floats<G>(1) + (init > fold ? init : fold);
     const int64_t walk = (int64_t)C * (G::CTT + 1) * G::row_floats;
     return chunked_rows_at<G>(C) + (rows > walk ? rows : walk);
@@ -773,8 +779,8 @@ void sig_bracket_chunked_kernel(Args A)
 
     // steps t0 .. t0 + steps - 1 below top0 - s * stride of every slot s into its part of a tile of the folds, negated; steps
     // outside (kmin, K] count as zero
-    auto stage_steps = [&](float *tile, int64_t top0, int64_t stride, int t0, int steps, int64_t kmin) __attribute__((always_inline)) {
-        for (int i = tid; i < C * kFoldTile * d; i += nthr) {
+    auto stage_steps = [&](float *tile, int slots, int64_t top0, int64_t stride, int t0, int steps, int64_t kmin) __attribute__((always_inline)) {
+        for (int i = tid; i < slots * kFoldTile * d; i += nthr) {
             const int s = i / (kFoldTile * d), x = i - s * (kFoldTile * d);
             const int t = x / d, a = x - t * d;
             if (t >= steps) continue;
@@ -812,7 +818,7 @@ void sig_bracket_chunked_kernel(Args A)
             for (int t0 = 0; t0 < count; t0 += kFoldTile) {
                 const int steps = count - t0 < kFoldTile ? count - t0 : kFoldTile;
                 __syncthreads();
-                stage_steps(tile, top0, stride, t0, steps, kmin);
+                stage_steps(tile, C, top0, stride, t0, steps, kmin);
                 __syncthreads();
                 if (active && lane < d) {
                     const float *row = tile + slot * kFoldTile * d;
@@ -866,20 +872,25 @@ void sig_bracket_chunked_kernel(Args A)
         __syncthreads();
     } else if constexpr (G::FN > 2) {
         using Fold = onchip::Lane<d, G::FN, G::PF>;
+        // `slots` slots of lanes, of which this thread is lane `u` of slot `at` if it folds at all
+        struct Place {
+            int slots, at;
+            unsigned u;
+            bool folds;
+        };
         float *tile = work;                           // [C][kFoldTile][d]
         float *buf = tile + C * kFoldTile * d;        // [C + 1][DR]
-        const bool folder = active && lane < G::QF;
-        const unsigned u = folder ? (unsigned)lane : 0u;
-        int letter[1] = {(int)u};
-        // folds `count` steps downwards from top(slot), those in (kmin, K], and joins the slots' results in order
-        auto fold = [&](Fold &ln, int64_t top0, int64_t stride, int count, int64_t kmin) __attribute__((always_inline)) {
+        const Place mine = {C, slot, active && lane < G::QF ? (unsigned)lane : 0u, active && lane < G::QF};
+        // folds `count` steps downwards from top0 - slot * stride, those in (kmin, K], and joins the slots' results in order
+        auto fold = [&](Fold &ln, const Place &p, float *rows, int64_t top0, int64_t stride, int count, int64_t kmin) __attribute__((always_inline)) {
+            int letter[1] = {(int)p.u};
             for (int t0 = 0; t0 < count; t0 += kFoldTile) {
                 const int steps = count - t0 < kFoldTile ? count - t0 : kFoldTile;
                 __syncthreads();
-                stage_steps(tile, top0, stride, t0, steps, kmin);
+                stage_steps(rows, p.slots, top0, stride, t0, steps, kmin);
                 __syncthreads();
-                if (folder) {
-                    const float *row = tile + slot * kFoldTile * d;
+                if (p.folds) {
+                    const float *row = rows + p.at * kFoldTile * d;
                     for (int t = 0; t < steps; ++t, row += d) {
                         onchip::Inc<d, G::PF> inc;
                         onchip::load_inc<d, G::PF>(inc, row, letter);
@@ -890,19 +901,19 @@ void sig_bracket_chunked_kernel(Args A)
         };
         // inclusive products over the slots 0 .. limit-1 in log2 rounds (rows alternate between two buffers, slot s at
         // row s + 1); returns the buffer that holds them
-        auto scan = [&](Fold &ln, float *cur, float *nxt, int limit) __attribute__((always_inline)) {
-            if (folder) onchip::store_state<d, G::FN, G::PF>(cur + (slot + 1) * DR, u, ln);
+        auto scan = [&](Fold &ln, const Place &p, float *cur, float *nxt, int limit) __attribute__((always_inline)) {
+            if (p.folds) onchip::store_state<d, G::FN, G::PF>(cur + (p.at + 1) * DR, p.u, ln);
             __syncthreads();
             for (int st = 1; st < limit; st <<= 1) {
-                if (folder) {
-                    if (slot < st) onchip::store_state<d, G::FN, G::PF>(nxt + (slot + 1) * DR, u, ln);
-                    if (slot + st < limit) {
-                        onchip::reg_product<d, G::FN, G::PF>(ln, cur + (slot + 1 + st) * DR, u);
-                        onchip::store_state<d, G::FN, G::PF>(nxt + (slot + 1 + st) * DR, u, ln);
+                if (p.folds) {
+                    if (p.at < st) onchip::store_state<d, G::FN, G::PF>(nxt + (p.at + 1) * DR, p.u, ln);
+                    if (p.at + st < limit) {
+                        onchip::reg_product<d, G::FN, G::PF>(ln, cur + (p.at + 1 + st) * DR, p.u);
+                        onchip::store_state<d, G::FN, G::PF>(nxt + (p.at + 1 + st) * DR, p.u, ln);
                     }
                 }
                 __syncthreads();
-                if (folder && slot < limit) onchip::load_state<d, G::FN, G::PF>(nxt + (slot + 1) * DR, u, ln);
+                if (p.folds && p.at < limit) onchip::load_state<d, G::FN, G::PF>(nxt + (p.at + 1) * DR, p.u, ln);
                 float *t = cur; cur = nxt; nxt = t;
             }
             return cur;
@@ -911,26 +922,31 @@ void sig_bracket_chunked_kernel(Args A)
         onchip::identity_state<d, G::FN, G::PF>(ln);
         const int64_t behind = K - k_end - 1;         // steps between the workgroup's first one and the end of the path
         if (behind > 0) {
-            const int count = (int)((behind + C - 1) / C);
-            fold(ln, K, count, count, k_end + 1);
-            const float *all = scan(ln, buf, moved, C) + C * DR;
+            const int CF = A.fold_slots;              // C, or more where the two buffers fit beside each other
+            const int at = tid / G::QF;
+            const Place wide = {CF, at, (unsigned)(tid - at * G::QF), at < CF};
+            const Place place = CF > C ? wide : mine;
+            const int count = (int)((behind + CF - 1) / CF);
+            float *cur = tile + CF * kFoldTile * d, *nxt = CF > C ? cur + (CF + 1) * DR : moved;
+            fold(ln, place, tile, K, count, count, k_end + 1);
+            const float *all = scan(ln, place, cur, nxt, CF) + CF * DR;
             __syncthreads();
             // every slot's lanes take what they need of it before the buffers are used again
             onchip::identity_state<d, G::FN, G::PF>(ln);
-            if (folder && slot == 0) onchip::load_state<d, G::FN, G::PF>(all, u, ln);
+            if (mine.folds && slot == 0) onchip::load_state<d, G::FN, G::PF>(all, mine.u, ln);
             __syncthreads();
         }
         int rounds = 0;
         for (int st = 1; st < C - 1; st <<= 1) ++rounds;
         // row 0: what lies behind the workgroup (zeros: nothing); the other rows end up in `moved` too
         float *first = rounds & 1 ? buf : moved, *second = rounds & 1 ? moved : buf;
-        if (folder && slot == 0) {
-            if (behind > 0) onchip::store_state<d, G::FN, G::PF>(moved, u, ln);
+        if (mine.folds && slot == 0) {
+            if (behind > 0) onchip::store_state<d, G::FN, G::PF>(moved, mine.u, ln);
         }
         if (behind <= 0)
             for (int i = tid; i < DR; i += nthr) moved[i] = 0.0f;
-        fold(ln, k_end + 1, T, T, 0);
-        scan(ln, first, second, C - 1);
+        fold(ln, mine, tile, k_end + 1, T, T, 0);
+        scan(ln, mine, first, second, C - 1);
         __syncthreads();
     }
 

@@ -41,6 +41,24 @@ int most_chunks()
     return C;
 }
 
+// Slots that fold what lies behind a workgroup: two dozen steps each, as far as the threads hold them and their rows leave as
+// many workgroups resident as before.  (6,5), one path of 2,000 points: 2 slots 281 us, 13 slots 80.
+template <class G>
+int fold_slots(int C, int64_t K)
+{
+    if constexpr (G::FN <= 2) return C;
+    else {
+        const int64_t now = chunked_lds_floats<G>(C) * (int64_t)sizeof(float);
+        int64_t most = kCuLdsBytes / (kCuLdsBytes / now) - 2048;   // (short of the step in which LDS is handed out)
+        if (most > kMaxLds) most = kMaxLds;
+        int64_t slots = G::CT / G::QF;
+        if (slots > kMaxChunks) slots = kMaxChunks;
+        if (slots > K / 24) slots = K / 24;
+        while (slots > C && chunked_lds_floats<G>(C, (int)slots) * (int64_t)sizeof(float) > most) --slots;
+        return slots > C ? (int)slots : C;
+    }
+}
+
 template <int d, int N, int P>
 hipError_t launch(const Args &A0, int cus, hipStream_t st)
 {
@@ -73,7 +91,8 @@ hipError_t launch(const Args &A0, int cus, hipStream_t st)
     A.chunks = (int32_t)C;
     A.steps = (int32_t)((K + C * W - 1) / (C * W));
     A.segs = (int32_t)((K + C * A.steps - 1) / (C * A.steps));   // no workgroup is left without steps
-    const size_t lds = (size_t)chunked_lds_floats<G>((int)C) * sizeof(float);
+    A.fold_slots = A.segs > 1 ? fold_slots<G>((int)C, K) : (int32_t)C;
+    const size_t lds = (size_t)chunked_lds_floats<G>((int)C, A.fold_slots) * sizeof(float);
     if (lds > (size_t)kMaxLds || C * G::LQ > threads || A.B * A.segs > INT32_MAX) return hipErrorInvalidValue;
     hipError_t e = allow_lds(&sig_bracket_chunked_kernel<d, N, P>, lds);
     if (e != hipSuccess) return e;
@@ -168,7 +187,7 @@ const Entry *find(int d, int depth)
 // folds everything behind it: from two dozen steps a chunk on while there are few paths, twice that for more than 32, at
 // most four workgroups per compute unit, and not where the rows that are read again exceed four megabytes.  Uncut and cut:
 // (9,3), five paths of 1,221 points 32.5 and 6.4 us; (10,4), one path of 1,000 points 123 and 47; (5,4), 128 paths of 2,000
-// points 45 and 36; (6,5), 112 paths of 500 points 153 and 144.
+// points 45 and 36; (6,5), 112 paths of 500 points 153 and 96.
 int bracket_segments(int d, int depth, int64_t B, int64_t L, int cus)
 {
     const bracket::Entry *e = bracket::find(d, depth);

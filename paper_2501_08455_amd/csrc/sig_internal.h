@@ -120,23 +120,6 @@ constexpr int64_t bracket_min_points(int d, int depth, int64_t B)
     if (D > 3000) return (D << (depth - 1)) / 2500 + (B < 1024 ? 0 : depth == 6 ? 9 : 1);
     return 12 + (depth >= 6 ? 2 : 1) * D / 150;
 }
-// Few long paths of shapes that leave a workgroup few chunks (or pay much for every workgroup's own bracket values): every
-// workgroup folds all that lies behind its stretch, up to K / 2 steps one after the other for (6,5), where the sweep on
-// signatures cut into segments (sig_backward_segments.hip) scans rows.  On brackets and on signatures, us: (6,5) one path of
-// 600 points 95 and 66, of 2,000 281 and 102, of 10,000 1,329 and 324, 10 paths of 800 104 and 134, of 2,000 242 and 184, 20 of
-// 600 73 and 132, of 800 167 and 151, of 2,000 408 and 251, 40 of 1,200 230 and 271; (4,6) one path of 600 65 and 53, of 2,000 109 and 88, 10 of 600 67 and 88; (10,4) one path of 2,000 75 and 90, of
-// 5,000 167 and 159, of 30,000 945 and 771.
-constexpr bool segments_instead_of_brackets(int d, int depth, int64_t B, int64_t L)
-{
-    if (d == 6 && depth == 5) return B <= 12 ? L > 250 + 100 * B : B <= 32 && L > 700;
-    if (d == 4 && depth == 6) return B <= 4 && L > 260;
-    if (d == 10 && depth == 4) return B <= 4 && L > 1000 + 3500 * B;
-    return false;
-}
-constexpr bool segments_compiled_beside_brackets(int d, int depth)
-{
-    return (d == 6 && depth == 5) || (d == 4 && depth == 6) || (d == 10 && depth == 4);
-}
 constexpr bool bracket_wanted(int d, int depth, int64_t B, int64_t L) { return bracket_compiled(d, depth) && L >= bracket_min_points(d, depth, B); }
 // workgroups a path's steps are cut across (1: not cut)
 int bracket_segments(int d, int depth, int64_t B, int64_t L, int cus);

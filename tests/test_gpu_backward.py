@@ -144,7 +144,7 @@ def test_backward_sliced_long_paths(gpu, oracle):
 
 
 SEGMENTED_CASES = [
-    # d, depth, B, L: few long paths in final mode, cut in time across workgroups: on brackets, but for (10,5) and (4,6), whose
+    # d, depth, B, L: few long paths in final mode, cut in time across workgroups: on brackets, but for (10,5), whose
     # segments keep signatures, running products and pulled-back gradients (more of these: ON_SIGNATURES); lengths that
     # leave a ragged last segment, one and several paths
     (5, 4, 1, 1000), (5, 4, 3, 777), (2, 3, 2, 4001), (4, 4, 5, 500), (3, 5, 2, 600), (5, 5, 1, 300), (9, 3, 2, 450),
