@@ -106,6 +106,11 @@ enum sig_variant {
  *                 prefix_depth - 1 letters only, once, and the fold reads it from LDS.  0 = chosen by the library
  *                 (taken for prefix_depth >= 4), 1 = insist (the plan is invalid where the kernel does not apply),
  *                 2 = every lane carries and re-evaluates its own prefix chain
+ *   row_workgroups  stream mode: 0 = the mapping of the other fields; n > 0 = each path is cut across n workgroups (at most 32,
+ *                 fewer where it is too short for that) that write their rows straight from registers, and the other
+ *                 fields are not used.  Compiled for 8-20 channels at depth 2, 3-12 at depth 3, 2-8 at depth 4, 2-4 at depth
+ *                 5, 2 and 3 at depth 6.  sig_plan sets it for few paths and for more than ten channels; the other fields
+ *                 then hold the mapping without it.  Final mode ignores it
  *   reserved      zero
  */
 typedef struct sig_plan_t {
@@ -119,7 +124,8 @@ typedef struct sig_plan_t {
     int32_t stagger_ticks;
     int32_t tile_loader;
     int32_t shared_chain;
-    int32_t reserved[2];
+    int32_t row_workgroups;
+    int32_t reserved[1];
 } sig_plan_t;
 
 /*

@@ -422,7 +422,7 @@ int check_level_scan(int64_t B, int64_t L, const RowShape &rs, int stream_flag, 
     return SIG_OK;
 }
 
-int plan_auto(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const RowShape &rs, sig_plan_t *pl)
+int plan_without_rows(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const RowShape &rs, sig_plan_t *pl)
 {
     const int cus = ctx ? ctx->num_cu : kDefaultCUs;
     const int64_t K = L - 1;
@@ -677,6 +677,14 @@ int plan_auto(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const R
     return SIG_OK;
 }
 
+int plan_auto(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const RowShape &rs, sig_plan_t *pl)
+{
+    const int rc = plan_without_rows(ctx, B, L, stream_flag, rs, pl);
+    if (rc == SIG_OK && stream_flag)
+        pl->row_workgroups = stream_rows_wanted(rs.d, rs.depth, B, L, ctx ? ctx->num_cu : kDefaultCUs, pl->variant == SIG_VARIANT_ON_CHIP);
+    return rc;
+}
+
 bool find_tuned(const sig_ctx *ctx, int64_t B, int64_t L, int d, int depth, int stream_flag, sig_plan_t *pl)
 {
     if (!ctx || ctx->tuned_count.load(std::memory_order_relaxed) == 0) return false;
@@ -696,6 +704,18 @@ int plan_for(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const Ro
 {
     if (find_tuned(ctx, B, L, rs.d, rs.depth, stream_flag, pl)) return SIG_OK;
     return plan_auto(ctx, B, L, stream_flag, rs, pl);
+}
+
+// stream mode by sig_stream_rows.h
+bool takes_stream_rows(const sig_plan_t &pl, int stream_flag) { return stream_flag && pl.row_workgroups > 0; }
+bool check_stream_rows(int64_t B, int64_t L, const RowShape &rs, const sig_plan_t &pl, int64_t *lds, int64_t *wgs)
+{
+    int threads = 0;
+    if (stream_rows_geometry(rs.d, rs.depth, B > 0 ? B : 1, L, pl.row_workgroups, kDefaultCUs, lds, wgs, &threads)) {
+        if (B == 0) *wgs = 0;
+        return true;
+    }
+    return false;
 }
 
 // The context's scratch for the launches of one call.  From get() until it goes out of scope, behind the call's last launch,
@@ -813,6 +833,12 @@ int run_plan(sig_ctx *ctx, const float *path, int64_t B, int64_t L, const RowSha
              float *out, const sig_plan_t &pl, hipStream_t st, bool fixed = false)
 {
     Scratch scratch;
+    if (takes_stream_rows(pl, stream_flag)) {
+        int64_t lds = 0, wgs = 0;
+        if (!check_stream_rows(B, L, rs, pl, &lds, &wgs)) return SIG_ERR_INVALID;
+        hipError_t e = launch_stream_rows(path, out, B, L, rs.d, rs.depth, pl.row_workgroups, ctx->num_cu, st);
+        return e == hipSuccess ? SIG_OK : SIG_ERR_HIP;
+    }
     if (pl.variant == SIG_VARIANT_HBM_STREAMING) {
         if (pl.prefix_depth < 0 || pl.prefix_depth > rs.depth - 1) return SIG_ERR_INVALID;
         if (pl.threads < kWave || pl.threads > 256 || pl.threads % kWave) return SIG_ERR_INVALID;
@@ -972,6 +998,10 @@ int sig_plan_validate(int64_t B, int64_t L, int d, int depth, int stream_flag, c
     RowShape rs;
     int rc = check_shape(B, L, d, depth, stream_flag, &rs);
     if (rc != SIG_OK) return rc;
+    if (takes_stream_rows(*plan, stream_flag)) {
+        int64_t lds = 0, wgs = 0;
+        return check_stream_rows(B, L, rs, *plan, &lds, &wgs) ? SIG_OK : SIG_ERR_INVALID;
+    }
     if (plan->variant == SIG_VARIANT_HBM_STREAMING) {
         if (plan->prefix_depth < 0 || plan->prefix_depth > rs.depth - 1) return SIG_ERR_INVALID;
         if (plan->threads < kWave || plan->threads > 256 || plan->threads % kWave) return SIG_ERR_INVALID;
@@ -995,7 +1025,9 @@ int sig_plan_footprint(int64_t B, int64_t L, int d, int depth, int stream_flag, 
     int rc = check_shape(B, L, d, depth, stream_flag, &rs);
     if (rc != SIG_OK) return rc;
     int64_t lds = 0, wgs = 0, scratch = 0;
-    if (plan->variant == SIG_VARIANT_HBM_STREAMING) {
+    if (takes_stream_rows(*plan, stream_flag)) {
+        if (!check_stream_rows(B, L, rs, *plan, &lds, &wgs)) return SIG_ERR_INVALID;
+    } else if (plan->variant == SIG_VARIANT_HBM_STREAMING) {
         rc = sig_plan_validate(B, L, d, depth, stream_flag, plan);
         if (rc != SIG_OK) return rc;
         int tile = 8192 / rs.d;
@@ -1093,7 +1125,7 @@ int sig_autotune(sig_ctx *ctx, int64_t B, int64_t L, int d, int depth, int strea
         ls.variant = SIG_VARIANT_LEVEL_SCAN;
         ls.threads = kThreads;
         ls.segments = 1;
-        if (base.variant != SIG_VARIANT_LEVEL_SCAN && check_level_scan(B, L, rs, stream_flag, ls) == SIG_OK &&
+        if ((base.variant != SIG_VARIANT_LEVEL_SCAN || takes_stream_rows(base, stream_flag)) && check_level_scan(B, L, rs, stream_flag, ls) == SIG_OK &&
             level_scan_scratch_floats(1, L, rs, stream_flag) <= kSliceFloats)
             cand[n++] = ls;
     }
@@ -1114,7 +1146,7 @@ int sig_autotune(sig_ctx *ctx, int64_t B, int64_t L, int d, int depth, int strea
             if (pl.chunks < 1 || !finish_on_chip(ki, ctx->num_cu, B, L, stream_flag, pl, rs, &args)) continue;
             bool dup = false;
             for (int i = 0; i < n; ++i)
-                dup = dup || (cand[i].variant == pl.variant && cand[i].prefix_depth == p && cand[i].chunks == pl.chunks &&
+                dup = dup || (!takes_stream_rows(cand[i], stream_flag) && cand[i].variant == pl.variant && cand[i].prefix_depth == p && cand[i].chunks == pl.chunks &&
                               cand[i].segments == pl.segments && cand[i].threads == pl.threads);
             if (!dup) cand[n++] = pl;
         }
@@ -1176,7 +1208,7 @@ int sig_autotune(sig_ctx *ctx, int64_t B, int64_t L, int d, int depth, int strea
     // second stage: the winner with smaller workgroups.  With a few workgroups per compute unit the number of paths a
     // workgroup takes decides how evenly they spread (measured 5-20 % either way on batches of 2,048 to 8,192 paths, with
     // no rule that the planner could follow), so the measurement decides.
-    if (status == SIG_OK && best >= 0 && cand[best].variant == SIG_VARIANT_ON_CHIP) {
+    if (status == SIG_OK && best >= 0 && cand[best].variant == SIG_VARIANT_ON_CHIP && !takes_stream_rows(cand[best], stream_flag)) {
         const OnChipKernelInfo *ki = find_on_chip(d, depth, cand[best].prefix_depth);
         const int sizes[3] = {192, 128, 64};
         for (int si = 0; si < 3 && ki && status == SIG_OK && n < (int)(sizeof(cand) / sizeof(cand[0])); ++si) {

@@ -227,6 +227,13 @@ inline int64_t on_chip_workgroups(int Q, const OnChipArgs &A)
     return grid;
 }
 
+// ---------------------------------------------------------------- stream mode, rows written straight from registers (sig_stream_rows.h)
+// workgroups a path is cut across, 0 if the call stays with the other kernels (held: register kernels of the on-chip family)
+int stream_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, bool held);
+// the launch with `segs` workgroups a path; false if there is none
+bool stream_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, int64_t *lds_bytes, int64_t *workgroups, int *threads);
+hipError_t launch_stream_rows(const float *path, float *out, int64_t B, int64_t L, int d, int depth, int segs, int cus, hipStream_t st);
+
 // table of compiled on-chip kernels; terminated by an entry with launch == nullptr
 // The compiled kernels live in several translation units (so that they build in parallel); sub-table i ends
 // with an entry whose launch pointer is null, and on_chip_subtable(i) is null past the last sub-table.  Entries

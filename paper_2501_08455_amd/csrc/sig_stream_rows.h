@@ -1,0 +1,222 @@
+// Stream mode, rows written straight from registers and few paths cut across workgroups (compiled per (d, depth N)).
+//
+// A slot of Q = d^{N-1} lanes folds a piece of a path with the fused step of sig_onchip.h at prefix depth N - 1: a lane owns
+// one word of length N - 1 and its d children.  Consecutive lanes then hold consecutive floats of a row's two longest
+// levels, so that a step's row goes from the registers to memory in whole runs, without a stop in LDS.
+//
+// Workgroup w of the W that share a path emits the C * T rows from step w C T on, a slot T of them.  What lies before is not
+// handed over by other workgroups (that would take a second launch): every workgroup folds it again, w T steps a slot, side by
+// side in its C slots, and joins the pieces by a tree of Eq. 4 products in LDS while the slots' own pieces go through a scan.
+//
+// Bound by latency on few paths (a launch, K / C steps of the fold, log2 C rounds of the scan, T steps that each store a row) and
+// by the stores on many.  Measured against what these calls took before (the register kernels of sig_onchip.h, one workgroup per
+// path, their rows staged in LDS; or one launch per level), us: (4,4) 64 paths of 256 points 24.6 -> 11.7, 4 of 1,075 63 -> 17;
+// (5,4) 16 of 100 17.6 -> 8.0; (10,3) 4 of 1,075 148 -> 40; (12,3) 1,024 of 100 490 -> 204.
+#ifndef SIG_STREAM_ROWS_H
+#define SIG_STREAM_ROWS_H
+
+#include "sig_onchip.h"
+
+namespace sig {
+namespace rows {
+
+using onchip::cpow;
+
+struct Args {
+    const float *path;   // [B][L][d]
+    float *out;          // [B][L-1][D]
+    int64_t B, L;
+    int32_t slots;       // C: pieces of a path side by side in a workgroup
+    int32_t segs;        // W: workgroups of a path
+    int32_t groups;      // G: paths of a workgroup (1 unless segs is)
+    int32_t steps;       // T: rows a slot emits; W * C * T >= L - 1
+    int32_t tile;        // steps of a slot that are staged in LDS together, of its own piece
+    int32_t behind;      // ... and of what lies before (segs > 1)
+};
+
+template <int d_, int N_>
+struct Geo {
+    static constexpr int d = d_, N = N_, P = N - 1;
+    static constexpr int Q = cpow(d, P);
+    static constexpr int D = onchip::Shape<d, N, P>::D;
+    static constexpr int SPW = Q <= kWave ? kWave / Q : 1;       // slots of a wavefront
+    static constexpr int WPS = (Q + kWave - 1) / kWave;          // wavefronts of a slot
+};
+constexpr int kMaxThreads = 1024;
+
+// a slot's increments in LDS: an odd stride puts the slots of a wavefront into different banks
+__host__ __device__ constexpr int tile_stride(int steps, int d) { return (steps * d) | 1; }
+// rows of a path in LDS: the slots' own pieces but for the last (twice where the scan takes rounds), and what lies before
+__host__ __device__ constexpr int lds_rows(int C, int W) { return (C - 1) * (C > 2 ? 2 : 1) + (W > 1 ? C : 0); }
+__host__ __device__ constexpr int tile_floats(const Args &A, int d)
+{
+    return (A.groups * A.slots * (tile_stride(A.tile, d) + (A.segs > 1 ? tile_stride(A.behind, d) : 0)) + 3) / 4 * 4;
+}
+
+extern __shared__ __align__(16) float sig_rows_smem[];
+
+template <int d, int N>
+__global__ __launch_bounds__(kMaxThreads) void sig_stream_rows_kernel(Args A)
+{
+    using G = Geo<d, N>;
+    constexpr int P = G::P, Q = G::Q, D = G::D;
+    using Lane = onchip::Lane<d, N, P>;
+    const int tid = threadIdx.x, nthr = blockDim.x;
+    const int wave = tid / kWave, lw = tid - wave * kWave, waves = nthr / kWave;
+    const int64_t K = A.L - 1;
+    const int C = A.slots, T = A.steps;
+    const unsigned unit = blockIdx.x / (unsigned)A.segs;
+    const int w = (int)(blockIdx.x - unit * (unsigned)A.segs);
+    const int64_t b0 = (int64_t)unit * A.groups;
+    const int paths = A.B - b0 < A.groups ? (int)(A.B - b0) : A.groups;
+    const int64_t k0 = (int64_t)w * C * T;          // first row of the workgroup
+    const int64_t before = (int64_t)w * T;          // steps of a slot of what lies before
+
+    int slot;
+    unsigned u;
+    bool active;
+    if constexpr (Q <= kWave) {
+        const int sw = lw / Q;
+        slot = wave * G::SPW + sw;
+        u = (unsigned)(lw - sw * Q);
+        active = sw < G::SPW && slot < paths * C;
+    } else {
+        slot = wave / G::WPS;
+        u = (unsigned)((wave - slot * G::WPS) * kWave + lw);
+        active = u < (unsigned)Q && slot < paths * C;
+    }
+    if (!active) { slot = 0; u = 0; }
+    const int p = slot / C, c = slot - p * C;       // path and piece
+    int letter[P];
+    {
+        unsigned rest = u;
+#pragma unroll
+        for (int m = P - 1; m >= 0; --m) { letter[m] = (int)(rest % d); rest /= d; }
+    }
+
+    const int own_stride = tile_stride(A.tile, d), old_stride = tile_stride(A.behind, d);
+    float *own = sig_rows_smem;                     // [slots][own_stride]
+    float *old = own + A.groups * C * own_stride;   // [slots][old_stride]
+    float *rows = sig_rows_smem + tile_floats(A, d) + p * lds_rows(C, A.segs) * D;
+
+    // `count` increments of every slot from step first + c * stride on, zeros beyond the path's end
+    auto stage = [&](float *tile, int row, int64_t first, int64_t stride, int count) __attribute__((always_inline)) {
+        for (int s = wave; s < paths * C; s += waves) {
+            const int sp = s / C;
+            const int64_t at = (first + (s - sp * C) * stride) * d;
+            const float *X = A.path + (b0 + sp) * A.L * d + at;
+            float *dst = tile + s * row;
+#pragma unroll 4
+            for (int r = lw; r < count * d; r += kWave) dst[r] = at + r < K * d ? X[r + d] - X[r] : 0.0f;
+        }
+    };
+    // (two steps a round, both increments read first: one wait for the pair; (4,4), 4 paths of 1,075 points 18.5 -> 17.1 us)
+    auto fold = [&](Lane &ln, const float *row, int count) __attribute__((always_inline)) {
+        int t = 0;
+        for (; t + 1 < count; t += 2, row += 2 * d) {
+            onchip::Inc<d, P> inc, inc2;
+            onchip::load_inc<d, P>(inc, row, letter);
+            onchip::load_inc<d, P>(inc2, row + d, letter);
+            onchip::fused_step<d, N, P>(ln, inc);
+            onchip::fused_step<d, N, P>(ln, inc2);
+        }
+        if (t < count) {
+            onchip::Inc<d, P> inc;
+            onchip::load_inc<d, P>(inc, row, letter);
+            onchip::fused_step<d, N, P>(ln, inc);
+        }
+    };
+    // the slot's own piece, tile by tile (staged once and for all where one tile holds it)
+    auto own_tiles = [&](auto &&f) __attribute__((always_inline)) {
+        for (int t0 = 0; t0 < T; t0 += A.tile) {
+            const int count = T - t0 < A.tile ? T - t0 : A.tile;
+            if (T > A.tile) {
+                __syncthreads();
+                stage(own, own_stride, k0 + t0, T, count);
+                __syncthreads();
+            }
+            f(own + slot * own_stride, t0, count);
+        }
+    };
+
+    Lane ln, bl;   // the slot's own piece, and what lies before it
+    onchip::identity_state<d, N, P>(bl);
+    if (T <= A.tile) stage(own, own_stride, k0, T, T);
+    // Folded block by block, a tile each, and the blocks multiplied: the rounding of a fold grows with the square root of its
+    // steps ((5,4), 16 paths of 2,000 points: error of blocks of 64 steps 1.8e-7, of the 500 steps of a piece in one go 3.7e-7, of one launch per
+    // level 2.2e-7).
+    float *join = rows + lds_rows(C, 1) * D;
+    for (int64_t t0 = 0; t0 < before; t0 += A.behind) {
+        const int count = before - t0 < A.behind ? (int)(before - t0) : A.behind;
+        if (t0 > 0) __syncthreads();
+        stage(old, old_stride, t0, before, count);
+        __syncthreads();
+        const float *row = old + slot * old_stride;
+        if (t0 == 0) {
+            fold(bl, row, count);
+        } else {
+            onchip::identity_state<d, N, P>(ln);
+            fold(ln, row, count);
+            if (active) onchip::store_state<d, N, P>(join + c * D, u, ln);
+            __syncthreads();
+            if (active) onchip::reg_product<d, N, P>(bl, join + c * D, u);
+        }
+    }
+    if (before == 0 || before > A.behind) __syncthreads();   // the own tile; the last block's rows have been read
+    if (C > 1) {
+        float *cur = rows, *nxt = C > 2 ? cur + (C - 1) * D : cur;
+        onchip::identity_state<d, N, P>(ln);
+        own_tiles([&](const float *row, int, int count) __attribute__((always_inline)) { fold(ln, row, count); });
+        if (active) {
+            if (c < C - 1) onchip::store_state<d, N, P>(cur + c * D, u, ln);
+            if (before > 0) onchip::store_state<d, N, P>(join + c * D, u, bl);
+        }
+        __syncthreads();
+        // Round with stride st.  Scan: the lanes of piece c multiply their value by the row of piece c + st and leave the product
+        // as that piece's new row (nobody needs the last one's).  Tree: piece c, a multiple of 2 st, absorbs piece c + st.
+        for (int st = 1; st < (before > 0 ? C : C - 1); st <<= 1) {
+            const bool scan = st < C - 1;
+            if (active) {
+                if (before > 0 && (c & (2 * st - 1)) == 0 && c + st < C) {
+                    onchip::reg_product<d, N, P>(bl, join + (c + st) * D, u);
+                    onchip::store_state<d, N, P>(join + c * D, u, bl);
+                }
+                if (scan) {
+                    if (c < st) onchip::store_state<d, N, P>(nxt + c * D, u, ln);
+                    if (c + st < C - 1) {
+                        onchip::reg_product<d, N, P>(ln, cur + (c + st) * D, u);
+                        onchip::store_state<d, N, P>(nxt + (c + st) * D, u, ln);
+                    }
+                }
+            }
+            __syncthreads();
+            if (scan) {
+                if (active && c < C - 1) onchip::load_state<d, N, P>(nxt + c * D, u, ln);
+                float *t = cur; cur = nxt; nxt = t;
+            }
+        }
+        if (before > 0) {
+            onchip::load_state<d, N, P>(join, u, bl);
+            if (c > 0) onchip::reg_product<d, N, P>(bl, cur + (c - 1) * D, u);
+        } else if (c > 0) {
+            onchip::load_state<d, N, P>(cur + (c - 1) * D, u, bl);
+        }
+    }
+
+    const int64_t k = k0 + (int64_t)c * T;
+    const int mine = !active || k >= K ? 0 : K - k < T ? (int)(K - k) : T;
+    float *dst = A.out + ((b0 + p) * K + k) * D;
+    own_tiles([&](const float *row, int t0, int count) __attribute__((always_inline)) {
+        for (int t = t0; t < t0 + count; ++t, row += d, dst += D) {
+            onchip::Inc<d, P> inc;
+            onchip::load_inc<d, P>(inc, row, letter);
+            onchip::fused_step<d, N, P>(bl, inc);
+            if (t < mine) onchip::store_state<d, N, P>(dst, u, bl);
+        }
+    });
+}
+
+}  // namespace rows
+}  // namespace sig
+
+#endif  // SIG_STREAM_ROWS_H

@@ -1,0 +1,59 @@
+"""Stream mode with the rows written straight from registers and the paths cut across workgroups (csrc/sig_stream_rows.h),
+against the fp64 oracle with the gates of test_gpu_parity.py, and the general route (the same plan without it)."""
+import numpy as np
+import pytest
+
+from paper_2501_08455_amd import workloads
+from test_gpu_parity import assert_parity, check, gpu, run_gpu  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+# d, depth, B, L, workgroups a path is cut across.  Slots of 8 lanes (eight to a wavefront) to 512 (eight wavefronts), whole
+# wavefronts and ragged ones; one piece or many; the shortest paths; pieces and workgroups left without steps; tiles that do not
+# hold a piece (one piece of 300 steps of (20,2)) nor what lies before it
+CASES = [
+    (2, 4, 3, 2, 1), (2, 4, 3, 3, 2), (2, 4, 5, 40, 1), (2, 4, 2, 257, 5), (3, 3, 7, 25, 1), (3, 3, 2, 90, 3), (4, 3, 3, 130, 4),
+    (8, 2, 4, 64, 1), (9, 2, 3, 200, 6), (10, 2, 2, 333, 2), (11, 2, 5, 33, 1), (16, 2, 3, 100, 4), (20, 2, 2, 301, 1),
+    (20, 2, 1, 1500, 2), (5, 3, 3, 99, 32), (8, 3, 2, 100, 3), (10, 3, 2, 75, 2), (11, 3, 2, 50, 2), (12, 3, 2, 61, 4),
+    (4, 4, 3, 256, 4), (4, 4, 1, 2, 1), (4, 4, 2, 700, 7), (5, 4, 2, 100, 16), (6, 4, 2, 60, 3), (7, 4, 1, 50, 2), (8, 4, 1, 40, 3),
+    (2, 5, 3, 70, 2), (3, 5, 2, 80, 3), (4, 5, 1, 60, 4), (2, 6, 2, 300, 3), (3, 6, 1, 50, 2),
+]
+
+
+@pytest.mark.parametrize("d,depth,B,L,segs", CASES)
+def test_rows_from_registers(gpu, oracle, d, depth, B, L, segs):  # noqa: F811
+    x = workloads.brownian_paths(B, L, d, seed=9100 + 31 * d + 7 * depth + L + segs)
+    plan = gpu.make_plan(gpu.SIG_VARIANT_ON_CHIP, row_workgroups=segs)
+    check(gpu, oracle, x, depth, True, plan, label="rows")
+
+
+@pytest.mark.parametrize("d,depth,B,L", [(4, 4, 64, 256), (5, 4, 16, 100), (3, 4, 300, 57), (16, 2, 1500, 40), (13, 2, 1027, 23),
+                                         (12, 3, 40, 90), (10, 3, 4, 700), (2, 6, 1025, 30), (20, 2, 5, 5000)])
+def test_planned_rows_agree_with_the_other_kernels(gpu, oracle, d, depth, B, L):  # noqa: F811
+    """The planner's own cut, whole paths side by side in a workgroup included, against the plan's other kernels: no row
+    further apart than two foldings of the same increments can be (assert_parity's bounds, on every row)."""
+    rc, plan = gpu.sig_plan(gpu.default_ctx(), B, L, d, depth, 1)
+    assert rc == gpu.SIG_OK and plan.row_workgroups >= 1, plan.as_dict()
+    x = workloads.brownian_paths(B, L, d, seed=9300 + d + L)
+    got = run_gpu(gpu, x, depth, True)
+    assert np.array_equal(got, run_gpu(gpu, x, depth, True, plan))
+    plan.row_workgroups = 0
+    assert_parity(got, run_gpu(gpu, x, depth, True, plan).astype(np.float64), x, depth, True)
+
+
+def test_a_point_that_is_not_a_number_spoils_the_same_coefficients(gpu):  # noqa: F811
+    x = workloads.brownian_paths(2, 120, 4, seed=77)
+    x[0, 71, 2] = np.nan
+    other = np.isfinite(run_gpu(gpu, x, 4, True, gpu.make_plan(gpu.SIG_VARIANT_ON_CHIP, prefix_depth=2)))
+    assert other[0, :70].all() and not other[0, 70:, 2].any()
+    for segs in (1, 4, 9):
+        got = run_gpu(gpu, x, 4, True, gpu.make_plan(gpu.SIG_VARIANT_ON_CHIP, row_workgroups=segs))
+        assert np.array_equal(np.isfinite(got), other)
+
+
+def test_rows_are_not_taken_where_they_do_not_apply(gpu):  # noqa: F811
+    for d, depth, L, segs in [(4, 6, 50, 2), (2, 3, 50, 1), (4, 4, 50, 33), (4, 4, 5, 5), (13, 3, 20, 1)]:
+        plan = gpu.make_plan(gpu.SIG_VARIANT_ON_CHIP, row_workgroups=segs)
+        assert gpu.sig_plan_validate(2, L, d, depth, 1, plan) == gpu.SIG_ERR_INVALID
+    assert gpu.sig_plan(None, 4096, 256, 4, 4, 1)[1].row_workgroups == 0
+    assert gpu.sig_plan(None, 64, 256, 4, 4, 0)[1].row_workgroups == 0
