@@ -141,6 +141,164 @@ struct Level {
     }
 };
 
+// ------------------------------------------------------------------------------------------
+// The sub-tree below a lane's word u, R = 1 or 2 levels of it, on matrix instructions.  The letters of a level stand in
+// QUADS groups of four and REST single ones.  v_mfma_f32_4x4x1 adds to a group in one instruction: four lanes side by
+// side, which must work on the same increment, hold one letter of it each (operand A), every lane has its own
+// multiplicand (operand B), and lane l's four accumulators take v[4 c + i] g[l] -- four fused multiply-adds, equal bit for
+// bit.  The rate of the pipe is that of the vector multiply-adds (9.5 cycles against 4 x 2.3), but a wavefront issues one
+// every 4 to 6 cycles whatever it does: with one to three wavefronts per SIMD it is the issue that binds, and four letters an
+// instruction lift it.  28 multiply-adds and 24 of these in a loop: 433 / 321 / 305 cycles a round at 1 / 3 / 4 wavefronts
+// per SIMD, 125 multiply-adds instead 630 / 371 / 395.  Alternating the two kinds costs up to a third of that (425 at three
+// wavefronts), so the vector ones come first and the matrix ones after them, behind a scheduling barrier.
+template <int d, int R>
+struct QuadTree {
+    static_assert(R == 1 || R == 2, "one or two levels below the word");
+    static constexpr int QUADS = d / 4;
+    static constexpr int REST = d - 4 * QUADS;
+    static constexpr int PARENTS = R == 2 ? d : 1;
+    static constexpr int SZ = geom(d, R + 1);
+    struct Words {
+        float low;                                            // u itself
+        vec4f mid[R == 2 && QUADS > 0 ? QUADS : 1];           // R == 2: the children of u
+        float mid_rest[R == 2 && REST > 0 ? REST : 1];
+        vec4f top[PARENTS][QUADS > 0 ? QUADS : 1];            // the last level
+        float top_rest[PARENTS][REST > 0 ? REST : 1];
+    };
+    struct Inc {   // an increment: groups of four letters across four lanes, then the single ones
+        float quad[QUADS > 0 ? QUADS : 1];
+        float rest[REST > 0 ? REST : 1];
+    };
+
+    static __device__ __forceinline__ vec4f add4(float v, float g, vec4f c) { return __builtin_amdgcn_mfma_f32_4x4x1f32(v, g, c, 0, 0, 0); }
+
+    static __device__ __forceinline__ void read(Inc &x, const float *row, int lane4)
+    {
+#pragma unroll
+        for (int c = 0; c < QUADS; ++c) x.quad[c] = row[4 * c + lane4];
+#pragma unroll
+        for (int a = 0; a < REST; ++a) x.rest[a] = row[4 * QUADS + a];
+    }
+
+    // everything below u; gu[r] the chain value at u for the target r levels below it
+    template <int E>
+    static __device__ __forceinline__ void step(Words &s, const Inc &x, const float (&gu)[E])
+    {
+        if constexpr (R == 1) {
+#pragma unroll
+            for (int a = 0; a < REST; ++a) s.top_rest[0][a] = fmaf(gu[1], x.rest[a], s.top_rest[0][a]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int c = 0; c < QUADS; ++c) s.top[0][c] = add4(x.quad[c], gu[1], s.top[0][c]);
+        } else {
+            // the chain values at the children (from their old coefficients), the children, then everything below them
+            const float half = gu[2] * 0.5f;
+            float g[d];
+#pragma unroll
+            for (int c = 0; c < QUADS; ++c) {
+                const vec4f q = add4(x.quad[c], half, s.mid[c]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) g[4 * c + i] = q[i];
+                s.mid[c] = add4(x.quad[c], gu[1], s.mid[c]);
+            }
+#pragma unroll
+            for (int a = 0; a < REST; ++a) {
+                g[4 * QUADS + a] = fmaf(half, x.rest[a], s.mid_rest[a]);
+                s.mid_rest[a] = fmaf(gu[1], x.rest[a], s.mid_rest[a]);
+            }
+#pragma unroll
+            for (int w = 0; w < d; ++w)
+#pragma unroll
+                for (int a = 0; a < REST; ++a) s.top_rest[w][a] = fmaf(g[w], x.rest[a], s.top_rest[w][a]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int w = 0; w < d; ++w)
+#pragma unroll
+                for (int c = 0; c < QUADS; ++c) s.top[w][c] = add4(x.quad[c], g[w], s.top[w][c]);
+        }
+    }
+
+    static __device__ __forceinline__ void clear(Words &s)
+    {
+        const vec4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
+        s.low = 0.0f;
+#pragma unroll
+        for (auto &q : s.mid) q = zero;
+#pragma unroll
+        for (auto &x : s.mid_rest) x = 0.0f;
+#pragma unroll
+        for (auto &w : s.top)
+#pragma unroll
+            for (auto &q : w) q = zero;
+#pragma unroll
+        for (auto &w : s.top_rest)
+#pragma unroll
+            for (auto &x : w) x = 0.0f;
+    }
+
+    // the words in the order of a lane's state: sub-level r at geom(d, r)
+    static __device__ __forceinline__ void unpack(const Words &s, float (&row)[SZ])
+    {
+        row[0] = s.low;
+        if constexpr (R == 2) {
+#pragma unroll
+            for (int a = 0; a < d; ++a) row[1 + a] = a < 4 * QUADS ? s.mid[a / 4][a % 4] : s.mid_rest[a - 4 * QUADS];
+        }
+#pragma unroll
+        for (int w = 0; w < PARENTS; ++w)
+#pragma unroll
+            for (int a = 0; a < d; ++a) row[geom(d, R) + w * d + a] = a < 4 * QUADS ? s.top[w][a / 4][a % 4] : s.top_rest[w][a - 4 * QUADS];
+    }
+};
+
+// Whether the final-mode folds of (d, N, P) run on matrix instructions (QuadTree): from four channels and depth 3 on, where the
+// arithmetic and not the reading of the path binds.  Four lanes side by side must share an increment, so a path (or a chunk of
+// one) takes lanes in fours; where that leaves more than one in 25 idle the vector multiply-adds stay: (5,4), 28 lanes for
+// 25, 65,536 paths of 100 points 172 us and 188 on matrix instructions; (7,4), 52 for 49, 1,024 paths of 40 points 13 and 16.
+// Vector multiply-adds and matrix instructions, us: (8,3) 128 paths of 150 points 7 and 6, 8,192 of 150 50 and 32, 65,536 of
+// 150 351 and 239; (9,3), 84 lanes for 81, 8,192 of 150 74 and 46; (10,3) 8,192 of 600 428 and 263; (8,4) 8,192 of 600 599 and
+// 478; (8,5) 128 of 600 142 and 91; (10,4) 8,192 of 150 428 and 388; (4,4) 65,536 of 150 134 and 128, 128 of 40 4.0 both (the
+// eight and ten letters of a step were as many reads of LDS; in fours across lanes they are two or three).
+template <int d, int N, int P>
+constexpr bool quad_fold()
+{
+    constexpr int Q = cpow(d, P);
+    return d >= 4 && d != 5 && N >= 3 && P >= 1 && (N - P == 1 || N - P == 2) && (Q + 3) / 4 * 4 * 24 <= Q * 25;
+}
+
+// One step of a lane on QuadTree: as Level / Descend below, the levels 1 .. P of u's prefixes here and the rest in the tree.
+template <int d, int N, int P>
+struct QuadStep {
+    using Sh = Shape<d, N, P>;
+    using Tree = QuadTree<d, N - P>;
+    struct Row {
+        typename Tree::Inc inc;
+        float du[P];   // the increment at the letters of u
+    };
+    static __device__ __forceinline__ void read(Row &x, const float *row, const int *letter, int lane4)
+    {
+        Tree::read(x.inc, row, lane4);
+#pragma unroll
+        for (int m = 0; m < P; ++m) x.du[m] = row[letter[m]];
+    }
+    static __device__ __forceinline__ void run(typename Tree::Words &s, float (&pre)[Sh::NPRE], const Row &x)
+    {
+        float gu[Sh::R + 1];
+        gu[0] = 0.0f;
+        static_for<0, N>([&](auto nc) __attribute__((always_inline)) {
+            constexpr int n = N - decltype(nc)::value;
+            constexpr int mtop = (n - 1 < P) ? n - 1 : P;
+            float g = 1.0f;
+#pragma unroll
+            for (int m = 1; m <= mtop; ++m) g = fmaf(g, x.du[m - 1] * (1.0f / (float)(n - m + 1)), m < P ? pre[m - 1] : s.low);
+            if constexpr (n > P) gu[n - P] = g;
+            else if constexpr (n == P) s.low = fmaf(g, x.du[n - 1], s.low);
+            else pre[n - 1] = fmaf(g, x.du[n - 1], pre[n - 1]);
+        });
+        Tree::step(s, x.inc, gu);
+    }
+};
+
 // one staged increment as a lane needs it: all d components and the components at its own prefix letters
 template <int d, int P>
 struct Inc {
@@ -414,11 +572,17 @@ constexpr int max_threads() { return (CHUNKED && Shape<d, N, P>::SZ <= 64) ? 512
 
 // Workgroups of the CHUNKED kernels may have up to 512 threads (when the lane state is small enough): only chunks * Q lanes fold, but every
 // thread takes part in the LDS products, which are latency bound with one wavefront per SIMD.
-template <int d, int N, int P, bool CHUNKED, bool STREAM, bool PIPE, bool FLAT = false>
-__global__ __launch_bounds__((max_threads<d, N, P, CHUNKED>())) void sig_on_chip_kernel(OnChipArgs A)
+// QUAD: the fold runs on matrix instructions (final mode, quad_fold); a chunk takes QS lanes, Q rounded up to fours.  (With
+// two wavefronts per SIMD asked for, 256 registers, the compiler keeps the accumulators in ordinary ones; three where the
+// state leaves room for them, which the loader that keeps a tile in registers would miss by a few registers.)
+template <int d, int N, int P, bool CHUNKED, bool STREAM, bool PIPE, bool FLAT = false, bool QUAD = false>
+__global__ __launch_bounds__((max_threads<d, N, P, CHUNKED>())) __attribute__((amdgpu_waves_per_eu(!QUAD ? 1 : Shape<d, N, P>::SZ + 4 * P <= 100 ? 3 : 2)))
+void sig_on_chip_kernel(OnChipArgs A)
 {
+    static_assert(!QUAD || (!STREAM && quad_fold<d, N, P>()), "final mode only");
     using Sh = Shape<d, N, P>;
     constexpr int Q = Sh::Q;
+    constexpr int QS = QUAD ? (Q + 3) / 4 * 4 : Q;
     constexpr int D = Sh::D;
 
     SIG_PRIO_MEMORY();
@@ -460,15 +624,18 @@ __global__ __launch_bounds__((max_threads<d, N, P, CHUNKED>())) void sig_on_chip
         active = sw < SPW && gi < G && group0 + gi < ngroups;
         if (sw >= SPW || gi >= G) { gi = 0; c = 0; }
     } else if (!big) {
-        const int LG = C * Q;
+        const int LG = C * QS;
         G = A.groups;
         gi = tid / LG;
         const int rem = tid - gi * LG;
-        c = CHUNKED ? rem / Q : 0;
-        u = (unsigned)(rem - c * Q);
+        c = CHUNKED ? rem / QS : 0;
+        u = (unsigned)(rem - c * QS);
         group0 = blockIdx.x * (unsigned)G;
         active = gi < G && group0 + gi < ngroups;
         if (gi >= G) { gi = 0; c = 0; }
+        if constexpr (QS != Q) {   // lanes that fill up a chunk's last four
+            if (u >= (unsigned)Q) { active = false; u = Q - 1; }
+        }
     } else {
         const unsigned NB = (Q + nthr - 1) / nthr;
         G = 1;
@@ -593,9 +760,40 @@ __global__ __launch_bounds__((max_threads<d, N, P, CHUNKED>())) void sig_on_chip
                 }
             }
         }
+        using QStep = QuadStep<d, N, QUAD ? P : N - 1>;
+        typename QStep::Tree::Words words;
+        if constexpr (QUAD) QStep::Tree::clear(words);
         auto consume = [&](const float *tile, int t0, int row_stride) {
             const int steps = (T - t0 < TT) ? T - t0 : TT;
             const float *row = tile + mygc * row_stride;
+            if constexpr (QUAD && PIPE && Sh::SZ > 64) {
+                // (a tile in registers beside a large state: no room for the next step's operands)
+                typename QStep::Row x;
+                for (int t = 0; t < steps; ++t, row += d) {
+                    QStep::read(x, row, letter, tid & 3);
+                    QStep::run(words, ln.pre, x);
+                }
+                return;
+            } else if constexpr (QUAD) {
+                // two steps per round; the next step's operands are read before this one's arithmetic, which covers their way
+                // from LDS (behind the last step its own row is read again)
+                typename QStep::Row x, y;
+                if (steps > 0) QStep::read(x, row, letter, tid & 3);
+                int t = 0;
+                for (; t + 2 <= steps; t += 2) {
+                    QStep::read(y, row + d, letter, tid & 3);
+                    __builtin_amdgcn_sched_barrier(0);
+                    QStep::run(words, ln.pre, x);
+                    __builtin_amdgcn_sched_barrier(0);
+                    row += t + 2 < steps ? 2 * d : d;
+                    QStep::read(x, row, letter, tid & 3);
+                    __builtin_amdgcn_sched_barrier(0);
+                    QStep::run(words, ln.pre, y);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (t < steps) QStep::run(words, ln.pre, x);
+                return;
+            }
             Inc<d, P> inc;
             int t = 0;
             if constexpr (!emit && Sh::SZ <= 40) {
@@ -789,6 +987,7 @@ __global__ __launch_bounds__((max_threads<d, N, P, CHUNKED>())) void sig_on_chip
                 __syncthreads();
             }
         }
+        if constexpr (QUAD) QStep::Tree::unpack(words, ln.s);
     };
 
     identity_state<d, N, P>(ln);
@@ -905,7 +1104,10 @@ __global__ __launch_bounds__((max_threads<d, N, P, CHUNKED>())) void sig_on_chip
 // in LDS (see the kernel for how).  A lane of the fold then needs per step one multiply-add per target level,
 //     g_P^{(n)}(u) = S_P[u] + table[step][u / d][n - P] * v[u_P],
 // before it descends into its own sub-tree; it keeps no prefix coefficients at all (127 vector instructions per
-// step instead of 170 for d = 10, depth 6).
+// step instead of 170 for d = 10, depth 6), and four letters of the sub-tree go to one matrix instruction (QuadTree: 28
+// vector and 24 matrix instructions in the place of the 127).  16 paths of 128 points, 10 channels, depth 6: 79 us on vector
+// multiply-adds alone, 84 with the two kinds mixed, 69 with the matrix instructions in a run of their own and the next
+// step's operands read ahead.
 template <int d, int N, int P>
 struct SharedChain {
     using Sh = Shape<d, N, P>;
@@ -915,44 +1117,23 @@ struct SharedChain {
     static __host__ __device__ constexpr int nq(int threads) { return (threads - 1) / d + 2; }
     // LDS of one tile: shared_chain_lds_floats (the kernel lays its arrays out in that order)
 
-    // sub-levels r >= 2 below the child `a` of u (local index idx in sub-level r - 1), target sub-level tgt
-    template <int tgt, int r>
-    static __device__ __forceinline__ void deeper(float (&s)[Sh::SZ], const float (&v)[d], float g, int idx)
-    {
-#pragma unroll
-        for (int a = 0; a < d; ++a) {
-            const int child = idx * d + a;
-            if constexpr (r == tgt) {
-                s[Sh::sub_off(tgt) + child] = fmaf(g, v[a], s[Sh::sub_off(tgt) + child]);
-            } else {
-                const float g2 = fmaf(g, v[a] * (1.0f / (float)(tgt - r + 1)), s[Sh::sub_off(r) + child]);
-                deeper<tgt, r + 1>(s, v, g2, child);
-            }
-        }
-    }
+    using Tree = QuadTree<d, R>;
+    struct Row {   // a step's operands: its increment, the chain values at u's parent, and the increment at u's last letter
+        typename Tree::Inc inc;
+        float G[E];
+        float duP;
+    };
 
     // One step S <- S (x) exp(v) on the sub-tree below u, given the chain values G at u's parent from the table and
     // duP = v[u_P] (Eq. 3 with Eqs. 2 and 4 in Horner form; deeper levels first, they read the old upper ones).
-    static __device__ __forceinline__ void step(float (&s)[Sh::SZ], const float (&v)[d], const float (&G)[E], float duP)
+    static __device__ __forceinline__ void step(typename Tree::Words &s, const Row &x)
     {
         // chain values at u for the target levels P + 1 .. N, then S[u] itself
         float gu[E];
 #pragma unroll
-        for (int e = 1; e < E; ++e) gu[e] = fmaf(G[e], duP, s[0]);
-        s[0] = fmaf(G[0], duP, s[0]);
-        // per child a of u: the chain values below it for the target sub-levels 2 .. R (from the old S[u a]), S[u a]
-        // itself, then everything below it, deepest target first (one child at a time keeps few chain values live)
-#pragma unroll
-        for (int a = 0; a < d; ++a) {
-            float g2[R > 1 ? R - 1 : 1];
-#pragma unroll
-            for (int tg = 2; tg <= R; ++tg) g2[tg - 2] = fmaf(gu[tg] * (1.0f / (float)tg), v[a], s[Sh::sub_off(1) + a]);
-            s[Sh::sub_off(1) + a] = fmaf(gu[1], v[a], s[Sh::sub_off(1) + a]);
-            static_for<2, R + 1>([&](auto tc) __attribute__((always_inline)) {
-                constexpr int tg = R + 2 - decltype(tc)::value;   // R .. 2
-                deeper<tg, 2>(s, v, g2[tg - 2], a);
-            });
-        }
+        for (int e = 1; e < E; ++e) gu[e] = fmaf(x.G[e], x.duP, s.low);
+        s.low = fmaf(x.G[0], x.duP, s.low);
+        Tree::step(s, x.inc, gu);
     }
 };
 
@@ -1086,24 +1267,43 @@ void sig_shared_chain_kernel(OnChipArgs A)
     SIG_PRIO_COMPUTE();
     const int myql = (int)(u / d - q0);
     const int letterP = (int)(u % d);
-    float st[Sh::SZ];
-#pragma unroll
-    for (int i = 0; i < Sh::SZ; ++i) st[i] = 0.0f;
+    typename SC::Tree::Words words;
+    SC::Tree::clear(words);
     if (wave_active) {
-        // operands of a step: the increment (all lanes of a wavefront read the same row: a broadcast), its component at
-        // u's last letter and the table's entries for u's parent
+        // operands of a step: the increment (four lanes side by side read four letters, the single ones are broadcasts), its
+        // component at u's last letter and the table's entries for u's parent
         const float *row = inc;
         const float *tab = table + myql * E;
-        for (int t = 0; t < steps; ++t, row += d, tab += NQ * E) {
-            float v[d], G[E];
+        auto on = [&](int n) __attribute__((always_inline)) {
+            row += n * d;
+            tab += n * NQ * E;
+        };
+        auto read = [&](typename SC::Row &x) __attribute__((always_inline)) {
+            SC::Tree::read(x.inc, row, tid & 3);
+            x.duP = row[letterP];
 #pragma unroll
-            for (int a = 0; a < d; ++a) v[a] = row[a];
-            const float duP = row[letterP];
-#pragma unroll
-            for (int e = 0; e < E; ++e) G[e] = tab[e];
-            SC::step(st, v, G, duP);
+            for (int e = 0; e < E; ++e) x.G[e] = tab[e];
+        };
+        // the next step's operands are read before this one's arithmetic, which covers their way from LDS
+        typename SC::Row x, y;
+        if (steps > 0) read(x);
+        int t = 0;
+        for (; t + 2 <= steps; t += 2) {
+            on(1);
+            read(y);
+            __builtin_amdgcn_sched_barrier(0);
+            SC::step(words, x);
+            __builtin_amdgcn_sched_barrier(0);
+            on(t + 2 < steps);
+            read(x);
+            __builtin_amdgcn_sched_barrier(0);
+            SC::step(words, y);
+            __builtin_amdgcn_sched_barrier(0);
         }
+        if (t < steps) SC::step(words, x);
     }
+    float st[Sh::SZ];
+    SC::Tree::unpack(words, st);
 
     // ---- results: the lanes' sub-trees, and the prefix words from the threads that hold their totals
     SIG_PRIO_MEMORY();
@@ -1409,20 +1609,30 @@ int64_t on_chip_lds_bytes(const OnChipArgs &A)
     return floats * (int64_t)sizeof(float);
 }
 
+// a workgroup holds as many chunks with lanes in fours as without, so plans need not know of them
+constexpr bool fours_fit(int Q)
+{
+    for (int threads = kWave; threads <= 512; threads += kWave)
+        if (threads / Q != threads / ((Q + 3) / 4 * 4)) return false;
+    return true;
+}
+
 template <int d, int N, int P, bool CHUNKED, bool STREAM>
 void on_chip_launch_pipe(const OnChipArgs &A, dim3 g, dim3 blk, size_t lds, hipStream_t st)
 {
+    constexpr bool QUAD = !STREAM && quad_fold<d, N, P>();
+    static_assert(!QUAD || fours_fit(Shape<d, N, P>::Q), "the launch is planned with Q lanes per chunk");
     if (A.pipe) {
-        hipLaunchKernelGGL((sig_on_chip_kernel<d, N, P, CHUNKED, STREAM, true>), g, blk, lds, st, A);
+        hipLaunchKernelGGL((sig_on_chip_kernel<d, N, P, CHUNKED, STREAM, true, false, QUAD>), g, blk, lds, st, A);
         return;
     }
     if constexpr (!CHUNKED) {
         if (A.flat_tile) {
-            hipLaunchKernelGGL((sig_on_chip_kernel<d, N, P, false, STREAM, false, true>), g, blk, lds, st, A);
+            hipLaunchKernelGGL((sig_on_chip_kernel<d, N, P, false, STREAM, false, true, QUAD>), g, blk, lds, st, A);
             return;
         }
     }
-    hipLaunchKernelGGL((sig_on_chip_kernel<d, N, P, CHUNKED, STREAM, false>), g, blk, lds, st, A);
+    hipLaunchKernelGGL((sig_on_chip_kernel<d, N, P, CHUNKED, STREAM, false, false, QUAD>), g, blk, lds, st, A);
 }
 
 // FINAL_ONLY: compiled without the kernels of stream mode
