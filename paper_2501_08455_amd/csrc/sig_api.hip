@@ -306,6 +306,11 @@ constexpr int kDeepShortPath = 256;      // increments up to which a deeper entr
 constexpr int kDeepShortPathHeavy = 768; // ... behind a few-lane or heavy entry
 constexpr int kDeepShortPathWide = 128;  // ... when the deeper entry has more than 128 lanes per path
 constexpr int kDeepBatchFactorFewLanes = 4;   // batch limit of the deeper entry, in units of one wavefront per SIMD
+constexpr int64_t kDeepExtraPerCu = 110000;   // multiply-adds per CU that a light deeper entry may cost a batch beyond the shallower one (0.6 us)
+constexpr int kDeepLightState = 16;      // ... a state of at most this many floats
+constexpr int kDeepLightLeast = 9;       // ... from this many increments on
+constexpr int kDeepLightShort = 48;      // ... up to this many,
+constexpr int kDeepLightLong = 500;      // ... and with two levels below the word from this many on
 constexpr int kStreamDeepShortPath = 128;   // stream mode, under-filled chip: the entry behind a small state up to this many increments ...
 constexpr int kStreamDeepHeavyState = 32;   // ... or at any length behind a small state of more floats than this
 constexpr int kStreamFewLanes = 10;      // stream mode: kernels with at most this many lanes per path aim at two wavefronts per SIMD
@@ -331,10 +336,23 @@ constexpr int kWideMostSteps = 128;           // in chunks of at most this many 
 // the range from 16 on has been measured, and fewer paths stay with the level-scan family until it has.
 bool wide_on_chip_wanted(int64_t B, int stream_flag) { return !stream_flag && B >= tune::kWideMinPaths; }
 
+// Vector multiply-adds of one step of a path with lanes that own the words below p letters (Level / Descend in sig_onchip.h)
+int64_t step_multiply_adds(int d, int depth, int p)
+{
+    int64_t lanes = 1, sum = 0;
+    for (int m = 0; m < p; ++m) lanes *= d;
+    for (int n = 1; n <= depth; ++n) {
+        sum += n < p ? n : p;
+        int64_t words = 1;
+        for (int r = 1; r <= n - p; ++r) sum += words *= d;
+    }
+    return lanes * sum;
+}
+
 // Which compiled prefix depth to use for (d, depth); entries of one (d, depth) are ordered by increasing prefix depth.
 //  - final mode: the first entry whose lane state is small (several wavefronts per SIMD, chunk tree in registers);
 //    an entry behind it (lighter steps, more lanes) for small batches of short paths, which are bound by the latency of
-//    the sequential steps; an entry whose lanes span several workgroups only while the batch cannot fill the chip;
+//    the sequential steps, and a light one for any batch whose arithmetic it hardly adds to; an entry whose lanes span several workgroups only while the batch cannot fill the chip;
 //  - stream mode: bound by the stores, so the deepest entry whose lanes fit a workgroup, but behind a small-state entry
 //    only while that one has few lanes per path.
 const OnChipKernelInfo *pick_on_chip(int d, int depth, int stream_flag, int64_t B, int64_t K, int cus)
@@ -345,7 +363,9 @@ const OnChipKernelInfo *pick_on_chip(int d, int depth, int stream_flag, int64_t 
         if (e->d != d || e->depth != depth) continue;
         if (!best) { best = e; continue; }
         const bool spans_workgroups = e->lanes_per_chunk > kThreads && best->lanes_per_chunk <= kThreads;
-        if (spans_workgroups && (stream_flag || B * best->lanes_per_chunk >= (int64_t)cus * kWave)) continue;
+        // (up to 20,480 lanes of the shallower entry on 256 CUs, a quarter beyond a wavefront on each: (8,4) 256 ... 320 paths of
+        // 8 ... 2,000 points 1.15-2.6x, 304 x 97 35 -> 13 us; (9,4) from 205 on 1.42x, (10,4) from 165 on 1.47x in the mean)
+        if (spans_workgroups && (stream_flag || B * best->lanes_per_chunk * 4 > (int64_t)cus * kWave * 5)) continue;
         const bool best_small = best->p > 0 && best->state_floats <= tune::kSmallState;
         const bool best_few_lanes = best->lanes_per_chunk < tune::kFewLanes;
         // final mode, behind a small-state entry: short paths and a batch below one wavefront per SIMD (four behind a
@@ -357,6 +377,20 @@ const OnChipKernelInfo *pick_on_chip(int d, int depth, int stream_flag, int64_t 
         const int64_t few_lanes = (int64_t)cus * 4 * kWave * (best_few_lanes ? tune::kDeepBatchFactorFewLanes : 1);
         const bool short_and_few = !stream_flag && best_small && e->lanes_per_chunk < kThreads &&
                                    B * e->lanes_per_chunk * (kThreads / e->lanes_per_chunk) <= few_lanes && K <= short_path;
+        // ... and light states, at depth 4 and less, wherever the multiply-adds that they cost beyond the shallower entry's take less
+        // than the shorter chain of a step saves: batches of short paths, and with two levels below the word long paths too.
+        // Shallower and deeper entry, us: (5,4) 512 paths of 25 points 5.8 and 4.3, (7,3) 8,192 of 25 13.2 and 10.5, (6,3) 4,096 of
+        // 25 7.7 and 5.0, (3,4) 8 of 800 12.8 and 8.5, 4,096 of 800 40.7 and 28.6; 6,953 random calls that the rules changed 1.38x in
+        // the mean, eight of them 0.92-0.97x.  Error against 64 bits 0.99 times what it was.  Behind the bound (28 million multiply-adds on 256 CUs) the shallower
+        // one leads: (5,4) 1,024 of 100 0.94x, (5,3) 8,192 of 200 0.79x, and between 48 and 500 increments either does ((3,4)
+        // 5,056 of 142 0.78x, 8,192 of 400 1.53x).  Behind states below 31 floats ((3,3) 0.56-1.2x) and behind 16 lanes and more
+        // of matrix instructions ((4,4) 2,048 of 50 0.87x) nothing is gained on balance.
+        const bool matrix = d >= 4 && d != 5 && d != 7 && depth >= 3 && best->lanes_per_chunk >= tune::kFewLanes;
+        const bool light = e->state_floats <= tune::kDeepLightState && depth <= 4 && best->state_floats >= tune::kFewLaneMinState && !matrix;
+        const bool light_length = (K >= tune::kDeepLightLeast && K <= tune::kDeepLightShort) || (depth - e->p >= 2 && K >= tune::kDeepLightLong);
+        const bool cheap = !stream_flag && best_small && e->lanes_per_chunk < kThreads && light && light_length &&
+                           B <= (int64_t)cus * tune::kDeepExtraPerCu / K &&
+                           B * K * (step_multiply_adds(d, depth, e->p) - step_multiply_adds(d, depth, best->p)) <= (int64_t)cus * tune::kDeepExtraPerCu;
         // stream mode, behind a small-state entry: only while that one has few lanes per path (the four-lane entry of
         // two channels measured 1.9-4.4x over the two-lane one at 1,024 to 16,384 paths as well as below)
         // ... or the batch leaves the small-state entry at most half a wavefront per SIMD and the deeper one fits a
@@ -372,7 +406,7 @@ const OnChipKernelInfo *pick_on_chip(int d, int depth, int stream_flag, int64_t 
         // state) measured 1.1-1.6x at every batch and length once it fits its small-state budget
         const bool two_lanes = !stream_flag && best_small && best->lanes_per_chunk <= 2 &&
                                e->state_floats <= tune::kSmallState && e->lanes_per_chunk <= 4;
-        if (stream_flag || best->state_floats > tune::kSmallState || best->p == 0 || short_and_few || two_lanes) best = e;
+        if (stream_flag || best->state_floats > tune::kSmallState || best->p == 0 || short_and_few || cheap || two_lanes) best = e;
     }
     return best;
 }
