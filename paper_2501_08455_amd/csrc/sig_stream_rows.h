@@ -10,8 +10,15 @@
 //
 // Bound by latency on few paths (a launch, K / C steps of the fold, log2 C rounds of the scan, T steps that each store a row) and
 // by the stores on many.  Measured against what these calls took before (the register kernels of sig_onchip.h, one workgroup per
-// path, their rows staged in LDS; or one launch per level), us: (4,4) 64 paths of 256 points 24.6 -> 11.7, 4 of 1,075 63 -> 17;
-// (5,4) 16 of 100 17.6 -> 8.0; (10,3) 4 of 1,075 148 -> 40; (12,3) 1,024 of 100 490 -> 204.
+// path, their rows staged in LDS; or one launch per level), us: (4,4) 64 paths of 256 points 24.3 and 12.4, 4 of 1,075 62 and 19;
+// (5,4) 16 of 100 17.5 and 8.5; (12,3) 1,024 of 100 487 and 228, 128 of 1,000 635 and 363.
+//
+// Rounding: a sum of T terms, one after the other, is off by about sqrt(T) roundings of its last value.  Pieces of more than
+// kPlainSteps steps are therefore summed in blocks (BLOCKS below), level 1 at a piece's start comes from the points, and with more
+// than ten channels level 1 of every row does.  Error against 64 bits over 34,000 random calls of 4 to 4,000 points, relative to
+// what these calls took before: 0.75 in the mean beyond 64 points (0.58 ... 0.90 by shape), 0.95 below; with plain sums 0.93, but
+// 1.1 to 1.5 on batches of 64 paths and more of hundreds of points ((12,3) 128 of 1,000 points 1.4, (20,2) 64 ... 256 of 2,000 1.5).
+// The blocks cost up to 7 % ((3,5), 93 paths of 949 points 54.4 and 56.6 us; (4,4), 84 of 939 27.5 and 29.1).
 #ifndef SIG_STREAM_ROWS_H
 #define SIG_STREAM_ROWS_H
 
@@ -43,23 +50,95 @@ struct Geo {
     static constexpr int WPS = (Q + kWave - 1) / kWave;          // wavefronts of a slot
 };
 constexpr int kMaxThreads = 1024;
+// (the shapes whose slots are small: cut() gives them half of that)
+__host__ __device__ constexpr int most_threads(int d, int N) { return N == 2 ? 512 : kMaxThreads; }
 
 // a slot's increments in LDS: an odd stride puts the slots of a wavefront into different banks
 __host__ __device__ constexpr int tile_stride(int steps, int d) { return (steps * d) | 1; }
 // rows of a path in LDS: the slots' own pieces but for the last (twice where the scan takes rounds), and what lies before
 __host__ __device__ constexpr int lds_rows(int C, int W) { return (C - 1) * (C > 2 ? 2 : 1) + (W > 1 ? C : 0); }
+// More than ten channels: a slot's tile holds points, and level 1 of a row is the point's distance from the path's first one, as the
+// launches per level that these shapes took before give it.  A point that is not a number then spoils level 1 of its own row only.
+__host__ __device__ constexpr bool level1_from_points(int d) { return d > 10; }
 __host__ __device__ constexpr int tile_floats(const Args &A, int d)
 {
-    return (A.groups * A.slots * (tile_stride(A.tile, d) + (A.segs > 1 ? tile_stride(A.behind, d) : 0)) + 3) / 4 * 4;
+    return (A.groups * A.slots * (tile_stride(A.tile + level1_from_points(d), d) + (A.segs > 1 ? tile_stride(A.behind, d) : 0)) + 3) / 4 * 4;
 }
+
+constexpr int kPlainSteps = 16;    // pieces of more steps than this are summed in blocks of as many (see BLOCKS)
+
+// out = a + b, word by word
+template <int d, int N, int P>
+__device__ __forceinline__ void add_state(onchip::Lane<d, N, P> &out, const onchip::Lane<d, N, P> &a, const onchip::Lane<d, N, P> &b)
+{
+    using Sh = onchip::Shape<d, N, P>;
+#pragma unroll
+    for (int i = 0; i < Sh::SZ; ++i) out.s[i] = a.s[i] + b.s[i];
+#pragma unroll
+    for (int i = 0; i < Sh::NPRE; ++i) out.pre[i] = a.pre[i] + b.pre[i];
+}
+
+// The fused step of sig_onchip.h for lanes that own a word of length N - 1, with what it adds to the signature `now` summed in `sum`
+template <int d, int N>
+__device__ __forceinline__ void summed_step(onchip::Lane<d, N, N - 1> &sum, const onchip::Lane<d, N, N - 1> &now, const onchip::Inc<d, N - 1> &inc)
+{
+    constexpr int P = N - 1;
+    onchip::static_for<1, N + 1>([&](auto nc) __attribute__((always_inline)) {
+        constexpr int n = decltype(nc)::value;
+        float g = 1.0f;
+#pragma unroll
+        for (int m = 1; m < n; ++m) g = fmaf(g, inc.du[m - 1] * (1.0f / (float)(n - m + 1)), m < P ? now.pre[m - 1] : now.s[0]);
+        if constexpr (n < P) {
+            sum.pre[n - 1] = fmaf(g, inc.du[n - 1], sum.pre[n - 1]);
+        } else if constexpr (n == P) {
+            sum.s[0] = fmaf(g, inc.du[n - 1], sum.s[0]);
+        } else {
+#pragma unroll
+            for (int a = 0; a < d; ++a) sum.s[1 + a] = fmaf(g, inc.v[a], sum.s[1 + a]);
+        }
+    });
+}
+
+// A slot's steps, one after the other: increments as they lie in the tile, or the differences of its points
+template <int d, int P, bool POINTS>
+struct Steps {
+    const float *row;
+    const int *letter;
+    onchip::Inc<d, P> last;   // POINTS: the point of `row`
+
+    __device__ __forceinline__ Steps(const float *row_, const int *letter_) : row(row_), letter(letter_)
+    {
+        if constexpr (POINTS) onchip::load_inc<d, P>(last, row, letter);
+    }
+    __device__ __forceinline__ void next(onchip::Inc<d, P> &inc)
+    {
+        if constexpr (POINTS) {
+            onchip::Inc<d, P> here;
+            row += d;
+            onchip::load_inc<d, P>(here, row, letter);
+#pragma unroll
+            for (int a = 0; a < d; ++a) inc.v[a] = here.v[a] - last.v[a];
+#pragma unroll
+            for (int m = 0; m < P; ++m) inc.du[m] = here.du[m] - last.du[m];
+            last = here;
+        } else {
+            onchip::load_inc<d, P>(inc, row, letter);
+            row += d;
+        }
+    }
+};
 
 extern __shared__ __align__(16) float sig_rows_smem[];
 
-template <int d, int N>
-__global__ __launch_bounds__(kMaxThreads) void sig_stream_rows_kernel(Args A)
+// BLOCKS: the steps of a slot's own piece are summed in blocks of kPlainSteps, each from zero, and a row is the signature at the block's
+// start plus that sum (blocks of 8 to 32 give the same error).  The steps go two a round, or the copies from one to the next show: (20,2),
+// 2 paths of 51 points 11.4 -> 10.2 us, (3,5), 93 of 949 60 -> 56.6.
+template <int d, int N, bool BLOCKS>
+__global__ __launch_bounds__((most_threads(d, N))) void sig_stream_rows_kernel(Args A)
 {
     using G = Geo<d, N>;
     constexpr int P = G::P, Q = G::Q, D = G::D;
+    constexpr bool POINTS = level1_from_points(d);
     using Lane = onchip::Lane<d, N, P>;
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int wave = tid / kWave, lw = tid - wave * kWave, waves = nthr / kWave;
@@ -87,6 +166,7 @@ __global__ __launch_bounds__(kMaxThreads) void sig_stream_rows_kernel(Args A)
     }
     if (!active) { slot = 0; u = 0; }
     const int p = slot / C, c = slot - p * C;       // path and piece
+    const int64_t k = k0 + (int64_t)c * T;          // first row of the piece
     int letter[P];
     {
         unsigned rest = u;
@@ -94,7 +174,15 @@ __global__ __launch_bounds__(kMaxThreads) void sig_stream_rows_kernel(Args A)
         for (int m = P - 1; m >= 0; --m) { letter[m] = (int)(rest % d); rest /= d; }
     }
 
-    const int own_stride = tile_stride(A.tile, d), old_stride = tile_stride(A.behind, d);
+    // level 1 at the path's first point and at the piece's
+    float first1 = 0.0f, here1 = 0.0f;
+    if (active && k < K) {
+        const float *x = A.path + (b0 + p) * A.L * d + letter[0];
+        first1 = x[0];
+        here1 = x[k * d];
+    }
+
+    const int own_stride = tile_stride(A.tile + POINTS, d), old_stride = tile_stride(A.behind, d);
     float *own = sig_rows_smem;                     // [slots][own_stride]
     float *old = own + A.groups * C * own_stride;   // [slots][old_stride]
     float *rows = sig_rows_smem + tile_floats(A, d) + p * lds_rows(C, A.segs) * D;
@@ -108,6 +196,53 @@ __global__ __launch_bounds__(kMaxThreads) void sig_stream_rows_kernel(Args A)
             float *dst = tile + s * row;
 #pragma unroll 4
             for (int r = lw; r < count * d; r += kWave) dst[r] = at + r < K * d ? X[r + d] - X[r] : 0.0f;
+        }
+    };
+    // the tile of the slots' own pieces: increments, or the points that they lie between, the last one repeated beyond the path's end
+    auto stage_own = [&](int t0, int count) __attribute__((always_inline)) {
+        if constexpr (POINTS) {
+            for (int s = wave; s < paths * C; s += waves) {
+                const int sp = s / C;
+                const int64_t at = (k0 + t0 + (int64_t)(s - sp * C) * T) * d;
+                const float *path = A.path + (b0 + sp) * A.L * d;
+                float *dst = own + s * own_stride;
+#pragma unroll 4
+                for (int r = lw; r < (count + 1) * d; r += kWave) dst[r] = path[at + r < A.L * d ? at + r : K * d + r % d];
+            }
+        } else {
+            stage(own, own_stride, k0 + t0, T, count);
+        }
+    };
+    // `count` steps of the slot's own piece, f after each of them; exact: with level 1 from the points (POINTS)
+    auto own_steps = [&](Lane &ln, const float *row, int count, auto exact, auto &&f) __attribute__((always_inline)) {
+        Steps<d, P, POINTS> steps(row, letter);
+        onchip::Inc<d, P> inc;
+        auto level1 = [&](Lane &now) __attribute__((always_inline)) {
+            if constexpr (POINTS && decltype(exact)::value) (P > 1 ? now.pre[0] : now.s[0]) = steps.last.du[0] - first1;
+        };
+        if constexpr (BLOCKS) {
+            for (int t0 = 0; t0 < count; t0 += kPlainSteps) {
+                const int end = count - t0 < kPlainSteps ? count : t0 + kPlainSteps;
+                Lane sum, now = ln;
+                onchip::identity_state<d, N, P>(sum);
+#pragma unroll 2
+                for (int t = t0; t < end; ++t) {
+                    steps.next(inc);
+                    summed_step<d, N>(sum, now, inc);
+                    add_state<d, N, P>(now, ln, sum);
+                    level1(now);
+                    f(now, t);
+                }
+                ln = now;
+            }
+        } else {
+#pragma unroll 2
+            for (int t = 0; t < count; ++t) {
+                steps.next(inc);
+                onchip::fused_step<d, N, P>(ln, inc);
+                level1(ln);
+                f(ln, t);
+            }
         }
     };
     // (two steps a round, both increments read first: one wait for the pair; (4,4), 4 paths of 1,075 points 18.5 -> 17.1 us)
@@ -132,7 +267,7 @@ __global__ __launch_bounds__(kMaxThreads) void sig_stream_rows_kernel(Args A)
             const int count = T - t0 < A.tile ? T - t0 : A.tile;
             if (T > A.tile) {
                 __syncthreads();
-                stage(own, own_stride, k0 + t0, T, count);
+                stage_own(t0, count);
                 __syncthreads();
             }
             f(own + slot * own_stride, t0, count);
@@ -141,7 +276,7 @@ __global__ __launch_bounds__(kMaxThreads) void sig_stream_rows_kernel(Args A)
 
     Lane ln, bl;   // the slot's own piece, and what lies before it
     onchip::identity_state<d, N, P>(bl);
-    if (T <= A.tile) stage(own, own_stride, k0, T, T);
+    if (T <= A.tile) stage_own(0, T);
     // Folded block by block, a tile each, and the blocks multiplied: the rounding of a fold grows with the square root of its
     // steps ((5,4), 16 paths of 2,000 points: error of blocks of 64 steps 1.8e-7, of the 500 steps of a piece in one go 3.7e-7, of one launch per
     // level 2.2e-7).
@@ -166,7 +301,10 @@ __global__ __launch_bounds__(kMaxThreads) void sig_stream_rows_kernel(Args A)
     if (C > 1) {
         float *cur = rows, *nxt = C > 2 ? cur + (C - 1) * D : cur;
         onchip::identity_state<d, N, P>(ln);
-        own_tiles([&](const float *row, int, int count) __attribute__((always_inline)) { fold(ln, row, count); });
+        own_tiles([&](const float *row, int, int count) __attribute__((always_inline)) {
+            if constexpr (BLOCKS || POINTS) own_steps(ln, row, count, std::false_type{}, [](const Lane &, int) {});
+            else fold(ln, row, count);
+        });
         if (active) {
             if (c < C - 1) onchip::store_state<d, N, P>(cur + c * D, u, ln);
             if (before > 0) onchip::store_state<d, N, P>(join + c * D, u, bl);
@@ -203,16 +341,19 @@ __global__ __launch_bounds__(kMaxThreads) void sig_stream_rows_kernel(Args A)
         }
     }
 
-    const int64_t k = k0 + (int64_t)c * T;
+    // level 1 of what lies before the piece, from the points: one rounding (0 * what the pieces give keeps their NaN where the rows
+    // add increments up)
+    if (k > 0) {
+        float &s1 = P > 1 ? bl.pre[0] : bl.s[0];
+        s1 = POINTS ? here1 - first1 : fmaf(0.0f, s1, here1 - first1);
+    }
     const int mine = !active || k >= K ? 0 : K - k < T ? (int)(K - k) : T;
     float *dst = A.out + ((b0 + p) * K + k) * D;
     own_tiles([&](const float *row, int t0, int count) __attribute__((always_inline)) {
-        for (int t = t0; t < t0 + count; ++t, row += d, dst += D) {
-            onchip::Inc<d, P> inc;
-            onchip::load_inc<d, P>(inc, row, letter);
-            onchip::fused_step<d, N, P>(bl, inc);
-            if (t < mine) onchip::store_state<d, N, P>(dst, u, bl);
-        }
+        own_steps(bl, row, count, std::true_type{}, [&](const Lane &now, int t) __attribute__((always_inline)) {
+            if (t0 + t < mine) onchip::store_state<d, N, P>(dst, u, now);
+            dst += D;
+        });
     });
 }
 

@@ -24,7 +24,9 @@ struct Shape {
 template <int d, int N>
 hipError_t launch(const Args &A, int threads, size_t lds, hipStream_t st)
 {
-    hipLaunchKernelGGL((sig_stream_rows_kernel<d, N>), dim3((unsigned)((A.B + A.groups - 1) / A.groups * A.segs)), dim3(threads), lds, st, A);
+    const dim3 grid((unsigned)((A.B + A.groups - 1) / A.groups * A.segs));
+    if (A.steps > kPlainSteps) hipLaunchKernelGGL((sig_stream_rows_kernel<d, N, true>), grid, dim3(threads), lds, st, A);
+    else hipLaunchKernelGGL((sig_stream_rows_kernel<d, N, false>), grid, dim3(threads), lds, st, A);
     return hipGetLastError();
 }
 
@@ -98,7 +100,7 @@ bool cut(const Shape &s, int64_t B, int64_t L, int forced_segs, int cus, Args *a
         }
         const int64_t room = kMaxLdsBytes / (int64_t)sizeof(float) - A.groups * lds_rows((int)C, A.segs) * s.D;
         const int64_t behind = (int64_t)(A.segs - 1) * T;
-        const int64_t fit = (room / (A.segs > 1 ? 2 : 1) / (A.groups * C) - 1) / s.d;
+        const int64_t fit = (room / (A.segs > 1 ? 2 : 1) / (A.groups * C) - 1) / s.d - level1_from_points(s.d);
         // tiles of less than two dozen steps cost more than the pieces they make room for
         const int64_t wanted = T > behind ? T : behind;
         if (fit < (wanted < kLeastTileSteps ? wanted : kLeastTileSteps)) {

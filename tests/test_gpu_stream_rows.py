@@ -57,3 +57,50 @@ def test_rows_are_not_taken_where_they_do_not_apply(gpu):  # noqa: F811
         assert gpu.sig_plan_validate(2, L, d, depth, 1, plan) == gpu.SIG_ERR_INVALID
     assert gpu.sig_plan(None, 4096, 256, 4, 4, 1)[1].row_workgroups == 0
     assert gpu.sig_plan(None, 64, 256, 4, 4, 0)[1].row_workgroups == 0
+
+
+def _errors(gpu, oracle, x, depth, plan, paths):
+    """Relative error of the planned rows and of the plan's other kernels against the fp64 oracle, over the first `paths` paths."""
+    import torch
+    want = oracle.signature(x[:paths].astype(np.float64), depth, stream=True)
+    xt = torch.from_numpy(x).cuda()
+    errs = []
+    for segs in (plan.row_workgroups, 0):
+        plan.row_workgroups = segs
+        out = torch.empty((x.shape[0], x.shape[1] - 1, want.shape[-1]), device="cuda")
+        assert gpu.sig_compute(gpu.default_ctx(), xt, depth, True, out, plan=plan) == gpu.SIG_OK
+        got = out[:paths].cpu().numpy().astype(np.float64)
+        del out
+        errs.append(np.linalg.norm(got - want) / np.linalg.norm(want))
+    return errs
+
+
+@pytest.mark.parametrize("d,depth,B,L,paths", [(12, 3, 130, 1000, 8), (11, 3, 130, 1500, 8), (20, 2, 130, 2000, 16), (17, 2, 200, 1500, 16),
+                                               (2, 5, 1100, 900, 64), (2, 6, 300, 1500, 64), (3, 5, 300, 290, 32), (12, 2, 64, 12, 64), (16, 2, 9, 20, 9)])
+def test_rounding_is_no_larger_than_the_other_kernels(gpu, oracle, d, depth, B, L, paths):  # noqa: F811
+    """Long pieces, and short paths whose level 1 dominates.  Both errors are means over thousands of rows of `paths` independent
+    paths; the ratio of two such means of equally accurate kernels stays within 1 +- 0.1 (with plain sums over the whole piece and
+    level 1 added up, every case here lies beyond)."""
+    rc, plan = gpu.sig_plan(gpu.default_ctx(), B, L, d, depth, 1)
+    assert rc == gpu.SIG_OK and plan.row_workgroups >= 1
+    x = workloads.brownian_paths(B, L, d, seed=9400 + d + L)
+    if L < 30:   # uniform increments: level 1 is not small against the others
+        x = workloads.uniform_paths(B, L, d, seed=9401 + d)
+    rows, other = _errors(gpu, oracle, x, depth, plan, paths)
+    assert rows <= 1.1 * other, (rows, other)
+
+
+@pytest.mark.parametrize("d,depth,L,segs", [(12, 2, 14, 1), (12, 2, 300, 3), (20, 2, 500, 1), (16, 2, 900, 5), (11, 3, 120, 2), (12, 3, 700, 1)])
+def test_level_1_of_many_channels_comes_from_the_points(gpu, d, depth, L, segs):  # noqa: F811
+    """Points that are not numbers, at a piece's first step too, spoil the same coefficients as in the launches per level: level 1
+    is finite again in the next row."""
+    x = workloads.brownian_paths(3, L, d, seed=78)
+    x[0, L // 2, 2] = np.nan
+    x[1, 1, d - 1] = np.inf
+    x[2, L - 2, 0] = np.nan
+    got = run_gpu(gpu, x, depth, True, gpu.make_plan(gpu.SIG_VARIANT_ON_CHIP, row_workgroups=segs))
+    want = run_gpu(gpu, x, depth, True, gpu.make_plan(gpu.SIG_VARIANT_LEVEL_SCAN, chunks=0))
+    assert np.array_equal(np.isfinite(got), np.isfinite(want))
+    assert np.isfinite(got[0, L // 2:, :d]).all() and not np.isfinite(got[0, L // 2 - 1, 2])
+    ok = np.isfinite(want[:, :, :d])
+    assert np.array_equal(got[:, :, :d][ok], want[:, :, :d][ok])   # one difference each: the same bits
