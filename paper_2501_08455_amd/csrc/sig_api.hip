@@ -715,7 +715,8 @@ int plan_auto(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const R
 {
     const int rc = plan_without_rows(ctx, B, L, stream_flag, rs, pl);
     if (rc == SIG_OK && stream_flag)
-        pl->row_workgroups = stream_rows_wanted(rs.d, rs.depth, B, L, ctx ? ctx->num_cu : kDefaultCUs, pl->variant == SIG_VARIANT_ON_CHIP);
+        pl->row_workgroups = stream_rows_wanted(rs.d, rs.depth, B, L, ctx ? ctx->num_cu : kDefaultCUs,
+                                                pl->variant == SIG_VARIANT_ON_CHIP ? pl->prefix_depth : -1);
     return rc;
 }
 

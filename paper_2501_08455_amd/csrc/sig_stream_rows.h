@@ -41,11 +41,16 @@ struct Args {
     int32_t behind;      // ... and of what lies before (segs > 1)
 };
 
+// a row in LDS: an odd stride where lanes and rows would otherwise all start in every 16th bank ((16,2), 200 paths of 200 points 35 and 31
+// us; elsewhere it costs the wide accesses a little: (8,3), 30 of 200, 14.4 and 15.0)
+__host__ __device__ constexpr int lds_row(int d, int64_t D) { return (int)(d % 16 == 0 ? D | 1 : D); }
+
 template <int d_, int N_>
 struct Geo {
     static constexpr int d = d_, N = N_, P = N - 1;
     static constexpr int Q = cpow(d, P);
     static constexpr int D = onchip::Shape<d, N, P>::D;
+    static constexpr int DS = lds_row(d, D);
     static constexpr int SPW = Q <= kWave ? kWave / Q : 1;       // slots of a wavefront
     static constexpr int WPS = (Q + kWave - 1) / kWave;          // wavefronts of a slot
 };
@@ -137,7 +142,7 @@ template <int d, int N, bool BLOCKS>
 __global__ __launch_bounds__((most_threads(d, N))) void sig_stream_rows_kernel(Args A)
 {
     using G = Geo<d, N>;
-    constexpr int P = G::P, Q = G::Q, D = G::D;
+    constexpr int P = G::P, Q = G::Q, D = G::D, DS = G::DS;
     constexpr bool POINTS = level1_from_points(d);
     using Lane = onchip::Lane<d, N, P>;
     const int tid = threadIdx.x, nthr = blockDim.x;
@@ -185,7 +190,7 @@ __global__ __launch_bounds__((most_threads(d, N))) void sig_stream_rows_kernel(A
     const int own_stride = tile_stride(A.tile + POINTS, d), old_stride = tile_stride(A.behind, d);
     float *own = sig_rows_smem;                     // [slots][own_stride]
     float *old = own + A.groups * C * own_stride;   // [slots][old_stride]
-    float *rows = sig_rows_smem + tile_floats(A, d) + p * lds_rows(C, A.segs) * D;
+    float *rows = sig_rows_smem + tile_floats(A, d) + p * lds_rows(C, A.segs) * DS;
 
     // `count` increments of every slot from step first + c * stride on, zeros beyond the path's end
     auto stage = [&](float *tile, int row, int64_t first, int64_t stride, int count) __attribute__((always_inline)) {
@@ -280,7 +285,7 @@ __global__ __launch_bounds__((most_threads(d, N))) void sig_stream_rows_kernel(A
     // Folded block by block, a tile each, and the blocks multiplied: the rounding of a fold grows with the square root of its
     // steps ((5,4), 16 paths of 2,000 points: error of blocks of 64 steps 1.8e-7, of the 500 steps of a piece in one go 3.7e-7, of one launch per
     // level 2.2e-7).
-    float *join = rows + lds_rows(C, 1) * D;
+    float *join = rows + lds_rows(C, 1) * DS;
     for (int64_t t0 = 0; t0 < before; t0 += A.behind) {
         const int count = before - t0 < A.behind ? (int)(before - t0) : A.behind;
         if (t0 > 0) __syncthreads();
@@ -292,22 +297,22 @@ __global__ __launch_bounds__((most_threads(d, N))) void sig_stream_rows_kernel(A
         } else {
             onchip::identity_state<d, N, P>(ln);
             fold(ln, row, count);
-            if (active) onchip::store_state<d, N, P>(join + c * D, u, ln);
+            if (active) onchip::store_state<d, N, P>(join + c * DS, u, ln);
             __syncthreads();
-            if (active) onchip::reg_product<d, N, P>(bl, join + c * D, u);
+            if (active) onchip::reg_product<d, N, P>(bl, join + c * DS, u);
         }
     }
     if (before == 0 || before > A.behind) __syncthreads();   // the own tile; the last block's rows have been read
     if (C > 1) {
-        float *cur = rows, *nxt = C > 2 ? cur + (C - 1) * D : cur;
+        float *cur = rows, *nxt = C > 2 ? cur + (C - 1) * DS : cur;
         onchip::identity_state<d, N, P>(ln);
         own_tiles([&](const float *row, int, int count) __attribute__((always_inline)) {
             if constexpr (BLOCKS || POINTS) own_steps(ln, row, count, std::false_type{}, [](const Lane &, int) {});
             else fold(ln, row, count);
         });
         if (active) {
-            if (c < C - 1) onchip::store_state<d, N, P>(cur + c * D, u, ln);
-            if (before > 0) onchip::store_state<d, N, P>(join + c * D, u, bl);
+            if (c < C - 1) onchip::store_state<d, N, P>(cur + c * DS, u, ln);
+            if (before > 0) onchip::store_state<d, N, P>(join + c * DS, u, bl);
         }
         __syncthreads();
         // Round with stride st.  Scan: the lanes of piece c multiply their value by the row of piece c + st and leave the product
@@ -316,28 +321,28 @@ __global__ __launch_bounds__((most_threads(d, N))) void sig_stream_rows_kernel(A
             const bool scan = st < C - 1;
             if (active) {
                 if (before > 0 && (c & (2 * st - 1)) == 0 && c + st < C) {
-                    onchip::reg_product<d, N, P>(bl, join + (c + st) * D, u);
-                    onchip::store_state<d, N, P>(join + c * D, u, bl);
+                    onchip::reg_product<d, N, P>(bl, join + (c + st) * DS, u);
+                    onchip::store_state<d, N, P>(join + c * DS, u, bl);
                 }
                 if (scan) {
-                    if (c < st) onchip::store_state<d, N, P>(nxt + c * D, u, ln);
+                    if (c < st) onchip::store_state<d, N, P>(nxt + c * DS, u, ln);
                     if (c + st < C - 1) {
-                        onchip::reg_product<d, N, P>(ln, cur + (c + st) * D, u);
-                        onchip::store_state<d, N, P>(nxt + (c + st) * D, u, ln);
+                        onchip::reg_product<d, N, P>(ln, cur + (c + st) * DS, u);
+                        onchip::store_state<d, N, P>(nxt + (c + st) * DS, u, ln);
                     }
                 }
             }
             __syncthreads();
             if (scan) {
-                if (active && c < C - 1) onchip::load_state<d, N, P>(nxt + c * D, u, ln);
+                if (active && c < C - 1) onchip::load_state<d, N, P>(nxt + c * DS, u, ln);
                 float *t = cur; cur = nxt; nxt = t;
             }
         }
         if (before > 0) {
             onchip::load_state<d, N, P>(join, u, bl);
-            if (c > 0) onchip::reg_product<d, N, P>(bl, cur + (c - 1) * D, u);
+            if (c > 0) onchip::reg_product<d, N, P>(bl, cur + (c - 1) * DS, u);
         } else if (c > 0) {
-            onchip::load_state<d, N, P>(cur + (c - 1) * D, u, bl);
+            onchip::load_state<d, N, P>(cur + (c - 1) * DS, u, bl);
         }
     }
 

@@ -46,7 +46,7 @@ const Shape *find(int d, int depth)
     return nullptr;
 }
 
-int64_t lds_floats(const Shape &s, const Args &A) { return tile_floats(A, s.d) + (int64_t)A.groups * lds_rows(A.slots, A.segs) * s.D; }
+int64_t lds_floats(const Shape &s, const Args &A) { return tile_floats(A, s.d) + (int64_t)A.groups * lds_rows(A.slots, A.segs) * lds_row(s.d, s.D); }
 
 // wavefronts of a launch that does not cut the paths
 int64_t uncut_waves(const Shape &s, int64_t B)
@@ -98,7 +98,7 @@ bool cut(const Shape &s, int64_t B, int64_t L, int forced_segs, int cus, Args *a
             A.groups = (int32_t)(s.slots(256) / C);
             *threads = s.threads((int)(A.groups * C));
         }
-        const int64_t room = kMaxLdsBytes / (int64_t)sizeof(float) - A.groups * lds_rows((int)C, A.segs) * s.D;
+        const int64_t room = kMaxLdsBytes / (int64_t)sizeof(float) - A.groups * lds_rows((int)C, A.segs) * lds_row(s.d, s.D);
         const int64_t behind = (int64_t)(A.segs - 1) * T;
         const int64_t fit = (room / (A.segs > 1 ? 2 : 1) / (A.groups * C) - 1) / s.d - level1_from_points(s.d);
         // tiles of less than two dozen steps cost more than the pieces they make room for
@@ -121,15 +121,21 @@ bool cut(const Shape &s, int64_t B, int64_t L, int forced_segs, int cus, Args *a
 
 }  // namespace rows
 
-// Which stream-mode calls take it.  `held`: the shape has a register kernel for stream mode and the planner would take it.
-//  - Otherwise the alternative is one launch per level, which is slower but for one to three paths whose pieces have hundreds of
-//    steps ((16,2), 8,192 paths of 100 points 434 and 299 us; (8,4), 128 of 300 456 and 209; (12,3), one of 1,000 62 and 71).
-//  - Against the register kernels, whose rows stop in LDS and reach memory in longer runs, it takes batches that leave the chip
-//    below a wavefront per SIMD uncut and rows of some hundred megabytes at most ((4,4), 1,024 paths of 256 points 93 and 79
-//    us, 4,096 284 and 295; (3,5), 500 of 1,000 173 and 275).  At depth 3 the crossing lies lower ((5,3), 1,000 of 100 17.6 and
-//    18.7), and slots of fewer than 16 lanes, whose stores are short pieces, pay for short paths or few ((3,3), 500 of 1,000 points
-//    23 and 34, of 12 5.3 and 3.8).
-int stream_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, bool held)
+// Which stream-mode calls take it.  `held_p`: prefix depth of the register kernel for stream mode that the planner would take, -1 if
+// it would take one launch per level.  Microseconds without and with it in brackets.
+//  - Against the launches per level: everywhere but on one to three paths whose pieces have hundreds of steps [(12,3), one of 488
+//    points 44 and 52; (8,4), four of 470 0.88x], where a row takes long to store and the joins stride LDS by a multiple of four, and, at depth 2 (two launches),
+//    on few paths that those launches still hold in one tile, 512 increments [(20,2), two of 490 21 and 28; (17,2), two of 405 19 and
+//    22; (16,2), whose lanes stride LDS by 16, ten of 230 16 and 20].
+//  - Against the register kernels, whose rows stop in LDS and reach memory in longer runs: batches that leave the chip below a
+//    wavefront per SIMD uncut and rows of some hundred megabytes at most [(4,4), 1,024 paths of 256 points 93 and 79, 4,096 284 and
+//    295; (3,5), 500 of 1,000 173 and 275].  At depth 3 the crossing lies lower [(5,3), 1,000 of 100 17.6 and 18.7;
+//    (8,3), 600 of 64 20.4 and 22.9; (9,3), 400 of 60 0.97x, but (10,3) 1.02 to 1.06x], and slots of fewer than 16 lanes, whose stores are
+//    short pieces, pay for short paths or few [(3,3), 500 of 1,000 points 23 and 34, of 12 5.3 and 3.8; 100 of 64 ... 180 0.97x].  Register
+//    kernels with the same lanes (a word of length N - 1 each) in several wavefronts a path lose only where the paths are cut
+//    [(6,4), 200 of 73 19.5 and 24.7, of 8 0.97x; 30 of 200 48 and 24], those with fewer lanes than that where a path has two
+//    wavefronts and rows of some hundred floats here [(5,4), more than 170 of 128 points and more 0.91 to 1.01x].
+int stream_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held_p)
 {
     const rows::Shape *s = rows::find(d, depth);
     if (!s || B < 1 || L < 2) return 0;
@@ -137,16 +143,24 @@ int stream_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, bool hel
     rows::Args A{};
     int threads = 0;
     size_t lds = 0;
-    if (held) {
+    if (held_p >= 0) {
         if (rows::uncut_waves(*s, B) > 4 * (int64_t)cus) return 0;
         const double bytes = 4.0 * (double)B * (double)K * (double)s->D;
         if (bytes > (s->waves_per_slot > 1 ? 2e8 : 4e8)) return 0;
-        if (depth == 3 && B > cus && B * K > 50000) return 0;
+        if (depth == 3 && B > cus && B * K > (s->lanes >= 64 && s->lanes < 100 ? 10000 : 50000)) return 0;
         if (s->lanes < 16 && B > (K > 32 ? 1 : 4) * (int64_t)cus) return 0;
         if (s->lanes < 9 && K > 32 && (K < 500 || B > cus / 2)) return 0;
+        if (depth == 3 && s->lanes < 10 && K > 60 && K < 180) return 0;
+        if (held_p < depth - 1 && s->waves_per_slot == 2 && s->D > 700 && 3 * B > 2 * (int64_t)cus) return 0;
+        if (held_p == depth - 1 && s->lanes > 128 && (B >= cus / 2 || K < 16)) return 0;
     }
     if (!rows::cut(*s, B, L, 0, cus, &A, &threads, &lds)) return 0;
-    if (!held && B < 4 && K / A.slots > 250) return 0;
+    if (held_p < 0) {
+        const bool one_tile = K < 512;
+        if (B < 4 && K / A.slots > 250) return 0;
+        if (depth == 2 && one_tile && (d % 16 ? d > 13 && B < 16 && K * d * d * d > 900000 : K > 110 && (B < 32 || (B < 64 && K < 250)))) return 0;
+        if (depth > 2 && d % 4 == 0 && s->D > 1800 && (one_tile ? B < 3 + s->D / 2000 && K > 380 : B < 2 && K > 590)) return 0;
+    }
     return A.segs;
 }
 

@@ -193,6 +193,25 @@ def test_stream_plans_of_few_long_paths_are_parallel_in_time():
             assert rc == binding.SIG_OK and pl.variant == binding.SIG_VARIANT_ON_CHIP
 
 
+def test_stream_rows_are_planned_only_where_they_lead():
+    """Which stream-mode calls write their rows from registers: calls on which that measured slower than the kernels they took
+    before (0.75-0.97x), each beside a neighbour on which it leads."""
+    rows = lambda B, L, d, depth: binding.sig_plan(None, B, L, d, depth, 1)[1].row_workgroups
+    # launches per level that hold a few paths in one tile (511 increments): depth 2, and long rows
+    for call in [(10, 230, 16, 2), (40, 200, 16, 2), (2, 490, 20, 2), (2, 405, 17, 2), (12, 400, 19, 2), (1, 488, 12, 3), (1, 720, 12, 3),
+                 (4, 470, 8, 4)]:
+        assert rows(*call) == 0, call
+    for call in [(10, 90, 16, 2), (100, 200, 16, 2), (10, 600, 16, 2), (2, 520, 20, 2), (40, 405, 17, 2), (4, 700, 12, 3), (1, 490, 11, 3),
+                 (8, 470, 8, 4)]:
+        assert rows(*call) > 0, call
+    # register kernels: with the same lanes in several wavefronts a path, few lanes and long paths, batches beyond the chip's units
+    for call in [(200, 73, 6, 4), (130, 20, 6, 4), (20, 8, 6, 4), (100, 100, 3, 3), (600, 64, 8, 3), (400, 60, 9, 3), (240, 180, 5, 4)]:
+        assert rows(*call) == 0, call
+    for call in [(60, 73, 6, 4), (20, 40, 6, 4), (100, 40, 3, 3), (100, 300, 3, 3), (100, 64, 8, 3), (400, 20, 9, 3), (240, 100, 5, 4),
+                 (200, 60, 3, 6), (300, 60, 10, 3)]:
+        assert rows(*call) > 0, call
+
+
 def test_level_scan_plans_are_checked_on_the_host():
     """The level-by-level family (Section 3.2) takes d <= 256, depth <= 8, chunks >= 0 and rows that 32-bit lane
     offsets can address; the planner chooses it only for shapes without an on-chip kernel."""
