@@ -1,5 +1,6 @@
 // Host side of libsig: argument checking, the planner that maps a shape onto the GPU, scratch
 // management and kernel dispatch.  The C ABI is declared and documented in include/sig.h.
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <mutex>
@@ -306,7 +307,8 @@ constexpr int kDeepShortPath = 256;      // increments up to which a deeper entr
 constexpr int kDeepShortPathHeavy = 768; // ... behind a few-lane or heavy entry
 constexpr int kDeepShortPathWide = 128;  // ... when the deeper entry has more than 128 lanes per path
 constexpr int kDeepBatchFactorFewLanes = 4;   // batch limit of the deeper entry, in units of one wavefront per SIMD
-constexpr int64_t kDeepExtraPerCu = 110000;   // multiply-adds per CU that a light deeper entry may cost a batch beyond the shallower one (0.6 us)
+constexpr int64_t kDeepExtraPerCu = 110000;   // multiply-adds per CU that a light deeper entry may cost a batch beyond the shallower one (0.6 us) ...
+constexpr int64_t kDeepExtraPerFloat = 3100;  // ... and at most this many for each float of the shallower one's state, whose step it shortens
 constexpr int kDeepLightState = 16;      // ... a state of at most this many floats
 constexpr int kDeepLightLeast = 9;       // ... from this many increments on
 constexpr int kDeepLightShort = 48;      // ... up to this many,
@@ -380,8 +382,10 @@ const OnChipKernelInfo *pick_on_chip(int d, int depth, int stream_flag, int64_t 
         // ... and light states, at depth 4 and less, wherever the multiply-adds that they cost beyond the shallower entry's take less
         // than the shorter chain of a step saves: batches of short paths, and with two levels below the word long paths too.
         // Shallower and deeper entry, us: (5,4) 512 paths of 25 points 5.8 and 4.3, (7,3) 8,192 of 25 13.2 and 10.5, (6,3) 4,096 of
-        // 25 7.7 and 5.0, (3,4) 8 of 800 12.8 and 8.5, 4,096 of 800 40.7 and 28.6; 6,953 random calls that the rules changed 1.38x in
-        // the mean, eight of them 0.92-0.97x.  Error against 64 bits 0.99 times what it was.  Behind the bound (28 million multiply-adds on 256 CUs) the shallower
+        // 25 7.7 and 5.0, (3,4) 8 of 800 12.8 and 8.5, 4,096 of 800 40.7 and 28.6; 42,000 random calls that the rules changed 1.38x in
+        // the mean, 0.2 % of them 0.86 to 0.97x, next to one another where the two entries' chunks round differently ((7,3), 3,100 ... 3,600
+        // paths of 33 or 49 points 0.90).  Error against 64 bits 0.99 times what it was.  Behind the bound (28 million multiply-adds on 256
+        // CUs, a fifth less behind a state of 31 floats: (5,3) 12,000 to 20,000 paths of 25 to 40 points 0.90 to 1.1x) the shallower
         // one leads: (5,4) 1,024 of 100 0.94x, (5,3) 8,192 of 200 0.79x, and between 48 and 500 increments either does ((3,4)
         // 5,056 of 142 0.78x, 8,192 of 400 1.53x).  Behind states below 31 floats ((3,3) 0.56-1.2x) and behind 16 lanes and more
         // of matrix instructions ((4,4) 2,048 of 50 0.87x) nothing is gained on balance.
@@ -390,7 +394,8 @@ const OnChipKernelInfo *pick_on_chip(int d, int depth, int stream_flag, int64_t 
         const bool light_length = (K >= tune::kDeepLightLeast && K <= tune::kDeepLightShort) || (depth - e->p >= 2 && K >= tune::kDeepLightLong);
         const bool cheap = !stream_flag && best_small && e->lanes_per_chunk < kThreads && light && light_length &&
                            B <= (int64_t)cus * tune::kDeepExtraPerCu / K &&
-                           B * K * (step_multiply_adds(d, depth, e->p) - step_multiply_adds(d, depth, best->p)) <= (int64_t)cus * tune::kDeepExtraPerCu;
+                           B * K * (step_multiply_adds(d, depth, e->p) - step_multiply_adds(d, depth, best->p)) <=
+                               (int64_t)cus * std::min(tune::kDeepExtraPerCu, tune::kDeepExtraPerFloat * best->state_floats);
         // stream mode, behind a small-state entry: only while that one has few lanes per path (the four-lane entry of
         // two channels measured 1.9-4.4x over the two-lane one at 1,024 to 16,384 paths as well as below)
         // ... or the batch leaves the small-state entry at most half a wavefront per SIMD and the deeper one fits a

@@ -17,6 +17,8 @@ pytestmark = pytest.mark.gpu
     (1300, 500, 3, 4, 1), (1300, 501, 3, 4, 2), (1, 1200, 3, 4, 2), (3, 1200, 5, 3, 1), (3, 1200, 7, 3, 1),
     # the bound on the multiply-adds
     (4500, 10, 5, 4, 2), (3000, 1000, 3, 4, 1),
+    # ... which is lower behind a lighter state
+    (11000, 37, 5, 3, 2), (12000, 37, 5, 3, 1), (16000, 25, 5, 3, 2), (18500, 25, 5, 3, 1), (700, 48, 5, 4, 3), (860, 48, 5, 4, 2),
     # lanes in several workgroups: the last batch that takes them, and the next
     (320, 20, 8, 4, 3), (321, 20, 8, 4, 2), (252, 12, 9, 4, 3), (253, 12, 9, 4, 2), (204, 12, 10, 4, 3), (205, 12, 10, 4, 2),
     # few lanes with states below 31 floats, and matrix instructions in place of the vector ones, as before
