@@ -389,7 +389,7 @@ const OnChipKernelInfo *pick_on_chip(int d, int depth, int stream_flag, int64_t 
         // one leads: (5,4) 1,024 of 100 0.94x, (5,3) 8,192 of 200 0.79x, and between 48 and 500 increments either does ((3,4)
         // 5,056 of 142 0.78x, 8,192 of 400 1.53x).  Behind states below 31 floats ((3,3) 0.56-1.2x) and behind 16 lanes and more
         // of matrix instructions ((4,4) 2,048 of 50 0.87x) nothing is gained on balance.
-        const bool matrix = d >= 4 && d != 5 && d != 7 && depth >= 3 && best->lanes_per_chunk >= tune::kFewLanes;
+        const bool matrix = best->matrix_fold && best->lanes_per_chunk >= tune::kFewLanes;
         const bool light = e->state_floats <= tune::kDeepLightState && depth <= 4 && best->state_floats >= tune::kFewLaneMinState && !matrix;
         const bool light_length = (K >= tune::kDeepLightLeast && K <= tune::kDeepLightShort) || (depth - e->p >= 2 && K >= tune::kDeepLightLong);
         const bool cheap = !stream_flag && best_small && e->lanes_per_chunk < kThreads && light && light_length &&

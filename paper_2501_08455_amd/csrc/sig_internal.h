@@ -199,6 +199,7 @@ struct OnChipKernelInfo {
     // out[b] = product over the `segments` partial rows of path b (second launch when segments > 1)
     hipError_t (*join)(const float *partial, float *out, int64_t B, int segments, hipStream_t);
     bool final_only;                           // no stream mode is compiled
+    bool matrix_fold;                          // final-mode folds on matrix instructions (quad_fold in sig_onchip.h)
 };
 
 // Work items of an on-chip launch with Q = d^p lanes per (path, chunk): one per slice of a path's lanes when they exceed

@@ -1788,7 +1788,8 @@ hipError_t on_chip_join_any(const float *partial, float *out, int64_t B, int W, 
     {                                                                                           \
         d, N, P, ::sig::onchip::Shape<d, N, P>::Q, ::sig::onchip::Shape<d, N, P>::SZ,           \
             d, &::sig::onchip::on_chip_launch<d, N, P, FINAL_ONLY>,                             \
-            &::sig::onchip::on_chip_lds_bytes<d, N, P>, &::sig::onchip::on_chip_join_any<d, N, P>, FINAL_ONLY \
+            &::sig::onchip::on_chip_lds_bytes<d, N, P>, &::sig::onchip::on_chip_join_any<d, N, P>, FINAL_ONLY, \
+            ::sig::onchip::quad_fold<d, N, P>()                                                 \
     }
 #define SIG_ON_CHIP_ENTRY(d, N, P) SIG_ON_CHIP_ENTRY_IN(d, N, P, false)
 #define SIG_ON_CHIP_FINAL_ENTRY(d, N, P) SIG_ON_CHIP_ENTRY_IN(d, N, P, true)
