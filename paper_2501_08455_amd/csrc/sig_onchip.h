@@ -255,6 +255,8 @@ struct QuadTree {
 // arithmetic and not the reading of the path binds.  Four lanes side by side must share an increment, so a path (or a chunk of
 // one) takes lanes in fours; where that leaves more than one in 25 idle the vector multiply-adds stay: (5,4), 28 lanes for
 // 25, 65,536 paths of 100 points 172 us and 188 on matrix instructions; (7,4), 52 for 49, 1,024 paths of 40 points 13 and 16.
+// So do they where one level of fewer than eight letters hangs below a word and a path takes several wavefronts ((6,4) with 216 lanes, 1
+// to 200 paths of 32 to 100 points 0.96x: one matrix instruction in the place of four of some 25 vector ones).
 // Vector multiply-adds and matrix instructions, us: (8,3) 128 paths of 150 points 7 and 6, 8,192 of 150 50 and 32, 65,536 of
 // 150 351 and 239; (9,3), 84 lanes for 81, 8,192 of 150 74 and 46; (10,3) 8,192 of 600 428 and 263; (8,4) 8,192 of 600 599 and
 // 478; (8,5) 128 of 600 142 and 91; (10,4) 8,192 of 150 428 and 388; (4,4) 65,536 of 150 134 and 128, 128 of 40 4.0 both (the
@@ -263,7 +265,30 @@ template <int d, int N, int P>
 constexpr bool quad_fold()
 {
     constexpr int Q = cpow(d, P);
-    return d >= 4 && d != 5 && N >= 3 && P >= 1 && (N - P == 1 || N - P == 2) && (Q + 3) / 4 * 4 * 24 <= Q * 25;
+    return d >= 4 && d != 5 && N >= 3 && P >= 1 && (N - P == 1 || N - P == 2) && (Q + 3) / 4 * 4 * 24 <= Q * 25 &&
+           !(d < 8 && N - P == 1 && Q > kWave);
+}
+
+// Which launches of such a shape keep the vector multiply-adds (the bits are the same): a wavefront issues its instructions
+// faster with matrix instructions, which no longer counts once the wavefronts of a SIMD fill the pipe.  Behind chains as long as a group of
+// letters is wide ((4,6): 26 multiply-adds beside the tree's 20) that is beyond one wavefront per SIMD (83 and 87 paths of 800 points
+// and more, 996 and 1,044 wavefronts on 1,024 SIMDs: 1.04x and 0.92x; 8,800 of 36 points 89 us and 95 on matrix instructions; under 48
+// steps not before 24 a SIMD, 300 paths of 20 points 1.04x); where three of
+// seven letters stand alone ((7,5)) between one and two, on paths beyond 150 increments (134 of 227 points 55 and 59; 256 paths and
+// more 1.04x); and where lanes of a hundred floats in several workgroups do little but store them ((10,5) under 20 increments, from 14
+// wavefronts per SIMD on: 1,380 paths of 4 points 214 and 241; 500 paths 1.00x).
+template <int d, int N, int P>
+constexpr bool vector_fold_too()
+{
+    return quad_fold<d, N, P>() && N - P == 2 && (P >= d || d % 4 == 3 || (cpow(d, P) > 256 && geom(d, N - P + 1) > 100));
+}
+template <int d, int N, int P>
+bool vector_fold_leads(const OnChipArgs &A, unsigned workgroups)
+{
+    const int64_t waves = (int64_t)workgroups * (A.threads / kWave), simds = 4 * (int64_t)A.num_cus;
+    if constexpr (P >= d) return waves > simds && (A.chunk_steps >= 48 || waves > 24 * simds);
+    else if constexpr (d % 4 == 3) return waves > simds && waves <= 2 * simds && A.chunk_steps > 150;
+    else return waves > 14 * simds && A.chunk_steps < 20;
 }
 
 // One step of a lane on QuadTree: as Level / Descend below, the levels 1 .. P of u's prefixes here and the rest in the tree.
@@ -1617,10 +1642,9 @@ constexpr bool fours_fit(int Q)
     return true;
 }
 
-template <int d, int N, int P, bool CHUNKED, bool STREAM>
-void on_chip_launch_pipe(const OnChipArgs &A, dim3 g, dim3 blk, size_t lds, hipStream_t st)
+template <int d, int N, int P, bool CHUNKED, bool STREAM, bool QUAD>
+void on_chip_launch_fold(const OnChipArgs &A, dim3 g, dim3 blk, size_t lds, hipStream_t st)
 {
-    constexpr bool QUAD = !STREAM && quad_fold<d, N, P>();
     static_assert(!QUAD || fours_fit(Shape<d, N, P>::Q), "the launch is planned with Q lanes per chunk");
     if (A.pipe) {
         hipLaunchKernelGGL((sig_on_chip_kernel<d, N, P, CHUNKED, STREAM, true, false, QUAD>), g, blk, lds, st, A);
@@ -1633,6 +1657,15 @@ void on_chip_launch_pipe(const OnChipArgs &A, dim3 g, dim3 blk, size_t lds, hipS
         }
     }
     hipLaunchKernelGGL((sig_on_chip_kernel<d, N, P, CHUNKED, STREAM, false, false, QUAD>), g, blk, lds, st, A);
+}
+
+template <int d, int N, int P, bool CHUNKED, bool STREAM>
+void on_chip_launch_pipe(const OnChipArgs &A, dim3 g, dim3 blk, size_t lds, hipStream_t st)
+{
+    if constexpr (!STREAM && vector_fold_too<d, N, P>()) {
+        if (vector_fold_leads<d, N, P>(A, g.x)) return on_chip_launch_fold<d, N, P, CHUNKED, false, false>(A, g, blk, lds, st);
+    }
+    on_chip_launch_fold<d, N, P, CHUNKED, STREAM, !STREAM && quad_fold<d, N, P>()>(A, g, blk, lds, st);
 }
 
 // FINAL_ONLY: compiled without the kernels of stream mode
