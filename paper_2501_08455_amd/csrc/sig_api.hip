@@ -357,17 +357,22 @@ int64_t step_multiply_adds(int d, int depth, int p)
 //    the sequential steps, and a light one for any batch whose arithmetic it hardly adds to; an entry whose lanes span several workgroups only while the batch cannot fill the chip;
 //  - stream mode: bound by the stores, so the deepest entry whose lanes fit a workgroup, but behind a small-state entry
 //    only while that one has few lanes per path.
-const OnChipKernelInfo *pick_on_chip(int d, int depth, int stream_flag, int64_t B, int64_t K, int cus)
+const OnChipKernelInfo *pick_on_chip(const RowShape &rs, int stream_flag, int64_t B, int64_t K, int cus)
 {
+    const int d = rs.d, depth = rs.depth;
     const OnChipKernelInfo *best = nullptr;
     for (int t = 0; on_chip_subtable(t); ++t)
     for (const OnChipKernelInfo *e = on_chip_subtable(t); e->launch; ++e) {
         if (e->d != d || e->depth != depth) continue;
         if (!best) { best = e; continue; }
         const bool spans_workgroups = e->lanes_per_chunk > kThreads && best->lanes_per_chunk <= kThreads;
-        // (up to 20,480 lanes of the shallower entry on 256 CUs, a quarter beyond a wavefront on each: (8,4) 256 ... 320 paths of
-        // 8 ... 2,000 points 1.15-2.6x, 304 x 97 35 -> 13 us; (9,4) from 205 on 1.42x, (10,4) from 165 on 1.47x in the mean)
-        if (spans_workgroups && (stream_flag || B * best->lanes_per_chunk * 4 > (int64_t)cus * kWave * 5)) continue;
+        // A wavefront on each unit, and a quarter beyond where the shallower entry would not be cut in two segments (rows too long
+        // for a join, or paths too short): (8,4) 256 ... 320 paths of 8 ... 96 points 1.15-1.4x, (9,4) from 205 on 1.42x, (10,4) from 165 on
+        // 1.47x in the mean.  Cut in two it takes longer still ((8,4) 257 paths of 300 points 45 us and 32), but sums half as
+        // many steps in a row: error against 64 bits 2.4e-7 and 3.1e-7.
+        const bool cut_in_two = K >= 2 * kMinSegmentChunkSteps && join_fits_lds(best, 2, rs);
+        const int64_t lanes = B * best->lanes_per_chunk, one_wave = (int64_t)cus * kWave;
+        if (spans_workgroups && (stream_flag || (cut_in_two ? lanes >= one_wave : 4 * lanes > 5 * one_wave))) continue;
         const bool best_small = best->p > 0 && best->state_floats <= tune::kSmallState;
         const bool best_few_lanes = best->lanes_per_chunk < tune::kFewLanes;
         // final mode, behind a small-state entry: short paths and a batch below one wavefront per SIMD (four behind a
@@ -384,8 +389,8 @@ const OnChipKernelInfo *pick_on_chip(int d, int depth, int stream_flag, int64_t 
         // Shallower and deeper entry, us: (5,4) 512 paths of 25 points 5.8 and 4.3, (7,3) 8,192 of 25 13.2 and 10.5, (6,3) 4,096 of
         // 25 7.7 and 5.0, (3,4) 8 of 800 12.8 and 8.5, 4,096 of 800 40.7 and 28.6; 42,000 random calls that the rules changed 1.38x in
         // the mean, 0.2 % of them 0.86 to 0.97x, next to one another where the two entries' chunks round differently ((7,3), 3,100 ... 3,600
-        // paths of 33 or 49 points 0.90).  Error against 64 bits 0.99 times what it was.  Behind the bound (28 million multiply-adds on 256
-        // CUs, a fifth less behind a state of 31 floats: (5,3) 12,000 to 20,000 paths of 25 to 40 points 0.90 to 1.1x) the shallower
+        // paths of 33 or 49 points 0.90).  Error against 64 bits 1.03 times what it was, 0.92 to 1.09 by shape and length (all below a
+        // rounding of the largest term, 1.1e-7).  Behind the bound (28 million multiply-adds on 256 CUs, a fifth less behind a state of 31 floats: (5,3) 12,000 to 20,000 paths of 25 to 40 points 0.90 to 1.1x) the shallower
         // one leads: (5,4) 1,024 of 100 0.94x, (5,3) 8,192 of 200 0.79x, and between 48 and 500 increments either does ((3,4)
         // 5,056 of 142 0.78x, 8,192 of 400 1.53x).  Behind states below 31 floats ((3,3) 0.56-1.2x) and behind 16 lanes and more
         // of matrix instructions ((4,4) 2,048 of 50 0.87x) nothing is gained on balance.
@@ -472,7 +477,7 @@ int plan_without_rows(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag,
     *pl = sig_plan_t{};
     pl->threads = kThreads;
 
-    const OnChipKernelInfo *ki = (B > 0) ? pick_on_chip(rs.d, rs.depth, stream_flag, B, K, cus) : nullptr;
+    const OnChipKernelInfo *ki = (B > 0) ? pick_on_chip(rs, stream_flag, B, K, cus) : nullptr;
     if (ki && ki->final_only && !wide_on_chip_wanted(B, stream_flag)) ki = nullptr;
     if (ki) {
         const int Q = ki->lanes_per_chunk;

@@ -21,6 +21,8 @@ pytestmark = pytest.mark.gpu
     (11000, 37, 5, 3, 2), (12000, 37, 5, 3, 1), (16000, 25, 5, 3, 2), (18500, 25, 5, 3, 1), (700, 48, 5, 4, 3), (860, 48, 5, 4, 2),
     # lanes in several workgroups: the last batch that takes them, and the next
     (320, 20, 8, 4, 3), (321, 20, 8, 4, 2), (252, 12, 9, 4, 3), (253, 12, 9, 4, 2), (204, 12, 10, 4, 3), (205, 12, 10, 4, 2),
+    # ... and not where the shallower entry is cut in two segments, which sum half as many steps in a row
+    (320, 96, 8, 4, 3), (256, 97, 8, 4, 2), (255, 97, 8, 4, 3), (252, 120, 9, 4, 3),
     # few lanes with states below 31 floats, and matrix instructions in place of the vector ones, as before
     (3000, 40, 3, 3, 1), (3000, 40, 4, 3, 1), (600, 30, 4, 4, 2)])
 def test_prefix_depth_on_either_side_of_a_border(gpu, oracle, B, L, d, depth, p):  # noqa: F811
