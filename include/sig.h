@@ -58,7 +58,7 @@ enum sig_status {
     SIG_ERR_UNSUPPORTED = 6 /* no kernel is compiled for this (d, depth), or the shape exceeds what it handles */
 };
 
-/* Which kernel family runs (see sig_plan). */
+/* Which kernel family runs (see sig_plan); in stream mode sig_plan_t.row_workgroups > 0 comes before it. */
 enum sig_variant {
     SIG_VARIANT_AUTO = 0,
     /* state of every path lives in HBM (in the output rows themselves) and is read-modified-written
@@ -108,9 +108,10 @@ enum sig_variant {
  *                 2 = every lane carries and re-evaluates its own prefix chain
  *   row_workgroups  stream mode: 0 = the mapping of the other fields; n > 0 = each path is cut across n workgroups (at most 32,
  *                 fewer where it is too short for that) that write their rows straight from registers, and the other
- *                 fields are not used.  Compiled for 8-20 channels at depth 2, 3-12 at depth 3, 2-8 at depth 4, 2-4 at depth
- *                 5, 2 and 3 at depth 6.  sig_plan sets it for few paths and for more than ten channels; the other fields
- *                 then hold the mapping without it.  Final mode ignores it
+ *                 fields are not used, though `variant` has to name a family.  Compiled for 8-20 channels at depth 2, 3-12 at
+ *                 depth 3, 2-8 at depth 4, 2-4 at depth 5, 2 and 3 at depth 6.  sig_plan sets it for most calls of few paths or
+ *                 more than ten channels; the other fields then hold the mapping without it, which runs once this one is
+ *                 set to 0 (a caller that edits them does so).  Final mode ignores it; a negative value is invalid in both
  *   reserved      zero
  */
 typedef struct sig_plan_t {

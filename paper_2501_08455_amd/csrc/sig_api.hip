@@ -751,6 +751,12 @@ int plan_for(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const Ro
     return plan_auto(ctx, B, L, stream_flag, rs, pl);
 }
 
+// What every plan must name, whichever fields its launch reads
+bool plan_in_range(const sig_plan_t &pl)
+{
+    return pl.variant >= SIG_VARIANT_HBM_STREAMING && pl.variant <= SIG_VARIANT_LEVEL_SCAN && pl.row_workgroups >= 0;
+}
+
 // stream mode by sig_stream_rows.h
 bool takes_stream_rows(const sig_plan_t &pl, int stream_flag) { return stream_flag && pl.row_workgroups > 0; }
 bool check_stream_rows(int64_t B, int64_t L, const RowShape &rs, const sig_plan_t &pl, int64_t *lds, int64_t *wgs)
@@ -877,6 +883,7 @@ int get_scratch(sig_ctx *ctx, Scratch &scratch, bool fixed, size_t bytes, hipStr
 int run_plan(sig_ctx *ctx, const float *path, int64_t B, int64_t L, const RowShape &rs, int stream_flag,
              float *out, const sig_plan_t &pl, hipStream_t st, bool fixed = false)
 {
+    if (!plan_in_range(pl)) return SIG_ERR_INVALID;
     Scratch scratch;
     if (takes_stream_rows(pl, stream_flag)) {
         int64_t lds = 0, wgs = 0;
@@ -1043,6 +1050,7 @@ int sig_plan_validate(int64_t B, int64_t L, int d, int depth, int stream_flag, c
     RowShape rs;
     int rc = check_shape(B, L, d, depth, stream_flag, &rs);
     if (rc != SIG_OK) return rc;
+    if (!plan_in_range(*plan)) return SIG_ERR_INVALID;
     if (takes_stream_rows(*plan, stream_flag)) {
         int64_t lds = 0, wgs = 0;
         return check_stream_rows(B, L, rs, *plan, &lds, &wgs) ? SIG_OK : SIG_ERR_INVALID;
@@ -1069,6 +1077,7 @@ int sig_plan_footprint(int64_t B, int64_t L, int d, int depth, int stream_flag, 
     RowShape rs;
     int rc = check_shape(B, L, d, depth, stream_flag, &rs);
     if (rc != SIG_OK) return rc;
+    if (!plan_in_range(*plan)) return SIG_ERR_INVALID;
     int64_t lds = 0, wgs = 0, scratch = 0;
     if (takes_stream_rows(*plan, stream_flag)) {
         if (!check_stream_rows(B, L, rs, *plan, &lds, &wgs)) return SIG_ERR_INVALID;

@@ -193,6 +193,20 @@ def test_stream_plans_of_few_long_paths_are_parallel_in_time():
             assert rc == binding.SIG_OK and pl.variant == binding.SIG_VARIANT_ON_CHIP
 
 
+def test_plan_fields_out_of_range_are_refused():
+    """A negative row_workgroups, and a variant that names no family, also where row_workgroups makes the variant unread."""
+    import ctypes
+    mk = binding.make_plan
+    on = binding.SIG_VARIANT_ON_CHIP
+    for stream in (0, 1):
+        for plan in (mk(on, prefix_depth=2, row_workgroups=-1), mk(on, prefix_depth=2, row_workgroups=-5), mk(77, row_workgroups=2),
+                     mk(0, row_workgroups=2), mk(-1, prefix_depth=2), mk(4, prefix_depth=2)):
+            assert binding.sig_plan_validate(4, 50, 4, 4, stream, plan) == binding.SIG_ERR_INVALID
+            assert binding.sig_plan_footprint(4, 50, 4, 4, stream, plan)[0] == binding.SIG_ERR_INVALID
+        assert binding.sig_plan_validate(4, 50, 4, 4, stream, mk(on, prefix_depth=2, row_workgroups=2)) == binding.SIG_OK
+    assert ctypes.sizeof(binding.sig_plan_t) == 12 * 4
+
+
 def test_stream_rows_are_planned_only_where_they_lead():
     """Which stream-mode calls write their rows from registers: calls on which that measured slower than the kernels they took
     before (0.75-0.97x), each beside a neighbour on which it leads."""
