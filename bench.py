@@ -107,7 +107,8 @@ def bench_config(binding, workloads, ctx, cfg, B, steps, warmup, plan=None, labe
            "roofline": roofline(flops, nbytes, ms_ev, None),
            "algorithmic": {"flops": flops, "bytes": nbytes}, "plan": pl.as_dict()}
     res["roofline"]["traffic"] = measured_traffic(res["workload"], res["plan"])
-    if plan is not None and plan.variant == binding.SIG_VARIANT_HBM_STREAMING:
+    rows_from_registers = cfg.stream and pl.row_workgroups > 0   # then the plan's variant does not run
+    if plan is not None and not rows_from_registers and plan.variant == binding.SIG_VARIANT_HBM_STREAMING:
         # the state-in-HBM design reads and writes every coefficient once per increment: its own byte count
         design_bytes = 8.0 * D * B * (cfg.L - 1)
         ach = design_bytes / (ms_ev * 1e-3) / 1e9
@@ -115,7 +116,7 @@ def bench_config(binding, workloads, ctx, cfg, B, steps, warmup, plan=None, labe
                            "frac": ach / PEAK_HBM_GBS, "traffic": None,
                            "note": "bytes of the state-in-HBM design (8 B per coefficient and increment); the HBM "
                                    "counters read the same amount (profiles/sig_hbm_streaming_C5.md)"}
-    if plan is not None and plan.variant == binding.SIG_VARIANT_LEVEL_SCAN:
+    if plan is not None and not rows_from_registers and plan.variant == binding.SIG_VARIANT_LEVEL_SCAN:
         # the level-by-level design keeps the lower levels of every prefix in memory: per path and step it writes
         # level n once (all levels in stream mode, all but the top one in final mode) and level n's launch reads
         # the distinct coefficients of levels 1 .. n-1 once.  (The kernels of the stream mode write the lower levels
@@ -274,7 +275,8 @@ def stream_families(binding, workloads, ctx):
                 ms_auto, _ = time_calls(binding, ctx, x, depth, 1, out, steps, warm)
                 ms_ls, _ = time_calls(binding, ctx, x, depth, 1, out, steps, warm, plan=ls_plan)
                 rows.append({"channels": d, "depth": depth, "length": L, "batch": B,
-                             "planner": "level-scan" if pl.variant == binding.SIG_VARIANT_LEVEL_SCAN else "on-chip",
+                             "planner": "rows" if pl.row_workgroups > 0 else
+                                        "level-scan" if pl.variant == binding.SIG_VARIANT_LEVEL_SCAN else "on-chip",
                              "us_auto": ms_auto * 1e3, "us_level_scan": ms_ls * 1e3})
                 del x, out
     return rows
