@@ -1169,17 +1169,23 @@ int sig_autotune(sig_ctx *ctx, int64_t B, int64_t L, int d, int depth, int strea
     rc = plan_auto(ctx, B, L, stream_flag, rs, &base);
     if (rc != SIG_OK) return rc;
 
-    // candidates: the planner's choice, the level-scan family, and for the register kernels every compiled prefix
-    // depth with the planner's time cut and with half and twice as many chunks
+    // candidates: the planner's choice, in stream mode the same with rows written from registers where it has none and without
+    // where it has, the level-scan family, and for the register kernels every compiled prefix depth with the planner's time cut
+    // and with half and twice as many chunks
     sig_plan_t cand[24];
     int n = 0;
     cand[n++] = base;
+    if (stream_flag) {
+        sig_plan_t other = base;
+        other.row_workgroups = takes_stream_rows(base, stream_flag) ? 0 : stream_rows_segments(d, depth, B, L, ctx->num_cu);
+        if (other.row_workgroups != base.row_workgroups) cand[n++] = other;
+    }
     {
         sig_plan_t ls{};
         ls.variant = SIG_VARIANT_LEVEL_SCAN;
         ls.threads = kThreads;
         ls.segments = 1;
-        if ((base.variant != SIG_VARIANT_LEVEL_SCAN || takes_stream_rows(base, stream_flag)) && check_level_scan(B, L, rs, stream_flag, ls) == SIG_OK &&
+        if (base.variant != SIG_VARIANT_LEVEL_SCAN && check_level_scan(B, L, rs, stream_flag, ls) == SIG_OK &&
             level_scan_scratch_floats(1, L, rs, stream_flag) <= kSliceFloats)
             cand[n++] = ls;
     }

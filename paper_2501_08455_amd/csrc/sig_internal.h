@@ -232,6 +232,8 @@ inline int64_t on_chip_workgroups(int Q, const OnChipArgs &A)
 // workgroups a path is cut across, 0 if the call stays with the other kernels (held_p: prefix depth of the register kernel that it
 // would take, -1 for one launch per level)
 int stream_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held_p);
+// ... that a launch would cut them across whether or not it is wanted, 0 if there is none
+int stream_rows_segments(int d, int depth, int64_t B, int64_t L, int cus);
 // the launch with `segs` workgroups a path; false if there is none
 bool stream_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, int64_t *lds_bytes, int64_t *workgroups, int *threads);
 hipError_t launch_stream_rows(const float *path, float *out, int64_t B, int64_t L, int d, int depth, int segs, int cus, hipStream_t st);

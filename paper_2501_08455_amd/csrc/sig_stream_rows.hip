@@ -164,6 +164,15 @@ int stream_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held
     return A.segs;
 }
 
+int stream_rows_segments(int d, int depth, int64_t B, int64_t L, int cus)
+{
+    const rows::Shape *s = rows::find(d, depth);
+    rows::Args A{};
+    int threads = 0;
+    size_t lds = 0;
+    return s && B >= 1 && L >= 2 && rows::cut(*s, B, L, 0, cus, &A, &threads, &lds) ? A.segs : 0;
+}
+
 bool stream_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, int64_t *lds_bytes, int64_t *workgroups, int *threads)
 {
     const rows::Shape *s = rows::find(d, depth);

@@ -66,6 +66,35 @@ def test_autotune_picks_a_correct_and_not_slower_plan(gpu, oracle, B, L, d, dept
         gpu.sig_destroy(ctx)
 
 
+def test_autotune_times_rows_from_registers_on_either_side_of_the_planners_rule(gpu, oracle):
+    """Stream mode: where the planner does not write rows from registers the tuner times that too (two paths of 1,144 points in
+    ten channels: 141 us by launches per level, 43 with it), and where it does also the planner's own mapping without."""
+    import torch
+    ctx = gpu.sig_create()
+    try:
+        B, L, d, depth = 2, 1144, 10, 3
+        assert gpu.sig_plan(ctx, B, L, d, depth, 1)[1].row_workgroups == 0
+        rc, chosen, us = gpu.sig_autotune(ctx, B, L, d, depth, 1)
+        assert rc == gpu.SIG_OK and chosen.row_workgroups > 0
+        x = workloads.brownian_paths(B, L, d, seed=311)
+        out = torch.full((B, L - 1, gpu.sig_size(d, depth)), float("nan"), device="cuda")
+        assert gpu.sig_compute(ctx, torch.from_numpy(x).cuda(), depth, 1, out) == gpu.SIG_OK
+        assert max(level_errors(out.cpu().numpy(), oracle.signature(x, depth, stream=True), d, depth)) <= TOL
+        for B, L, d, depth in [(782, 160, 3, 4), (9, 300, 2, 6), (40, 30, 12, 2)]:
+            rc, planned = gpu.sig_plan(ctx, B, L, d, depth, 1)
+            assert rc == gpu.SIG_OK and planned.row_workgroups > 0
+            xt = torch.from_numpy(workloads.brownian_paths(B, L, d, seed=312)).cuda()
+            out = torch.empty((B, L - 1, gpu.sig_size(d, depth)), device="cuda")
+            t = [time_calls(gpu, ctx, xt, depth, True, out, plan=planned)]
+            planned.row_workgroups = 0
+            t.append(time_calls(gpu, ctx, xt, depth, True, out, plan=planned))
+            assert gpu.sig_autotune(ctx, B, L, d, depth, 1)[0] == gpu.SIG_OK
+            assert time_calls(gpu, ctx, xt, depth, True, out) <= 1.15 * min(t) + 1.0
+    finally:
+        torch.cuda.synchronize()
+        gpu.sig_destroy(ctx)
+
+
 def test_autotune_status_codes(gpu):
     ctx = gpu.sig_create()
     try:
