@@ -174,7 +174,10 @@ def test_stream_plans_of_few_long_paths_are_parallel_in_time():
     """One path of 500 points in 8 channels at depth 4: 499 dependent steps in the register kernel against one
     launch per level (measured 737 against 49 us); the configurations keep their register kernels."""
     rc, pl = binding.sig_plan(None, 1, 500, 8, 4, 1)
-    assert rc == binding.SIG_OK and pl.variant == binding.SIG_VARIANT_LEVEL_SCAN
+    assert rc == binding.SIG_OK and pl.variant == binding.SIG_VARIANT_LEVEL_SCAN and pl.row_workgroups == 0
+    # (shorter, the rows go from registers to memory, a path cut across workgroups)
+    rc, pl = binding.sig_plan(None, 1, 300, 8, 4, 1)
+    assert rc == binding.SIG_OK and pl.row_workgroups > 1
     rc, pl = binding.sig_plan(None, 1, 500, 8, 4, 0)
     assert rc == binding.SIG_OK and pl.variant == binding.SIG_VARIANT_ON_CHIP
     # final mode: rows too long for the LDS of a join (10 channels at depth 4) are cut into a power of two of

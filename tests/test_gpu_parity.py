@@ -357,6 +357,9 @@ def test_shape_grid(gpu, oracle, shape):
             # test_on_chip_cases cover the register kernels' stream paths)
             assert pl.variant in (gpu.SIG_VARIANT_ON_CHIP, gpu.SIG_VARIANT_LEVEL_SCAN)
             check(gpu, oracle, x, depth, stream, label="grid auto")
+            if stream and pl.row_workgroups > 0:
+                pl.row_workgroups = 0
+                check(gpu, oracle, x, depth, stream, pl, label="grid, without rows from registers")
     x = workloads.brownian_paths(4, 41, d, seed=6100 + d + depth)
     forced = [(1, 3, 4, False), (1, 1, 7, True)]
     if Q <= 64:
@@ -519,3 +522,6 @@ def test_stream_mode_auto_with_the_deeper_prefix_entries(gpu, oracle, d, depth):
         assert rc == gpu.SIG_OK
         x = workloads.brownian_paths(B, L, d, seed=5400 + 13 * B + L + d)
         check(gpu, oracle, x, depth, True, None, label="auto, stream, plan p=%d c=%d t=%d" % (pl.prefix_depth, pl.chunks, pl.threads))
+        if pl.row_workgroups > 0:   # the call wrote its rows from registers: the plan's own mapping as well
+            pl.row_workgroups = 0
+            check(gpu, oracle, x, depth, True, pl, label="the entry itself")

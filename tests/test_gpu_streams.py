@@ -230,9 +230,18 @@ def scratch_call(gpu, ctx, i, seed):
     D = gpu.sig_size(d, depth)
     rows = (B, L - 1, D) if stream_flag else (B, D)
     if not backward:
+        rc, plan = gpu.sig_plan(ctx, B, L, d, depth, stream_flag)
+        plan.row_workgroups = 0   # (rows written straight from registers keep nothing in scratch)
+        rc, _, _, scratch = gpu.sig_plan_footprint(B, L, d, depth, stream_flag, plan)
+        assert rc == gpu.SIG_OK and scratch > 0
+
         def forward(stream):
             out = torch.full(rows, float("nan"), device="cuda")
-            assert gpu.sig_compute(ctx, x, depth, stream_flag, out, stream=stream) == gpu.SIG_OK
+            if not stream_flag:
+                assert gpu.sig_compute(ctx, x, depth, stream_flag, out, stream=stream) == gpu.SIG_OK
+            else:
+                handle = torch.cuda.ExternalStream(stream) if isinstance(stream, int) else stream
+                assert gpu.sig_compute(ctx, x, depth, stream_flag, out, stream=handle, plan=plan) == gpu.SIG_OK
             return out
         return forward
     out, g = torch.empty(rows, device="cuda"), torch.randn(rows, device="cuda", generator=gen)
