@@ -104,20 +104,22 @@ __device__ __forceinline__ void summed_step(onchip::Lane<d, N, N - 1> &sum, cons
     });
 }
 
-// A slot's steps, one after the other: increments as they lie in the tile, or the differences of its points
-template <int d, int P, bool POINTS>
+// A slot's steps, one after the other: increments as they lie in the tile, or the differences of its points.  KEEP: the point behind a
+// step stays in registers for the next one; else it is read again.  (Beside the block sums of 17 letters and more it would take the kernel past 128
+// registers, and every unit's second workgroup with them: (19,2), 373 paths of 589 points 217 us and 187.)
+template <int d, int P, bool POINTS, bool KEEP>
 struct Steps {
     const float *row;
     const int *letter;
-    onchip::Inc<d, P> last;   // POINTS: the point of `row`
+    onchip::Inc<d, P> last;   // POINTS: the point of `row`; without KEEP only at the lane's letters
 
     __device__ __forceinline__ Steps(const float *row_, const int *letter_) : row(row_), letter(letter_)
     {
-        if constexpr (POINTS) onchip::load_inc<d, P>(last, row, letter);
+        if constexpr (POINTS && KEEP) onchip::load_inc<d, P>(last, row, letter);
     }
     __device__ __forceinline__ void next(onchip::Inc<d, P> &inc)
     {
-        if constexpr (POINTS) {
+        if constexpr (POINTS && KEEP) {
             onchip::Inc<d, P> here;
             row += d;
             onchip::load_inc<d, P>(here, row, letter);
@@ -126,6 +128,18 @@ struct Steps {
 #pragma unroll
             for (int m = 0; m < P; ++m) inc.du[m] = here.du[m] - last.du[m];
             last = here;
+        } else if constexpr (POINTS) {
+#pragma unroll
+            for (int m = 0; m < P; ++m) {
+                last.du[m] = row[d + letter[m]];
+                inc.du[m] = last.du[m] - row[letter[m]];
+            }
+#pragma unroll
+            for (int a = 0; a < d; ++a) {
+                if (a == d / 2) __builtin_amdgcn_sched_barrier(0);   // half the letters' reads at a time, for the registers
+                inc.v[a] = row[d + a] - row[a];
+            }
+            row += d;
         } else {
             onchip::load_inc<d, P>(inc, row, letter);
             row += d;
@@ -136,10 +150,11 @@ struct Steps {
 extern __shared__ __align__(16) float sig_rows_smem[];
 
 // BLOCKS: the steps of a slot's own piece are summed in blocks of kPlainSteps, each from zero, and a row is the signature at the block's
-// start plus that sum (blocks of 8 to 32 give the same error).  The steps go two a round, or the copies from one to the next show: (20,2),
-// 2 paths of 51 points 11.4 -> 10.2 us, (3,5), 93 of 949 60 -> 56.6.
+// start plus that sum (blocks of 8 to 32 give the same error).  The steps go two a round, or the copies from one to the next show: (20,2), 2
+// paths of 51 points 11.4 and 10.2 us, (3,5), 93 of 949 60 and 56.6.
+// Four wavefronts a SIMD: two workgroups of 512 threads on a unit, or one of 1,024.
 template <int d, int N, bool BLOCKS>
-__global__ __launch_bounds__((most_threads(d, N))) void sig_stream_rows_kernel(Args A)
+__global__ __launch_bounds__((most_threads(d, N))) __attribute__((amdgpu_waves_per_eu(4))) void sig_stream_rows_kernel(Args A)
 {
     using G = Geo<d, N>;
     constexpr int P = G::P, Q = G::Q, D = G::D, DS = G::DS;
@@ -220,7 +235,7 @@ __global__ __launch_bounds__((most_threads(d, N))) void sig_stream_rows_kernel(A
     };
     // `count` steps of the slot's own piece, f after each of them; exact: with level 1 from the points (POINTS)
     auto own_steps = [&](Lane &ln, const float *row, int count, auto exact, auto &&f) __attribute__((always_inline)) {
-        Steps<d, P, POINTS> steps(row, letter);
+        Steps<d, P, POINTS, d <= 16 || !BLOCKS> steps(row, letter);
         onchip::Inc<d, P> inc;
         auto level1 = [&](Lane &now) __attribute__((always_inline)) {
             if constexpr (POINTS && decltype(exact)::value) (P > 1 ? now.pre[0] : now.s[0]) = steps.last.du[0] - first1;
@@ -238,7 +253,8 @@ __global__ __launch_bounds__((most_threads(d, N))) void sig_stream_rows_kernel(A
                     level1(now);
                     f(now, t);
                 }
-                ln = now;
+                add_state<d, N, P>(ln, ln, sum);   // (not ln = now: the words that no chain reads would stay in registers beside the sum)
+                if constexpr (POINTS && decltype(exact)::value) (P > 1 ? ln.pre[0] : ln.s[0]) = P > 1 ? now.pre[0] : now.s[0];
             }
         } else {
 #pragma unroll 2
