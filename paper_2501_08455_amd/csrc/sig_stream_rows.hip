@@ -123,10 +123,11 @@ bool cut(const Shape &s, int64_t B, int64_t L, int forced_segs, int cus, Args *a
 
 // Which stream-mode calls take it.  `held_p`: prefix depth of the register kernel for stream mode that the planner would take, -1 if
 // it would take one launch per level.  Microseconds without and with it in brackets.
-//  - Against the launches per level: everywhere but on one to three paths whose pieces have hundreds of steps [(12,3), one of 488
-//    points 44 and 52; (8,4), four of 470 0.88x], where a row takes long to store and the joins stride LDS by a multiple of four, and, at depth 2 (two launches),
-//    on few paths that those launches still hold in one tile, 512 increments [(20,2), two of 490 21 and 28; (17,2), two of 405 19 and
-//    22; (16,2), whose lanes stride LDS by 16, ten of 230 16 and 20].
+//  - Against the launches per level: everywhere but on a few paths of hundreds of points whose rows take long to store while the joins
+//    stride LDS by a multiple of four [(12,3), one of 488 points 44 and 52; (8,4), four of 470 0.88x, two of 1,415 122 and 191; but (7,4), two
+//    of 1,415 0.86 to 1.6x, (9,3) two of 1,180 124 and 40, (20,2) two of 3,000 1.4x], and, at depth 2 (two launches), on few paths that those
+//    launches still hold in one tile, 512 increments [(20,2), two of 490 21 and 28; (17,2), two of 405 19 and 22; (16,2), whose lanes
+//    stride LDS by 16, ten of 230 16 and 20].
 //  - Against the register kernels, whose rows stop in LDS and reach memory in longer runs: batches that leave the chip below a
 //    wavefront per SIMD uncut and rows of some hundred megabytes at most [(4,4), 1,024 paths of 256 points 93 and 79, 4,096 284 and
 //    295; (3,5), 500 of 1,000 173 and 275].  At depth 3 the crossing lies lower [(5,3), 1,000 of 100 17.6 and 18.7;
@@ -157,9 +158,9 @@ int stream_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held
     if (!rows::cut(*s, B, L, 0, cus, &A, &threads, &lds)) return 0;
     if (held_p < 0) {
         const bool one_tile = K < 512;
-        if (B < 4 && K / A.slots > 250) return 0;
+        if (B < 5 && s->D > 4000 && K / A.slots > 250) return 0;
         if (depth == 2 && one_tile && (d % 16 ? d > 13 && B < 16 && K * d * d * d > 900000 : K > 110 && (B < 32 || (B < 64 && K < 250)))) return 0;
-        if (depth > 2 && d % 4 == 0 && s->D > 1800 && (one_tile ? B < 3 + s->D / 2000 && K > 380 : B < 2 && K > 590)) return 0;
+        if (depth > 2 && d % 4 == 0 && s->D > 1800 && (one_tile ? B < 3 + s->D / 2000 && K > 380 : B < 3 && K > 590 && K < 1024)) return 0;
     }
     return A.segs;
 }
