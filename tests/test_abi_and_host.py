@@ -196,6 +196,20 @@ def test_stream_plans_of_few_long_paths_are_parallel_in_time():
             assert rc == binding.SIG_OK and pl.variant == binding.SIG_VARIANT_ON_CHIP
 
 
+def test_bench_finds_the_measured_traffic_of_the_planned_launches():
+    """bench.py reports a workload's bytes from the profile that was taken with the plan it runs: every configuration whose plan
+    is the profiled one, rows written from registers included; none for another plan."""
+    import bench
+    for name, B in [("C1", 0), ("C2", 0), ("C4", 0), ("C5", 0), ("C4", 4096), ("C5", 64)]:
+        cfg = workloads.CONFIGS[name]
+        B = B or cfg.B
+        rc, pl = binding.sig_plan(None, B, cfg.L, cfg.d, cfg.depth, int(cfg.stream))
+        label = "%s B=%d L=%d d=%d depth=%d %s" % (name, B, cfg.L, cfg.d, cfg.depth, "stream" if cfg.stream else "final")
+        assert rc == binding.SIG_OK and bench.measured_traffic(label, pl.as_dict()) > 0, label
+        pl.row_workgroups += 1
+        assert bench.measured_traffic(label, pl.as_dict()) is None
+
+
 def test_plan_fields_out_of_range_are_refused():
     """A negative row_workgroups, and a variant that names no family, also where row_workgroups makes the variant unread."""
     import ctypes
