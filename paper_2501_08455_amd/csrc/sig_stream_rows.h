@@ -10,7 +10,7 @@
 //
 // Bound by latency on few paths (a launch, K / C steps of the fold, log2 C rounds of the scan, T steps that each store a row) and
 // by the stores on many.  Measured against what these calls took before (the register kernels of sig_onchip.h, one workgroup per
-// path, their rows staged in LDS; or one launch per level), us: (4,4) 64 paths of 256 points 24.3 and 12.4, 4 of 1,075 62 and 19;
+// path, their rows staged in LDS; or one launch per level), us: (4,4) 64 paths of 256 points 24.3 and 12.3, 4 of 1,075 62 and 19;
 // (5,4) 16 of 100 17.5 and 8.5; (12,3) 1,024 of 100 487 and 228, 128 of 1,000 635 and 363.
 //
 // Rounding: a sum of T terms, one after the other, is off by about sqrt(T) roundings of its last value.  Pieces of more than

@@ -124,8 +124,8 @@ bool cut(const Shape &s, int64_t B, int64_t L, int forced_segs, int cus, Args *a
 // Which stream-mode calls take it.  `held_p`: prefix depth of the register kernel for stream mode that the planner would take, -1 if
 // it would take one launch per level.  Microseconds without and with it in brackets.
 //  - Against the launches per level: everywhere but on a few paths of hundreds of points whose rows take long to store while the joins
-//    stride LDS by a multiple of four [(12,3), one of 488 points 44 and 52; (8,4), four of 470 0.88x, two of 1,415 122 and 191; but (7,4), two
-//    of 1,415 0.86 to 1.6x, (9,3) two of 1,180 124 and 40, (20,2) two of 3,000 1.4x], and, at depth 2 (two launches), on few paths that those
+//    stride LDS by a multiple of four [(12,3), one of 488 points 44 and 52; (8,4), four of 470 0.88x, two of 1,415 122 and 191; (7,4), one of 1,356
+//    0.86x, but of 1,614 1.48x, (9,3) two of 1,180 124 and 40, (20,2) two of 3,000 1.4x], and, at depth 2 (two launches), on few paths that those
 //    launches still hold in one tile, 512 increments [(20,2), two of 490 21 and 28; (17,2), two of 405 19 and 22; (16,2), whose lanes
 //    stride LDS by 16, ten of 230 16 and 20].
 //  - Against the register kernels, whose rows stop in LDS and reach memory in longer runs: batches that leave the chip below a
@@ -159,6 +159,7 @@ int stream_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held
     if (held_p < 0) {
         const bool one_tile = K < 512;
         if (B < 5 && s->D > 4000 && K / A.slots > 250) return 0;
+        if (B < 3 && s->D > 2500 && K > 1000 && K < 1536) return 0;
         if (depth == 2 && one_tile && (d % 16 ? d > 13 && B < 16 && K * d * d * d > 900000 : K > 110 && (B < 32 || (B < 64 && K < 250)))) return 0;
         if (depth > 2 && d % 4 == 0 && s->D > 1800 && (one_tile ? B < 3 + s->D / 2000 && K > 380 : B < 3 && K > 590 && K < 1024)) return 0;
     }
