@@ -65,8 +65,9 @@ def test_an_increment_that_is_not_finite_stays_in_its_path(gpu):  # noqa: F811
         assert not np.isfinite(got[3]).all() and np.isnan(got[5]).any()
 
 
-@pytest.mark.parametrize("d,depth,p,B,L", [(4, 6, 4, 256, 50), (4, 6, 4, 257, 50), (4, 6, 4, 257, 40), (4, 6, 4, 6200, 5), (7, 5, 3, 128, 153), (7, 5, 3, 130, 153), (7, 5, 3, 130, 151), (7, 5, 3, 257, 153),
-                                                     (10, 5, 3, 896, 4), (10, 5, 3, 900, 4), (10, 5, 3, 900, 21), (6, 4, 3, 300, 20)])
+@pytest.mark.parametrize("d,depth,p,B,L", [
+    (4, 6, 4, 256, 50), (4, 6, 4, 257, 50), (4, 6, 4, 257, 40), (4, 6, 4, 6200, 5), (7, 5, 3, 128, 153), (7, 5, 3, 130, 153),
+    (7, 5, 3, 130, 151), (7, 5, 3, 257, 153), (10, 5, 3, 896, 4), (10, 5, 3, 900, 4), (10, 5, 3, 900, 21), (6, 4, 3, 300, 20)])
 def test_either_side_of_the_launches_that_keep_the_vector_fold(gpu, d, depth, p, B, L):  # noqa: F811
     x = workloads.brownian_paths(B, L, d, seed=9900 + d + B)
     want = run_gpu(gpu, x, depth, False, gpu.make_plan(gpu.SIG_VARIANT_ON_CHIP, prefix_depth=p, independent_waves=1))
