@@ -243,6 +243,9 @@ int sig_combine(sig_ctx *ctx, const float *a, const float *b, int64_t B, int d, 
  * steps cut into chunks, or (few long paths) into up to 32 stretches swept by different workgroups.  Paths of a dozen
  * points or so (fewer than d at depth 2, up to 78 at (4,6); the batch moves this) and every other shape are swept on the
  * signature itself, as below.
+ * Stream mode at depth 2, two to twenty channels: one launch over sums of the rows behind each step (two for a few long paths,
+ * with context scratch of a row of d (d + 1) floats for each of up to 32 workgroups a path; where scratch cannot be had a path
+ * stays in one workgroup); `out` is not read.  Rows too long for its 32-bit offsets (d (d + 1) L beyond 2^31) are swept as below.
  * The other sweeps start from the signature at the end and undo one increment at a time.  Shapes with a compiled register
  * kernel (see sig_backward_available) whose paths fit its LDS staging take it.  Few long paths and paths too long for that
  * staging are cut into up to 32 time segments that are swept by different workgroups: by Eq. 3 a segment can start from the
@@ -266,14 +269,15 @@ int sig_combine(sig_ctx *ctx, const float *a, const float *b, int64_t B, int d, 
 int sig_backward(sig_ctx *ctx, const float *path, int64_t B, int64_t L, int d, int depth, int stream_flag,
                  const float *out, const float *grad_out, float *grad_path, void *hip_stream);
 
-/* 1 if sig_backward has a compiled register kernel for (d, depth), 0 if stream mode would take the general sweep (final
- * mode has its own compiled shapes, see sig_backward).  Host only. */
+/* 1 if sig_backward has a compiled register kernel for (d, depth), 0 if stream mode beyond depth 2 would take the general sweep (final
+ * mode and depth 2 have their own compiled shapes, see sig_backward).  Host only. */
 int sig_backward_available(int d, int depth);
 
 /*
  * How sig_backward would sweep this shape.  Host only; ctx may be NULL (a device with 256 compute units is assumed).
  * Returns the number of time segments the sweep may be cut into across workgroups (2 .. 32; final-mode sweeps on brackets
- * pack whole paths instead where that is faster), 1 for an uncut sweep, 0 for shapes without a register kernel, or minus the SIG_ERR_* status with which sig_backward would reject the arguments.
+ * pack whole paths instead where that is faster; stream mode at depth 2 has a cut of its own, which this does not report: the
+ * number is that of the sweep on signatures), 1 for an uncut sweep, 0 for shapes without a register kernel, or minus the SIG_ERR_* status with which sig_backward would reject the arguments.
  */
 int sig_backward_segments(const sig_ctx *ctx, int64_t B, int64_t L, int d, int depth, int stream_flag);
 

@@ -1345,6 +1345,20 @@ int sig_backward(sig_ctx *ctx, const float *path, int64_t B, int64_t L, int d, i
         hipError_t eb = launch_bracket(path, out, grad_out, grad_path, B, L, d, depth, segs, ctx->num_cu, st);
         return eb == hipSuccess ? SIG_OK : SIG_ERR_HIP;
     }
+    if (stream_flag && depth == 2) {
+        // sums over the rows behind a step; where scratch cannot be had a path stays in one workgroup
+        const int64_t floats = stream_gradient_scratch_floats(d, B, L, ctx->num_cu);
+        if (floats >= 0) {
+            const size_t bytes = (size_t)floats * sizeof(float);
+            if (floats > 0 && Scratch::within_reach(ctx, bytes, st)) {
+                rc = scratch.get(ctx, bytes, st, &work);
+                if (rc == SIG_ERR_ALLOC) work = nullptr;
+                else if (rc != SIG_OK) return rc;
+            }
+            hipError_t er = launch_stream_gradient(path, grad_out, grad_path, work, B, L, d, ctx->num_cu, st);
+            return er == hipSuccess ? SIG_OK : SIG_ERR_HIP;
+        }
+    }
     const bool fits = backward_available(d, depth) && backward_fits(d, depth, L);
     if (backward_available(d, depth)) {
         // few long paths (or paths too long for the LDS of the uncut sweep): the sweep cut in time across workgroups

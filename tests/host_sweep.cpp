@@ -12,6 +12,8 @@
 namespace sig {   // csrc/sig_internal.h
 bool bracket_depth2_geometry(int d, int64_t B, int64_t L, int cus, int64_t *grid, int64_t *segs, int64_t *steps, int64_t *groups,
                              int64_t *lds_bytes);
+bool stream_gradient_geometry(int d, int64_t B, int64_t L, int cus, bool scratch, int64_t *scratch_floats, int64_t *grid, int64_t *segs,
+                              int64_t *groups, int64_t *chunks, int64_t *steps, int64_t *rows);
 }
 
 static uint64_t state = 0x9E3779B97F4A7C15ull;
@@ -111,6 +113,26 @@ int main()
         EXPECT(ok && grid >= 1 && grid * 256 < (int64_t)1 << 32 && lds <= 64 * 1024, "depth 2, d=%d B=%lld L=%lld: %d grid %lld lds %lld", d, (long long)B, (long long)L, ok, (long long)grid, (long long)lds);
         if (segs > 1) EXPECT(grid == B * segs && groups == 1 && segs * steps >= L && (segs - 1) * steps < L, "stretches: d=%d B=%lld L=%lld %lld x %lld", d, (long long)B, (long long)L, (long long)segs, (long long)steps);
         else EXPECT(grid * groups >= B && (grid - 1) * groups < B, "paths: d=%d B=%lld L=%lld grid %lld x %lld", d, (long long)B, (long long)L, (long long)grid, (long long)groups);
+        ++checked;
+    }
+
+    // ---- the launches of the every-prefix gradient at depth 2: every row of every path has its slot, in one workgroup only
+    for (int it = 0; it < 20000; ++it) {
+        const int d = 2 + (int)(rnd() % 19);
+        const int64_t L = it & 1 ? pick(Ls, sizeof Ls / sizeof *Ls) : 2 + (int64_t)(rnd() % 3000), K = L - 1, D = d + d * d;
+        if (L < 2) continue;
+        const int64_t B = it & 2 ? (int64_t)1 << (rnd() % 33) : 1 + (int64_t)(rnd() % ((uint64_t)1 << (1 + rnd() % 20)));
+        const bool scratch = (it & 4) != 0;
+        int64_t floats = 0, grid = 0, segs = 0, groups = 0, chunks = 0, steps = 0, rows = 0;
+        if (!sig::stream_gradient_geometry(d, B, L, 256, scratch, &floats, &grid, &segs, &groups, &chunks, &steps, &rows)) {
+            EXPECT(L * D * 2 > INT32_MAX || B > (int64_t)1 << 24, "no launch: d=%d B=%lld L=%lld", d, (long long)B, (long long)L);
+            continue;
+        }
+        EXPECT(grid >= 1 && grid * 256 < (int64_t)1 << 35 && groups * L * D <= (int64_t)INT32_MAX + L * D, "offsets: d=%d B=%lld L=%lld", d, (long long)B, (long long)L);
+        EXPECT(floats == (segs > 1 ? B * segs * D : 0) && (scratch || segs == 1) && segs <= 32, "scratch: d=%d B=%lld L=%lld", d, (long long)B, (long long)L);
+        if (segs > 1) EXPECT(grid == B * segs && groups == 1 && rows % (chunks * steps) == 0 && segs * rows >= K && (segs - 1) * rows < K, "d=%d B=%lld L=%lld: %lld x %lld rows", d, (long long)B, (long long)L, (long long)segs, (long long)rows);
+        else EXPECT(grid * groups >= B && (grid - 1) * groups < B && (groups == 1 || chunks * steps >= K), "d=%d B=%lld L=%lld: %lld paths", d, (long long)B, (long long)L, (long long)groups);
+        EXPECT(groups * chunks <= 4 * (64 / d), "slots: d=%d B=%lld L=%lld", d, (long long)B, (long long)L);
         ++checked;
     }
 

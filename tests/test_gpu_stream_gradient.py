@@ -1,0 +1,77 @@
+"""The every-prefix gradient at depth 2 (csrc/sig_stream_gradient.hip) at the edges of its launches, against the fp64 oracle with
+the gates of test_gpu_backward.py: fewer rows than a tile, ragged last tiles, stretches, blocks and workgroups, whole paths side by
+side with a ragged last wavefront, every channel count; and without scratch, as a captured call may have to run."""
+import numpy as np
+import pytest
+
+from paper_2501_08455_amd import workloads
+from test_gpu_backward import check, gpu, launches, sampled_backward, say  # noqa: F401  (gpu is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+# d, B, L: a stretch per slot (several paths in a workgroup, or one), several blocks of a workgroup, several workgroups a path
+CUT = [(2, 3, 2), (2, 5, 130), (3, 2, 85), (5, 3, 9), (6, 1, 4), (9, 4, 2), (10, 3, 26), (13, 2, 17), (17, 2, 13), (20, 5, 60),
+       (16, 128, 40), (20, 300, 70), (2, 40, 1025), (9, 300, 1300), (18, 300, 301),
+       (10, 1, 1445), (4, 2, 3001), (19, 1, 700), (12, 3, 501)]
+
+
+@pytest.mark.parametrize("d,B,L", CUT)
+def test_stretches_side_by_side(gpu, oracle, d, B, L):
+    x = workloads.brownian_paths(B, L, d, seed=9600 + d + L)
+    say("every-prefix gradient, depth 2, cut in time: %s" % ((d, B, L),))
+    sampled_backward(gpu, oracle, x, 2, True, sorted({0, B // 2, B - 1}), seed=d + L)
+
+
+# whole paths side by side: more of them than a wavefront holds, and rows that are no multiple of a tile
+@pytest.mark.parametrize("d,B,L", [(2, 40001, 3), (2, 9001, 34), (3, 22003, 2), (5, 13001, 12), (7, 9002, 31), (10, 8193, 9), (16, 4099, 5),
+                                   (20, 3001, 8), (13, 4501, 3)])
+def test_whole_paths_side_by_side(gpu, oracle, d, B, L):
+    x = workloads.brownian_paths(B, L, d, seed=9700 + d + L)
+    say("every-prefix gradient, depth 2, uncut: %s" % ((d, B, L),))
+    sampled_backward(gpu, oracle, x, 2, True, [0, 1, B // 2, B - 2, B - 1], seed=d + L)
+
+
+@pytest.mark.parametrize("d", range(2, 21))
+def test_errors_stay_at_the_rounding_of_float32(gpu, oracle, d):
+    """A row's point is a sum of K terms of the rows behind it: u sqrt(K) = 6.6e-7 of its norm for K = 120 at worst, measured
+    1.7e-7 at most."""
+    import torch
+    rng = np.random.default_rng(9800 + d)
+    x = (rng.normal(size=(5, 121, d)) * 121 ** -0.5).cumsum(1).astype(np.float32)
+    path = torch.from_numpy(x).cuda()
+    out = gpu.signature(path, 2, stream=True)
+    g = torch.from_numpy(rng.normal(size=tuple(out.shape)).astype(np.float32)).cuda()
+    gx = torch.full_like(path, float("nan"))
+    assert gpu.sig_backward(gpu.default_ctx(), path, 2, 1, out, g, gx) == gpu.SIG_OK
+    want = oracle.signature_backward(x, 2, g.cpu().numpy(), stream=True)
+    err = np.linalg.norm(gx.cpu().numpy() - want) / np.linalg.norm(want)
+    say("  d = %d: rel err %.2e" % (d, err))
+    assert err <= 6.6e-7
+
+
+def test_a_capture_that_cannot_grow_scratch_keeps_a_path_in_one_workgroup(gpu, oracle):
+    """One long path takes two launches and scratch; on a context without any, while a graph is recorded, one launch."""
+    import torch
+    x = workloads.brownian_paths(1, 1500, 6, seed=9900)
+    xt = torch.from_numpy(x).cuda()
+    out = gpu.signature(xt, 2, stream=True)
+    g = torch.from_numpy(np.random.default_rng(5).normal(size=tuple(out.shape)).astype(np.float32)).cuda()
+    want = oracle.signature_backward(x, 2, g.cpu().numpy(), stream=True)
+    fresh, gx = gpu.sig_create(), torch.empty_like(xt)
+    call = lambda ctx: gpu.sig_backward(ctx, xt, 2, 1, out, g, gx)   # noqa: E731
+    try:
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            assert call(fresh) == gpu.SIG_OK
+        for _ in range(3):
+            gx.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.linalg.norm(gx.cpu().numpy() - want) <= 1e-5 * np.linalg.norm(want)
+        assert launches(gpu, lambda: call(fresh)) == 1
+        assert call(fresh) == gpu.SIG_OK            # the scratch grows here
+        assert launches(gpu, lambda: call(fresh)) == 2
+    finally:
+        torch.cuda.synchronize()
+        gpu.sig_destroy(fresh)
