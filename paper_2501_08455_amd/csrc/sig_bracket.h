@@ -115,7 +115,9 @@ struct Geo {
 
 // Wavefronts per SIMD the kernels are built for: what a lane's words and some fifty more registers allow.  Without the bound
 // the compiler spends registers on the sums over the rows, before the words exist, and halves the residency.
-constexpr int min_waves(int state) { return state > 100 ? 2 : state > 57 ? 3 : 1; }
+// The words of (5,4) to (7,4) fit four wavefronts, which takes a spare register off (5,4) (134 otherwise; 65,536 paths of 100
+// points 186 -> 177 us); at depth 5 and 6 it would spill ((4,5) 113 -> 126 us).
+constexpr int min_waves(int depth, int state) { return state > 100 ? 2 : state > 57 ? 3 : depth == 4 && state > 24 ? 4 : 1; }
 
 // Summands that `threads` threads split one of cnt sums per path into
 constexpr int sum_parts(int threads, int paths, int cnt)
@@ -552,9 +554,10 @@ extern __shared__ __align__(16) float sig_bracket_smem[];
 // path for the bracket values.  Bound by waiting, mostly for LDS: (5,4), 100 points, 65,536 paths issue 81,000 vector
 // instructions per SIMD in 414,000 cycles (5.1 cycles each, against 2.2 where the pipe is full), the LDS is busy 70 % of
 // the time (28 % of that bank conflicts), and 531 MB move where 507 must (205 us under the counters).  Registers decide
-// the residency (135 there: three wavefronts per SIMD; two to seven over the shapes); keeping the paths' bracket values in
+// the residency (128 there: four wavefronts per SIMD; two to seven over the shapes); keeping the paths' bracket values in
 // registers as they are formed, instead of all paths' in LDS, and having the next path's rows in flight took a quarter
-// off (246 -> 188 us on one card).
+// off (246 -> 188 us on one card).  The counters are from three wavefronts; places of the tile in 32 bits, loaded without a
+// condition, and the fourth wavefront: 195 -> 175 us (82 of them the bracket values), (2,6) with 700 points 365 -> 280.
 template <class G>
 constexpr int packed_lds_floats()
 {
@@ -564,7 +567,7 @@ constexpr int packed_lds_floats()
 }
 
 template <int d, int N, int P>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(min_waves(Geo<d, N, P>::SZ))))
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(min_waves(N, Geo<d, N, P>::SZ))))
 void sig_bracket_packed_kernel(Args A)
 {
     using G = Geo<d, N, P>;
@@ -618,28 +621,25 @@ void sig_bracket_packed_kernel(Args A)
     const int path_floats = (int)A.L * d;               // PG paths stay below 2^31 floats (checked on the host)
     const float *block = A.path + b0 * path_floats;
     float *grads = A.grad_path + b0 * path_floats;
-    int place[NV], where[NV];                           // float of the tile of its path (-1: none), and its row in LDS
+    int from_block[NV], where[NV];                      // its place in the tile of its path, in the block, and its row in LDS (-1: none)
     float lo[NV], hi[NV];
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
         const int i = tid + j * kWave;
         const int p = i / (TT * d), x = i - p * (TT * d);
         const int kk = x / d, a = x - kk * d;
-        place[j] = p < npaths ? x : -1;
-        where[j] = (p * (TT + 1) + TT - kk) * G::VS + a;
+        from_block[j] = p < npaths ? p * path_floats + x : 0;
+        where[j] = p < PG ? (p * (TT + 1) + TT - kk) * G::VS + a : -1;
     }
+    // (steps below the first one, and slots without a path, bring floats that nothing reads: the places are only kept inside the block)
     auto fetch = [&](int t0) __attribute__((always_inline)) {
         const int from = (K - t0 - TT) * d;             // of the tile in its path; below 0 in the last tile
-        const int least = from < 0 ? -from : 0;
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-            lo[j] = hi[j] = 0.0f;
-            if (place[j] >= least) {
-                const int i = tid + j * kWave;
-                const float *src = block + (i / (TT * d)) * path_floats + from + place[j];
-                lo[j] = src[0];
-                hi[j] = src[d];
-            }
+            const int at = from_block[j] + from;
+            const float *src = block + (unsigned)(at > 0 ? at : 0);
+            lo[j] = src[0];
+            hi[j] = src[d];
         }
     };
     fetch(0);
@@ -668,7 +668,7 @@ void sig_bracket_packed_kernel(Args A)
         }
 #pragma unroll
         for (int j = 0; j < NV; ++j)
-            if (place[j] >= 0) vrows[where[j]] = lo[j] - hi[j];
+            if (where[j] >= 0) vrows[where[j]] = lo[j] - hi[j];
         if (t0 + TT < K) fetch(t0 + TT);
         __syncthreads();
         for (int t = 1; t <= steps; ++t) {
@@ -722,7 +722,7 @@ int64_t chunked_lds_floats(int C, int fold_slots = 0)
 }
 
 template <int d, int N, int P>
-__global__ __launch_bounds__((Geo<d, N, P>::CT)) __attribute__((amdgpu_waves_per_eu(min_waves(Geo<d, N, P>::SZ))))
+__global__ __launch_bounds__((Geo<d, N, P>::CT)) __attribute__((amdgpu_waves_per_eu(min_waves(N, Geo<d, N, P>::SZ))))
 void sig_bracket_chunked_kernel(Args A)
 {
     using G = Geo<d, N, P>;
