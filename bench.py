@@ -37,8 +37,9 @@ def measured_traffic(workload, plan):
             taken_with = json.loads(cells[2].strip("`"))
         except ValueError:
             continue
-        # (profiles of plans without rows from registers do not name that field)
-        if taken_with is None or dict({"row_workgroups": 0}, **taken_with) != dict({"row_workgroups": 0}, **plan):
+        # (profiles of plans without rows from registers, or split across workgroups, do not name those fields)
+        newer = {"row_workgroups": 0, "split_rows": 0}
+        if taken_with is None or dict(newer, **taken_with) != dict(newer, **plan):
             continue
         try:
             rd, wr = (float(v) for v in cells[5].split(" + "))
@@ -279,7 +280,7 @@ def stream_families(binding, workloads, ctx):
                 ms_auto, _ = time_calls(binding, ctx, x, depth, 1, out, steps, warm)
                 ms_ls, _ = time_calls(binding, ctx, x, depth, 1, out, steps, warm, plan=ls_plan)
                 rows.append({"channels": d, "depth": depth, "length": L, "batch": B,
-                             "planner": "rows" if pl.row_workgroups > 0 else
+                             "planner": "split rows" if pl.split_rows > 0 else "rows" if pl.row_workgroups > 0 else
                                         "level-scan" if pl.variant == binding.SIG_VARIANT_LEVEL_SCAN else "on-chip",
                              "us_auto": ms_auto * 1e3, "us_level_scan": ms_ls * 1e3})
                 del x, out

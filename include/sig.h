@@ -58,7 +58,7 @@ enum sig_status {
     SIG_ERR_UNSUPPORTED = 6 /* no kernel is compiled for this (d, depth), or the shape exceeds what it handles */
 };
 
-/* Which kernel family runs (see sig_plan); in stream mode sig_plan_t.row_workgroups > 0 comes before it. */
+/* Which kernel family runs (see sig_plan); in stream mode sig_plan_t.split_rows > 0 and row_workgroups > 0 come before it. */
 enum sig_variant {
     SIG_VARIANT_AUTO = 0,
     /* state of every path lives in HBM (in the output rows themselves) and is read-modified-written
@@ -112,7 +112,14 @@ enum sig_variant {
  *                 depth 3, 2-8 at depth 4, 2-4 at depth 5, 2 and 3 at depth 6.  sig_plan sets it for most calls of few paths or
  *                 more than ten channels; the other fields then hold the mapping without it, which runs once this one is
  *                 set to 0 (a caller that edits them does so).  Final mode ignores it; a negative value is invalid in both
- *   reserved      zero
+ *   split_rows    stream mode: 0 = the mapping of the other fields; n > 0 = the rows of a path are split across workgroups, which
+ *                 write them from registers, and each path is cut into n stretches (at most 32 and no more than increments, fewer
+ *                 where they would be short) that follow each other in different workgroups.  Before row_workgroups; of the other
+ *                 fields only `variant` and row_workgroups are read: they say whether a point that is not a number spoils level 1
+ *                 of the rows behind it, as in the mapping without split_rows.  Compiled for (10,3), 8-10 channels at
+ *                 depth 4, 5 and 6 at depth 5, 4 at depth 6.  Context scratch for the stretches' signatures, (n - 1) D floats a path;
+ *                 where it cannot be had (or exceeds 8 GiB) a stretch folds what lies before it again.  Final mode ignores
+ *                 it; a negative value is invalid in both
  */
 typedef struct sig_plan_t {
     int32_t variant;
@@ -126,7 +133,7 @@ typedef struct sig_plan_t {
     int32_t tile_loader;
     int32_t shared_chain;
     int32_t row_workgroups;
-    int32_t reserved[1];
+    int32_t split_rows;
 } sig_plan_t;
 
 /*

@@ -32,10 +32,10 @@ class sig_plan_t(ctypes.Structure):
                 ("threads", ctypes.c_int32), ("tile_steps", ctypes.c_int32),
                 ("independent_waves", ctypes.c_int32), ("stagger_ticks", ctypes.c_int32),
                 ("tile_loader", ctypes.c_int32), ("shared_chain", ctypes.c_int32),
-                ("row_workgroups", ctypes.c_int32), ("reserved", ctypes.c_int32 * 1)]
+                ("row_workgroups", ctypes.c_int32), ("split_rows", ctypes.c_int32)]
 
     def as_dict(self):
-        skip = ("reserved", "independent_waves", "stagger_ticks", "tile_loader", "shared_chain")
+        skip = ("independent_waves", "stagger_ticks", "tile_loader", "shared_chain")
         return {k: int(getattr(self, k)) for k, _ in self._fields_ if k not in skip}
 
 
@@ -186,13 +186,14 @@ def sig_plan_footprint(B, L, d, depth, stream_flag, plan):
 
 
 def make_plan(variant, prefix_depth=0, chunks=1, segments=1, threads=256, tile_steps=0, independent_waves=0,
-              stagger_ticks=0, tile_loader=0, shared_chain=0, row_workgroups=0):
+              stagger_ticks=0, tile_loader=0, shared_chain=0, row_workgroups=0, split_rows=0):
     pl = sig_plan_t()
     pl.independent_waves = int(independent_waves)
     pl.stagger_ticks = int(stagger_ticks)
     pl.tile_loader = int(tile_loader)
     pl.shared_chain = int(shared_chain)
     pl.row_workgroups = int(row_workgroups)
+    pl.split_rows = int(split_rows)
     pl.variant, pl.prefix_depth, pl.chunks = int(variant), int(prefix_depth), int(chunks)
     pl.segments, pl.threads, pl.tile_steps = int(segments), int(threads), int(tile_steps)
     return pl

@@ -727,6 +727,9 @@ int plan_auto(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const R
     if (rc == SIG_OK && stream_flag)
         pl->row_workgroups = stream_rows_wanted(rs.d, rs.depth, B, L, ctx ? ctx->num_cu : kDefaultCUs,
                                                 pl->variant == SIG_VARIANT_ON_CHIP ? pl->prefix_depth : -1);
+    if (rc == SIG_OK && stream_flag)
+        pl->split_rows = split_rows_wanted(rs.d, rs.depth, B, L, ctx ? ctx->num_cu : kDefaultCUs,
+                                           pl->variant == SIG_VARIANT_ON_CHIP ? pl->prefix_depth : -1, pl->row_workgroups > 0);
     return rc;
 }
 
@@ -754,7 +757,7 @@ int plan_for(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const Ro
 // What every plan must name, whichever fields its launch reads
 bool plan_in_range(const sig_plan_t &pl)
 {
-    return pl.variant >= SIG_VARIANT_HBM_STREAMING && pl.variant <= SIG_VARIANT_LEVEL_SCAN && pl.row_workgroups >= 0;
+    return pl.variant >= SIG_VARIANT_HBM_STREAMING && pl.variant <= SIG_VARIANT_LEVEL_SCAN && pl.row_workgroups >= 0 && pl.split_rows >= 0;
 }
 
 // stream mode by sig_stream_rows.h
@@ -767,6 +770,15 @@ bool check_stream_rows(int64_t B, int64_t L, const RowShape &rs, const sig_plan_
         return true;
     }
     return false;
+}
+
+// stream mode by sig_split_rows.h, which comes before it
+bool takes_split_rows(const sig_plan_t &pl, int stream_flag) { return stream_flag && pl.split_rows > 0; }
+bool check_split_rows(int64_t B, int64_t L, const RowShape &rs, const sig_plan_t &pl, int64_t *lds, int64_t *wgs, int64_t *scratch_floats)
+{
+    if (!split_rows_geometry(rs.d, rs.depth, B > 0 ? B : 1, L, pl.split_rows, kDefaultCUs, lds, wgs, scratch_floats)) return false;
+    if (B == 0) *wgs = *scratch_floats = 0;
+    return true;
 }
 
 // The context's scratch for the launches of one call.  From get() until it goes out of scope, behind the call's last launch,
@@ -885,6 +897,22 @@ int run_plan(sig_ctx *ctx, const float *path, int64_t B, int64_t L, const RowSha
 {
     if (!plan_in_range(pl)) return SIG_ERR_INVALID;
     Scratch scratch;
+    if (takes_split_rows(pl, stream_flag)) {
+        int64_t lds = 0, wgs = 0, floats = 0;
+        if (!check_split_rows(B, L, rs, pl, &lds, &wgs, &floats)) return SIG_ERR_INVALID;
+        float *work = nullptr;
+        const size_t bytes = (size_t)floats * sizeof(float);
+        // (a call that cannot have the scratch folds what lies before a stretch again)
+        if (floats > 0 && floats <= kSliceFloats && (fixed ? bytes <= kFixedScratchBytes : Scratch::within_reach(ctx, bytes, st))) {
+            const int rc = get_scratch(ctx, scratch, fixed, bytes, st, &work);
+            if (rc == SIG_ERR_ALLOC) work = nullptr;
+            else if (rc != SIG_OK) return rc;
+        }
+        // level 1 of the rows behind a point that is not a number: as in the kernels that the plan's other fields name
+        const bool sticky = rs.d <= 10 && (pl.variant != SIG_VARIANT_LEVEL_SCAN || pl.row_workgroups > 0);
+        hipError_t e = launch_split_rows(path, out, work, B, L, rs.d, rs.depth, pl.split_rows, sticky, ctx->num_cu, st);
+        return e == hipSuccess ? SIG_OK : SIG_ERR_HIP;
+    }
     if (takes_stream_rows(pl, stream_flag)) {
         int64_t lds = 0, wgs = 0;
         if (!check_stream_rows(B, L, rs, pl, &lds, &wgs)) return SIG_ERR_INVALID;
@@ -1051,6 +1079,10 @@ int sig_plan_validate(int64_t B, int64_t L, int d, int depth, int stream_flag, c
     int rc = check_shape(B, L, d, depth, stream_flag, &rs);
     if (rc != SIG_OK) return rc;
     if (!plan_in_range(*plan)) return SIG_ERR_INVALID;
+    if (takes_split_rows(*plan, stream_flag)) {
+        int64_t lds = 0, wgs = 0, floats = 0;
+        return check_split_rows(B, L, rs, *plan, &lds, &wgs, &floats) ? SIG_OK : SIG_ERR_INVALID;
+    }
     if (takes_stream_rows(*plan, stream_flag)) {
         int64_t lds = 0, wgs = 0;
         return check_stream_rows(B, L, rs, *plan, &lds, &wgs) ? SIG_OK : SIG_ERR_INVALID;
@@ -1079,7 +1111,10 @@ int sig_plan_footprint(int64_t B, int64_t L, int d, int depth, int stream_flag, 
     if (rc != SIG_OK) return rc;
     if (!plan_in_range(*plan)) return SIG_ERR_INVALID;
     int64_t lds = 0, wgs = 0, scratch = 0;
-    if (takes_stream_rows(*plan, stream_flag)) {
+    if (takes_split_rows(*plan, stream_flag)) {
+        if (!check_split_rows(B, L, rs, *plan, &lds, &wgs, &scratch)) return SIG_ERR_INVALID;
+        scratch = scratch <= kSliceFloats ? scratch * (int64_t)sizeof(float) : 0;
+    } else if (takes_stream_rows(*plan, stream_flag)) {
         if (!check_stream_rows(B, L, rs, *plan, &lds, &wgs)) return SIG_ERR_INVALID;
     } else if (plan->variant == SIG_VARIANT_HBM_STREAMING) {
         rc = sig_plan_validate(B, L, d, depth, stream_flag, plan);
@@ -1169,13 +1204,17 @@ int sig_autotune(sig_ctx *ctx, int64_t B, int64_t L, int d, int depth, int strea
     rc = plan_auto(ctx, B, L, stream_flag, rs, &base);
     if (rc != SIG_OK) return rc;
 
-    // candidates: the planner's choice, in stream mode the same with rows written from registers where it has none and without
+    // candidates: the planner's choice, in stream mode the same without rows split across workgroups where it has them, else with rows written from registers where it has none and without
     // where it has, the level-scan family, and for the register kernels every compiled prefix depth with the planner's time cut
     // and with half and twice as many chunks
     sig_plan_t cand[24];
     int n = 0;
     cand[n++] = base;
-    if (stream_flag) {
+    if (takes_split_rows(base, stream_flag)) {
+        sig_plan_t other = base;
+        other.split_rows = 0;
+        cand[n++] = other;
+    } else if (stream_flag) {
         sig_plan_t other = base;
         other.row_workgroups = takes_stream_rows(base, stream_flag) ? 0 : stream_rows_segments(d, depth, B, L, ctx->num_cu);
         if (other.row_workgroups != base.row_workgroups) cand[n++] = other;
@@ -1206,7 +1245,7 @@ int sig_autotune(sig_ctx *ctx, int64_t B, int64_t L, int d, int depth, int strea
             if (pl.chunks < 1 || !finish_on_chip(ki, ctx->num_cu, B, L, stream_flag, pl, rs, &args)) continue;
             bool dup = false;
             for (int i = 0; i < n; ++i)
-                dup = dup || (!takes_stream_rows(cand[i], stream_flag) && cand[i].variant == pl.variant && cand[i].prefix_depth == p && cand[i].chunks == pl.chunks &&
+                dup = dup || (!takes_split_rows(cand[i], stream_flag) && !takes_stream_rows(cand[i], stream_flag) && cand[i].variant == pl.variant && cand[i].prefix_depth == p && cand[i].chunks == pl.chunks &&
                               cand[i].segments == pl.segments && cand[i].threads == pl.threads);
             if (!dup) cand[n++] = pl;
         }
@@ -1268,7 +1307,8 @@ int sig_autotune(sig_ctx *ctx, int64_t B, int64_t L, int d, int depth, int strea
     // second stage: the winner with smaller workgroups.  With a few workgroups per compute unit the number of paths a
     // workgroup takes decides how evenly they spread (measured 5-20 % either way on batches of 2,048 to 8,192 paths, with
     // no rule that the planner could follow), so the measurement decides.
-    if (status == SIG_OK && best >= 0 && cand[best].variant == SIG_VARIANT_ON_CHIP && !takes_stream_rows(cand[best], stream_flag)) {
+    if (status == SIG_OK && best >= 0 && cand[best].variant == SIG_VARIANT_ON_CHIP && !takes_split_rows(cand[best], stream_flag) &&
+        !takes_stream_rows(cand[best], stream_flag)) {
         const OnChipKernelInfo *ki = find_on_chip(d, depth, cand[best].prefix_depth);
         const int sizes[3] = {192, 128, 64};
         for (int si = 0; si < 3 && ki && status == SIG_OK && n < (int)(sizeof(cand) / sizeof(cand[0])); ++si) {

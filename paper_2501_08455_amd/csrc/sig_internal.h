@@ -247,6 +247,16 @@ int stream_rows_segments(int d, int depth, int64_t B, int64_t L, int cus);
 bool stream_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, int64_t *lds_bytes, int64_t *workgroups, int *threads);
 hipError_t launch_stream_rows(const float *path, float *out, int64_t B, int64_t L, int d, int depth, int segs, int cus, hipStream_t st);
 
+// ---------------------------------------------------------------- stream mode, rows split across workgroups (sig_split_rows.h)
+// stretches a path is cut into, 0 if the call stays with the other kernels
+int split_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held_p, bool held_rows);
+// the launch with `segs` stretches a path; false if there is none
+bool split_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, int64_t *lds_bytes, int64_t *workgroups, int64_t *scratch_floats);
+// scratch: those floats, or null (what lies before a stretch is folded again).  sticky: a point that is not a number spoils level 1 of the
+// rows behind it, not of its own row only.
+hipError_t launch_split_rows(const float *path, float *out, float *scratch, int64_t B, int64_t L, int d, int depth, int segs, bool sticky,
+                             int cus, hipStream_t st);
+
 // table of compiled on-chip kernels; terminated by an entry with launch == nullptr
 // The compiled kernels live in several translation units (so that they build in parallel); sub-table i ends
 // with an entry whose launch pointer is null, and on_chip_subtable(i) is null past the last sub-table.  Entries
