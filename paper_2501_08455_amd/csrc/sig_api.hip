@@ -324,11 +324,14 @@ constexpr double kSegmentOccupancyWaves = 2.0;  // segments on a busy chip: this
 constexpr int kMaxLdsJoinSegments = 8;
 constexpr int kFillByChunksMinSteps = 200;    // from this many increments on, never fewer chunks than fill the chip (final mode)
 constexpr int kWideMinPaths = 16;             // on-chip kernels of more than ten channels: from this many paths on,
-constexpr int kWideMostSteps = 128;           // in chunks of at most this many steps
+constexpr int kWideMostSteps = 128;           // in chunks of at most this many steps,
+constexpr int kWideLongSteps = 512;           // ... or this many where eight pieces or more are joined
 }  // namespace tune
 
 // The on-chip kernels of more than ten channels (sig_onchip_table_wide.hip): final mode, from 16 paths on, chunks of at most
-// kWideMostSteps steps (more segments are taken for that; where eight do not do, the call stays with the level-scan family).
+// kWideMostSteps steps (more segments are taken for that, then more chunks), or kWideLongSteps in eight pieces and more: the
+// level-scan family's running sums over the whole path are off by more than a piece of it ((12,3), 2,000 paths of 1,990 points 4,464
+// and 468 us, error 6.1e-7 and 2.7e-7; (11,3) 9,000 of 2,500 23,469 and 1,636; (20,2) 9,000 of 5,000 12,099 and 1,956).
 // Level-scan family against these, us: (12,3) 128 paths of 100 points 35.5 and 7.7, 1,024 of 500 392 and 119, 8,192 of 128
 // 773 and 208, 30,000 of 60 1,472 and 352; (11,2) 128 of 2,000 106 and 17; (20,2) 512 of 130 41 and 8, 8,192 of 250 374 and
 // 106; the other 71 points 1.3-15x.  The bound on the steps keeps the rounding where it was: error against 64 bits 2.3e-7 at
@@ -590,6 +593,16 @@ int plan_without_rows(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag,
                 W = ceil_div(K, C * tune::kWideMostSteps);
                 if (W > tune::kMaxLdsJoinSegments) W = tune::kMaxLdsJoinSegments;
                 while (W > 1 && !join_fits_lds(ki, (int)W, rs)) --W;
+                // where eight segments do not do, on batches that fill the chip without any cut: chunks side by side as far as
+                // the workgroup holds them, then segments (one launch level by level 27,909 paths of 1,027 points of (19,2) 8,020 us,
+                // nine chunks 610)
+                if (ceil_div(K, C * W) > tune::kWideMostSteps && cmax > C) {
+                    C = ceil_div(K, tune::kWideMostSteps);
+                    if (C > cmax) C = cmax;
+                    W = ceil_div(K, C * tune::kWideMostSteps);
+                    if (W > tune::kMaxLdsJoinSegments) W = tune::kMaxLdsJoinSegments;
+                    while (W > 1 && !join_fits_lds(ki, (int)W, rs)) --W;
+                }
             }
             pl->chunks = (int)C;
             pl->segments = (int)W;
@@ -678,7 +691,10 @@ int plan_without_rows(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag,
                 if (c != want.chunks) pl->segments = 1;
                 OnChipArgs args{};
                 if (finish_on_chip(ki, cus, B, L, stream_flag, *pl, rs, &args)) {
-                    if (ki->final_only && args.chunk_steps > tune::kWideMostSteps) return take_level_scan();
+                    if (ki->final_only) {
+                        const bool pieces = args.chunks * args.segments >= tune::kMaxLdsJoinSegments;
+                        if (args.chunk_steps > (pieces ? tune::kWideLongSteps : tune::kWideMostSteps)) return take_level_scan();
+                    }
                     if (prefer_level_scan(*pl)) return take_level_scan();
                     pl->tile_steps = args.tile_steps;
                     return SIG_OK;

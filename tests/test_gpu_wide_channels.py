@@ -46,6 +46,35 @@ def test_against_the_oracle(oracle, d, depth):
         check_rows(oracle, x, out, d, depth, (B, L))
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,depth,B,L,paths", [(12, 3, 300, 1100, 24), (12, 3, 16, 4000, 8), (11, 3, 700, 2500, 8), (20, 2, 14000, 1500, 64), (13, 2, 30000, 1027, 64)])
+def test_long_paths_in_eight_pieces_and_more(oracle, d, depth, B, L, paths):
+    """Beyond 128 steps a piece, or by chunks where the batch alone fills the chip: against the oracle, and no further from it than one
+    launch per level, which summed the whole path in one go (measured 0.2 to 0.75 of its error)."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    rc, pl = binding.sig_plan(None, B, L, d, depth, 0)
+    assert rc == binding.SIG_OK and pl.variant == binding.SIG_VARIANT_ON_CHIP and pl.chunks * pl.segments >= 8
+    print("wide forward, long: %d paths of %d points, (%d,%d)" % (B, L, d, depth), flush=True)
+    x = torch.zeros((B, L, d), device="cuda")
+    x[:, 1:].normal_(0.0, L ** -0.5, generator=torch.Generator(device="cuda").manual_seed(d + L))
+    x = x.cumsum(1)
+    out = torch.full((B, binding.sig_size(d, depth)), float("nan"), device="cuda")
+    assert binding.sig_compute(binding.default_ctx(), x, depth, 0, out) == binding.SIG_OK
+    assert bool(torch.isfinite(out).all())
+    pick = np.unique(np.linspace(0, B - 1, paths).astype(int))
+    idx = torch.from_numpy(pick).cuda()
+    few = x[idx].contiguous()
+    want = oracle.signature(few.cpu().numpy(), depth)
+    level = torch.empty((len(pick), out.shape[1]), device="cuda")
+    plan = binding.make_plan(binding.SIG_VARIANT_LEVEL_SCAN, chunks=1 if B * d ** (depth - 1) > 200000 else 0)
+    assert binding.sig_compute(binding.default_ctx(), few, depth, 0, level, plan=plan) == binding.SIG_OK
+    error = lambda y: np.linalg.norm(y.cpu().numpy() - want) / np.linalg.norm(want)   # noqa: E731
+    print("  rel err %.2e, level by level %.2e" % (error(out[idx]), error(level)))
+    assert error(out[idx]) <= 1e-4 and error(out[idx]) <= 1.1 * error(level)
+
+
 def check_rows(oracle, x, out, d, depth, label):
     B = x.shape[0]
     rows = sorted({0, 1, 7, B // 2, B - 2, B - 1} & set(range(B)))
