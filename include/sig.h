@@ -252,7 +252,9 @@ int sig_combine(sig_ctx *ctx, const float *a, const float *b, int64_t B, int d, 
  * signature itself, as below.
  * Stream mode at depth 2, two to twenty channels: one launch over sums of the rows behind each step (two for a few long paths,
  * with context scratch of a row of d (d + 1) floats for each of up to 32 workgroups a path; where scratch cannot be had a path
- * stays in one workgroup); `out` is not read.  Rows too long for its 32-bit offsets (d (d + 1) L beyond 2^31) are swept as below.
+ * stays in one workgroup); `out` is not read.  Depth 3, eleven and twelve channels: first a sweep over the rows' third level that
+ * leaves rows of d (d + 2) floats in context scratch, then the same over those (without that scratch, or where it would exceed
+ * 8 GiB, the general sweep).  Rows too long for its 32-bit offsets (d (d + 1) L beyond 2^31) are swept as below.
  * The other sweeps start from the signature at the end and undo one increment at a time.  Shapes with a compiled register
  * kernel (see sig_backward_available) whose paths fit its LDS staging take it.  Few long paths and paths too long for that
  * staging are cut into up to 32 time segments that are swept by different workgroups: by Eq. 3 a segment can start from the

@@ -1415,6 +1415,19 @@ int sig_backward(sig_ctx *ctx, const float *path, int64_t B, int64_t L, int d, i
             return er == hipSuccess ? SIG_OK : SIG_ERR_HIP;
         }
     }
+    if (stream_flag && depth == 3) {
+        // (a call that cannot have the scratch takes the general sweep, which needs less)
+        const int64_t floats = stream_gradient3_scratch_floats(d, B, L, ctx->num_cu);
+        const size_t bytes = (size_t)floats * sizeof(float);
+        if (floats > 0 && floats <= kSliceFloats && Scratch::within_reach(ctx, bytes, st)) {
+            rc = scratch.get(ctx, bytes, st, &work);
+            if (rc == SIG_OK) {
+                hipError_t er = launch_stream_gradient3(path, out, grad_out, grad_path, work, B, L, d, ctx->num_cu, st);
+                return er == hipSuccess ? SIG_OK : SIG_ERR_HIP;
+            }
+            if (rc != SIG_ERR_ALLOC) return rc;
+        }
+    }
     const bool fits = backward_available(d, depth) && backward_fits(d, depth, L);
     if (backward_available(d, depth)) {
         // few long paths (or paths too long for the LDS of the uncut sweep): the sweep cut in time across workgroups

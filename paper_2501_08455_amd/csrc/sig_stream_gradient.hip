@@ -1,4 +1,5 @@
-// Gradient of the every-prefix signature with respect to the path at depth 2 (stream mode; two to twenty channels).
+// Gradient of the every-prefix signature with respect to the path at depth 2 (stream mode; two to twenty channels), and at depth 3
+// for eleven and twelve channels (second part).
 //
 // With loss gradients G_j of row j = 1 .. K (levels G1_j and the d x d matrix M_j), the loss as a function of an element
 // inserted after step k is the sum over the rows behind it (file comment of sig_bracket.h, one F per row), so that with
@@ -31,9 +32,11 @@ typedef float vec4f_8 __attribute__((ext_vector_type(4), aligned(8)));
 
 struct Args {
     const float *path;      // [B][L][d]
-    const float *grad_out;  // [B][K][d + d * d]
+    const float *sig;       // depth 3: [B][K][D], level 2 is read
+    const float *grad_out;  // [B][K][D]
+    float *reduced;         // depth 3: [B][K][2 d + d * d], what it leaves for the sweep of depth 2
     float *grad_path;       // [B][L][d]
-    float *totals;          // [B][W][d * d + d]: the sums over a workgroup's rows (W > 1)
+    float *totals;          // [B][W][d * d + d] (depth 3: [d * d * d]): the sums over a workgroup's rows (W > 1)
     int64_t B;
     int32_t L;
     int32_t chunks;         // C: stretches of a path side by side in a workgroup
@@ -52,19 +55,22 @@ constexpr int threads_of(int mode) { return mode == UNCUT ? kWave : 4 * kWave; }
 constexpr int slots_of(int mode, int d) { return threads_of(mode) / kWave * (kWave / d); }
 constexpr int sums_of(int d) { return d * d + d; }   // A, and a slot's share of the sums that settle point 0
 
-// Rows of each slot that a wavefront stages at a time: some 1,600 floats in all, whole 16-byte vectors (a row is of even length)
-constexpr int tile_rows(int d)
+// Rows of each slot that a wavefront stages at a time: some 1,600 floats in all, whole 16-byte vectors
+constexpr int row_floats(int d, bool given) { return (given ? 2 : 1) * d + d * d; }
+constexpr int tile_rows(int d, bool given)
 {
-    const int row = d + d * d, unit = row % 4 == 0 ? 1 : 2;
+    const int row = row_floats(d, given), unit = row % 4 == 0 ? 1 : row % 2 == 0 ? 2 : 4;
     const int fit = 1600 / (kWave / d * row * unit);
     return unit * (fit < 1 ? 1 : fit > 16 / unit ? 16 / unit : fit);
 }
 
 // A wavefront's tile: R rows of each of its slots, as they lie in memory, and the R + 1 points around them
-template <int d>
+// (GIVEN: rows that the kernel of depth 3 left, of d (2 + d) floats)
+template <int d, bool GIVEN>
 struct Tile {
-    static constexpr int D = d + d * d, SLOTS = kWave / d;
-    static constexpr int R = tile_rows(d);
+    static constexpr int D = row_floats(d, GIVEN), SLOTS = kWave / d;
+    static constexpr int MAT = D - d * d;                         // where a row's matrix begins
+    static constexpr int R = tile_rows(d, GIVEN);
     static constexpr int VECS = R * D / 4;                        // vectors of a slot
     static constexpr int NV = (SLOTS * VECS + kWave - 1) / kWave; // ... that a lane brings
     static constexpr int PX = (R + 1) * d;                        // floats of a slot's points
@@ -74,10 +80,8 @@ struct Tile {
     static constexpr int XS = (d + 3) / 4 * 4;
     static constexpr int FLOATS = SLOTS * (STRIDE + (R + 1) * XS);
 };
-template <int d>
-constexpr int tiles_floats(int mode) { return threads_of(mode) / kWave * Tile<d>::FLOATS; }
-template <int d>
-constexpr int lds_floats(int mode) { return tiles_floats<d>(mode) + (mode == UNCUT ? 0 : (slots_of(mode, d) + 1) * sums_of(d)); }
+template <int d, bool GIVEN>
+constexpr int lds_floats(int mode) { return threads_of(mode) / kWave * Tile<d, GIVEN>::FLOATS + (mode == UNCUT ? 0 : (slots_of(mode, d) + 1) * sums_of(d)); }
 
 extern __shared__ __align__(16) float sig_stream_gradient_smem[];
 
@@ -105,10 +109,11 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
-template <int d, int MODE>
+template <int d, int MODE, bool GIVEN>
 __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_eu(2))) void sig_stream_depth2_kernel(Args A)
 {
-    using Tl = Tile<d>;
+    using Tl = Tile<d, GIVEN>;
+    using vec_lds = std::conditional_t<Tl::D % 2 == 0, vec4f_8, vec4f_u>;   // (the last vector of fewer than R rows)
     constexpr int NT = threads_of(MODE), WSLOTS = Tl::SLOTS, M = sums_of(d), D = Tl::D, R = Tl::R, XS = Tl::XS;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int K = A.L - 1;
@@ -122,7 +127,7 @@ __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_e
     const int slot = wave * WSLOTS + wslot;
     const int group = slot / C, chunk = slot - group * C;
     const bool active = wslot < WSLOTS && group < npaths;
-    const float *points = A.path + b0 * A.L * d, *grads = A.grad_out + b0 * K * D;   // (of all its paths: below 2^31 floats)
+    const float *points = A.path + b0 * A.L * d, *grads = (GIVEN ? A.reduced : A.grad_out) + b0 * K * D;   // (of all its paths: below 2^31 floats)
     const float *X = A.path + (b0 + (active ? group : 0)) * A.L * d;
     float *dX = A.grad_path + (b0 + (active ? group : 0)) * A.L * d;
 
@@ -159,7 +164,7 @@ __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_e
 #pragma unroll
         for (int j = 0; j < Tl::NV; ++j) {
             const int i = lane + j * kWave, ws = i / Tl::VECS, at = 4 * (i - ws * Tl::VECS);
-            if (ws < WSLOTS) *reinterpret_cast<vec4f_8 *>(gtile + ws * Tl::STRIDE + (at < last ? at : last)) = gv[j];
+            if (ws < WSLOTS) *reinterpret_cast<vec_lds *>(gtile + ws * Tl::STRIDE + (at < last ? at : last)) = gv[j];
         }
 #pragma unroll
         for (int j = 0; j < Tl::NX; ++j) {
@@ -203,18 +208,18 @@ __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_e
     auto row_of = [&](int j, const float *g, const float *x, auto sum, auto settle) __attribute__((always_inline)) {
         constexpr bool SUM = decltype(sum)::value, SETTLE = decltype(settle)::value;
         float row[d], at[XS], before[XS];
-        read_floats<d>(row, g + d + b * d);
+        read_floats<d>(row, g + Tl::MAT + b * d);
         read_floats<XS>(at, x + XS);
         float h = g[b], below = 0.0f;
-        if constexpr (SUM) start += h;
+        if constexpr (SUM) start += GIVEN ? g[d + b] : h;
         if constexpr (SETTLE) read_floats<XS>(before, x);
 #pragma unroll
         for (int a = 0; a < d; ++a) {
-            const float col = g[d + a * d + b], s = at[a] - x0[a];
+            const float col = g[Tl::MAT + a * d + b], s = at[a] - x0[a];
             m[a] += col - row[a];
-            if constexpr (SUM) start = fmaf(s, row[a], start);
+            if constexpr (SUM && !GIVEN) start = fmaf(s, row[a], start);
             if constexpr (SETTLE) {
-                h = fmaf(s, col, h);
+                if constexpr (!GIVEN) h = fmaf(s, col, h);
                 below = fmaf(at[a] - before[a], m[a], below);
             }
         }
@@ -288,6 +293,277 @@ __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_e
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// Depth 3.  With T_j[abc] = sum_{i >= j} G3_i[abc] and v = v_j,
+//     P_j[ab] = sum_c v[c] (T_j[cab] - T_j[abc]),      Z_j[b] = sum_a v[a] (P_j[ab] - P_j[ba]),
+// the level above adds to the gradient what a problem of depth 2 with the rows
+//     e1_j = H_j + Z_{j+1} / 3 + Z_j / 6,      E2_j = G2_j + sum_u S1_j[u] G3_j[u ab] - P_{j+1}
+// adds in place of its own (moving a functional from step j + 1 to j conjugates by exp(v_{j+1}); the derivative of the exponential
+// brings the rest), with H_j[b] = <G_j, S_j (x) e_b> of all levels and f0_j[b] = <G_j, e_b (x) S_j> (less Z_1 / 3 at j = 1) for point 0.  This kernel
+// leaves the rows [e1, f0, E2]; the one above sweeps them.  T is a plain sum over the rows behind as well, so that paths are cut as there.
+//
+// For eleven and twelve channels, which had the general sweep: (12,3) 46 paths of 71 points 544 -> 60 us, one of 2,000 17,340 -> 154,
+// 1,000 of 100 1,096 -> 644; rounding 1.7e-7 to 3.2e-7 of the gradient's norm where that had 2.9e-7 to 4.1e-6.  Bound by latency,
+// 0.8 us a row in three barriers.  With fewer channels the sweep on signatures is the faster one on batches ((6,3), 2,011 paths
+// of 421 points 374 us and 690; (10,3), 40 of 266 68 and 119).
+//
+// Lanes.  Lane (a, b) of d * d holds m[c] = T[cab] - T[abc]; a workgroup's slots stage their next R rows of G, level 2 of the rows of
+// S (1 / d of the bytes) and their points in LDS.  The sums over a or b of a step go through LDS, R steps at a time.
+template <int d>
+struct Tile3 {
+    static constexpr int Q = d * d, D = d + d * d + d * d * d, MAT = 2 * d + d * d;
+    static constexpr int NT = (2 * Q + kWave - 1) / kWave * kWave;             // two slots
+    static constexpr int SLOTS = NT / Q;
+    static constexpr int R = 2;                                                 // (what LDS holds beside the sums)
+    static constexpr int VECS = (R * D + 3) / 4, NV = (SLOTS * VECS + NT - 1) / NT;
+    static constexpr int NS = (SLOTS * R * Q + NT - 1) / NT;                   // floats of level 2 of S that a lane brings
+    static constexpr int PX = (R + 1) * d, NX = (SLOTS * PX + NT - 1) / NT;
+    static constexpr int XS = (d + 3) / 4 * 4;
+    static constexpr int STRIDE = VECS * 4, SSTRIDE = (R * Q + 3) / 4 * 4, XSTRIDE = (R + 1) * XS;
+    static constexpr int PARK = R * 3 * Q + 2 * Q;
+    static constexpr int M = Q * d;
+    static constexpr int tile_floats = (SLOTS * (STRIDE + SSTRIDE + XSTRIDE + PARK + 2) + 3) / 4 * 4;
+    static constexpr int lds_floats(int mode) { return tile_floats + (mode == UNCUT ? 0 : (SLOTS + 1) * M); }
+};
+
+template <int d, int MODE>
+__global__ __launch_bounds__((Tile3<d>::NT)) __attribute__((amdgpu_waves_per_eu(2))) void sig_stream_depth3_kernel(Args A)
+{
+    using Tl = Tile3<d>;
+    constexpr int NT = Tl::NT, SLOTS = Tl::SLOTS, Q = Tl::Q, M = Tl::M, D = Tl::D, R = Tl::R, XS = Tl::XS;
+    const int tid = threadIdx.x;
+    const int K = A.L - 1;
+    const int C = MODE == UNCUT ? 1 : A.chunks, W = MODE == UNCUT ? 1 : A.segs, T = MODE == UNCUT ? K : A.steps;
+    const int64_t b0 = W > 1 ? blockIdx.x / W : (int64_t)blockIdx.x * A.groups;
+    const int seg = W > 1 ? (int)(blockIdx.x - b0 * W) : 0;
+    const int k0 = W > 1 ? seg * A.rows : 0;
+    const int k1 = W > 1 && K - k0 > A.rows ? k0 + A.rows : K;
+    const int npaths = W > 1 ? 1 : A.B - b0 < A.groups ? (int)(A.B - b0) : A.groups;
+    const int slot = tid / Q, ab = tid - slot * Q, a = ab / d, b = ab - a * d;
+    const int group = slot / C, chunk = slot - group * C;
+    const bool active = slot < SLOTS && group < npaths;
+    const int sl = active ? slot : 0;
+    const float *points = A.path + b0 * A.L * d, *grads = A.grad_out + b0 * K * D, *sigs = A.sig + b0 * K * D;
+    const float *X = points + (active ? group : 0) * A.L * d;
+    float *rows = A.reduced + b0 * K * Tl::MAT;
+
+    float *gtile = sig_stream_gradient_smem, *stile = gtile + SLOTS * Tl::STRIDE, *xtile = stile + SLOTS * Tl::SSTRIDE;
+    float *parks = xtile + SLOTS * Tl::XSTRIDE;
+    int *tops = reinterpret_cast<int *>(parks + SLOTS * Tl::PARK);   // [SLOTS]: last row of the slot's stretch; then the first one
+    float *sums = sig_stream_gradient_smem + Tl::tile_floats, *base = sums + SLOTS * M;
+    float *park = parks + sl * Tl::PARK;
+    const int have = (K < R ? K : R) * D;              // floats of a slot's rows
+
+    auto low_of = [&](int top, int t0) __attribute__((always_inline)) { return top - t0 > R ? top - t0 - R + 1 : 1; };
+    auto row_of = [&](int s, int low) __attribute__((always_inline)) { return s / C < npaths ? s / C * K + low - 1 : 0; };
+
+    vec4f_u gv[Tl::NV];
+    float sv[Tl::NS], xv[Tl::NX];
+    auto fetch = [&](int t0, auto level2) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < Tl::NV; ++j) {
+            const int i = tid + j * NT, s = i / Tl::VECS, at = 4 * (i - s * Tl::VECS);
+            if (s < SLOTS) {
+                const float *src = grads + row_of(s, low_of(tops[s], t0)) * D;
+                if (at + 4 <= have) gv[j] = *reinterpret_cast<const vec4f_u *>(src + at);
+                else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) gv[j][e] = src[at + e < have ? at + e : 0];
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < Tl::NX; ++j) {
+            const int i = tid + j * NT, s = i / Tl::PX, at = i - s * Tl::PX;
+            if (s < SLOTS) xv[j] = points[(row_of(s, low_of(tops[s], t0)) + (s / C < npaths ? s / C : 0)) * d + (at < have / D * d + d ? at : 0)];
+        }
+        if constexpr (decltype(level2)::value) {
+#pragma unroll
+            for (int j = 0; j < Tl::NS; ++j) {
+                const int i = tid + j * NT, s = i / (R * Q), x = i - s * (R * Q), r = x / Q;
+                if (s < SLOTS) sv[j] = sigs[(row_of(s, low_of(tops[s], t0)) + (r < K ? r : 0)) * D + d + (x - r * Q)];
+            }
+        }
+    };
+    auto put = [&](auto level2) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < Tl::NV; ++j) {
+            const int i = tid + j * NT, s = i / Tl::VECS, at = 4 * (i - s * Tl::VECS);
+            if (s < SLOTS) *reinterpret_cast<float4 *>(gtile + s * Tl::STRIDE + at) = make_float4(gv[j][0], gv[j][1], gv[j][2], gv[j][3]);
+        }
+#pragma unroll
+        for (int j = 0; j < Tl::NX; ++j) {
+            const int i = tid + j * NT, s = i / Tl::PX, x = i - s * Tl::PX;
+            if (s < SLOTS) xtile[(s * (R + 1) + x / d) * XS + x % d] = xv[j];
+        }
+        if constexpr (decltype(level2)::value) {
+#pragma unroll
+            for (int j = 0; j < Tl::NS; ++j) {
+                const int i = tid + j * NT, s = i / (R * Q), x = i - s * (R * Q);
+                if (s < SLOTS) stile[s * Tl::SSTRIDE + x] = sv[j];
+            }
+        }
+    };
+
+    float m[d], x0[d];
+#pragma unroll
+    for (int c = 0; c < d; ++c) {
+        m[c] = 0.0f;
+        x0[c] = X[c];
+    }
+    float above = 0.0f, above_a = 0.0f, above_b = 0.0f;   // P_{j+1}[ab], and times v_{j+1}[a], v_{j+1}[b]
+    auto first_of = [&](int hi, int c) __attribute__((always_inline)) {
+        const int64_t below = (int64_t)hi - (int64_t)(C - c) * T;
+        return below > 0 ? (int)below + 1 : 1;
+    };
+    // the rows of a block, from the last one of every slot down: their sums, or (SETTLE) what they leave for depth 2 as well
+    auto walk = [&](int hi, auto settle) __attribute__((always_inline)) {
+        constexpr bool SETTLE = decltype(settle)::value;
+        __syncthreads();
+        if (tid < SLOTS) {
+            const int c = tid - tid / C * C;
+            const int64_t top = (int64_t)hi - (int64_t)(C - 1 - c) * T;
+            tops[tid] = top < K ? (int)top : K;
+            tops[SLOTS + tid] = first_of(hi, c);
+        }
+        __syncthreads();
+        const int top = tops[sl], least = tops[SLOTS + sl];
+        fetch(0, settle);
+        for (int t0 = 0; t0 < T; t0 += R) {
+            __syncthreads();
+            put(settle);
+            __syncthreads();
+            if (T - t0 > R) fetch(t0 + R, settle);
+            const int low = low_of(top, t0);
+#pragma unroll 1
+            for (int r = R - 1; r >= 0; --r) {
+                const int j = low + r;
+                if (!active || j < least || j > top - t0) continue;
+                const float *g = gtile + slot * Tl::STRIDE + r * D, *g3 = g + d + Q;
+                const float *x = xtile + slot * Tl::XSTRIDE + r * XS;
+                float row[d];
+                read_floats<d>(row, g3 + ab * d);
+                if constexpr (!SETTLE) {
+#pragma unroll
+                    for (int c = 0; c < d; ++c) m[c] += g3[c * Q + ab] - row[c];
+                } else {
+                    const float *s2 = stile + slot * Tl::SSTRIDE + r * Q;
+                    float at[XS], before[XS];
+                    read_floats<XS>(at, x + XS);
+                    read_floats<XS>(before, x);
+                    const float g2 = g[d + ab], va = x[XS + a] - x[a], vb = x[XS + b] - x[b];
+                    float e2 = g2 - above, into_b = (x[XS + a] - X[a]) * g2, from_a = (x[XS + b] - X[b]) * g2, P = 0.0f;
+#pragma unroll
+                    for (int c = 0; c < d; ++c) {
+                        const float col = g3[c * Q + ab];
+                        e2 = fmaf(at[c] - x0[c], col, e2);
+                        into_b = fmaf(s2[c * d + a], col, into_b);
+                        from_a = fmaf(s2[b * d + c], row[c], from_a);
+                        m[c] += col - row[c];
+                        P = fmaf(at[c] - before[c], m[c], P);
+                    }
+                    const float pa = va * P, pb = vb * P;
+                    park[(r * 3 + 0) * Q + ab] = into_b + fmaf(above_a, 1.0f / 3.0f, pa * (1.0f / 6.0f));
+                    park[(r * 3 + 1) * Q + ab] = -fmaf(above_b, 1.0f / 3.0f, pb * (1.0f / 6.0f));
+                    park[(r * 3 + 2) * Q + ab] = from_a;
+                    if (j == 1) {
+                        park[R * 3 * Q + ab] = pa;
+                        park[R * 3 * Q + Q + ab] = pb;
+                    }
+                    rows[(group * K + j - 1) * Tl::MAT + 2 * d + ab] = e2;
+                    above = P;
+                    above_a = pa;
+                    above_b = pb;
+                }
+            }
+            if constexpr (SETTLE) {
+                __syncthreads();
+                for (int i = tid; i < npaths * C * R * 2 * d; i += NT) {
+                    const int s = i / (R * 2 * d), x = i - s * (R * 2 * d), r = x / (2 * d), o = x - r * (2 * d);
+                    const int end = tops[s], j = low_of(end, t0) + r;
+                    if (j < tops[SLOTS + s] || j > end - t0) continue;
+                    const float *p = parks + s * Tl::PARK + r * 3 * Q, *z = parks + s * Tl::PARK + R * 3 * Q;
+                    const int e = o < d ? o : o - d;
+                    float sum = gtile[s * Tl::STRIDE + r * D + e];
+                    if (o < d) {
+#pragma unroll
+                        for (int c = 0; c < d; ++c) sum += p[c * d + e] + p[Q + e * d + c];
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < d; ++c) sum += p[2 * Q + e * d + c];
+                        if (j == 1) {
+                            float z1 = 0.0f;
+#pragma unroll
+                            for (int c = 0; c < d; ++c) z1 += z[c * d + e] - z[Q + e * d + c];
+                            sum = fmaf(z1, -1.0f / 3.0f, sum);
+                        }
+                    }
+                    rows[(s / C * K + j - 1) * Tl::MAT + o] = sum;
+                }
+            }
+        }
+    };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+
+    if constexpr (MODE == UNCUT) {
+        walk(K, yes);
+    } else {
+        for (int e = tid; e < M; e += NT) {
+            float sum = 0.0f;
+            if constexpr (MODE == CUT)
+                for (int w = W - 1; w > seg; --w) sum += A.totals[(b0 * W + w) * M + e];
+            base[e] = sum;
+        }
+        const int span = C * T < k1 - k0 ? C * T : k1 - k0, blocks = (k1 - k0 + span - 1) / span;
+        for (int blk = blocks - 1; blk >= 0; --blk) {
+            const int hi = k0 + blk * span + C * T;
+#pragma unroll
+            for (int c = 0; c < d; ++c) m[c] = 0.0f;
+            walk(hi, no);
+            __syncthreads();
+            if (active) {
+#pragma unroll
+                for (int c = 0; c < d; ++c) sums[slot * M + c * Q + ab] = m[c];
+            }
+            __syncthreads();
+            for (int i = tid; i < npaths * M; i += NT) {
+                const int g = i / M, e = i - g * M;
+                float *s = sums + g * C * M + e;
+                float sum = npaths == 1 ? base[e] : 0.0f;
+#pragma unroll 4
+                for (int c = C - 1; c >= 0; --c) {
+                    const float own = s[c * M];
+                    s[c * M] = sum;
+                    sum += own;
+                }
+                if (npaths == 1) base[e] = sum;
+            }
+            __syncthreads();
+            if constexpr (MODE == CUT) {
+                const int top = tops[sl];
+                above = above_a = above_b = 0.0f;
+                if (active) {
+#pragma unroll
+                    for (int c = 0; c < d; ++c) m[c] = sums[slot * M + c * Q + ab];
+                    if (top < K && top > 0) {
+                        const float *x = X + (int64_t)top * d;
+#pragma unroll
+                        for (int c = 0; c < d; ++c) above = fmaf(x[d + c] - x[c], m[c], above);
+                        above_a = (x[d + a] - x[a]) * above;
+                        above_b = (x[d + b] - x[b]) * above;
+                    }
+                }
+                walk(hi, yes);
+            }
+        }
+        if constexpr (MODE == TOTALS) {
+            __syncthreads();
+            for (int e = tid; e < M; e += NT) A.totals[(b0 * W + seg) * M + e] = base[e];
+        }
+    }
+}
+
 struct Cut {
     int mode;               // UNCUT or CUT
     int chunks, segs, groups, steps, rows;
@@ -295,7 +571,7 @@ struct Cut {
     int64_t grid;
 };
 
-template <int d>
+template <int d, bool GIVEN>
 hipError_t launch(const Args &A0, const Cut &c, hipStream_t st)
 {
     Args A = A0;
@@ -306,29 +582,29 @@ hipError_t launch(const Args &A0, const Cut &c, hipStream_t st)
     A.rows = c.rows;
     const dim3 grid((unsigned)c.grid);
     if (c.mode == UNCUT) {
-        constexpr size_t lds = (size_t)lds_floats<d>(UNCUT) * sizeof(float);
+        constexpr size_t lds = (size_t)lds_floats<d, GIVEN>(UNCUT) * sizeof(float);
         static_assert(lds <= (size_t)kMaxLdsBytes, "a wavefront's tile fits its workgroup's LDS");
-        hipLaunchKernelGGL((sig_stream_depth2_kernel<d, UNCUT>), grid, dim3(threads_of(UNCUT)), lds, st, A);
+        hipLaunchKernelGGL((sig_stream_depth2_kernel<d, UNCUT, GIVEN>), grid, dim3(threads_of(UNCUT)), lds, st, A);
         return hipGetLastError();
     }
-    constexpr size_t lds = (size_t)lds_floats<d>(CUT) * sizeof(float);
+    constexpr size_t lds = (size_t)lds_floats<d, GIVEN>(CUT) * sizeof(float);
     static_assert(lds <= (size_t)kMaxLdsBytes, "the tiles and sums of a workgroup's slots fit its LDS");
     if (c.segs > 1) {
-        hipLaunchKernelGGL((sig_stream_depth2_kernel<d, TOTALS>), grid, dim3(threads_of(TOTALS)), lds, st, A);
+        hipLaunchKernelGGL((sig_stream_depth2_kernel<d, TOTALS, GIVEN>), grid, dim3(threads_of(TOTALS)), lds, st, A);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((sig_stream_depth2_kernel<d, CUT>), grid, dim3(threads_of(CUT)), lds, st, A);
+    hipLaunchKernelGGL((sig_stream_depth2_kernel<d, CUT, GIVEN>), grid, dim3(threads_of(CUT)), lds, st, A);
     return hipGetLastError();
 }
 
 // UNCUT (W == 0) or CUT with W workgroups a path and at most `most_chunks` stretches side by side; false where a launch would hold 2^32 threads or an offset 2^31 floats.
-bool cut(int d, int64_t B, int64_t L, int64_t W, int most_chunks, Cut *c)
+bool cut(int d, bool given, int64_t B, int64_t L, int64_t W, int most_chunks, Cut *c)
 {
-    const int64_t K = L - 1, D = d + d * d, slots = slots_of(W > 0 ? CUT : UNCUT, d);
+    const int64_t K = L - 1, D = row_floats(d, given), slots = slots_of(W > 0 ? CUT : UNCUT, d);
     if (L > INT32_MAX / D) return false;
     c->chunks = c->segs = 1;
-    c->tile = tile_rows(d);
+    c->tile = tile_rows(d, given);
     c->steps = c->rows = (int)K;
     if (W == 0) {
         c->mode = UNCUT;
@@ -386,13 +662,13 @@ double microseconds(int d, int64_t B, int64_t L, int cus, const Cut &c)
     return (us > least ? us : least) + (c.segs > 1 ? 3.5 + 0.19 * c.segs : 0.0);
 }
 
-bool choose(int d, int64_t B, int64_t L, int cus, bool scratch, Cut *best)
+bool choose(int d, bool given, int64_t B, int64_t L, int cus, bool scratch, Cut *best)
 {
     bool found = false;
     double least = 0.0;
     auto consider = [&](int64_t W, int most_chunks) {
         Cut c;
-        if (!cut(d, B, L, W, most_chunks, &c)) return;
+        if (!cut(d, given, B, L, W, most_chunks, &c)) return;
         const double us = microseconds(d, B, L, cus, c);
         if (found && us >= least) return;
         found = true;
@@ -409,13 +685,84 @@ bool choose(int d, int64_t B, int64_t L, int cus, bool scratch, Cut *best)
     return found;
 }
 
+// The same for depth 3: UNCUT (W == 0), or CUT with W workgroups a path
+template <int d>
+hipError_t launch3(const Args &A0, const Cut &c, hipStream_t st)
+{
+    using Tl = Tile3<d>;
+    Args A = A0;
+    A.chunks = c.chunks;
+    A.segs = c.segs;
+    A.groups = c.groups;
+    A.steps = c.steps;
+    A.rows = c.rows;
+    const dim3 grid((unsigned)c.grid);
+    constexpr size_t lds = (size_t)Tl::lds_floats(CUT) * sizeof(float), uncut = (size_t)Tl::lds_floats(UNCUT) * sizeof(float);
+    static_assert(lds <= (size_t)kMaxLdsBytes, "the tiles, parked sums and sums of a workgroup's slots fit its LDS");
+    if (c.mode == UNCUT) {
+        hipLaunchKernelGGL((sig_stream_depth3_kernel<d, UNCUT>), grid, dim3(Tl::NT), uncut, st, A);
+        return hipGetLastError();
+    }
+    if (c.segs > 1) {
+        hipLaunchKernelGGL((sig_stream_depth3_kernel<d, TOTALS>), grid, dim3(Tl::NT), lds, st, A);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((sig_stream_depth3_kernel<d, CUT>), grid, dim3(Tl::NT), lds, st, A);
+    return hipGetLastError();
+}
+
+int threads3(int d) { return d == 11 ? Tile3<11>::NT : Tile3<12>::NT; }
+
+bool cut3(int d, int64_t B, int64_t L, int64_t W, Cut *c)
+{
+    const int64_t K = L - 1, D = d + d * d + (int64_t)d * d * d, threads = threads3(d), slots = threads / (d * d);
+    if (slots * L > INT32_MAX / D) return false;          // (offsets in the rows of a workgroup's paths)
+    c->mode = W == 0 ? UNCUT : CUT;
+    c->chunks = c->segs = 1;
+    c->steps = c->rows = (int)K;
+    c->groups = (int)slots;
+    if (W == 0) {
+        c->grid = (B + slots - 1) / slots;
+        return c->grid * threads < (int64_t)1 << 32;
+    }
+    int64_t rows = (K + W - 1) / W;
+    const int64_t C = rows < slots ? rows : slots;
+    int64_t T = (rows + C - 1) / C;
+    int64_t most = kBlockBytes / (C * D * (int64_t)sizeof(float));
+    if (most < 8) most = 8;
+    const int64_t blocks = (T + most - 1) / most;
+    T = (T + blocks - 1) / blocks;
+    if (W > 1) {
+        rows = (rows + C * T - 1) / (C * T) * (C * T);
+        W = (K + rows - 1) / rows;
+    }
+    c->chunks = (int)C;
+    c->steps = (int)T;
+    c->rows = (int)rows;
+    c->segs = (int)W;
+    c->groups = W > 1 || C * T < K ? 1 : (int)(slots / C);
+    c->grid = W > 1 ? B * W : (B + c->groups - 1) / c->groups;
+    return c->grid * threads < (int64_t)1 << 32;
+}
+
+// Workgroups of a path: as many as give every unit one, four rows a workgroup at least ((12,3), 46 paths of 71 points: one 107 us, four 60,
+// sixteen 94; one of 2,000 points: one 2,537, 32 of them 154).  Whole batches of tens of thousands of paths are not cut.
+bool choose3(int d, int64_t B, int64_t L, int cus, Cut *c)
+{
+    if (B >= 16 * (int64_t)cus * (threads3(d) / (d * d))) return cut3(d, B, L, 0, c);
+    int64_t W = 1;
+    while (W < 32 && B * W * 2 <= cus && (L - 1) / (2 * W) >= 4) W *= 2;
+    return cut3(d, B, L, W, c);
+}
+
 }  // namespace stream_gradient
 
 bool stream_gradient_geometry(int d, int64_t B, int64_t L, int cus, bool scratch, int64_t *scratch_floats, int64_t *grid, int64_t *segs,
                               int64_t *groups, int64_t *chunks, int64_t *steps, int64_t *rows)
 {
     stream_gradient::Cut c;
-    if (d < 2 || d > stream_gradient::kMostChannels || B <= 0 || L < 2 || !stream_gradient::choose(d, B, L, cus, scratch, &c)) return false;
+    if (d < 2 || d > stream_gradient::kMostChannels || B <= 0 || L < 2 || !stream_gradient::choose(d, false, B, L, cus, scratch, &c)) return false;
     *scratch_floats = c.segs > 1 ? B * c.segs * stream_gradient::sums_of(d) : 0;
     *grid = c.grid;
     *segs = c.segs;
@@ -429,8 +776,39 @@ bool stream_gradient_geometry(int d, int64_t B, int64_t L, int cus, bool scratch
 int64_t stream_gradient_scratch_floats(int d, int64_t B, int64_t L, int cus)
 {
     stream_gradient::Cut c;
-    if (d < 2 || d > stream_gradient::kMostChannels || !stream_gradient::choose(d, B, L, cus, true, &c)) return -1;
+    if (d < 2 || d > stream_gradient::kMostChannels || !stream_gradient::choose(d, false, B, L, cus, true, &c)) return -1;
     return c.segs > 1 ? B * c.segs * stream_gradient::sums_of(d) : 0;
+}
+
+int64_t stream_gradient3_scratch_floats(int d, int64_t B, int64_t L, int cus)
+{
+    using namespace stream_gradient;
+    Cut c3, c2;
+    if (d < 11 || d > 12 || B < 1 || L < 2 || !choose3(d, B, L, cus, &c3) || !choose(d, true, B, L, cus, true, &c2)) return -1;
+    const int64_t D = row_floats(d, true), rows = B * (L - 1);
+    if (rows > INT64_MAX / 16 / D) return -1;
+    const int64_t sums3 = c3.segs > 1 ? B * c3.segs * d * d * d : 0, sums2 = c2.segs > 1 ? B * c2.segs * sums_of(d) : 0;
+    return (rows * D + 3) / 4 * 4 + (sums3 > sums2 ? sums3 : sums2);
+}
+
+hipError_t launch_stream_gradient3(const float *path, const float *sig, const float *grad_out, float *grad_path, float *scratch, int64_t B,
+                                   int64_t L, int d, int cus, hipStream_t st)
+{
+    using namespace stream_gradient;
+    Cut c3, c2;
+    if (!scratch || d < 11 || d > 12 || B < 1 || L < 2 || !choose3(d, B, L, cus, &c3) || !choose(d, true, B, L, cus, true, &c2)) return hipErrorInvalidValue;
+    Args A{};
+    A.path = path;
+    A.sig = sig;
+    A.grad_out = grad_out;
+    A.grad_path = grad_path;
+    A.reduced = scratch;
+    A.totals = scratch + (B * (L - 1) * row_floats(d, true) + 3) / 4 * 4;
+    A.B = B;
+    A.L = (int32_t)L;
+    const hipError_t e = d == 11 ? launch3<11>(A, c3, st) : launch3<12>(A, c3, st);
+    if (e != hipSuccess) return e;
+    return d == 11 ? launch<11, true>(A, c2, st) : launch<12, true>(A, c2, st);
 }
 
 hipError_t launch_stream_gradient(const float *path, const float *grad_out, float *grad_path, float *scratch, int64_t B, int64_t L,
@@ -438,7 +816,7 @@ hipError_t launch_stream_gradient(const float *path, const float *grad_out, floa
 {
     using namespace stream_gradient;
     Cut c;
-    if (B <= 0 || L < 2 || !choose(d, B, L, cus, scratch != nullptr, &c)) return hipErrorInvalidValue;
+    if (B <= 0 || L < 2 || !choose(d, false, B, L, cus, scratch != nullptr, &c)) return hipErrorInvalidValue;
     Args A{};
     A.path = path;
     A.grad_out = grad_out;
@@ -447,7 +825,7 @@ hipError_t launch_stream_gradient(const float *path, const float *grad_out, floa
     A.B = B;
     A.L = (int32_t)L;
     switch (d) {
-#define SIG_STREAM_GRADIENT(d_) case d_: return launch<d_>(A, c, st);
+#define SIG_STREAM_GRADIENT(d_) case d_: return launch<d_, false>(A, c, st);
     SIG_STREAM_GRADIENT(2) SIG_STREAM_GRADIENT(3) SIG_STREAM_GRADIENT(4) SIG_STREAM_GRADIENT(5) SIG_STREAM_GRADIENT(6)
     SIG_STREAM_GRADIENT(7) SIG_STREAM_GRADIENT(8) SIG_STREAM_GRADIENT(9) SIG_STREAM_GRADIENT(10) SIG_STREAM_GRADIENT(11)
     SIG_STREAM_GRADIENT(12) SIG_STREAM_GRADIENT(13) SIG_STREAM_GRADIENT(14) SIG_STREAM_GRADIENT(15) SIG_STREAM_GRADIENT(16)

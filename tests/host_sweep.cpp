@@ -14,6 +14,7 @@ bool bracket_depth2_geometry(int d, int64_t B, int64_t L, int cus, int64_t *grid
                              int64_t *lds_bytes);
 bool stream_gradient_geometry(int d, int64_t B, int64_t L, int cus, bool scratch, int64_t *scratch_floats, int64_t *grid, int64_t *segs,
                               int64_t *groups, int64_t *chunks, int64_t *steps, int64_t *rows);
+int64_t stream_gradient3_scratch_floats(int d, int64_t B, int64_t L, int cus);
 }
 
 static uint64_t state = 0x9E3779B97F4A7C15ull;
@@ -132,6 +133,10 @@ int main()
         EXPECT(floats == (segs > 1 ? B * segs * D : 0) && (scratch || segs == 1) && segs <= 32, "scratch: d=%d B=%lld L=%lld", d, (long long)B, (long long)L);
         if (segs > 1) EXPECT(grid == B * segs && groups == 1 && rows % (chunks * steps) == 0 && segs * rows >= K && (segs - 1) * rows < K, "d=%d B=%lld L=%lld: %lld x %lld rows", d, (long long)B, (long long)L, (long long)segs, (long long)rows);
         else EXPECT(grid * groups >= B && (grid - 1) * groups < B && (groups == 1 || chunks * steps >= K), "d=%d B=%lld L=%lld: %lld paths", d, (long long)B, (long long)L, (long long)groups);
+        if (d == 11 || d == 12) {
+            const int64_t need = sig::stream_gradient3_scratch_floats(d, B, L, 256);
+            EXPECT(need >= B * K * d * (d + 2) || (need == -1 && (L * D * d * 2 > INT32_MAX || B > (int64_t)1 << 24)), "depth 3: d=%d B=%lld L=%lld scratch %lld", d, (long long)B, (long long)L, (long long)need);
+        }
         EXPECT(groups * chunks <= 4 * (64 / d), "slots: d=%d B=%lld L=%lld", d, (long long)B, (long long)L);
         ++checked;
     }

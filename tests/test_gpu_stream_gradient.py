@@ -1,4 +1,4 @@
-"""The every-prefix gradient at depth 2 (csrc/sig_stream_gradient.hip) at the edges of its launches, against the fp64 oracle with
+"""The every-prefix gradient at depth 2 and, for 11 and 12 channels, 3 (csrc/sig_stream_gradient.hip) at the edges of its launches, against the fp64 oracle with
 the gates of test_gpu_backward.py: fewer rows than a tile, ragged last tiles, stretches, blocks and workgroups, whole paths side by
 side with a ragged last wavefront, every channel count; and without scratch, as a captured call may have to run."""
 import numpy as np
@@ -29,6 +29,32 @@ def test_whole_paths_side_by_side(gpu, oracle, d, B, L):
     x = workloads.brownian_paths(B, L, d, seed=9700 + d + L)
     say("every-prefix gradient, depth 2, uncut: %s" % ((d, B, L),))
     sampled_backward(gpu, oracle, x, 2, True, [0, 1, B // 2, B - 2, B - 1], seed=d + L)
+
+
+# depth 3: fewer rows than a tile, odd numbers of them, several paths in a workgroup, blocks, workgroups a path (few paths), uncut
+@pytest.mark.parametrize("d,B,L", [(11, 1, 2), (12, 3, 2), (11, 2, 3), (12, 5, 4), (11, 300, 4), (12, 46, 71), (11, 9, 96), (12, 1, 300), (11, 260, 60),
+                                   (12, 270, 41), (11, 8200, 3), (12, 8195, 4)])
+def test_depth_three(gpu, oracle, d, B, L):
+    x = workloads.brownian_paths(B, L, d, seed=9750 + d + L)
+    say("every-prefix gradient, depth 3: %s" % ((d, B, L),))
+    sampled_backward(gpu, oracle, x, 3, True, sorted({0, B // 2, B - 1}), seed=d + L)
+
+
+@pytest.mark.parametrize("d,L", [(11, 121), (12, 121), (12, 700)])
+def test_errors_at_depth_three_stay_at_the_rounding_of_float32(gpu, oracle, d, L):
+    """As below: u sqrt(K) of the norm, measured 1.6e-7 to 2.4e-7."""
+    import torch
+    rng = np.random.default_rng(9850 + d)
+    x = (rng.normal(size=(3, L, d)) * L ** -0.5).cumsum(1).astype(np.float32)
+    path = torch.from_numpy(x).cuda()
+    out = gpu.signature(path, 3, stream=True)
+    g = torch.from_numpy(rng.normal(size=tuple(out.shape)).astype(np.float32)).cuda()
+    gx = torch.full_like(path, float("nan"))
+    assert gpu.sig_backward(gpu.default_ctx(), path, 3, 1, out, g, gx) == gpu.SIG_OK
+    want = oracle.signature_backward(x, 3, g.cpu().numpy(), stream=True)
+    err = np.linalg.norm(gx.cpu().numpy() - want) / np.linalg.norm(want)
+    say("  d = %d, L = %d: rel err %.2e" % (d, L, err))
+    assert err <= 2.0 ** -24 * (L - 1) ** 0.5
 
 
 @pytest.mark.parametrize("d", range(2, 21))
@@ -72,6 +98,36 @@ def test_a_capture_that_cannot_grow_scratch_keeps_a_path_in_one_workgroup(gpu, o
         assert launches(gpu, lambda: call(fresh)) == 1
         assert call(fresh) == gpu.SIG_OK            # the scratch grows here
         assert launches(gpu, lambda: call(fresh)) == 2
+    finally:
+        torch.cuda.synchronize()
+        gpu.sig_destroy(fresh)
+
+
+def test_depth_three_without_enough_scratch_takes_the_general_sweep(gpu, oracle):
+    """A capture on a context whose scratch holds what the general sweep needs, but not the reduced rows."""
+    import torch
+    x = workloads.brownian_paths(2, 40, 12, seed=9910)
+    xt = torch.from_numpy(x).cuda()
+    out = gpu.signature(xt, 3, stream=True)
+    g = torch.from_numpy(np.random.default_rng(6).normal(size=tuple(out.shape)).astype(np.float32)).cuda()
+    want = oracle.signature_backward(x, 3, g.cpu().numpy(), stream=True)
+    fresh, gx = gpu.sig_create(), torch.empty_like(xt)
+    call = lambda: gpu.sig_backward(fresh, xt, 3, 1, out, g, gx)   # noqa: E731
+    try:
+        small = torch.from_numpy(workloads.brownian_paths(8, 14, 13, seed=3)).cuda()     # the general sweep of (13,3): 8 x 13 x 13 floats and more
+        rows = gpu.signature(small, 3, stream=True)
+        assert gpu.sig_backward(fresh, small, 3, 1, rows, torch.ones_like(rows), torch.empty_like(small)) == gpu.SIG_OK
+        general = launches(gpu, call)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            assert call() == gpu.SIG_OK
+        for _ in range(3):
+            gx.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.linalg.norm(gx.cpu().numpy() - want) <= 1e-5 * np.linalg.norm(want)
+        assert call() == gpu.SIG_OK                 # the scratch grows here
+        assert launches(gpu, call) != general
     finally:
         torch.cuda.synchronize()
         gpu.sig_destroy(fresh)
