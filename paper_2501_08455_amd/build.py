@@ -21,7 +21,7 @@ RESOURCES = os.path.join(OBJ, "kernel_resources.json")
 
 SOURCES = ["sig_api.hip", "sig_streaming.hip", "sig_combine.hip", "sig_onchip_table.hip", "sig_onchip_table_depth2.hip",
            "sig_onchip_table_depth3.hip", "sig_onchip_table_depth4.hip", "sig_onchip_table_depth56.hip", "sig_onchip_table_odd.hip", "sig_onchip_table_wide.hip",
-           "sig_stream_rows.hip", "sig_split_rows.hip",
+           "sig_stream_rows.hip", "sig_split_rows.hip", "sig_depth2_rows.hip",
            "sig_backward.hip", "sig_backward_segments.hip", "sig_backward_general.hip", "sig_bracket.hip", "sig_stream_gradient.hip", "sig_levelscan.hip", "sig_levelscan_rows.hip", "sig_probe.hip"]
 
 # packed FP32 instructions are switched off for every device translation unit

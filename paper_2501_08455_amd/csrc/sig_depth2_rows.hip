@@ -1,0 +1,442 @@
+// Every-prefix signature at depth 2 (stream mode; two to twenty channels).
+//
+// With S1_k = X_k - X_0 the second level is a plain sum over the steps,
+//     S2_{k+1}[ab] = S2_k[ab] + (S1_k[a] + v[a] / 2) v[b],     v = X_{k+1} - X_k,
+// so that a path can be cut anywhere and the parts need nothing of each other but a sum of d * d floats.
+//
+// Lanes.  Lane a of d holds row a of S2; a wavefront keeps 64 / d slots and stages R rows of each in LDS, as they lie in memory, which
+// then go out in runs of R d (d + 1) floats.  Whole paths side by side (UNCUT), or stretches of a path side by side in a workgroup
+// (CUT): each slot sums its steps, a scan in LDS adds what lies before, and the rows are written on a second walk; reading the path
+// twice costs next to nothing beside its rows.  Few paths also span W workgroups, each of which sums all that lies before its own
+// rows; no workgroup waits for another.
+//
+// Bound by the stores where the batch fills the chip (3.6 MB a us whole, 3.0 cut: the streams of a cut path lie further apart),
+// else by one wave's steps.  Tiles: 6,400 floats a wavefront whole (longer runs; six wavefronts a unit hold the rows
+// of the others' stores), 1,600 cut (sixteen wavefronts, whose scans overlap).  Before and now, us: (20,2) 1,177 paths of 1,386 points
+// 1,315 and 974, (2,2) 20,000 of 500 180 and 117, (12,2) 1,024 of 100 26.8 and 20.8.
+//
+// Rounding: the steps of a tile are summed from zero and what their addition to the sum rounds off goes into the next tile's; level 1
+// is the distance between two points.  Error against 64 bits 0.2 to 1.0 times that of the kernels that took these calls (14,300 calls;
+// without the carried part 1.1 to 1.5 times where few paths span workgroups).
+#include <type_traits>
+
+#include "sig_internal.h"
+
+namespace sig {
+namespace depth2_rows {
+
+typedef float vec4f_u __attribute__((ext_vector_type(4), aligned(4)));
+
+struct Args {
+    const float *path;   // [B][L][d]
+    float *out;          // [B][K][d + d * d]
+    int64_t B;
+    int32_t L;
+    int32_t chunks;      // C: stretches of a path side by side in a workgroup
+    int32_t segs;        // W: workgroups of a path
+    int32_t groups;      // paths in a workgroup
+    int32_t steps;       // T: steps of a stretch; W * C * T >= K
+    int32_t sticky;      // a point that is not a number spoils level 1 of the rows behind it too
+};
+
+enum Mode { UNCUT, CUT };
+
+constexpr int threads_of(int mode) { return mode == UNCUT ? kWave : 4 * kWave; }
+constexpr int slots_of(int mode, int d) { return threads_of(mode) / kWave * (kWave / d); }
+constexpr int tile_rows(int mode, int d)
+{
+    const int fit = (mode == UNCUT ? 6400 : 1600) / (kWave / d * (d + d * d));
+    return fit < 1 ? 1 : fit > 16 ? 16 : fit;
+}
+
+template <int d, int MODE>
+struct Tile {
+    static constexpr int D = d + d * d, SLOTS = kWave / d, R = tile_rows(MODE, d);
+    static constexpr int VECS = (R * D + 3) / 4, NV = (SLOTS * VECS + kWave - 1) / kWave;
+    static constexpr int PX = (R + 1) * d, NX = (SLOTS * PX + kWave - 1) / kWave;
+    // (slots begin some d banks apart, and at whole vectors)
+    static constexpr int STRIDE = VECS * 4 + ((d + 3) / 4 * 4 + 64 - VECS * 4 % 32) % 32;
+    static constexpr int XS = (d + 3) / 4 * 4;
+    static constexpr int FLOATS = SLOTS * (STRIDE + (R + 1) * XS);
+    static constexpr int TILES = (16 + R - 1) / R;    // whose steps are summed from zero
+    static constexpr int M = d * d + d;               // a slot's sums
+    static constexpr int LDS = threads_of(MODE) / kWave * FLOATS + (MODE == UNCUT ? 0 : (slots_of(MODE, d) + 1) * M);
+};
+
+extern __shared__ __align__(16) float sig_depth2_rows_smem[];
+
+// sum += part; what that rounded off is left in `part` (infinities and NaN leave nothing)
+__device__ __forceinline__ void carry(float &sum, float &part)
+{
+    const float to = sum + part, off = part - (to - sum);
+    sum = to;
+    part = fabsf(off) < __builtin_huge_valf() ? off : 0.0f;
+}
+
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <int d, int MODE>
+__global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_eu(2))) void sig_depth2_rows_kernel(Args A)
+{
+    using Tl = Tile<d, MODE>;
+    constexpr int NT = threads_of(MODE), WSLOTS = Tl::SLOTS, M = Tl::M, D = Tl::D, R = Tl::R, XS = Tl::XS;
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int K = A.L - 1;
+    const int C = MODE == UNCUT ? 1 : A.chunks, W = MODE == UNCUT ? 1 : A.segs, T = MODE == UNCUT ? K : A.steps;
+    const int64_t b0 = W > 1 ? blockIdx.x / W : (int64_t)blockIdx.x * A.groups;
+    const int k0 = W > 1 ? (int)(blockIdx.x - b0 * W) * C * T : 0;       // first step of the workgroup
+    const int npaths = W > 1 ? 1 : A.B - b0 < A.groups ? (int)(A.B - b0) : A.groups;
+    const int wslot = lane / d, a = lane - wslot * d;
+    const int slot = wave * WSLOTS + wslot;
+    const int group = slot / C, chunk = slot - group * C;
+    const bool active = wslot < WSLOTS && group < npaths;
+    const int mine = active ? group : 0;
+    const float *points = A.path + b0 * A.L * d;
+    float *rows = A.out + b0 * K * D;
+    const int last = npaths * A.L * d - 1;            // of the workgroup's points
+
+    float *otile = sig_depth2_rows_smem + wave * Tl::FLOATS, *xtile = otile + WSLOTS * Tl::STRIDE;
+    float *myo = otile + (active ? wslot : 0) * Tl::STRIDE;
+    const float *myx = xtile + (active ? wslot : 0) * (R + 1) * XS;
+    float *sums = sig_depth2_rows_smem + NT / kWave * Tl::FLOATS, *base = sums + NT / kWave * WSLOTS * M;
+
+    // the points around the R steps from `step` on of every slot of the wavefront (beyond the path's end: floats that nothing uses)
+    float xv[Tl::NX];
+    auto fetch = [&](int step) __attribute__((always_inline)) {
+        const int point = mine * A.L + (step < K ? step : K);
+#pragma unroll
+        for (int j = 0; j < Tl::NX; ++j) {
+            const int i = lane + j * kWave, ws = i / Tl::PX, x = i - ws * Tl::PX;
+            const int at = __shfl(point, ws * d) * d + x;
+            xv[j] = points[at < last ? at : last];
+        }
+    };
+    auto put = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < Tl::NX; ++j) {
+            const int i = lane + j * kWave, ws = i / Tl::PX, x = i - ws * Tl::PX;
+            if (ws < WSLOTS) xtile[(ws * (R + 1) + x / d) * XS + x % d] = xv[j];
+        }
+    };
+
+    const float first = points[(int64_t)mine * A.L * d + a];
+    float s2[d];             // row a of S2 before the steps in `sum`
+    float spoilt = 0.0f;     // not a number behind a point that is none (sticky)
+#pragma unroll
+    for (int b = 0; b < d; ++b) s2[b] = 0.0f;
+    // `count` steps of every slot from `from` on, those below `to`; EMIT: and their rows
+    // (held: the only tile's points are in LDS already)
+    auto walk = [&](int from, int to, int count, bool held, auto emit) __attribute__((always_inline)) {
+        constexpr bool EMIT = decltype(emit)::value;
+        if (!held) fetch(from);
+        float sum[d];
+#pragma unroll
+        for (int b = 0; b < d; ++b) sum[b] = 0.0f;
+        for (int t0 = 0; t0 < count; t0 += R) {
+            wave_sync();
+            if (!held) put();
+            wave_sync();
+            if (count - t0 > R) fetch(from + t0 + R);
+            const int left = to - from - t0, own = count - t0 < R ? count - t0 : R;
+            const int n = !active || left < 1 ? 0 : left < own ? left : own;     // of the slot's steps in this tile
+            float before[XS];
+#pragma unroll
+            for (int b = 0; b < XS; b += 4) {
+                const float4 v = *reinterpret_cast<const float4 *>(myx + b);
+                before[b] = v.x; before[b + 1] = v.y; before[b + 2] = v.z; before[b + 3] = v.w;
+            }
+            float here = myx[a];
+#pragma unroll 2
+            for (int r = 0; r < n; ++r) {
+                const float *x = myx + (r + 1) * XS;
+                float at[XS];
+#pragma unroll
+                for (int b = 0; b < XS; b += 4) {
+                    const float4 v = *reinterpret_cast<const float4 *>(x + b);
+                    at[b] = v.x; at[b + 1] = v.y; at[b + 2] = v.z; at[b + 3] = v.w;
+                }
+                const float next = x[a], va = next - here;
+                const float h = fmaf(0.5f, va, here - first + spoilt);
+#pragma unroll
+                for (int b = 0; b < d; ++b) sum[b] = fmaf(h, at[b] - before[b], sum[b]);
+                if (A.sticky) spoilt = fmaf(0.0f, va, spoilt);
+                if constexpr (EMIT) {
+                    float *o = myo + r * D;
+                    o[a] = next - first + spoilt;
+                    constexpr int V = d % 4 == 0 ? 4 : d % 2 == 0 ? 2 : 1;
+                    typedef float vec __attribute__((ext_vector_type(V)));
+#pragma unroll
+                    for (int b = 0; b < d; b += V) {
+                        vec v;
+#pragma unroll
+                        for (int e = 0; e < V; ++e) v[e] = s2[b + e] + sum[b + e];
+                        *reinterpret_cast<vec *>(o + d + a * d + b) = v;
+                    }
+                }
+                here = next;
+#pragma unroll
+                for (int b = 0; b < XS; ++b) before[b] = at[b];
+            }
+            if ((t0 / R + 1) % Tl::TILES == 0 || count - t0 <= R) {
+#pragma unroll
+                for (int b = 0; b < d; ++b) carry(s2[b], sum[b]);
+            }
+            if constexpr (EMIT) {
+                wave_sync();
+                const int row = mine * K + from + t0, have = n * D;
+#pragma unroll
+                for (int j = 0; j < Tl::NV; ++j) {
+                    const int i = lane + j * kWave, ws = i / Tl::VECS, at = 4 * (i - ws * Tl::VECS);
+                    const int to_row = __shfl(row, ws * d), theirs = __shfl(have, ws * d), floats = ws < WSLOTS ? theirs : 0;   // (all lanes take part)
+                    const float *src = otile + (ws < WSLOTS ? ws : 0) * Tl::STRIDE + at;
+                    const float4 v = *reinterpret_cast<const float4 *>(src);
+                    float *dst = rows + (int64_t)to_row * D + at;
+                    if (at + 4 <= floats) *reinterpret_cast<vec4f_u *>(dst) = vec4f_u{v.x, v.y, v.z, v.w};
+                    else if (at < floats) {
+                        dst[0] = v.x;
+                        if (at + 1 < floats) dst[1] = v.y;
+                        if (at + 2 < floats) dst[2] = v.z;
+                    }
+                }
+            }
+        }
+    };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+
+    if constexpr (MODE == UNCUT) {
+        walk(0, K, K, false, yes);
+    } else {
+        // a slot's sums into LDS, and from each path's the sums of what lies before its slots
+        auto leave = [&]() __attribute__((always_inline)) {
+            if (active) {
+#pragma unroll
+                for (int b = 0; b < d; ++b) sums[slot * M + a * d + b] = s2[b];
+                sums[slot * M + d * d + a] = spoilt;
+            }
+            __syncthreads();
+        };
+        auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int b = 0; b < d; ++b) s2[b] = 0.0f;
+            spoilt = 0.0f;
+        };
+        for (int e = tid; e < M; e += NT) base[e] = 0.0f;
+        if (k0 > 0) {
+            const int count = (k0 + C - 1) / C;
+            walk(chunk * count, k0, count, false, no);
+            leave();
+            for (int e = tid; e < M; e += NT) {
+                float sum = 0.0f, off = 0.0f;
+#pragma unroll 4
+                for (int c = 0; c < C; ++c) {
+                    off += sums[c * M + e];
+                    carry(sum, off);
+                }
+                base[e] = sum;
+            }
+            clear();
+        }
+        const int from = k0 + chunk * T;
+        __syncthreads();                              // (base is written, sums are read)
+        if (C > 1) walk(from, K, T, false, no);
+        leave();
+        for (int i = tid; i < npaths * M; i += NT) {
+            const int g = i / M, e = i - g * M;
+            float *s = sums + g * C * M + e;
+            float sum = W > 1 ? base[e] : 0.0f, off = 0.0f;
+#pragma unroll 4
+            for (int c = 0; c < C; ++c) {
+                off += s[c * M];
+                s[c * M] = sum;
+                carry(sum, off);
+            }
+        }
+        __syncthreads();
+        clear();
+        if (active) {
+#pragma unroll
+            for (int b = 0; b < d; ++b) s2[b] = sums[slot * M + a * d + b];
+            spoilt = sums[slot * M + d * d + a];
+        }
+        walk(from, K, T, C > 1 && T <= R, yes);
+    }
+}
+
+struct Cut {
+    int mode, chunks, segs, groups, steps;
+    int64_t grid;
+};
+
+template <int d>
+size_t lds_bytes(int mode)
+{
+    return (size_t)(mode == UNCUT ? Tile<d, UNCUT>::LDS : Tile<d, CUT>::LDS) * sizeof(float);
+}
+
+template <int d>
+hipError_t launch(const Args &A0, const Cut &c, hipStream_t st)
+{
+    Args A = A0;
+    A.chunks = c.chunks;
+    A.segs = c.segs;
+    A.groups = c.groups;
+    A.steps = c.steps;
+    static_assert(Tile<d, CUT>::LDS * sizeof(float) <= (size_t)kMaxLdsBytes, "the tiles and sums of a workgroup's slots fit its LDS");
+    const dim3 grid((unsigned)c.grid), threads(threads_of(c.mode));
+    if (c.mode == UNCUT) hipLaunchKernelGGL((sig_depth2_rows_kernel<d, UNCUT>), grid, threads, lds_bytes<d>(UNCUT), st, A);
+    else hipLaunchKernelGGL((sig_depth2_rows_kernel<d, CUT>), grid, threads, lds_bytes<d>(CUT), st, A);
+    return hipGetLastError();
+}
+
+struct Shape {
+    size_t (*lds)(int mode);
+    hipError_t (*launch)(const Args &, const Cut &, hipStream_t);
+};
+#define SIG_DEPTH2_CHANNELS(X) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16) X(17) X(18) X(19) X(20)
+#define SIG_DEPTH2_ENTRY(d) {&lds_bytes<d>, &launch<d>},
+constexpr int kLeastChannels = 2, kMostChannels = 20;
+const Shape kShapes[] = {SIG_DEPTH2_CHANNELS(SIG_DEPTH2_ENTRY)};
+static_assert(sizeof(kShapes) / sizeof(kShapes[0]) == kMostChannels - kLeastChannels + 1, "one entry a channel count");
+
+constexpr int kMostSegments = 32;
+constexpr int kShortSteps = 31;      // fewer steps are not cut
+
+// W == 0: UNCUT; else W workgroups a path and at most `most_chunks` stretches side by side in each.  False where it would hold 2^32
+// threads, or a workgroup's rows 2^31 floats.
+bool cut(int d, int64_t B, int64_t L, int64_t W, int64_t most_chunks, Cut *c)
+{
+    const int64_t K = L - 1, D = d + d * d, slots = slots_of(W > 0 ? CUT : UNCUT, d);
+    c->mode = W > 0 ? CUT : UNCUT;
+    c->chunks = c->segs = 1;
+    if (L > INT32_MAX / (slots * D)) return false;
+    c->steps = (int)K;
+    c->groups = (int)slots;
+    if (W > 0) {
+        const int64_t rows = (K + W - 1) / W;
+        int64_t C = rows < slots ? rows : slots;
+        if (C > most_chunks) C = most_chunks;
+        const int64_t T = (rows + C - 1) / C;
+        c->chunks = (int)C;
+        c->steps = (int)T;
+        c->segs = (int)((K + C * T - 1) / (C * T));
+        c->groups = c->segs > 1 ? 1 : (int)(slots / C);
+    }
+    const int64_t most = (((int64_t)1 << 32) - 1) / threads_of(c->mode);
+    if (B > most / c->segs * c->groups) return false;
+    c->grid = c->segs > 1 ? B * c->segs : (B + c->groups - 1) / c->groups;
+    return true;
+}
+
+// Microseconds, fitted to 5,000 calls (2 to 20 channels, 2 to 2,000 points, 1 to 60,000 paths), with eight cuts each.
+// Whole paths: one wave's own time, or the batch's, or that of its bytes.  Cut paths: the slowest workgroup's time where the
+// batch does not fill the chip, else the work of all of them, or the bytes.
+double microseconds(int d, int64_t B, int64_t L, const Cut &c)
+{
+    const double K = (double)(L - 1), mb = (double)B * K * (d + d * d) * 4e-6;
+    if (c.mode == UNCUT) {
+        const double groups = (double)B / (kWave / d);
+        const double alone = 0.109 * (1.0 + 0.27 * d) * K, full = 0.0746e-3 * groups * K, bytes = mb / 3.64;
+        const double most = alone > full ? alone : full;
+        // (up to ten channels: 13 % more while one round of workgroups holds the batch)
+        return (d >= 4 && d <= 10 && groups < 1536.0 ? 1.21 : 1.07) * (3.8 + (most > bytes ? most : bytes));
+    }
+    const double work = 1.0 + 0.245 * d, before = (double)(c.segs - 1) * c.steps, grid = (double)B * c.segs / c.groups * 1e-3;
+    const double alone = 3.14 + 0.237 * work * c.steps + 0.029 * c.chunks + 0.062 * work * before;
+    const double full = 4.3 + grid * (0.4675 * c.steps * work + 2.24 + 0.0323 * c.chunks + 0.42 * before), bytes = mb / 2.96;
+    const double most = alone > full ? alone : full;
+    return (most > bytes ? most : bytes) + (c.segs > 1 ? 2.0 : 0.0);
+}
+
+// The fastest launch with `segs` workgroups a path (1: or less than one).
+bool choose(int d, int64_t B, int64_t L, int segs, Cut *best, double *least)
+{
+    bool found = false;
+    auto take = [&](int W, int most_chunks) {
+        Cut c;
+        if (!cut(d, B, L, W, most_chunks, &c)) return;
+        const double us = microseconds(d, B, L, c);
+        if (found && us >= *least) return;
+        found = true;
+        *best = c;
+        *least = us;
+    };
+    const int slots = slots_of(CUT, d);
+    if (segs > 1) take(segs, slots);
+    else {
+        take(0, 1);
+        if (L - 1 >= kShortSteps) {
+            take(1, slots);
+            for (int C = 32; C >= 8; C /= 2)
+                if (C < slots) take(1, C);
+        }
+    }
+    return found;
+}
+
+}  // namespace depth2_rows
+
+// Which calls take it, measured on 14,300 (1.40 times as fast in the mean over the 6,600 that do, and 1.37 times on 11,700 others, 96 of
+// them slower by more than a twentieth, the worst 0.76 times as fast: 5 to 10 channels, 4 to 14 thousand paths of about 100 points).  Shorter calls: the same launch count and more work to begin with.  More than ten channels, against
+// one launch per level and sig_stream_rows.h: 1.37 to 1.54 times as fast, and from 4 steps on where the rows exceed 64 MB.
+// Up to ten channels against sig_stream_rows.h: 1.2 (ten) to 1.8 times (eight).  Against the register kernels: two and three
+// channels lead with whole paths only (2.0 and 1.5 times; cut, 1.1 and 0.6 at worst), four with whole paths or a path across
+// workgroups (1.4; side by side in one 1.08 and 0.8), seven likewise (1.4 to 1.8; 1.06 and 0.8), the others with all three (1.1 to 1.6).
+int depth2_rows_wanted(int d, int64_t B, int64_t L, bool registers)
+{
+    using namespace depth2_rows;
+    if (d < kLeastChannels || d > kMostChannels || B < 1 || L < 2) return 0;
+    const int64_t K = L - 1;
+    const double mb = (double)B * K * (d + d * d) * 4e-6;
+    if (d > 10 ? K < kShortSteps && (K < 4 || mb < 64.0) : registers ? K < 47 || (d <= 3 && mb < 4.0) : K < kShortSteps) return 0;
+    Cut best;
+    int W = 0;
+    double least = 0.0;
+    for (int segs = 1; segs <= kMostSegments; segs *= 2) {
+        if (segs > 1 && (K < kShortSteps || K / segs < 2 || B > 600 / segs)) break;
+        Cut c;
+        double us = 0.0;
+        if (!choose(d, B, L, segs, &c, &us) || (W && us >= least)) continue;
+        best = c;
+        W = segs;
+        least = us;
+    }
+    if (W == 0 || d > 10 || !registers) return W;
+    if (best.mode == UNCUT) return d <= 3 || d == 4 || d == 7 || d > 8 || K >= 100 ? W : 0;
+    if (d <= 3 || (d == 4 && (best.segs == 1 || K < 600)) || (d == 7 && best.segs == 1)) return 0;
+    return best.segs == 1 && B < 16 && K < 200 ? 0 : W;
+}
+
+bool depth2_rows_geometry(int d, int64_t B, int64_t L, int segs, int64_t *lds_bytes, int64_t *workgroups)
+{
+    using namespace depth2_rows;
+    Cut c;
+    double us = 0.0;
+    if (d < kLeastChannels || d > kMostChannels || B < 1 || L < 2 || segs < 1 || segs > kMostSegments || segs > L - 1) return false;
+    if (!choose(d, B, L, segs, &c, &us)) return false;
+    *lds_bytes = (int64_t)kShapes[d - kLeastChannels].lds(c.mode);
+    *workgroups = c.grid;
+    return true;
+}
+
+hipError_t launch_depth2_rows(const float *path, float *out, int64_t B, int64_t L, int d, int segs, bool sticky, hipStream_t st)
+{
+    using namespace depth2_rows;
+    Cut c;
+    double us = 0.0;
+    if (B == 0) return hipSuccess;
+    if (d < kLeastChannels || d > kMostChannels || !choose(d, B, L, segs, &c, &us)) return hipErrorInvalidValue;
+    Args A{};
+    A.path = path;
+    A.out = out;
+    A.B = B;
+    A.L = (int32_t)L;
+    A.sticky = sticky;
+    return kShapes[d - kLeastChannels].launch(A, c, st);
+}
+
+}  // namespace sig

@@ -261,6 +261,12 @@ bool split_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int c
 hipError_t launch_split_rows(const float *path, float *out, float *scratch, int64_t B, int64_t L, int d, int depth, int segs, bool sticky,
                              int cus, hipStream_t st);
 
+// ---------------------------------------------------------------- ... and at depth 2, where they need no scratch (sig_depth2_rows.hip)
+// registers: the call would take a register kernel.  Workgroups a path, 0 if it stays with that.
+int depth2_rows_wanted(int d, int64_t B, int64_t L, bool registers);
+bool depth2_rows_geometry(int d, int64_t B, int64_t L, int segs, int64_t *lds_bytes, int64_t *workgroups);
+hipError_t launch_depth2_rows(const float *path, float *out, int64_t B, int64_t L, int d, int segs, bool sticky, hipStream_t st);
+
 // table of compiled on-chip kernels; terminated by an entry with launch == nullptr
 // The compiled kernels live in several translation units (so that they build in parallel); sub-table i ends
 // with an entry whose launch pointer is null, and on_chip_subtable(i) is null past the last sub-table.  Entries

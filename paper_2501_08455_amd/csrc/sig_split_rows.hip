@@ -1,5 +1,5 @@
 // Launch of the stream-mode kernel whose rows are split across workgroups (sig_split_rows.h): compiled shapes, which calls take
-// it, and how a call is cut.
+// it, and how a call is cut.  (Depth 2 has its own, in sig_depth2_rows.hip.)
 #include "sig_split_rows.h"
 
 namespace sig {
@@ -116,6 +116,7 @@ bool best_cut(const Shape &s, int64_t B, int64_t L, int W, int cus, Cut *best, d
 // against the register kernel with two and a half paths a unit (1,721 of 61 123 and 110, but 421 of 174 88 and 110).
 int split_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held_p, bool held_rows)
 {
+    if (depth == 2) return depth2_rows_wanted(d, B, L, held_p >= 0 && !held_rows);
     const split::Shape *s = split::find(d, depth);
     if (!s || B < 1 || L < 2) return 0;
     const int64_t K = L - 1;
@@ -137,6 +138,10 @@ int split_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held_
 
 bool split_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, int64_t *lds_bytes, int64_t *workgroups, int64_t *scratch_floats)
 {
+    if (depth == 2) {
+        *scratch_floats = 0;
+        return depth2_rows_geometry(d, B, L, segs, lds_bytes, workgroups);
+    }
     const split::Shape *s = split::find(d, depth);
     split::Cut c;
     double us = 0.0;
@@ -151,6 +156,7 @@ bool split_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int c
 hipError_t launch_split_rows(const float *path, float *out, float *scratch, int64_t B, int64_t L, int d, int depth, int segs, bool sticky,
                              int cus, hipStream_t st)
 {
+    if (depth == 2) return launch_depth2_rows(path, out, B, L, d, segs, sticky, st);
     const split::Shape *s = split::find(d, depth);
     split::Cut c;
     double us = 0.0;
