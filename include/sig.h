@@ -280,7 +280,7 @@ int sig_backward(sig_ctx *ctx, const float *path, int64_t B, int64_t L, int d, i
                  const float *out, const float *grad_out, float *grad_path, void *hip_stream);
 
 /* 1 if sig_backward has a compiled register kernel for (d, depth), 0 if stream mode beyond depth 2 would take the general sweep (final
- * mode and depth 2 have their own compiled shapes, see sig_backward).  Host only. */
+ * mode, depth 2, and depth 3 of eleven and twelve channels have their own compiled shapes, see sig_backward).  Host only. */
 int sig_backward_available(int d, int depth);
 
 /*
