@@ -12,8 +12,8 @@
 //
 // Bound by the stores where the batch fills the chip (3.6 MB a us whole, 3.0 cut: the streams of a cut path lie further apart),
 // else by one wave's steps.  Tiles: 6,400 floats a wavefront whole (longer runs; six wavefronts a unit hold the rows
-// of the others' stores), 1,600 cut (sixteen wavefronts, whose scans overlap).  Before and now, us: (20,2) 1,177 paths of 1,386 points
-// 1,315 and 974, (2,2) 20,000 of 500 180 and 117, (12,2) 1,024 of 100 26.8 and 20.8.
+// of the others' stores), 1,600 cut (sixteen wavefronts, whose scans overlap; twelve with more points in LDS, see cut()).  Before and now, us: (20,2) 1,177 paths of 1,386 points
+// 1,315 and 708, (2,2) 20,000 of 500 180 and 117, (12,2) 1,024 of 100 26.8 and 20.8.
 //
 // Rounding: the steps of a tile are summed from zero and what their addition to the sum rounds off goes into the next tile's; level 1
 // is the distance between two points.  Error against 64 bits 0.2 to 1.0 times that of the kernels that took these calls (14,300 calls;
@@ -39,7 +39,8 @@ struct Args {
     int32_t sticky;      // a point that is not a number spoils level 1 of the rows behind it too
 };
 
-enum Mode { UNCUT, CUT };
+enum Mode { UNCUT, CUT, LONG };      // LONG: CUT with the points of eight rows' steps staged together
+constexpr int kLongChannels = 14;    // the least that LONG is compiled for (one row a tile)
 
 constexpr int threads_of(int mode) { return mode == UNCUT ? kWave : 4 * kWave; }
 constexpr int slots_of(int mode, int d) { return threads_of(mode) / kWave * (kWave / d); }
@@ -53,12 +54,12 @@ template <int d, int MODE>
 struct Tile {
     static constexpr int D = d + d * d, SLOTS = kWave / d, R = tile_rows(MODE, d);
     static constexpr int VECS = (R * D + 3) / 4, NV = (SLOTS * VECS + kWave - 1) / kWave;
-    static constexpr int PX = (R + 1) * d, NX = (SLOTS * PX + kWave - 1) / kWave;
+    static constexpr int P = MODE == LONG ? 8 * R : R;     // steps whose points are staged together
+    static constexpr int PX = (P + 1) * d, NX = (SLOTS * PX + kWave - 1) / kWave;
     // (slots begin some d banks apart, and at whole vectors)
     static constexpr int STRIDE = VECS * 4 + ((d + 3) / 4 * 4 + 64 - VECS * 4 % 32) % 32;
     static constexpr int XS = (d + 3) / 4 * 4;
-    static constexpr int FLOATS = SLOTS * (STRIDE + (R + 1) * XS);
-    static constexpr int TILES = (16 + R - 1) / R;    // whose steps are summed from zero
+    static constexpr int FLOATS = SLOTS * (STRIDE + (P + 1) * XS);
     static constexpr int M = d * d + d;               // a slot's sums
     static constexpr int LDS = threads_of(MODE) / kWave * FLOATS + (MODE == UNCUT ? 0 : (slots_of(MODE, d) + 1) * M);
 };
@@ -80,10 +81,10 @@ __device__ __forceinline__ void wave_sync()
 }
 
 template <int d, int MODE>
-__global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_eu(2))) void sig_depth2_rows_kernel(Args A)
+__global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_eu(MODE == LONG ? 3 : 2))) void sig_depth2_rows_kernel(Args A)
 {
     using Tl = Tile<d, MODE>;
-    constexpr int NT = threads_of(MODE), WSLOTS = Tl::SLOTS, M = Tl::M, D = Tl::D, R = Tl::R, XS = Tl::XS;
+    constexpr int NT = threads_of(MODE), WSLOTS = Tl::SLOTS, M = Tl::M, D = Tl::D, R = Tl::R, P = Tl::P, XS = Tl::XS;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int K = A.L - 1;
     const int C = MODE == UNCUT ? 1 : A.chunks, W = MODE == UNCUT ? 1 : A.segs, T = MODE == UNCUT ? K : A.steps;
@@ -101,10 +102,10 @@ __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_e
 
     float *otile = sig_depth2_rows_smem + wave * Tl::FLOATS, *xtile = otile + WSLOTS * Tl::STRIDE;
     float *myo = otile + (active ? wslot : 0) * Tl::STRIDE;
-    const float *myx = xtile + (active ? wslot : 0) * (R + 1) * XS;
+    const float *myx = xtile + (active ? wslot : 0) * (P + 1) * XS;
     float *sums = sig_depth2_rows_smem + NT / kWave * Tl::FLOATS, *base = sums + NT / kWave * WSLOTS * M;
 
-    // the points around the R steps from `step` on of every slot of the wavefront (beyond the path's end: floats that nothing uses)
+    // the points around the P steps from `step` on of every slot of the wavefront (beyond the path's end: floats that nothing uses)
     float xv[Tl::NX];
     auto fetch = [&](int step) __attribute__((always_inline)) {
         const int point = mine * A.L + (step < K ? step : K);
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_e
 #pragma unroll
         for (int j = 0; j < Tl::NX; ++j) {
             const int i = lane + j * kWave, ws = i / Tl::PX, x = i - ws * Tl::PX;
-            if (ws < WSLOTS) xtile[(ws * (R + 1) + x / d) * XS + x % d] = xv[j];
+            if (ws < WSLOTS) xtile[(ws * (P + 1) + x / d) * XS + x % d] = xv[j];
         }
     };
 
@@ -136,23 +137,29 @@ __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_e
         float sum[d];
 #pragma unroll
         for (int b = 0; b < d; ++b) sum[b] = 0.0f;
-        for (int t0 = 0; t0 < count; t0 += R) {
+        constexpr int S = EMIT ? R : P, TILES = (16 + S - 1) / S;      // steps of a round; rounds whose steps are summed from zero
+        float before[XS], here = 0.0f;
+        for (int t0 = 0; t0 < count; t0 += S) {
+            const int in = P == S ? 0 : t0 % P;       // of the points' tile
             wave_sync();
-            if (!held) put();
-            wave_sync();
-            if (count - t0 > R) fetch(from + t0 + R);
-            const int left = to - from - t0, own = count - t0 < R ? count - t0 : R;
-            const int n = !active || left < 1 ? 0 : left < own ? left : own;     // of the slot's steps in this tile
-            float before[XS];
-#pragma unroll
-            for (int b = 0; b < XS; b += 4) {
-                const float4 v = *reinterpret_cast<const float4 *>(myx + b);
-                before[b] = v.x; before[b + 1] = v.y; before[b + 2] = v.z; before[b + 3] = v.w;
+            if (in == 0) {
+                if (!held) put();
+                wave_sync();
+                if (count - t0 > P) fetch(from + t0 + P);
             }
-            float here = myx[a];
+            const int left = to - from - t0, own = count - t0 < S ? count - t0 : S;
+            const int n = !active || left < 1 ? 0 : left < own ? left : own;     // of the slot's steps in this tile
+            if (in == 0) {
+#pragma unroll
+                for (int b = 0; b < XS; b += 4) {
+                    const float4 v = *reinterpret_cast<const float4 *>(myx + b);
+                    before[b] = v.x; before[b + 1] = v.y; before[b + 2] = v.z; before[b + 3] = v.w;
+                }
+                here = myx[a];
+            }
 #pragma unroll 2
             for (int r = 0; r < n; ++r) {
-                const float *x = myx + (r + 1) * XS;
+                const float *x = myx + (in + r + 1) * XS;
                 float at[XS];
 #pragma unroll
                 for (int b = 0; b < XS; b += 4) {
@@ -181,7 +188,7 @@ __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_e
 #pragma unroll
                 for (int b = 0; b < XS; ++b) before[b] = at[b];
             }
-            if ((t0 / R + 1) % Tl::TILES == 0 || count - t0 <= R) {
+            if ((t0 / S + 1) % TILES == 0 || count - t0 <= S) {
 #pragma unroll
                 for (int b = 0; b < d; ++b) carry(s2[b], sum[b]);
             }
@@ -263,7 +270,7 @@ __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_e
             for (int b = 0; b < d; ++b) s2[b] = sums[slot * M + a * d + b];
             spoilt = sums[slot * M + d * d + a];
         }
-        walk(from, K, T, C > 1 && T <= R, yes);
+        walk(from, K, T, C > 1 && T <= P, yes);
     }
 }
 
@@ -275,7 +282,7 @@ struct Cut {
 template <int d>
 size_t lds_bytes(int mode)
 {
-    return (size_t)(mode == UNCUT ? Tile<d, UNCUT>::LDS : Tile<d, CUT>::LDS) * sizeof(float);
+    return (size_t)(mode == UNCUT ? Tile<d, UNCUT>::LDS : mode == LONG ? Tile<d, LONG>::LDS : Tile<d, CUT>::LDS) * sizeof(float);
 }
 
 template <int d>
@@ -287,9 +294,11 @@ hipError_t launch(const Args &A0, const Cut &c, hipStream_t st)
     A.groups = c.groups;
     A.steps = c.steps;
     static_assert(Tile<d, CUT>::LDS * sizeof(float) <= (size_t)kMaxLdsBytes, "the tiles and sums of a workgroup's slots fit its LDS");
+    static_assert(d < kLongChannels || Tile<d, LONG>::LDS * sizeof(float) <= (size_t)kMaxLdsBytes, "these too");
     const dim3 grid((unsigned)c.grid), threads(threads_of(c.mode));
     if (c.mode == UNCUT) hipLaunchKernelGGL((sig_depth2_rows_kernel<d, UNCUT>), grid, threads, lds_bytes<d>(UNCUT), st, A);
-    else hipLaunchKernelGGL((sig_depth2_rows_kernel<d, CUT>), grid, threads, lds_bytes<d>(CUT), st, A);
+    else if (c.mode == CUT) hipLaunchKernelGGL((sig_depth2_rows_kernel<d, CUT>), grid, threads, lds_bytes<d>(CUT), st, A);
+    else if constexpr (d >= kLongChannels) hipLaunchKernelGGL((sig_depth2_rows_kernel<d, LONG>), grid, threads, lds_bytes<d>(LONG), st, A);
     return hipGetLastError();
 }
 
@@ -329,6 +338,12 @@ bool cut(int d, int64_t B, int64_t L, int64_t W, int64_t most_chunks, Cut *c)
     const int64_t most = (((int64_t)1 << 32) - 1) / threads_of(c->mode);
     if (B > most / c->segs * c->groups) return false;
     c->grid = c->segs > 1 ? B * c->segs : (B + c->groups - 1) / c->groups;
+    // A tile's points arrive only once the stores before them are through: eight steps' at a time where a stretch has four or more,
+    // unless that leaves a round of workgroups (four a unit) more than the chip then holds (three).  Before and with
+    // it, us, the same bits: (15,2) 1,493 paths of 1,885 points 1,060 and 696, (18,2) 15 of 1,481 56.4 and 37.1, (20,2) 1,177 of 1,386 971 and 708; none of
+    // 2,000 calls slower by more than 4 %.  Stretches of two or three steps are up to a quarter slower with it, and eight to thirteen
+    // channels, which stage two and three rows, gain 1.1 to 1.2 on long ones and lose as much on the others.
+    if (W > 0 && d >= kLongChannels && c->steps >= 4 && (c->grid <= 768 || c->grid > 1024)) c->mode = LONG;
     return true;
 }
 

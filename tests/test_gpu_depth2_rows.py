@@ -15,7 +15,7 @@ CASES = [(2, 1, 2, 1), (2, 33, 17, 1), (2, 31, 18, 1), (2, 3, 40, 1), (2, 2, 300
          (4, 17, 20, 1), (4, 2, 530, 8), (5, 12, 9, 1), (5, 13, 34, 1), (6, 11, 7, 1), (6, 1, 201, 5), (7, 9, 33, 1), (8, 8, 12, 1), (8, 9, 65, 2),
          (9, 8, 14, 1), (10, 7, 31, 1), (10, 2, 100, 7), (11, 6, 11, 1), (11, 5, 45, 1), (12, 5, 32, 1), (12, 6, 33, 1), (13, 4, 70, 4), (14, 5, 30, 1),
          (15, 4, 35, 1), (16, 5, 6, 1), (16, 16, 33, 1), (16, 17, 40, 1), (17, 3, 64, 9), (18, 4, 33, 1), (19, 3, 5, 1), (19, 13, 50, 1), (20, 4, 4, 1),
-         (20, 1, 333, 16), (20, 2, 5, 4)]
+         (20, 1, 333, 16), (20, 2, 5, 4), (14, 16, 81, 1), (15, 2, 130, 2), (17, 12, 70, 1), (20, 2, 400, 2)]
 
 
 @pytest.mark.parametrize("d,B,L,segs", CASES)
