@@ -830,6 +830,7 @@ public:
         }
         if (rc == SIG_ERR_HIP) (void)hipGetLastError();
         *p = ctx->scratch;
+        if (rc != SIG_OK) hold_.unlock();   // (the call may ask again, for less)
         return rc;
     }
 

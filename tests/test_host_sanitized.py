@@ -20,9 +20,12 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CLANGXX = "/opt/rocm/lib/llvm/bin/clang++"
 
 
-def test_host_logic_runs_clean_under_sanitizers(tmp_path):
+@pytest.fixture(scope="module")
+def linked(tmp_path_factory):
+    """linked(program, *link flags): the library's host code and tests/<program> with both sanitizers, as an executable."""
     if not os.path.exists(CLANGXX):
         pytest.skip("no ROCm clang++ here")
+    tmp_path = tmp_path_factory.mktemp("host")
     flags = ["--cuda-host-only", "-O1", "-g", "-std=c++17", "-fPIC", "-fno-omit-frame-pointer",
              "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
              "-Xarch_host", "-fno-sanitize-recover=all", "-Wno-unused-command-line-argument",
@@ -47,15 +50,32 @@ def test_host_logic_runs_clean_under_sanitizers(tmp_path):
     stub_c = tmp_path / "fatbin_stubs.c"
     stub_c.write_text("".join('__attribute__((aligned(4096))) const char %s[32] = "__CLANG_OFFLOAD_BUNDLE__";\n' % s
                               for s in stubs))
-    exe = str(tmp_path / "host_sweep")
-    link = subprocess.run([CLANGXX, "-fsanitize=address", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-g",
-                           "-I" + os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "host_sweep.cpp"),
-                           "-x", "c", str(stub_c), "-x", "none"] + objs +
-                          ["-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib", "-o", exe],
-                          capture_output=True, text=True)
-    assert link.returncode == 0, link.stderr[-3000:]
+
+    def link(program):
+        exe = str(tmp_path / os.path.splitext(program)[0])
+        res = subprocess.run([CLANGXX, "-fsanitize=address", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-g",
+                              "-D__HIP_PLATFORM_AMD__=1", "-isystem", "/opt/rocm/include",
+                              "-I" + os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", program),
+                              "-x", "c", str(stub_c), "-x", "none"] + objs +
+                             ["-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib", "-o", exe],
+                             capture_output=True, text=True)
+        assert res.returncode == 0, res.stderr[-3000:]
+        return exe
+
+    return link
+
+
+def run(exe, done):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=0:verify_asan_link_order=0",
                UBSAN_OPTIONS="print_stacktrace=1:halt_on_error=1")
     ran = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=600)
     assert ran.returncode == 0, (ran.stdout[-4000:] + ran.stderr[-4000:])
-    assert "host sweep ok" in ran.stdout
+    assert done in ran.stdout
+
+
+def test_host_logic_runs_clean_under_sanitizers(linked):
+    run(linked("host_sweep.cpp"), "host sweep ok")
+
+
+def test_calls_that_cannot_have_scratch_return(linked):
+    run(linked("host_no_scratch.cpp"), "no scratch ok")
