@@ -126,7 +126,7 @@ __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_e
 
     const float first = points[(int64_t)mine * A.L * d + a];
     float s2[d];             // row a of S2 before the steps in `sum`
-    float spoilt = 0.0f;     // not a number behind a point that is none (sticky)
+    float spoilt = 0.0f;     // not a number behind a point that is none (sticky; infinite points too, but the first: the distance from that stays infinite)
 #pragma unroll
     for (int b = 0; b < d; ++b) s2[b] = 0.0f;
     // `count` steps of every slot from `from` on, those below `to`; EMIT: and their rows
@@ -170,7 +170,6 @@ __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_e
                 const float h = fmaf(0.5f, va, here - first + spoilt);
 #pragma unroll
                 for (int b = 0; b < d; ++b) sum[b] = fmaf(h, at[b] - before[b], sum[b]);
-                if (A.sticky) spoilt = fmaf(0.0f, va, spoilt);
                 if constexpr (EMIT) {
                     float *o = myo + r * D;
                     o[a] = next - first + spoilt;
@@ -184,6 +183,7 @@ __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_e
                         *reinterpret_cast<vec *>(o + d + a * d + b) = v;
                     }
                 }
+                if (A.sticky) spoilt = fmaf(0.0f, next, spoilt);
                 here = next;
 #pragma unroll
                 for (int b = 0; b < XS; ++b) before[b] = at[b];

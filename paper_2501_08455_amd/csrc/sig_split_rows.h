@@ -28,6 +28,7 @@ namespace split {
 using onchip::cpow;
 using onchip::vec4f_u;
 using rows::add_state;
+using rows::level1_of;
 using rows::summed_step;
 
 struct Args {
@@ -97,7 +98,8 @@ __global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(4))
         for (int m = P - 1; m >= 0; --m) { letter[m] = (int)(rest % d); rest /= d; }
     }
     const float *X = A.path + b * A.L * d;
-    const float first1 = X[(PIECES ? k0 * d : 0) + letter[0]];   // level 1 is the distance from this point
+    const float first1 = X[(PIECES ? k0 * d : 0) + letter[0]];   // level 1 is the distance from this point,
+    float spoilt = 0.0f;   // not a number behind a point that is none (sticky; infinite points too, but that first one: the distance from it stays infinite)
 
     constexpr int NV = (G::TILE + kWave - 1) / kWave;   // (of a wavefront alone)
     float next[NV];
@@ -176,8 +178,9 @@ __global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(4))
         const float *piece = A.pieces + b * (W - 1) * D;
         onchip::load_state<d, N, P>(piece, u, ln);
         for (int s = 1; s < w; ++s) onchip::reg_product<d, N, P>(ln, piece + (int64_t)s * D, u);
-        const float exact = X[k0 * d + letter[0]] - first1;
-        ln.pre[0] = A.sticky ? fmaf(0.0f, ln.pre[0], exact) : exact;
+        const float here1 = X[k0 * d + letter[0]];
+        if (A.sticky) spoilt = fmaf(0.0f, here1, ln.pre[0] != ln.pre[0] ? ln.pre[0] : 0.0f);
+        ln.pre[0] = level1_of(here1 - first1, ln.pre[0], A.sticky);
     }
     float *const rows0 = PIECES ? nullptr : A.out + (b * K + k0) * D;
     float *out = rows0;
@@ -204,8 +207,8 @@ __global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(4))
                 it.next(inc);
                 summed_step<d, N>(sum, now, inc);
                 add_state<d, N, P>(now, ln, sum);
-                const float exact = it.last.du[0] - first1;
-                now.pre[0] = A.sticky ? fmaf(0.0f, now.pre[0], exact) : exact;
+                now.pre[0] = it.last.du[0] - first1 + spoilt;
+                if (A.sticky) spoilt = fmaf(0.0f, it.last.du[0], spoilt);
                 if constexpr (decltype(emit)::value) {
                     if (out != rows0) write_back(out - D);
                     put(out, now);

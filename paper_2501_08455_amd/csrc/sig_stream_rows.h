@@ -83,6 +83,14 @@ __device__ __forceinline__ void add_state(onchip::Lane<d, N, P> &out, const onch
     for (int i = 0; i < Sh::NPRE; ++i) out.pre[i] = a.pre[i] + b.pre[i];
 }
 
+// Level 1 of what lies before a piece: the distance `exact` of two points (one rounding), but where one of the two is no finite
+// number, what adding the increments up gave (sticky).  An infinite point leaves level 1 infinite in its own row and NaN behind it, and one
+// at the path's start leaves it infinite in all rows.
+__device__ __forceinline__ float level1_of(float exact, float added, bool sticky)
+{
+    return !sticky || fabsf(exact - added) < __builtin_huge_valf() ? exact : added;
+}
+
 // The fused step of sig_onchip.h for lanes that own a word of length N - 1, with what it adds to the signature `now` summed in `sum`
 template <int d, int N>
 __device__ __forceinline__ void summed_step(onchip::Lane<d, N, N - 1> &sum, const onchip::Lane<d, N, N - 1> &now, const onchip::Inc<d, N - 1> &inc)
@@ -362,11 +370,9 @@ __global__ __launch_bounds__((most_threads(d, N))) __attribute__((amdgpu_waves_p
         }
     }
 
-    // level 1 of what lies before the piece, from the points: one rounding (0 * what the pieces give keeps their NaN where the rows
-    // add increments up)
     if (k > 0) {
         float &s1 = P > 1 ? bl.pre[0] : bl.s[0];
-        s1 = POINTS ? here1 - first1 : fmaf(0.0f, s1, here1 - first1);
+        s1 = level1_of(here1 - first1, s1, !POINTS);
     }
     const int mine = !active || k >= K ? 0 : K - k < T ? (int)(K - k) : T;
     float *dst = A.out + ((b0 + p) * K + k) * D;

@@ -5,7 +5,7 @@ import pytest
 
 from paper_2501_08455_amd import workloads
 from test_gpu_parity import assert_parity, check, gpu, run_gpu  # noqa: F401
-from test_gpu_stream_rows import _errors  # noqa: F401
+from test_gpu_stream_rows import _errors, assert_level1_is_added_up, infinite_points  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -85,3 +85,22 @@ def test_a_point_that_is_not_a_number_spoils_the_same_coefficients(gpu, d, B, L)
     assert np.array_equal(np.isnan(got[[0, 1, B - 1]]), np.isnan(other[[0, 1, B - 1]]))
     assert np.array_equal(np.isfinite(got[3:-1]), np.isfinite(other[3:-1])) and not np.isfinite(got[2, -1, d:]).all()
     assert np.isfinite(got[2, :, :d]).all() and not np.isfinite(got[2, -1, d]) and not np.isfinite(other[2, -1, d])
+
+
+# whole paths, stretches of a path side by side (an infinite point at every border of them), and (few paths, several calls) at every
+# border of workgroups
+@pytest.mark.parametrize("d,B,L,segs", [(2, 60003, 60, 1), (3, 40001, 130, 1), (4, 6000, 60, 1), (5, 300, 70, 1), (8, 300, 150, 1), (9, 100, 80, 1), (4, 4, 900, 8),
+                                        (6, 4, 900, 5), (10, 60, 200, 4), (12, 90, 90, 1), (20, 60, 60, 1), (13, 8000, 40, 1), (20, 5, 700, 16)])
+def test_infinite_points(gpu, d, B, L, segs):  # noqa: F811
+    rc, plan = gpu.sig_plan(gpu.default_ctx(), B, L, d, 2, 1)
+    assert rc == gpu.SIG_OK
+    sticky = d <= 10 and (plan.variant != gpu.SIG_VARIANT_LEVEL_SCAN or plan.row_workgroups > 0)
+    slots, rows = 4 * (64 // d), -(-(L - 1) // segs)
+    chunks = min(rows, slots)
+    border = chunks * -(-rows // chunks)          # rows of a workgroup
+    for first in ([0, 1, L - 1] + [w * border for w in range(1, segs) if w * border < L] if segs > 1 else [0]):
+        x = infinite_points(B, L, d, 87 + d + first, first, 0 if segs > 1 else 1)
+        plan.split_rows = segs
+        got = run_gpu(gpu, x, 2, True, plan)
+        plan.split_rows = 0
+        assert_level1_is_added_up(x, got, run_gpu(gpu, x, 2, True, plan), sticky)

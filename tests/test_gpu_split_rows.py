@@ -5,7 +5,7 @@ import pytest
 
 from paper_2501_08455_amd import workloads
 from test_gpu_parity import assert_parity, check, gpu, run_gpu  # noqa: F401
-from test_gpu_stream_rows import _errors  # noqa: F401
+from test_gpu_stream_rows import _errors, assert_level1_is_added_up, infinite_points  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -69,6 +69,19 @@ def test_a_point_that_is_not_a_number_spoils_the_same_coefficients(gpu, d, depth
     got = np.isfinite(run_gpu(gpu, x, depth, True))
     plan.split_rows = 0
     assert np.array_equal(got, np.isfinite(run_gpu(gpu, x, depth, True, plan)))
+
+
+@pytest.mark.parametrize("d,depth,B,L,segs", [(10, 3, 40, 40, 1), (10, 4, 8, 48, 3), (9, 4, 20, 40, 1), (6, 5, 9, 64, 4), (5, 5, 40, 40, 2), (4, 6, 25, 50, 3), (8, 4, 50, 50, 3)])
+def test_infinite_points(gpu, d, depth, B, L, segs):  # noqa: F811
+    """At the path's start, inside a block of steps and at its borders, at every border of stretches, and at the path's end."""
+    rc, plan = gpu.sig_plan(gpu.default_ctx(), B, L, d, depth, 1)
+    assert rc == gpu.SIG_OK
+    sticky = plan.variant != gpu.SIG_VARIANT_LEVEL_SCAN or plan.row_workgroups > 0
+    x = infinite_points(B, L, d, seed=89 + d, step=1 if B >= L else 8)
+    plan.split_rows = segs
+    got = run_gpu(gpu, x, depth, True, plan)
+    plan.split_rows = 0
+    assert_level1_is_added_up(x, got, run_gpu(gpu, x, depth, True, plan), sticky)
 
 
 def test_without_scratch_what_lies_before_is_folded_again(gpu):  # noqa: F811

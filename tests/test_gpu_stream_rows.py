@@ -51,6 +51,37 @@ def test_a_point_that_is_not_a_number_spoils_the_same_coefficients(gpu):  # noqa
         assert np.array_equal(np.isfinite(got), other)
 
 
+def infinite_points(B, L, d, seed, first=0, step=1):
+    """Paths with one infinite point each, of either sign: path b's is point (first + b * step) % L."""
+    x = workloads.brownian_paths(B, L, d, seed=seed)
+    for b in range(B):
+        x[b, (first + b * step) % L, b % d] = np.inf if b % 3 else -np.inf
+    return x
+
+
+def assert_level1_is_added_up(x, got, other, sticky=True):
+    """Level 1 is infinite or NaN where the sum of the increments is (or, not sticky, the distance from the first point), with the
+    same sign; the other kernels agree, and on which coefficients of the other levels are finite."""
+    d = x.shape[-1]
+    with np.errstate(invalid="ignore"):
+        want = np.diff(x.astype(np.float64), axis=1).cumsum(1) if sticky else x[:, 1:] - x[:, :1]
+    for rows in (got, other):
+        for kind in (np.isnan, np.isposinf, np.isneginf):
+            assert np.array_equal(kind(rows[..., :d]), kind(want))
+    assert np.array_equal(np.isfinite(got), np.isfinite(other))
+
+
+@pytest.mark.parametrize("d,depth,B,L,segs", [(4, 4, 64, 50, 1), (4, 4, 90, 90, 4), (8, 2, 70, 70, 3), (5, 3, 60, 60, 5), (10, 3, 40, 40, 2),
+                                              (12, 2, 60, 60, 2), (11, 3, 30, 30, 1)])
+def test_infinite_points(gpu, d, depth, B, L, segs):  # noqa: F811
+    """At the path's start, at every border of pieces and workgroups, and at its end."""
+    x = infinite_points(B, L, d, seed=85 + d)
+    got = run_gpu(gpu, x, depth, True, gpu.make_plan(gpu.SIG_VARIANT_ON_CHIP, row_workgroups=segs))
+    rc, plan = gpu.sig_plan(gpu.default_ctx(), B, L, d, depth, 1)
+    plan.row_workgroups = plan.split_rows = 0
+    assert_level1_is_added_up(x, got, run_gpu(gpu, x, depth, True, plan), sticky=d <= 10)
+
+
 def test_rows_are_not_taken_where_they_do_not_apply(gpu):  # noqa: F811
     for d, depth, L, segs in [(4, 6, 50, 2), (2, 3, 50, 1), (4, 4, 50, 33), (4, 4, 5, 5), (13, 3, 20, 1)]:
         plan = gpu.make_plan(gpu.SIG_VARIANT_ON_CHIP, row_workgroups=segs)
