@@ -116,7 +116,7 @@ enum sig_variant {
  *                 write them from registers, and each path is cut into n stretches (at most 32 and no more than increments, fewer
  *                 where they would be short) that follow each other in different workgroups.  Before row_workgroups; of the other
  *                 fields only `variant` and row_workgroups are read: they say whether a point that is not a number spoils level 1
- *                 of the rows behind it, as in the mapping without split_rows.  Compiled for (10,3), 8-10 channels at
+ *                 of the rows behind it, as in the mapping without split_rows, and at depth 2 which cuts lead.  Compiled for (10,3), 8-10 channels at
  *                 depth 4, 5 and 6 at depth 5, 4 at depth 6; and for 2-20 channels at depth 2, where n is the workgroups of a path (1:
  *                 or several paths in one) and nothing below applies.  Context scratch for the stretches' signatures, (n - 1) D floats a path;
  *                 where it cannot be had (or exceeds 8 GiB) a stretch folds what lies before it again.  Final mode ignores

@@ -745,7 +745,7 @@ int plan_auto(const sig_ctx *ctx, int64_t B, int64_t L, int stream_flag, const R
                                                 pl->variant == SIG_VARIANT_ON_CHIP ? pl->prefix_depth : -1);
     if (rc == SIG_OK && stream_flag)
         pl->split_rows = split_rows_wanted(rs.d, rs.depth, B, L, ctx ? ctx->num_cu : kDefaultCUs,
-                                           pl->variant == SIG_VARIANT_ON_CHIP ? pl->prefix_depth : -1, pl->row_workgroups > 0);
+                                           pl->variant == SIG_VARIANT_ON_CHIP ? pl->chunks : 0, pl->row_workgroups > 0);
     return rc;
 }
 
@@ -790,9 +790,10 @@ bool check_stream_rows(int64_t B, int64_t L, const RowShape &rs, const sig_plan_
 
 // stream mode by sig_split_rows.h, which comes before it
 bool takes_split_rows(const sig_plan_t &pl, int stream_flag) { return stream_flag && pl.split_rows > 0; }
+bool held_by_registers(const sig_plan_t &pl) { return pl.variant == SIG_VARIANT_ON_CHIP && pl.row_workgroups == 0; }   // without split_rows
 bool check_split_rows(int64_t B, int64_t L, const RowShape &rs, const sig_plan_t &pl, int64_t *lds, int64_t *wgs, int64_t *scratch_floats)
 {
-    if (!split_rows_geometry(rs.d, rs.depth, B > 0 ? B : 1, L, pl.split_rows, kDefaultCUs, lds, wgs, scratch_floats)) return false;
+    if (!split_rows_geometry(rs.d, rs.depth, B > 0 ? B : 1, L, pl.split_rows, kDefaultCUs, held_by_registers(pl), lds, wgs, scratch_floats)) return false;
     if (B == 0) *wgs = *scratch_floats = 0;
     return true;
 }
@@ -927,7 +928,7 @@ int run_plan(sig_ctx *ctx, const float *path, int64_t B, int64_t L, const RowSha
         }
         // level 1 of the rows behind a point that is not a number: as in the kernels that the plan's other fields name
         const bool sticky = rs.d <= 10 && (pl.variant != SIG_VARIANT_LEVEL_SCAN || pl.row_workgroups > 0);
-        hipError_t e = launch_split_rows(path, out, work, B, L, rs.d, rs.depth, pl.split_rows, sticky, ctx->num_cu, st);
+        hipError_t e = launch_split_rows(path, out, work, B, L, rs.d, rs.depth, pl.split_rows, sticky, held_by_registers(pl), ctx->num_cu, st);
         return e == hipSuccess ? SIG_OK : SIG_ERR_HIP;
     }
     if (takes_stream_rows(pl, stream_flag)) {

@@ -18,6 +18,7 @@
 // Rounding: the steps of a tile are summed from zero and what their addition to the sum rounds off goes into the next tile's; level 1
 // is the distance between two points.  Error against 64 bits 0.2 to 1.0 times that of the kernels that took these calls (14,300 calls;
 // without the carried part 1.1 to 1.5 times where few paths span workgroups).
+#include <cmath>
 #include <type_traits>
 
 #include "sig_internal.h"
@@ -317,7 +318,7 @@ constexpr int kShortSteps = 31;      // fewer steps are not cut
 
 // W == 0: UNCUT; else W workgroups a path and at most `most_chunks` stretches side by side in each.  False where it would hold 2^32
 // threads, or a workgroup's rows 2^31 floats.
-bool cut(int d, int64_t B, int64_t L, int64_t W, int64_t most_chunks, Cut *c)
+bool cut(int d, int64_t B, int64_t L, int64_t W, int64_t most_chunks, int cus, Cut *c)
 {
     const int64_t K = L - 1, D = d + d * d, slots = slots_of(W > 0 ? CUT : UNCUT, d);
     c->mode = W > 0 ? CUT : UNCUT;
@@ -343,38 +344,53 @@ bool cut(int d, int64_t B, int64_t L, int64_t W, int64_t most_chunks, Cut *c)
     // it, us, the same bits: (15,2) 1,493 paths of 1,885 points 1,060 and 696, (18,2) 15 of 1,481 56.4 and 37.1, (20,2) 1,177 of 1,386 971 and 708; none of
     // 2,000 calls slower by more than 4 %.  Stretches of two or three steps are up to a quarter slower with it, and eight to thirteen
     // channels, which stage two and three rows, gain 1.1 to 1.2 on long ones and lose as much on the others.
-    if (W > 0 && d >= kLongChannels && c->steps >= 4 && (c->grid <= 768 || c->grid > 1024)) c->mode = LONG;
+    if (W > 0 && d >= kLongChannels && c->steps >= 4 && (c->grid <= 3 * (int64_t)cus || c->grid > 4 * (int64_t)cus)) c->mode = LONG;
     return true;
 }
 
-// Microseconds, fitted to 5,000 calls (2 to 20 channels, 2 to 2,000 points, 1 to 60,000 paths), with eight cuts each.
-// Whole paths: one wave's own time, or the batch's, or that of its bytes.  Cut paths: the slowest workgroup's time where the
-// batch does not fill the chip, else the work of all of them, or the bytes.
-double microseconds(int d, int64_t B, int64_t L, const Cut &c)
+// Microseconds, fitted to 20,300 calls (2 to 20 channels, 4 to 2,000 points, 1 to 60,000 paths) with all their cuts, 107,000 launches: 7 (whole paths)
+// and 9 % off in the mean.  The workgroups' rounds, and the bytes: within 240 MB the last-level cache takes the stores of whole paths as fast as
+// they come; beyond, several paths cut side by side in a workgroup cost the memory a third.  The choice costs 1.014 times the best cut in the mean (1.037
+// before it knew of rounds: 1,445 workgroups of whole paths where the chip holds 1,280, 14,441 paths of 79 points of six channels, were
+// priced as many of a larger batch, 68 us, the best cut 54).
+double microseconds(int d, int64_t B, int64_t L, int cus, const Cut &c)
 {
-    const double K = (double)(L - 1), mb = (double)B * K * (d + d * d) * 4e-6;
+    const double K = (double)(L - 1), mb = (double)B * K * (d + d * d) * 4e-6, cache = 240.0, chip = cus / 256.0;
+    const int by_lds = held_by_lds(kShapes[d - kLeastChannels].lds(c.mode)), held = c.mode != UNCUT && by_lds > 4 ? 4 : by_lds;   // (four by their registers)
+    const double load = rounds_of(c.grid, cus, held, c.mode == UNCUT ? 0.110 : 0.166);
     if (c.mode == UNCUT) {
-        const double groups = (double)B / (kWave / d);
-        const double alone = 0.109 * (1.0 + 0.27 * d) * K, full = 0.0746e-3 * groups * K, bytes = mb / 3.64;
-        const double most = alone > full ? alone : full;
-        // (up to ten channels: 13 % more while one round of workgroups holds the batch)
-        return (d >= 4 && d <= 10 && groups < 1536.0 ? 1.21 : 1.07) * (3.8 + (most > bytes ? most : bytes));
+        const double work = 4.14 + 0.1152 * (1.0 + 0.26 * d) * K * load, bytes = mb / (mb > cache ? 3.95 : 9.61) / chip;
+        return std::sqrt(std::sqrt(work * work * work * work + bytes * bytes * bytes * bytes));
     }
-    const double work = 1.0 + 0.245 * d, before = (double)(c.segs - 1) * c.steps, grid = (double)B * c.segs / c.groups * 1e-3;
-    const double alone = 3.14 + 0.237 * work * c.steps + 0.029 * c.chunks + 0.062 * work * before;
-    const double full = 4.3 + grid * (0.4675 * c.steps * work + 2.24 + 0.0323 * c.chunks + 0.42 * before), bytes = mb / 2.96;
-    const double most = alone > full ? alone : full;
-    return (most > bytes ? most : bytes) + (c.segs > 1 ? 2.0 : 0.0);
+    const double step = 1.0 + 0.0973 * d, before = (double)(c.segs - 1) * c.steps;
+    const int R = tile_rows(c.mode, d);
+    const double tiles = c.mode == LONG ? 4.01 * ((c.steps + 7) / 8) - 0.88 : 0.829 * ((c.steps + R - 1) / R);
+    const double work = 1.81 + load * (0.217 * step * c.steps + tiles + 0.58 + 0.0356 * c.chunks + 0.0913 * step * before);
+    const double bytes = 2.64 + ((mb < cache ? mb : cache) / 5.26 + (mb > cache ? mb - cache : 0.0) / 3.0 * (c.groups > 1 ? 1.3 : 1.0)) / chip;
+    // (beyond the cache a path to each workgroup unless several are clearly faster: their stores lie closer together)
+    return std::sqrt(work * work + bytes * bytes) * (c.groups > 1 && mb > cache ? 1.05 : 1.0) + (c.segs > 1 ? 1.18 : 0.0);
 }
 
-// The fastest launch with `segs` workgroups a path (1: or less than one).
-bool choose(int d, int64_t B, int64_t L, int segs, Cut *best, double *least)
+// Where the register kernels are the alternative, whole paths of five, six and eight channels lead from a hundred increments on (0.7 to 1.1 times as
+// fast before: rows that the last-level cache takes as fast as a register kernel writes them), and stretches side by side in a workgroup
+// never with up to four channels and seven (0.8 to 1.1).
+constexpr int kLeastSteps = 47;      // fewer stay with the register kernels
+bool leads(int d, int64_t K, const Cut &c)
 {
+    if (c.mode == UNCUT) return (d != 5 && d != 6 && d != 8) || K >= 100;
+    return c.segs > 1 || (d > 4 && d != 7);
+}
+
+// The fastest launch with `segs` workgroups a path (1: or less than one).  registers: of those that lead on the register kernels, where any do.
+bool choose(int d, int64_t B, int64_t L, int segs, int cus, bool registers, Cut *best, double *least)
+{
+    const int64_t K = L - 1;
+    const bool leading = registers && d <= 10 && K >= kLeastSteps;
     bool found = false;
     auto take = [&](int W, int most_chunks) {
         Cut c;
-        if (!cut(d, B, L, W, most_chunks, &c)) return;
-        const double us = microseconds(d, B, L, c);
+        if (!cut(d, B, L, W, most_chunks, cus, &c) || (leading && !leads(d, K, c))) return;
+        const double us = microseconds(d, B, L, cus, c);
         if (found && us >= *least) return;
         found = true;
         *best = c;
@@ -384,67 +400,75 @@ bool choose(int d, int64_t B, int64_t L, int segs, Cut *best, double *least)
     if (segs > 1) take(segs, slots);
     else {
         take(0, 1);
-        if (L - 1 >= kShortSteps) {
+        if (K >= kShortSteps) {
             take(1, slots);
             for (int C = 32; C >= 8; C /= 2)
                 if (C < slots) take(1, C);
         }
     }
-    return found;
+    return found || (leading && choose(d, B, L, segs, cus, false, best, least));
 }
 
 }  // namespace depth2_rows
 
-// Which calls take it, measured on 14,300 (1.40 times as fast in the mean over the 6,600 that do, and 1.37 times on 11,700 others, 96 of
-// them slower by more than a twentieth, the worst 0.76 times as fast: 5 to 10 channels, 4 to 14 thousand paths of about 100 points).  Shorter calls: the same launch count and more work to begin with.  More than ten channels, against
+// Which calls take it.  Shorter calls: the same launch count and more work to begin with.  More than ten channels, against
 // one launch per level and sig_stream_rows.h: 1.37 to 1.54 times as fast, and from 4 steps on where the rows exceed 64 MB.
-// Up to ten channels against sig_stream_rows.h: 1.2 (ten) to 1.8 times (eight).  Against the register kernels: two and three
-// channels lead with whole paths only (2.0 and 1.5 times; cut, 1.1 and 0.6 at worst), four with whole paths or a path across
-// workgroups (1.4; side by side in one 1.08 and 0.8), seven likewise (1.4 to 1.8; 1.06 and 0.8), the others with all three (1.1 to 1.6).
-int depth2_rows_wanted(int d, int64_t B, int64_t L, bool registers)
+// Up to ten channels against sig_stream_rows.h: 1.2 (ten) to 1.8 times (eight).  Against the register kernels (chunks: of their plan, 0
+// where the call would not take them) by what leads there (see leads()): 1.31 times as fast in the mean over 6,700 calls of four to ten
+// channels, two thirds of them from the bands where the two lie close, 100 slower by more than a twentieth (0.82 at worst).  Not taken: short paths
+// that a register kernel walks whole, in one pass ((8,2), 20,000 paths of 60 points 92 us and 104); few paths (the launch decides); four
+// channels across workgroups under 600 increments (1,000 from a quarter of the units' number of paths on); six side by side in batches that keep the chip busy (5,000 to 20,000 paths of 50 to 190 points
+// 0.8 to 1.1); up to four channels and seven where the cuts that do not lead are the faster ones by the
+// model (on long paths by a tenth and a quarter: there whole paths lead by more than the model is off).
+int depth2_rows_wanted(int d, int64_t B, int64_t L, int cus, int chunks)
 {
     using namespace depth2_rows;
     if (d < kLeastChannels || d > kMostChannels || B < 1 || L < 2) return 0;
     const int64_t K = L - 1;
     const double mb = (double)B * K * (d + d * d) * 4e-6;
-    if (d > 10 ? K < kShortSteps && (K < 4 || mb < 64.0) : registers ? K < 47 || (d <= 3 && mb < 4.0) : K < kShortSteps) return 0;
+    const bool registers = chunks > 0;
+    if (d > 10 ? K < kShortSteps && (K < 4 || mb < 64.0) : registers ? K < kLeastSteps || (d <= 3 && mb < 4.0) : K < kShortSteps) return 0;
+    const bool narrow = registers && (d <= 4 || d == 7);
     Cut best;
     int W = 0;
-    double least = 0.0;
+    double least = 0.0, least_of_all = 0.0;
     for (int segs = 1; segs <= kMostSegments; segs *= 2) {
-        if (segs > 1 && (K < kShortSteps || K / segs < 2 || B > 600 / segs)) break;
+        if (segs > 1 && (K < kShortSteps || K / segs < 2 || B > 600 * (int64_t)cus / 256 / segs)) break;
         Cut c;
         double us = 0.0;
-        if (!choose(d, B, L, segs, &c, &us) || (W && us >= least)) continue;
+        if (narrow && choose(d, B, L, segs, cus, false, &c, &us) && (least_of_all == 0.0 || us < least_of_all)) least_of_all = us;
+        if (narrow && segs > 1 && (d <= 3 || (d == 4 && K < (B > cus / 4 ? 1000 : 600)))) continue;
+        if (!choose(d, B, L, segs, cus, registers, &c, &us) || (W && us >= least)) continue;
         best = c;
         W = segs;
         least = us;
     }
     if (W == 0 || d > 10 || !registers) return W;
-    if (best.mode == UNCUT) return d <= 3 || d == 4 || d == 7 || d > 8 || K >= 100 ? W : 0;
-    if (d <= 3 || (d == 4 && (best.segs == 1 || K < 600)) || (d == 7 && best.segs == 1)) return 0;
-    return best.segs == 1 && B < 16 && K < 200 ? 0 : W;
+    if (narrow) return least <= (best.segs > 1 || K < 100 ? 1.0 : K < 300 ? 1.1 : 1.25) * least_of_all ? W : 0;
+    if ((d == 5 || d == 6 || d == 8) && K < 100 && chunks == 1) return 0;
+    if (best.mode != UNCUT && best.segs == 1 && ((B < 16 && K < 200) || (d == 6 && K < 190 && B > 5000 * (int64_t)cus / 256))) return 0;
+    return W;
 }
 
-bool depth2_rows_geometry(int d, int64_t B, int64_t L, int segs, int64_t *lds_bytes, int64_t *workgroups)
+bool depth2_rows_geometry(int d, int64_t B, int64_t L, int segs, int cus, bool registers, int64_t *lds_bytes, int64_t *workgroups)
 {
     using namespace depth2_rows;
     Cut c;
     double us = 0.0;
     if (d < kLeastChannels || d > kMostChannels || B < 1 || L < 2 || segs < 1 || segs > kMostSegments || segs > L - 1) return false;
-    if (!choose(d, B, L, segs, &c, &us)) return false;
+    if (!choose(d, B, L, segs, cus, registers, &c, &us)) return false;
     *lds_bytes = (int64_t)kShapes[d - kLeastChannels].lds(c.mode);
     *workgroups = c.grid;
     return true;
 }
 
-hipError_t launch_depth2_rows(const float *path, float *out, int64_t B, int64_t L, int d, int segs, bool sticky, hipStream_t st)
+hipError_t launch_depth2_rows(const float *path, float *out, int64_t B, int64_t L, int d, int segs, bool sticky, bool registers, int cus, hipStream_t st)
 {
     using namespace depth2_rows;
     Cut c;
     double us = 0.0;
     if (B == 0) return hipSuccess;
-    if (d < kLeastChannels || d > kMostChannels || !choose(d, B, L, segs, &c, &us)) return hipErrorInvalidValue;
+    if (d < kLeastChannels || d > kMostChannels || !choose(d, B, L, segs, cus, registers, &c, &us)) return hipErrorInvalidValue;
     Args A{};
     A.path = path;
     A.out = out;

@@ -251,21 +251,38 @@ int stream_rows_segments(int d, int depth, int64_t B, int64_t L, int cus);
 bool stream_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, int64_t *lds_bytes, int64_t *workgroups, int *threads);
 hipError_t launch_stream_rows(const float *path, float *out, int64_t B, int64_t L, int d, int depth, int segs, int cus, hipStream_t st);
 
+// ---------------------------------------------------------------- what the planners of the kernels below and of the every-prefix gradient share
+// Workgroups of so much LDS that a unit holds at once (it hands LDS out in 128 pieces of 1,280 bytes)
+inline int held_by_lds(size_t bytes)
+{
+    const int fit = (int)(128 / ((bytes + 1279) / 1280));
+    return fit < 1 ? 1 : fit;
+}
+// Time of `grid` equal workgroups, in units of one that has its unit to itself; `held`: how many a unit holds at once; `beside`: what each
+// other one on the unit adds.  They start and end together, so that a round that is not full takes as long as if every unit had
+// one more.
+inline double rounds_of(int64_t grid, int cus, int held, double beside)
+{
+    const int64_t each = (grid + cus - 1) / cus, full = each / held, rest = each - full * held;
+    return (double)full * (1.0 + beside * (held - 1)) + (rest > 0 ? 1.0 + beside * (double)(rest - 1) : 0.0);
+}
+
 // ---------------------------------------------------------------- stream mode, rows split across workgroups (sig_split_rows.h)
 // stretches a path is cut into, 0 if the call stays with the other kernels
-int split_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held_p, bool held_rows);
+int split_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held_chunks, bool held_rows);
 // the launch with `segs` stretches a path; false if there is none
-bool split_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, int64_t *lds_bytes, int64_t *workgroups, int64_t *scratch_floats);
+bool split_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, bool registers, int64_t *lds_bytes, int64_t *workgroups, int64_t *scratch_floats);
 // scratch: those floats, or null (what lies before a stretch is folded again).  sticky: a point that is not a number spoils level 1 of the
 // rows behind it, not of its own row only.
 hipError_t launch_split_rows(const float *path, float *out, float *scratch, int64_t B, int64_t L, int d, int depth, int segs, bool sticky,
-                             int cus, hipStream_t st);
+                             bool registers, int cus, hipStream_t st);
 
 // ---------------------------------------------------------------- ... and at depth 2, where they need no scratch (sig_depth2_rows.hip)
-// registers: the call would take a register kernel.  Workgroups a path, 0 if it stays with that.
-int depth2_rows_wanted(int d, int64_t B, int64_t L, bool registers);
-bool depth2_rows_geometry(int d, int64_t B, int64_t L, int segs, int64_t *lds_bytes, int64_t *workgroups);
-hipError_t launch_depth2_rows(const float *path, float *out, int64_t B, int64_t L, int d, int segs, bool sticky, hipStream_t st);
+// chunks: of the register kernel that the call would take, 0 if it would take another.  Workgroups a path, 0 if it stays with those.
+// registers: that it would take one (its plan without split_rows), which decides between the cuts.
+int depth2_rows_wanted(int d, int64_t B, int64_t L, int cus, int chunks);
+bool depth2_rows_geometry(int d, int64_t B, int64_t L, int segs, int cus, bool registers, int64_t *lds_bytes, int64_t *workgroups);
+hipError_t launch_depth2_rows(const float *path, float *out, int64_t B, int64_t L, int d, int segs, bool sticky, bool registers, int cus, hipStream_t st);
 
 // table of compiled on-chip kernels; terminated by an entry with launch == nullptr
 // The compiled kernels live in several translation units (so that they build in parallel); sub-table i ends

@@ -108,19 +108,19 @@ bool best_cut(const Shape &s, int64_t B, int64_t L, int W, int cus, Cut *best, d
 
 }  // namespace split
 
-// Which stream-mode calls take it.  `held_p`: prefix depth of the register kernel that the planner would take, -1 for one launch per level;
+// Which stream-mode calls take it.  `held_chunks`: of the register kernel that the planner would take, 0 for one launch per level;
 // `held_rows`: the call would write its rows from registers by sig_stream_rows.h.  The shapes that kernel is not compiled for: every
 // call (2,815 of 4 to 2,001 points and 1 to 10,000 paths: 1.7 (4,6) to 2.4 times (6,5) as fast in the mean, sixteen slower by up to
 // 9 %).  (8,4): against the register kernel until its own rows fill the chip (1,000 paths of 120 points 443 us and 463, 130 of 60
 // 2.6 times as fast), against the others from 160 increments on (55 of 1,379 491 and 340; 2 of 60 0.8 times as fast).  (10,3):
 // against the register kernel with two and a half paths a unit (1,721 of 61 123 and 110, but 421 of 174 88 and 110).
-int split_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held_p, bool held_rows)
+int split_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held_chunks, bool held_rows)
 {
-    if (depth == 2) return depth2_rows_wanted(d, B, L, held_p >= 0 && !held_rows);
+    const bool registers = held_chunks > 0 && !held_rows;
+    if (depth == 2) return depth2_rows_wanted(d, B, L, cus, registers ? held_chunks : 0);
     const split::Shape *s = split::find(d, depth);
     if (!s || B < 1 || L < 2) return 0;
     const int64_t K = L - 1;
-    const bool registers = held_p >= 0 && !held_rows;
     if (d == 10 && depth == 3 && (!registers || 2 * B < 5 * (int64_t)cus)) return 0;
     if (d == 8 && (registers ? B > 60000 / K : K < 160)) return 0;
     int best = 0;
@@ -136,11 +136,12 @@ int split_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held_
     return best;
 }
 
-bool split_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, int64_t *lds_bytes, int64_t *workgroups, int64_t *scratch_floats)
+bool split_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, bool registers, int64_t *lds_bytes, int64_t *workgroups,
+                         int64_t *scratch_floats)
 {
     if (depth == 2) {
         *scratch_floats = 0;
-        return depth2_rows_geometry(d, B, L, segs, lds_bytes, workgroups);
+        return depth2_rows_geometry(d, B, L, segs, cus, registers, lds_bytes, workgroups);
     }
     const split::Shape *s = split::find(d, depth);
     split::Cut c;
@@ -154,9 +155,9 @@ bool split_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int c
 }
 
 hipError_t launch_split_rows(const float *path, float *out, float *scratch, int64_t B, int64_t L, int d, int depth, int segs, bool sticky,
-                             int cus, hipStream_t st)
+                             bool registers, int cus, hipStream_t st)
 {
-    if (depth == 2) return launch_depth2_rows(path, out, B, L, d, segs, sticky, st);
+    if (depth == 2) return launch_depth2_rows(path, out, B, L, d, segs, sticky, registers, cus, st);
     const split::Shape *s = split::find(d, depth);
     split::Cut c;
     double us = 0.0;
