@@ -20,6 +20,7 @@
 // of 1,777 of 9 5,440 -> 493, 55,774 of 446 of 2 786 -> 386, one of 1,445 of 10 55 -> 16; over 4,013 calls 2.9 times as fast in
 // the mean.  Rounding against 64 bits: 3e-8 to 1.7e-6 of the gradient's norm, 0.1 to 1.0 times the sweep's (its A is undone
 // and carried as well).
+#include <cmath>
 #include <type_traits>
 
 #include "sig_internal.h"
@@ -64,6 +65,20 @@ constexpr int tile_rows(int d, bool given)
     return unit * (fit < 1 ? 1 : fit > 16 / unit ? 16 / unit : fit);
 }
 
+// Floats between a slot's rows and the next one's, and between its points: rows begin some d banks behind the neighbour's, so that the slots'
+// lanes read their columns from different banks
+constexpr int rows_stride(int d, bool given)
+{
+    const int floats = tile_rows(d, given) * row_floats(d, given);
+    return floats + ((d + 3) / 4 * 4 + 64 - floats % 32) % 32;
+}
+constexpr int point_stride(int d) { return (d + 3) / 4 * 4; }
+constexpr int lds_floats(int d, bool given, int mode)
+{
+    const int tile = kWave / d * (rows_stride(d, given) + (tile_rows(d, given) + 1) * point_stride(d));
+    return threads_of(mode) / kWave * tile + (mode == UNCUT ? 0 : (slots_of(mode, d) + 1) * sums_of(d));
+}
+
 // A wavefront's tile: R rows of each of its slots, as they lie in memory, and the R + 1 points around them
 // (GIVEN: rows that the kernel of depth 3 left, of d (2 + d) floats)
 template <int d, bool GIVEN>
@@ -75,13 +90,9 @@ struct Tile {
     static constexpr int NV = (SLOTS * VECS + kWave - 1) / kWave; // ... that a lane brings
     static constexpr int PX = (R + 1) * d;                        // floats of a slot's points
     static constexpr int NX = (SLOTS * PX + kWave - 1) / kWave;
-    // a slot's rows begin some d banks behind its neighbour's, so that the slots' lanes read their columns from different banks
-    static constexpr int STRIDE = R * D + ((d + 3) / 4 * 4 + 64 - R * D % 32) % 32;
-    static constexpr int XS = (d + 3) / 4 * 4;
+    static constexpr int STRIDE = rows_stride(d, GIVEN), XS = point_stride(d);
     static constexpr int FLOATS = SLOTS * (STRIDE + (R + 1) * XS);
 };
-template <int d, bool GIVEN>
-constexpr int lds_floats(int mode) { return threads_of(mode) / kWave * Tile<d, GIVEN>::FLOATS + (mode == UNCUT ? 0 : (slots_of(mode, d) + 1) * sums_of(d)); }
 
 extern __shared__ __align__(16) float sig_stream_gradient_smem[];
 
@@ -568,6 +579,7 @@ struct Cut {
     int mode;               // UNCUT or CUT
     int chunks, segs, groups, steps, rows;
     int tile;               // rows of a slot that a wavefront stages at a time
+    size_t lds;             // bytes of a workgroup
     int64_t grid;
 };
 
@@ -582,12 +594,12 @@ hipError_t launch(const Args &A0, const Cut &c, hipStream_t st)
     A.rows = c.rows;
     const dim3 grid((unsigned)c.grid);
     if (c.mode == UNCUT) {
-        constexpr size_t lds = (size_t)lds_floats<d, GIVEN>(UNCUT) * sizeof(float);
+        constexpr size_t lds = (size_t)lds_floats(d, GIVEN, UNCUT) * sizeof(float);
         static_assert(lds <= (size_t)kMaxLdsBytes, "a wavefront's tile fits its workgroup's LDS");
         hipLaunchKernelGGL((sig_stream_depth2_kernel<d, UNCUT, GIVEN>), grid, dim3(threads_of(UNCUT)), lds, st, A);
         return hipGetLastError();
     }
-    constexpr size_t lds = (size_t)lds_floats<d, GIVEN>(CUT) * sizeof(float);
+    constexpr size_t lds = (size_t)lds_floats(d, GIVEN, CUT) * sizeof(float);
     static_assert(lds <= (size_t)kMaxLdsBytes, "the tiles and sums of a workgroup's slots fit its LDS");
     if (c.segs > 1) {
         hipLaunchKernelGGL((sig_stream_depth2_kernel<d, TOTALS, GIVEN>), grid, dim3(threads_of(TOTALS)), lds, st, A);
@@ -605,6 +617,7 @@ bool cut(int d, bool given, int64_t B, int64_t L, int64_t W, int most_chunks, Cu
     if (L > INT32_MAX / D) return false;
     c->chunks = c->segs = 1;
     c->tile = tile_rows(d, given);
+    c->lds = (size_t)lds_floats(d, given, W > 0 ? CUT : UNCUT) * sizeof(float);
     c->steps = c->rows = (int)K;
     if (W == 0) {
         c->mode = UNCUT;
@@ -635,31 +648,33 @@ bool cut(int d, bool given, int64_t B, int64_t L, int64_t W, int most_chunks, Cu
     return C * T <= INT32_MAX && c->grid * threads_of(CUT) < (int64_t)1 << 32;
 }
 
-// Microseconds of a launch, fitted to 3,450 calls (2 to 20 channels, 1 to 20,000 paths of 2 to 2,000 points, every cut; 12 and
-// 13 % off in the mean).  Uncut, a row follows the other in 0.1 (1 + 0.3 d) us until the wavefronts or the bytes set the pace; cut, a
-// block costs its steps (twice), the scan over its stretches and their barriers, less where a stretch is one tile that stays in
-// LDS.  The choice costs 1.03 times the best cut in the mean: tens of thousands of short paths uncut (16,294 of 135 points of 4
+// Microseconds of a launch, fitted to 16,500 calls (2 to 20 channels, 4 to 2,000 points, 1 to 60,000 paths) with all their cuts, 99,000
+// launches: 8 (uncut) and 11 % off in the mean.  The rounds of workgroups, and the bytes, which come a second time from memory where the
+// blocks of the workgroups that run together exceed the caches near the units; a stretch that is one tile stays in LDS.  Long stretches cost
+// more than the fit has them, hence the last factor.  The choice costs 1.011
+// times the best cut in the mean (1.047 before it knew of rounds: 2,631 paths of 255 points of 8 channels uncut 115 us, in eight stretches 67):
+// tens of thousands of short paths uncut (16,294 of 135 points of 4
 // channels 46 us, the best cut 58), thousands in a few stretches each (1,719 of 97 of 2: uncut 19, 16 stretches 6.3, 96 of them 25),
 // one path of 1,445 of 10 across 16 workgroups (uncut 687, one workgroup 72, 16 of them 16).
-double microseconds(int d, int64_t B, int64_t L, int cus, const Cut &c)
+double microseconds(int d, bool given, int64_t B, int64_t L, int cus, const Cut &c)
 {
-    const double K = (double)(L - 1), chip = cus / 256.0;
-    const double thousands = (double)c.grid / 1000.0 / chip;
-    const double gigabytes = (double)B * K * sums_of(d) * sizeof(float) * 1e-9;
+    const double K = (double)(L - 1), row = row_floats(d, given) * 4e-6, mb = (double)B * K * row, cache = 240.0, chip = cus / 256.0;
+    const double within = mb < cache ? mb : cache, beyond = mb - within;
+    const int by_lds = held_by_lds(c.lds), by_registers = c.mode != UNCUT ? 3 : d <= 10 ? 16 : 12, held = by_lds < by_registers ? by_lds : by_registers;
     if (c.mode == UNCUT) {
-        const double chain = 0.105 * (1 + 0.32 * d) * K, waves = 0.1 * (1 - 0.04 * (d < 16 ? d : 16)) * thousands * K;
-        const double bytes = gigabytes / 4.2e-3 / chip;
-        return 3.0 + (chain > waves ? (chain > bytes ? chain : bytes) : waves > bytes ? waves : bytes);
+        const double work = 2.22 + 0.1244 * (1.0 + 0.264 * d) * K * rounds_of(c.grid, cus, held, 0.120);
+        const double bytes = (within / 5.03 + beyond / 3.47) / chip;
+        return std::sqrt(std::sqrt(work * work * work * work + bytes * bytes * bytes * bytes));
     }
-    const double span = (double)c.chunks * c.steps;
-    const double blocks = c.segs > 1 ? c.rows / span : K > span ? K / span : 1.0;
-    const double walk = c.steps * (1 + 0.2 * d), held = c.steps <= c.tile ? 1.0 : 0.0;
-    const double alone = 2.7 + blocks * (0.3 * walk + 0.93 + 0.033 * c.chunks - 1.03 * held);
-    const double full = 4.9 + thousands * blocks * (0.51 * walk + 5.95 + 0.06 * c.chunks - 3.6 * held);
-    const double bytes = gigabytes / 1.9e-3 / chip;
-    const double least = c.chunks > 1 ? 5.2 : 3.5;
-    const double us = alone > full ? (alone > bytes ? alone : bytes) : full > bytes ? full : bytes;
-    return (us > least ? us : least) + (c.segs > 1 ? 3.5 + 0.19 * c.segs : 0.0);
+    const int64_t span = (int64_t)c.chunks * c.steps, blocks = c.segs > 1 ? c.rows / span : (L - 1 + span - 1) / span;
+    const bool stays = c.steps <= c.tile && blocks == 1;
+    const double walk = stays ? 0.83 : 0.316 * (1.0 + 0.171 * d) * c.steps;
+    const double work = 1.56 + rounds_of(c.grid, cus, held, 0.155) * (double)blocks * (walk + 2.09 + 0.0166 * c.chunks);
+    const double together = (double)(c.grid < (int64_t)cus * held ? c.grid : (int64_t)cus * held) * c.groups * (double)span * row;
+    const double again = stays || together < 63.0 ? 0.0 : 1.0 - 63.0 / together;
+    const double bytes = 1.85 + (within / 3.68 + beyond / 3.40) * (1.0 + 0.60 * again) / chip;
+    const double us = std::sqrt(work * work + bytes * bytes) + (c.segs > 1 ? 4.3 + 0.215 * c.segs : 0.0);
+    return us * (1.05 + (c.segs == 1 && c.steps > 8 ? 0.084 * std::log2(c.steps / 8.0) : 0.0));
 }
 
 bool choose(int d, bool given, int64_t B, int64_t L, int cus, bool scratch, Cut *best)
@@ -669,7 +684,7 @@ bool choose(int d, bool given, int64_t B, int64_t L, int cus, bool scratch, Cut 
     auto consider = [&](int64_t W, int most_chunks) {
         Cut c;
         if (!cut(d, given, B, L, W, most_chunks, &c)) return;
-        const double us = microseconds(d, B, L, cus, c);
+        const double us = microseconds(d, given, B, L, cus, c);
         if (found && us >= least) return;
         found = true;
         least = us;
