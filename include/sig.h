@@ -255,7 +255,7 @@ int sig_combine(sig_ctx *ctx, const float *a, const float *b, int64_t B, int d, 
  * with context scratch of a row of d (d + 1) floats for each of up to 32 workgroups a path; where scratch cannot be had a path
  * stays in one workgroup); `out` is not read.  Depth 3, eleven and twelve channels: first a sweep over the rows' third level that
  * leaves rows of d (d + 2) floats in context scratch, then the same over those (without that scratch, or where it would exceed
- * 8 GiB, the general sweep).  Rows too long for its 32-bit offsets (d (d + 1) L beyond 2^31) are swept as below.
+ * 8 GiB, the general sweep).  Paths of 2^30 points, and rows of 2^31 floats where scratch cannot be had, take the general sweep.
  * The other sweeps start from the signature at the end and undo one increment at a time.  Shapes with a compiled register
  * kernel (see sig_backward_available) whose paths fit its LDS staging take it.  Few long paths and paths too long for that
  * staging are cut into up to 32 time segments that are swept by different workgroups: by Eq. 3 a segment can start from the
@@ -285,9 +285,10 @@ int sig_backward_available(int d, int depth);
 
 /*
  * How sig_backward would sweep this shape.  Host only; ctx may be NULL (a device with 256 compute units is assumed).
- * Returns the number of time segments the sweep may be cut into across workgroups (2 .. 32; final-mode sweeps on brackets
- * pack whole paths instead where that is faster; stream mode at depth 2 has a cut of its own, which this does not report: the
- * number is that of the sweep on signatures), 1 for an uncut sweep, 0 for shapes without a register kernel, or minus the SIG_ERR_* status with which sig_backward would reject the arguments.
+ * Returns the number of time segments that different workgroups sweep (2 .. 32; final-mode sweeps on brackets may
+ * pack whole paths instead where that is faster; a stream-mode call at depth 2, or depth 3 of eleven and twelve channels, that
+ * cannot have scratch takes fewer), 1 for a sweep that is not cut across workgroups, 0 for shapes without a register kernel
+ * otherwise, or minus the SIG_ERR_* status with which sig_backward would reject the arguments.
  */
 int sig_backward_segments(const sig_ctx *ctx, int64_t B, int64_t L, int d, int depth, int stream_flag);
 

@@ -1413,8 +1413,9 @@ int sig_backward(sig_ctx *ctx, const float *path, int64_t B, int64_t L, int d, i
                 if (rc == SIG_ERR_ALLOC) work = nullptr;
                 else if (rc != SIG_OK) return rc;
             }
+            // (rows of 2^31 floats and more take several workgroups a path)
             hipError_t er = launch_stream_gradient(path, grad_out, grad_path, work, B, L, d, ctx->num_cu, st);
-            return er == hipSuccess ? SIG_OK : SIG_ERR_HIP;
+            if (er != hipErrorNotSupported) return er == hipSuccess ? SIG_OK : SIG_ERR_HIP;
         }
     }
     if (stream_flag && depth == 3) {
@@ -1430,8 +1431,9 @@ int sig_backward(sig_ctx *ctx, const float *path, int64_t B, int64_t L, int d, i
             if (rc != SIG_ERR_ALLOC) return rc;
         }
     }
-    const bool fits = backward_available(d, depth) && backward_fits(d, depth, L);
-    if (backward_available(d, depth)) {
+    // (stream mode at depth 2 has no sweep on signatures but the general one)
+    const bool swept = backward_available(d, depth) && !(stream_flag && depth == 2), fits = swept && backward_fits(d, depth, L);
+    if (swept) {
         // few long paths (or paths too long for the LDS of the uncut sweep): the sweep cut in time across workgroups
         const int segs = backward_segments(d, depth, B, L, ctx->num_cu, fits, stream_flag);
         if (segs > 1) {
@@ -1444,7 +1446,7 @@ int sig_backward(sig_ctx *ctx, const float *path, int64_t B, int64_t L, int d, i
             return es == hipSuccess ? SIG_OK : SIG_ERR_HIP;
         }
     }
-    if (!fits && !(backward_available(d, depth) && backward_tiles_fit(d, depth))) {
+    if (!fits && !(swept && backward_tiles_fit(d, depth))) {
         // no register kernel for this shape: the general sweep
         if (!backward_general_available(d) || B > INT32_MAX) return SIG_ERR_UNSUPPORTED;
         const int64_t need = backward_general_scratch_floats(B, L, rs);
@@ -1468,6 +1470,11 @@ int sig_backward_segments(const sig_ctx *ctx, int64_t B, int64_t L, int d, int d
     RowShape rs;
     const int rc = check_shape(B, L, d, depth, stream_flag, &rs);
     if (rc != SIG_OK) return -rc;
+    if (stream_flag) {
+        const int segs = stream_gradient_segments(d, depth, B > 0 ? B : 1, L, ctx ? ctx->num_cu : kDefaultCUs);
+        if (segs > 0) return segs;
+        if (depth == 2) return backward_general_available(d) ? 0 : -SIG_ERR_UNSUPPORTED;
+    }
     if (!backward_available(d, depth)) return backward_general_available(d) ? 0 : -SIG_ERR_UNSUPPORTED;
     if (!stream_flag && bracket_wanted(d, depth, B, L)) return bracket_segments(d, depth, B, L, ctx ? ctx->num_cu : kDefaultCUs);
     const bool fits = backward_fits(d, depth, L);

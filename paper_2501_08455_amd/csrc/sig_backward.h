@@ -899,13 +899,15 @@ int backward_sliced_steps(int64_t L)
 
 // Every compiled (d, depth, prefix depth) of the reverse sweep, one prefix depth per (d, depth): the one whose two
 // lane states (S and its adjoint) fit the registers.  REG: the d^P lanes of a path fit a workgroup; SLICED: they
-// span several (sliced sweep).
+// span several (sliced sweep).  Depth 2 has the sweep for the few points that final mode does not sweep on brackets; in
+// stream mode sig_stream_gradient.hip takes its paths.
+#define SIG_BACKWARD_DEPTH2_SHAPES(REG) \
+    REG(2, 2, 1) REG(3, 2, 1) REG(4, 2, 1) REG(5, 2, 1) REG(6, 2, 1) REG(7, 2, 1) REG(8, 2, 1) REG(9, 2, 1) REG(10, 2, 1)
 #define SIG_BACKWARD_SHAPES(REG, SLICED) \
-    REG(2, 2, 1) REG(3, 2, 1) REG(4, 2, 1) REG(5, 2, 1) REG(6, 2, 1) REG(8, 2, 1) REG(10, 2, 1) REG(2, 3, 1) \
-    REG(3, 3, 1) REG(4, 3, 1) REG(5, 3, 1) REG(6, 3, 1) REG(7, 3, 1) REG(8, 3, 2) REG(10, 3, 2) REG(2, 4, 1) \
+    REG(2, 3, 1) REG(3, 3, 1) REG(4, 3, 1) REG(5, 3, 1) REG(6, 3, 1) REG(7, 3, 1) REG(8, 3, 2) REG(10, 3, 2) REG(2, 4, 1) \
     REG(3, 4, 1) REG(4, 4, 2) REG(5, 4, 2) REG(6, 4, 2) REG(7, 4, 2) REG(2, 5, 1) REG(3, 5, 2) REG(4, 5, 3) \
     REG(5, 5, 3) REG(2, 6, 1) REG(3, 6, 3) SLICED(8, 4, 3) SLICED(10, 4, 3) SLICED(6, 5, 3) SLICED(4, 6, 4) \
-    SLICED(5, 6, 4) SLICED(10, 6, 4) REG(7, 2, 1) REG(9, 2, 1) REG(9, 3, 2) SLICED(9, 4, 3) SLICED(7, 5, 3) \
+    SLICED(5, 6, 4) SLICED(10, 6, 4) REG(9, 3, 2) SLICED(9, 4, 3) SLICED(7, 5, 3) \
     SLICED(8, 5, 3) SLICED(9, 5, 3) SLICED(10, 5, 3)
 
 #endif  // SIG_BACKWARD_H_

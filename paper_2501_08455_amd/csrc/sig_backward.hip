@@ -528,11 +528,9 @@ hipError_t backward_short_launch(const BackwardArgs &A0, int threads, int cus, h
 }
 
 template <int d, int N, int P>
-hipError_t backward_launch(const BackwardArgs &A0, float *scratch, int threads, int cus, hipStream_t st)
+hipError_t backward_stream_launch(const BackwardArgs &A0, float *scratch, int threads, int cus, hipStream_t st)
 {
     constexpr int Q = Shape<d, N, P>::Q;
-    if (threads < Q || threads > 256 || threads % kWave) return hipErrorInvalidValue;
-    if (!A0.stream_flag) return backward_short_launch<d, N, P>(A0, threads, cus, st);
     BackwardArgs A = A0;
     // Lanes below which the sweep is cut in time inside the workgroup (one path per workgroup): a wavefront per CU.  The cut
     // sweeps every increment three times and multiplies rows between the chunks, so it pays only while the plain sweep would
@@ -540,12 +538,12 @@ hipError_t backward_launch(const BackwardArgs &A0, float *scratch, int threads, 
     const int64_t few_lanes = (int64_t)cus * kWave;
     // A shape that fills at most half of a workgroup's lanes (see backward_starved) ...
     bool half_empty = backward_starved<d, N, P>(A.L);
-    if (half_empty && Q < kStarvedChunkedMaxLanes && N >= 3) {
+    if (half_empty && Q < kStarvedChunkedMaxLanes) {
         // ... unless, for the kernels with few lanes per path, the plain sweep still keeps enough lanes on a CU.  The
         // cut in time sweeps every increment three times and multiplies whole rows between the chunks, which costs more
         // the deeper the signature: measured on 14 shapes x 64 ... 2,000 points x 2,048 ... 32,768 paths, the plain sweep
         // is 1.1-7x faster above these lane counts (256 points, 8,192 paths: (2,6) 2,504 -> 501 us, (3,4) 843 -> 261, (5,3)
-        // 636 -> 426) and up to 5x slower below them; at depth 2 the cut always wins.
+        // 636 -> 426) and up to 5x slower below them.
         int G = threads / Q;
         while (G > 1 && backward_lds_bytes<d, N, P>(A.L, G) > kMaxLdsBytes) --G;
         const int64_t lanes = resident_sweep_workgroups<d, N, P>(A.L, threads, G, 0) * G * Q;
@@ -637,6 +635,15 @@ hipError_t backward_launch(const BackwardArgs &A0, float *scratch, int threads, 
     return hipGetLastError();
 }
 
+template <int d, int N, int P>
+hipError_t backward_launch(const BackwardArgs &A, float *scratch, int threads, int cus, hipStream_t st)
+{
+    if (threads < Shape<d, N, P>::Q || threads > 256 || threads % kWave) return hipErrorInvalidValue;
+    if (!A.stream_flag) return backward_short_launch<d, N, P>(A, threads, cus, st);
+    if constexpr (N == 2) return hipErrorInvalidValue;   // (sig_stream_gradient.hip)
+    else return backward_stream_launch<d, N, P>(A, scratch, threads, cus, st);
+}
+
 }  // namespace onchip
 
 namespace {
@@ -652,6 +659,7 @@ struct BackwardEntry {
     {d, N, &onchip::backward_sliced_launch<d, N, P>, &onchip::backward_sliced_lds_bytes<d, N, P>, \
      &onchip::backward_sliced_scratch_floats<d, N, P>},
 const BackwardEntry kBackward[] = {
+    SIG_BACKWARD_DEPTH2_SHAPES(SIG_BACKWARD_ENTRY)
     SIG_BACKWARD_SHAPES(SIG_BACKWARD_ENTRY, SIG_BACKWARD_SLICED)
     {0, 0, nullptr, nullptr, nullptr},
 };

@@ -434,7 +434,7 @@ int backward_segments(int d, int depth, int64_t B, int64_t L, int cus, bool uncu
         const int chunks = e->uncut_chunks(L);
         if (chunks >= 8) min_steps = 512;
         if (B > 32 && chunks >= 6) busy = true;
-        // stream mode, rows of a few dozen floats (d = 2 at depth 3, d = 5 at depth 2): the plain sweep with its
+        // stream mode, rows of a few dozen floats (d = 2 at depth 3 and 4): the plain sweep with its
         // chunks is as fast at every measured length
         if (stream_flag && chunks >= 8 && e->row <= 32) busy = true;
     }

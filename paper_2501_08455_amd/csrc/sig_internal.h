@@ -129,13 +129,15 @@ hipError_t launch_bracket(const float *path, const float *sig, const float *grad
                           int d, int depth, int segs, int cus, hipStream_t st);
 
 // ---------------------------------------------------------------- gradient of the every-prefix signature at depth 2 and 3 (sig_stream_gradient.hip)
-// Floats of scratch the launch would like (0: none); < 0 if there is no such launch (more than 20 channels, rows or batches
-// beyond its offsets).  Without scratch (null) a path stays in one workgroup.
+// Floats of scratch the launch would like (0: none); < 0 if there is no such launch (more than 20 channels, 2^30 points).  Without
+// scratch (null) a path stays in one workgroup (hipErrorNotSupported: its rows take 2^31 floats).
 int64_t stream_gradient_scratch_floats(int d, int64_t B, int64_t L, int cus);
 bool stream_gradient_geometry(int d, int64_t B, int64_t L, int cus, bool scratch, int64_t *scratch_floats, int64_t *grid, int64_t *segs,
                               int64_t *groups, int64_t *chunks, int64_t *steps, int64_t *rows);
 hipError_t launch_stream_gradient(const float *path, const float *grad_out, float *grad_path, float *scratch, int64_t B, int64_t L,
                                   int d, int cus, hipStream_t st);
+// Workgroups a path, of either depth's launch with scratch (0: there is none)
+int stream_gradient_segments(int d, int depth, int64_t B, int64_t L, int cus);
 // Depth 3, eleven and twelve channels: floats of scratch the launches need (< 0: there are none), and the launches.  sig: [B][L-1][D]
 int64_t stream_gradient3_scratch_floats(int d, int64_t B, int64_t L, int cus);
 hipError_t launch_stream_gradient3(const float *path, const float *sig, const float *grad_out, float *grad_path, float *scratch, int64_t B,

@@ -127,20 +127,23 @@ __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_e
     using vec_lds = std::conditional_t<Tl::D % 2 == 0, vec4f_8, vec4f_u>;   // (the last vector of fewer than R rows)
     constexpr int NT = threads_of(MODE), WSLOTS = Tl::SLOTS, M = sums_of(d), D = Tl::D, R = Tl::R, XS = Tl::XS;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-    const int K = A.L - 1;
-    const int C = MODE == UNCUT ? 1 : A.chunks, W = MODE == UNCUT ? 1 : A.segs, T = MODE == UNCUT ? K : A.steps;
+    const int C = MODE == UNCUT ? 1 : A.chunks, W = MODE == UNCUT ? 1 : A.segs, T = MODE == UNCUT ? A.L - 1 : A.steps;
     const int64_t b0 = W > 1 ? blockIdx.x / W : (int64_t)blockIdx.x * A.groups;
     const int seg = W > 1 ? (int)(blockIdx.x - b0 * W) : 0;
-    const int k0 = W > 1 ? seg * A.rows : 0;                             // the workgroup's rows are k0 + 1 .. k1
+    // The workgroup's rows are k0 + 1 .. k1.  Row and point numbers count from `under`, which a stretch's last tile may reach: offsets take 32 bits
+    // where those of the whole path do not.
+    const int under = W > 1 && seg * A.rows > R ? seg * A.rows - R : 0;
+    const int K = A.L - 1 - under;
+    const int k0 = W > 1 ? seg * A.rows - under : 0;
     const int k1 = W > 1 && K - k0 > A.rows ? k0 + A.rows : K;
     const int npaths = W > 1 ? 1 : A.B - b0 < A.groups ? (int)(A.B - b0) : A.groups;
     const int wslot = lane / d, b = lane - wslot * d;
     const int slot = wave * WSLOTS + wslot;
     const int group = slot / C, chunk = slot - group * C;
     const bool active = wslot < WSLOTS && group < npaths;
-    const float *points = A.path + b0 * A.L * d, *grads = (GIVEN ? A.reduced : A.grad_out) + b0 * K * D;   // (of all its paths: below 2^31 floats)
-    const float *X = A.path + (b0 + (active ? group : 0)) * A.L * d;
-    float *dX = A.grad_path + (b0 + (active ? group : 0)) * A.L * d;
+    const float *points = A.path + (b0 * A.L + under) * d, *grads = (GIVEN ? A.reduced : A.grad_out) + (b0 * (A.L - 1) + under) * D;
+    const float *first = A.path + (b0 + (active ? group : 0)) * A.L * d, *X = first + (int64_t)under * d;
+    float *dX = A.grad_path + ((b0 + (active ? group : 0)) * A.L + under) * d;
 
     float *gtile = sig_stream_gradient_smem + wave * Tl::FLOATS, *xtile = gtile + WSLOTS * Tl::STRIDE;
     const float *myg = gtile + (active ? wslot : 0) * Tl::STRIDE, *myx = xtile + (active ? wslot : 0) * (R + 1) * XS;
@@ -212,7 +215,7 @@ __global__ __launch_bounds__(threads_of(MODE)) __attribute__((amdgpu_waves_per_e
 #pragma unroll
     for (int a = 0; a < d; ++a) {
         m[a] = 0.0f;
-        x0[a] = X[a];
+        x0[a] = first[a];
     }
     // a row's share of the sums (SUM) and the gradient of its point (SETTLE)
     float above = 0.0f;      // sum_a v_{j+1}[a] A_{j+1}[a b]
@@ -610,11 +613,12 @@ hipError_t launch(const Args &A0, const Cut &c, hipStream_t st)
     return hipGetLastError();
 }
 
-// UNCUT (W == 0) or CUT with W workgroups a path and at most `most_chunks` stretches side by side; false where a launch would hold 2^32 threads or an offset 2^31 floats.
+// UNCUT (W == 0) or CUT with W workgroups a path and at most `most_chunks` stretches side by side; false where a launch would hold 2^32
+// threads, a path 2^30 points, or a workgroup's rows 2^31 floats.
 bool cut(int d, bool given, int64_t B, int64_t L, int64_t W, int most_chunks, Cut *c)
 {
     const int64_t K = L - 1, D = row_floats(d, given), slots = slots_of(W > 0 ? CUT : UNCUT, d);
-    if (L > INT32_MAX / D) return false;
+    if (L > INT32_MAX / 2) return false;
     c->chunks = c->segs = 1;
     c->tile = tile_rows(d, given);
     c->lds = (size_t)lds_floats(d, given, W > 0 ? CUT : UNCUT) * sizeof(float);
@@ -645,7 +649,7 @@ bool cut(int d, bool given, int64_t B, int64_t L, int64_t W, int most_chunks, Cu
     c->segs = (int)W;
     c->groups = W > 1 || C * T < K ? 1 : (int)(slots / C);
     c->grid = W > 1 ? B * W : (B + c->groups - 1) / c->groups;
-    return C * T <= INT32_MAX && c->grid * threads_of(CUT) < (int64_t)1 << 32;
+    return c->groups * (W > 1 ? rows + c->tile : K) <= INT32_MAX / D && c->grid * threads_of(CUT) < (int64_t)1 << 32;
 }
 
 // Microseconds of a launch, fitted to 16,500 calls (2 to 20 channels, 4 to 2,000 points, 1 to 60,000 paths) with all their cuts, 99,000
@@ -795,6 +799,15 @@ int64_t stream_gradient_scratch_floats(int d, int64_t B, int64_t L, int cus)
     return c.segs > 1 ? B * c.segs * stream_gradient::sums_of(d) : 0;
 }
 
+int stream_gradient_segments(int d, int depth, int64_t B, int64_t L, int cus)
+{
+    using namespace stream_gradient;
+    Cut c;
+    if (B <= 0 || L < 2 || d < 2) return 0;
+    if (depth == 2) return d <= kMostChannels && choose(d, false, B, L, cus, true, &c) ? c.segs : 0;
+    return depth == 3 && stream_gradient3_scratch_floats(d, B, L, cus) >= 0 && choose3(d, B, L, cus, &c) ? c.segs : 0;
+}
+
 int64_t stream_gradient3_scratch_floats(int d, int64_t B, int64_t L, int cus)
 {
     using namespace stream_gradient;
@@ -831,7 +844,8 @@ hipError_t launch_stream_gradient(const float *path, const float *grad_out, floa
 {
     using namespace stream_gradient;
     Cut c;
-    if (B <= 0 || L < 2 || !choose(d, false, B, L, cus, scratch != nullptr, &c)) return hipErrorInvalidValue;
+    if (B <= 0 || L < 2 || d < 2 || d > kMostChannels) return hipErrorInvalidValue;
+    if (!choose(d, false, B, L, cus, scratch != nullptr, &c)) return hipErrorNotSupported;
     Args A{};
     A.path = path;
     A.grad_out = grad_out;

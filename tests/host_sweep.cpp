@@ -125,11 +125,16 @@ int main()
         const int64_t B = it & 2 ? (int64_t)1 << (rnd() % 33) : 1 + (int64_t)(rnd() % ((uint64_t)1 << (1 + rnd() % 20)));
         const bool scratch = (it & 4) != 0;
         int64_t floats = 0, grid = 0, segs = 0, groups = 0, chunks = 0, steps = 0, rows = 0;
+        const int answer = sig_backward_segments(nullptr, B, L, d, 2, 1);
         if (!sig::stream_gradient_geometry(d, B, L, 256, scratch, &floats, &grid, &segs, &groups, &chunks, &steps, &rows)) {
-            EXPECT(L * D * 2 > INT32_MAX || B > (int64_t)1 << 24, "no launch: d=%d B=%lld L=%lld", d, (long long)B, (long long)L);
+            // (a path to each workgroup at least, or whole paths side by side, and offsets of 32 bits)
+            EXPECT(L > INT32_MAX / 2 || K > INT32_MAX / D / (scratch && B <= 8 ? 32 : 1) - 16 || B >= (int64_t)1 << 26 || (B >= (int64_t)1 << 24 && L > INT32_MAX / D / (64 / d)), "no launch: d=%d B=%lld L=%lld", d, (long long)B, (long long)L);
             continue;
         }
-        EXPECT(grid >= 1 && grid * 256 < (int64_t)1 << 35 && groups * L * D <= (int64_t)INT32_MAX + L * D, "offsets: d=%d B=%lld L=%lld", d, (long long)B, (long long)L);
+        EXPECT(!scratch || answer == segs || answer < 0, "sig_backward_segments = %d for %lld: d=%d B=%lld L=%lld", answer, (long long)segs, d, (long long)B, (long long)L);
+        const bool uncut = segs == 1 && chunks == 1 && groups == 64 / d;
+        EXPECT(grid >= 1 && grid * (uncut ? 64 : 256) < (int64_t)1 << 32, "threads: d=%d B=%lld L=%lld", d, (long long)B, (long long)L);
+        EXPECT(groups * (segs > 1 ? rows : K) <= INT32_MAX / D, "offsets: d=%d B=%lld L=%lld", d, (long long)B, (long long)L);
         EXPECT(floats == (segs > 1 ? B * segs * D : 0) && (scratch || segs == 1) && segs <= 32, "scratch: d=%d B=%lld L=%lld", d, (long long)B, (long long)L);
         if (segs > 1) EXPECT(grid == B * segs && groups == 1 && rows % (chunks * steps) == 0 && segs * rows >= K && (segs - 1) * rows < K, "d=%d B=%lld L=%lld: %lld x %lld rows", d, (long long)B, (long long)L, (long long)segs, (long long)rows);
         else EXPECT(grid * groups >= B && (grid - 1) * groups < B && (groups == 1 || chunks * steps >= K), "d=%d B=%lld L=%lld: %lld paths", d, (long long)B, (long long)L, (long long)groups);
@@ -139,6 +144,14 @@ int main()
         }
         EXPECT(groups * chunks <= 4 * (64 / d), "slots: d=%d B=%lld L=%lld", d, (long long)B, (long long)L);
         ++checked;
+    }
+
+    // ---- ... and of calls whose whole paths take one workgroup more than the chip holds, or too few of them
+    const int64_t bands[][3] = {{8, 2631, 255}, {10, 1970, 318}, {7, 2970, 311}, {7, 3072, 380}, {9, 2498, 243}, {6, 3588, 338}};
+    for (const auto &b : bands) {
+        int64_t floats = 0, grid = 0, segs = 0, groups = 0, chunks = 0, steps = 0, rows = 0;
+        EXPECT(sig::stream_gradient_geometry((int)b[0], b[1], b[2], 256, true, &floats, &grid, &segs, &groups, &chunks, &steps, &rows) && chunks > 1,
+               "d=%lld B=%lld L=%lld stays uncut", (long long)b[0], (long long)b[1], (long long)b[2]);
     }
 
     // ---- arbitrary plans through the checks: they may be refused, they must not misbehave

@@ -322,7 +322,10 @@ def test_backward_segment_rule():
     # paths too long for the LDS of one workgroup: cut across workgroups in final mode at any batch size ...
     assert seg(300, 3500, 5, 4) >= 2 and seg(1, 20000, 5, 4) >= 2
     # ... and walked in tiles by one workgroup where that is not possible (stream mode; final mode beyond 32 segments)
-    assert seg(300, 1500, 10, 4, 1) == 1 and seg(2, 60000, 10, 2) == 1 and seg(2, 60000, 10, 2, 1) == 1
+    assert seg(300, 1500, 10, 4, 1) == 1 and seg(2, 60000, 10, 2) == 1 and seg(2, 45001, 9, 3, 1) == 1
+    # stream mode at depth 2, and at depth 3 of eleven and twelve channels: workgroups of a path in sums over the rows behind a step
+    assert 2 <= seg(2, 60000, 10, 2, 1) <= 32 and seg(2000, 100, 10, 2, 1) == 1 and seg(4, 50, 20, 2, 1) >= 1 and seg(46, 71, 12, 3, 1) == 4
+    assert seg(4, 50, 13, 3, 1) == 0 and seg(4, 50, 21, 2, 1) == 0 and seg(4, 50, 300, 2, 1) == -binding.SIG_ERR_UNSUPPORTED
     assert seg(100000, 5000, 5, 4) == 1
     # no register kernel: the general sweep; beyond its limits and bad arguments: minus the status
     assert seg(4, 50, 11, 2) == 0 and seg(4, 50, 300, 2) == -binding.SIG_ERR_UNSUPPORTED

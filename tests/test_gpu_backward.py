@@ -182,9 +182,10 @@ def test_backward_sliced_reproducible_and_after_a_larger_call(gpu, oracle):
 
 
 # shapes without a compiled register kernel: the general sweep (state of a path in LDS, or in device scratch for the
-# last three; the final mode of (11,2), (11,3), (12,3) and (20,2) is swept on brackets), one channel, depth 1, more channels than coefficients per level allow to vectorise, deep and narrow
+# last three; the final mode of (11,2), (11,3), (12,3) and (20,2) is swept on brackets, their stream mode by sums over the rows behind
+# a step), one channel, depth 1, more channels than coefficients per level allow to vectorise, deep and narrow
 GENERAL_SHAPES = [(11, 2), (11, 3), (7, 6), (1, 5), (12, 1), (12, 3), (3, 8), (2, 10), (20, 2), (64, 2), (3, 7), (6, 6),
-                  (12, 4)]
+                  (12, 4), (13, 3), (21, 2)]
 
 
 @pytest.mark.parametrize("shape", GENERAL_SHAPES, ids=lambda c: "-".join(str(v) for v in c))
@@ -206,8 +207,8 @@ def test_backward_paths_too_long_for_one_workgroup(gpu, oracle):
         check(gpu, oracle, x, 4, stream, seed=L, label="long path")
 
 
-@pytest.mark.parametrize("case", [(10, 4, 300, 1500, True), (8, 4, 600, 2100, True), (10, 2, 2, 60000, True),
-                                  (10, 2, 2, 60000, False), (10, 3, 3, 40001, True), (5, 2, 600, 3500, True)], ids=lambda c: "-".join(str(v) for v in c))
+@pytest.mark.parametrize("case", [(10, 4, 300, 1500, True), (8, 4, 600, 2100, True), (9, 3, 2, 45001, True),
+                                  (10, 2, 2, 60000, False), (10, 3, 3, 40001, True), (5, 3, 600, 3500, True)], ids=lambda c: "-".join(str(v) for v in c))
 def test_backward_walks_long_paths_in_tiles(gpu, oracle, case):
     """Paths too long for LDS where the sweep is not cut across workgroups — stream mode of the sliced shapes at a
     batch that fills the chip (checked on its first paths), and paths too long even for 32 segments: one workgroup
@@ -239,7 +240,7 @@ STREAM_SEGMENTED_CASES = [
     # segment with a scan over the segments between them; lengths with ragged last segments, one and several paths,
     # paths too long for the LDS of the uncut sweep at a batch that fills the chip
     (5, 4, 1, 600), (5, 4, 3, 777), (2, 3, 2, 30001), (4, 4, 2, 1000), (3, 5, 1, 700), (5, 5, 1, 300), (6, 4, 2, 400),
-    (8, 3, 1, 900), (7, 3, 2, 2500), (2, 6, 1, 1200), (10, 2, 70, 1700), (9, 3, 2, 350), (5, 4, 3, 3300),
+    (8, 3, 1, 900), (7, 3, 2, 2500), (2, 6, 1, 1200), (10, 3, 24, 1700), (9, 3, 2, 350), (5, 4, 3, 3300),
     # the sliced shapes (lanes of a path in several workgroups: the prefix words' partial adjoints are added across slices)
     (10, 4, 1, 600), (8, 4, 2, 777), (9, 4, 1, 400), (6, 5, 1, 300), (4, 6, 2, 500), (7, 5, 1, 200), (10, 4, 3, 1500),
     (10, 5, 1, 150),
@@ -413,7 +414,7 @@ def test_backward_saturated_variants_sampled(gpu, oracle, name, B):
     (5, 4, 700, 5400, False),     # final mode, here and below: on brackets
     (4, 4, 1200, 8300, False),
     (4, 3, 500, 33000, False),
-    (10, 2, 500, 1700, True),     # ten lanes per path, stream mode: cut in time inside the workgroup
+    (7, 3, 500, 3000, True),      # seven lanes per path, stream mode: cut in time inside the workgroup
     (5, 4, 700, 700, True),       # stream mode, 25 lanes per path: walked in tiles
     # the same kind of shape with paths short enough for the plain sweep to keep enough lanes on a CU: not cut
     (2, 6, 128, 8200, True),      # two lanes per path, stream mode (pipelined fetch would not apply: the chip is full)
@@ -423,7 +424,7 @@ def test_backward_saturated_variants_sampled(gpu, oracle, name, B):
     # few-lane kernels whose LDS holds fewer paths than a workgroup has lanes for, on batches that need the plain sweep's
     # resident workgroups several times over: walked in short tiles
     (5, 3, 100, 66000, False),
-    (10, 2, 100, 17000, True),
+    (7, 3, 100, 17000, True),
     (5, 3, 256, 16500, True),
     (6, 3, 100, 33000, False),
 ])

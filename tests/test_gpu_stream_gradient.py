@@ -131,3 +131,39 @@ def test_depth_three_without_enough_scratch_takes_the_general_sweep(gpu, oracle)
     finally:
         torch.cuda.synchronize()
         gpu.sig_destroy(fresh)
+
+
+def test_rows_of_more_floats_than_32_bits_count(gpu):
+    """One path whose rows take 2^31 floats and more: workgroups count from their own first row.  Upstream gradients in a few rows
+    only, at the borders of stretches and workgroups among them, so that float64 gives the gradient of every point: products of twenty
+    terms, a few roundings each."""
+    import torch
+    d, L = 20, 5_200_000
+    K, D = L - 1, d + d * d
+    assert K * D > 2 ** 31 and gpu.sig_backward_segments(None, 1, L, d, 2, 1) > 1
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((1, L, d), device="cuda", generator=gen)
+    g = torch.zeros((1, K, D), device="cuda")
+    W = gpu.sig_backward_segments(None, 1, L, d, 2, 1)
+    rows = sorted({0, 1, K // 3, K - 1} | {K // W * w + o for w in (1, 2, W - 1) for o in range(-40, 41, 8)})
+    g[0, rows] = torch.randn((len(rows), D), device="cuda", generator=gen)
+    gx = torch.full_like(x, float("nan"))
+    assert gpu.sig_backward(gpu.default_ctx(), x, 2, 1, g, g, gx) == gpu.SIG_OK      # (the rows of S are not read)
+    X, G = x[0].double(), g[0, rows].double()
+    del g
+    M = G[:, d:].reshape(-1, d, d)
+    sums = torch.cat([(M - M.transpose(1, 2)).flip(0).cumsum(0).flip(0), torch.zeros_like(M[:1])])   # A of the rows up to each of `rows`
+    v = X[1:] - X[:-1]
+    half = torch.empty_like(v)                         # half of sum_a v[a] A[a b]
+    at = [0] + [r + 1 for r in rows] + [K]
+    for i in range(len(at) - 1):
+        half[at[i]:at[i + 1]] = 0.5 * v[at[i]:at[i + 1]] @ sums[i]
+    want = torch.zeros_like(X)
+    want[1:] -= half
+    want[:-1] -= half
+    S = X[[r + 1 for r in rows]] - X[0]
+    want[[r + 1 for r in rows]] += G[:, :d] + (S.unsqueeze(2) * M).sum(1)
+    want[0] -= (G[:, :d] + (M * S.unsqueeze(1)).sum(2)).sum(0)
+    err = float((gx[0].double() - want).norm() / want.norm())
+    say("  %d rows of %d floats: rel err %.2e" % (K, D, err))
+    assert bool(torch.isfinite(gx).all()) and err <= 1e-6
