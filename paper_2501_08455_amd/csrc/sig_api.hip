@@ -793,8 +793,11 @@ bool takes_split_rows(const sig_plan_t &pl, int stream_flag) { return stream_fla
 bool held_by_registers(const sig_plan_t &pl) { return pl.variant == SIG_VARIANT_ON_CHIP && pl.row_workgroups == 0; }   // without split_rows
 bool check_split_rows(int64_t B, int64_t L, const RowShape &rs, const sig_plan_t &pl, int64_t *lds, int64_t *wgs, int64_t *scratch_floats)
 {
-    if (!split_rows_geometry(rs.d, rs.depth, B > 0 ? B : 1, L, pl.split_rows, kDefaultCUs, held_by_registers(pl), lds, wgs, scratch_floats)) return false;
-    if (B == 0) *wgs = *scratch_floats = 0;
+    SplitRowsCut cut;
+    if (!split_rows_geometry(rs.d, rs.depth, B > 0 ? B : 1, L, pl.split_rows, kDefaultCUs, held_by_registers(pl), &cut)) return false;
+    *lds = cut.lds_bytes;
+    *wgs = B > 0 ? cut.workgroups : 0;
+    *scratch_floats = B > 0 ? cut.scratch_floats : 0;
     return true;
 }
 

@@ -450,15 +450,15 @@ int depth2_rows_wanted(int d, int64_t B, int64_t L, int cus, int chunks)
     return W;
 }
 
-bool depth2_rows_geometry(int d, int64_t B, int64_t L, int segs, int cus, bool registers, int64_t *lds_bytes, int64_t *workgroups)
+bool depth2_rows_geometry(int d, int64_t B, int64_t L, int segs, int cus, bool registers, SplitRowsCut *cut)
 {
     using namespace depth2_rows;
     Cut c;
     double us = 0.0;
     if (d < kLeastChannels || d > kMostChannels || B < 1 || L < 2 || segs < 1 || segs > kMostSegments || segs > L - 1) return false;
     if (!choose(d, B, L, segs, cus, registers, &c, &us)) return false;
-    *lds_bytes = (int64_t)kShapes[d - kLeastChannels].lds(c.mode);
-    *workgroups = c.grid;
+    *cut = SplitRowsCut{(int64_t)kShapes[d - kLeastChannels].lds(c.mode), c.grid, 0, threads_of(c.mode), c.segs,
+                        (int64_t)c.chunks * c.steps, 1, slots_of(c.mode, d), c.chunks, c.groups};
     return true;
 }
 

@@ -272,8 +272,15 @@ inline double rounds_of(int64_t grid, int cus, int held, double beside)
 // ---------------------------------------------------------------- stream mode, rows split across workgroups (sig_split_rows.h)
 // stretches a path is cut into, 0 if the call stays with the other kernels
 int split_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held_chunks, bool held_rows);
-// the launch with `segs` stretches a path; false if there is none
-bool split_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, bool registers, int64_t *lds_bytes, int64_t *workgroups, int64_t *scratch_floats);
+// The launch with `segs` stretches a path; false if there is none.  registers: the plan without it takes a register kernel (depth 2).
+struct SplitRowsCut {
+    int64_t lds_bytes, workgroups, scratch_floats;
+    int threads;                  // of a workgroup
+    int64_t segs, rows;           // stretches of a path in different workgroups, and their rows
+    int64_t slices, lanes;        // workgroups of a stretch, and their words (depth 2: 1, and the slots of a workgroup)
+    int64_t chunks, groups;       // depth 2: stretches side by side in a workgroup, of so many paths (1)
+};
+bool split_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, bool registers, SplitRowsCut *cut);
 // scratch: those floats, or null (what lies before a stretch is folded again).  sticky: a point that is not a number spoils level 1 of the
 // rows behind it, not of its own row only.
 hipError_t launch_split_rows(const float *path, float *out, float *scratch, int64_t B, int64_t L, int d, int depth, int segs, bool sticky,
@@ -283,7 +290,7 @@ hipError_t launch_split_rows(const float *path, float *out, float *scratch, int6
 // chunks: of the register kernel that the call would take, 0 if it would take another.  Workgroups a path, 0 if it stays with those.
 // registers: that it would take one (its plan without split_rows), which decides between the cuts.
 int depth2_rows_wanted(int d, int64_t B, int64_t L, int cus, int chunks);
-bool depth2_rows_geometry(int d, int64_t B, int64_t L, int segs, int cus, bool registers, int64_t *lds_bytes, int64_t *workgroups);
+bool depth2_rows_geometry(int d, int64_t B, int64_t L, int segs, int cus, bool registers, SplitRowsCut *cut);
 hipError_t launch_depth2_rows(const float *path, float *out, int64_t B, int64_t L, int d, int segs, bool sticky, bool registers, int cus, hipStream_t st);
 
 // table of compiled on-chip kernels; terminated by an entry with launch == nullptr

@@ -136,21 +136,16 @@ int split_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held_
     return best;
 }
 
-bool split_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, bool registers, int64_t *lds_bytes, int64_t *workgroups,
-                         int64_t *scratch_floats)
+bool split_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, bool registers, SplitRowsCut *cut)
 {
-    if (depth == 2) {
-        *scratch_floats = 0;
-        return depth2_rows_geometry(d, B, L, segs, cus, registers, lds_bytes, workgroups);
-    }
+    if (depth == 2) return depth2_rows_geometry(d, B, L, segs, cus, registers, cut);
     const split::Shape *s = split::find(d, depth);
     split::Cut c;
     double us = 0.0;
     if (!s || B < 1 || L < 2 || segs < 1 || segs > split::kMostSegments || segs > L - 1) return false;
     if (!split::best_cut(*s, B, L, segs, cus, &c, &us)) return false;
-    *lds_bytes = (int64_t)c.lds;
-    *workgroups = B * c.args.segs * c.args.slices;
-    *scratch_floats = B * (c.args.segs - 1) * s->D;
+    const split::Args &A = c.args;
+    *cut = SplitRowsCut{(int64_t)c.lds, B * A.segs * A.slices, B * (A.segs - 1) * s->D, c.threads, A.segs, A.rows, A.slices, A.lanes, 1, 1};
     return true;
 }
 

@@ -15,6 +15,14 @@ bool bracket_depth2_geometry(int d, int64_t B, int64_t L, int cus, int64_t *grid
 bool stream_gradient_geometry(int d, int64_t B, int64_t L, int cus, bool scratch, int64_t *scratch_floats, int64_t *grid, int64_t *segs,
                               int64_t *groups, int64_t *chunks, int64_t *steps, int64_t *rows);
 int64_t stream_gradient3_scratch_floats(int d, int64_t B, int64_t L, int cus);
+struct SplitRowsCut {
+    int64_t lds_bytes, workgroups, scratch_floats;
+    int threads;
+    int64_t segs, rows;
+    int64_t slices, lanes;
+    int64_t chunks, groups;
+};
+bool split_rows_geometry(int d, int depth, int64_t B, int64_t L, int segs, int cus, bool registers, SplitRowsCut *cut);
 }
 
 static uint64_t state = 0x9E3779B97F4A7C15ull;
@@ -152,6 +160,36 @@ int main()
         int64_t floats = 0, grid = 0, segs = 0, groups = 0, chunks = 0, steps = 0, rows = 0;
         EXPECT(sig::stream_gradient_geometry((int)b[0], b[1], b[2], 256, true, &floats, &grid, &segs, &groups, &chunks, &steps, &rows) && chunks > 1,
                "d=%lld B=%lld L=%lld stays uncut", (long long)b[0], (long long)b[1], (long long)b[2]);
+    }
+
+    // ---- rows split across workgroups, and depth-2 rows: every word of every row of every path has its lane, in one workgroup only
+    const int split_shapes[][2] = {{10, 3}, {8, 4}, {9, 4}, {10, 4}, {5, 5}, {6, 5}, {4, 6}};
+    for (int it = 0; it < 40000; ++it) {
+        const bool two = it % 3 != 0;
+        const int *shape = split_shapes[rnd() % 7];
+        const int d = two ? 2 + (int)(rnd() % 19) : shape[0], depth = two ? 2 : shape[1];
+        const int64_t L = it & 1 ? pick(Ls, sizeof Ls / sizeof *Ls) : 2 + (int64_t)(rnd() % 3000), K = L - 1;
+        const int64_t B = it & 2 ? (int64_t)1 << (rnd() % 33) : 1 + (int64_t)(rnd() % ((uint64_t)1 << (1 + rnd() % 20)));
+        const int segs = 1 + (int)(rnd() % 32), cus = it & 4 ? 256 : 64 << (rnd() % 3);
+        int64_t words = 1, row = 0, power = 1;
+        for (int n = 1; n < depth; ++n) words *= d;
+        for (int n = 1; n <= depth; ++n) row += power *= d;
+        sig::SplitRowsCut c{};
+        if (!sig::split_rows_geometry(d, depth, B, L, segs, cus, (it & 8) != 0, &c)) {
+            EXPECT(L < 2 || segs > K || L > INT32_MAX / (two ? 32 * row : 2) || B >= ((int64_t)1 << (two ? 24 : 21)) / segs, "no cut: d=%d depth=%d B=%lld L=%lld segs=%d", d, depth, (long long)B, (long long)L, segs);
+            continue;
+        }
+        EXPECT(c.lds_bytes <= 64 * 1024 && c.workgroups >= 1 && c.workgroups * c.threads < (int64_t)1 << 32, "d=%d depth=%d B=%lld L=%lld segs=%d: %lld x %d threads", d, depth, (long long)B, (long long)L, segs, (long long)c.workgroups, c.threads);
+        EXPECT(c.segs >= 1 && c.segs <= segs && c.segs * c.rows >= K && (c.segs - 1) * c.rows < K, "rows: d=%d depth=%d B=%lld L=%lld segs=%d: %lld x %lld", d, depth, (long long)B, (long long)L, segs, (long long)c.segs, (long long)c.rows);
+        if (two) {
+            EXPECT(c.groups * c.chunks <= c.lanes && c.lanes <= c.threads / 64 * (64 / d) && c.scratch_floats == 0, "slots: d=%d B=%lld L=%lld segs=%d", d, (long long)B, (long long)L, segs);
+            EXPECT(c.segs > 1 ? c.groups == 1 && c.workgroups == B * c.segs : c.workgroups * c.groups >= B && (c.workgroups - 1) * c.groups < B, "paths: d=%d B=%lld L=%lld segs=%d", d, (long long)B, (long long)L, segs);
+            EXPECT(c.groups * L <= INT32_MAX / row, "offsets: d=%d B=%lld L=%lld segs=%d", d, (long long)B, (long long)L, segs);
+        } else {
+            EXPECT(c.workgroups == B * c.segs * c.slices && c.scratch_floats == B * (c.segs - 1) * row && c.rows % 8 == 0, "d=%d depth=%d B=%lld L=%lld segs=%d", d, depth, (long long)B, (long long)L, segs);
+            EXPECT(c.slices * c.lanes >= words && (c.slices - 1) * c.lanes < words && c.lanes <= c.threads && c.lanes > c.threads - 64, "words: d=%d depth=%d B=%lld L=%lld segs=%d: %lld x %lld", d, depth, (long long)B, (long long)L, segs, (long long)c.slices, (long long)c.lanes);
+        }
+        ++checked;
     }
 
     // ---- arbitrary plans through the checks: they may be refused, they must not misbehave

@@ -226,8 +226,12 @@ def test_plan_fields_out_of_range_are_refused():
 
 def test_stream_rows_are_planned_only_where_they_lead():
     """Which stream-mode calls write their rows from registers: calls on which that measured slower than the kernels they took
-    before (0.75-0.97x), each beside a neighbour on which it leads."""
-    rows = lambda B, L, d, depth: binding.sig_plan(None, B, L, d, depth, 1)[1].row_workgroups
+    before (0.75-0.97x), each beside a neighbour on which it leads.  (Depth 2 and (8,4): of the mapping below split_rows, which all
+    of these calls at depth 2 and the long ones of (8,4) run.)"""
+    def rows(B, L, d, depth):
+        rc, plan = binding.sig_plan(None, B, L, d, depth, 1)
+        assert rc == binding.SIG_OK and (plan.split_rows > 0) == (depth == 2 or (d, depth) == (8, 4)), (B, L, d, depth)
+        return plan.row_workgroups
     # launches per level that hold a few paths in one tile (511 increments): depth 2, and long rows
     for call in [(10, 230, 16, 2), (40, 200, 16, 2), (2, 490, 20, 2), (2, 405, 17, 2), (12, 400, 19, 2), (1, 488, 12, 3), (1, 720, 12, 3), (2, 950, 12, 3),
                  (4, 470, 8, 4), (2, 1415, 8, 4), (1, 1356, 7, 4)]:

@@ -5,7 +5,7 @@ import pytest
 
 from paper_2501_08455_amd import workloads
 from test_gpu_parity import assert_parity, check, gpu, run_gpu  # noqa: F401
-from test_gpu_stream_rows import _errors, assert_level1_is_added_up, infinite_points  # noqa: F401
+from test_gpu_stream_rows import _errors, assert_level1_is_added_up, copy_plan, infinite_points  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -59,13 +59,12 @@ def test_depth2_rows_are_not_taken_where_they_do_not_apply(gpu):  # noqa: F811
 @pytest.mark.parametrize("d,B,L,paths", [(2, 30003, 200, 40), (4, 2, 1500, 2), (5, 300, 170, 16), (8, 1000, 150, 10), (10, 3, 1200, 3), (12, 600, 300, 8),
                                          (13, 8000, 40, 20), (20, 5, 2000, 1)])
 def test_rounding_is_no_larger_than_the_other_kernels(gpu, oracle, d, B, L, paths):  # noqa: F811
-    """Both errors are means over hundreds of rows of many coefficients: the ratio for equally accurate kernels is 1 +- 0.1."""
+    """The kernels that the rest of the plan names: register kernels, and for (10,2), (12,2), (13,2) and (20,2) rows from registers.
+    Both errors are means over hundreds of rows of many coefficients: the ratio for equally accurate kernels is 1 +- 0.1."""
     rc, plan = gpu.sig_plan(gpu.default_ctx(), B, L, d, 2, 1)
-    assert rc == gpu.SIG_OK and plan.split_rows >= 1
+    assert rc == gpu.SIG_OK and plan.split_rows >= 1 and (plan.row_workgroups >= 1) == (d >= 10)
     x = workloads.brownian_paths(B, L, d, seed=9870 + d + L)
-    mine = _errors(gpu, oracle, x, 2, plan, paths)[0]
-    plan.split_rows = 0
-    other = _errors(gpu, oracle, x, 2, plan, paths)[0]
+    mine, other = _errors(gpu, oracle, x, 2, [plan, copy_plan(plan, split_rows=0)], paths)
     assert mine <= 1.1 * other, (mine, other)
 
 

@@ -5,7 +5,7 @@ import pytest
 
 from paper_2501_08455_amd import workloads
 from test_gpu_parity import assert_parity, check, gpu, run_gpu  # noqa: F401
-from test_gpu_stream_rows import _errors, assert_level1_is_added_up, infinite_points  # noqa: F401
+from test_gpu_stream_rows import _errors, assert_level1_is_added_up, copy_plan, infinite_points  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -49,11 +49,7 @@ def test_rounding_is_no_larger_than_the_other_kernels(gpu, oracle, d, depth, B, 
     rc, plan = gpu.sig_plan(gpu.default_ctx(), B, L, d, depth, 1)
     assert rc == gpu.SIG_OK and plan.split_rows >= 1
     x = workloads.brownian_paths(B, L, d, seed=9700 + d + L)
-    held = plan.split_rows
-    split = _errors(gpu, oracle, x, depth, plan, paths)[0]
-    plan.split_rows = 0
-    other = _errors(gpu, oracle, x, depth, plan, paths)[0]
-    plan.split_rows = held
+    split, other = _errors(gpu, oracle, x, depth, [plan, copy_plan(plan, split_rows=0)], paths)
     assert split <= 1.1 * other, (split, other)
 
 

@@ -27,18 +27,38 @@ def test_rows_from_registers(gpu, oracle, d, depth, B, L, segs):  # noqa: F811
     check(gpu, oracle, x, depth, True, plan, label="rows")
 
 
+def copy_plan(plan, **fields):
+    other = type(plan).from_buffer_copy(plan)
+    for name, value in fields.items():
+        setattr(other, name, value)
+    return other
+
+
+def rows_plan(plan):
+    """The plan's rows from registers, as they run where no split_rows come before them."""
+    assert plan.row_workgroups >= 1
+    return copy_plan(plan, split_rows=0)
+
+
+def other_plan(plan):
+    """... and its register or level kernels."""
+    return copy_plan(plan, split_rows=0, row_workgroups=0)
+
+
 @pytest.mark.parametrize("d,depth,B,L", [(4, 4, 64, 256), (5, 4, 16, 100), (3, 4, 300, 57), (16, 2, 1500, 40), (13, 2, 1027, 23),
                                          (12, 3, 40, 90), (10, 3, 4, 700), (2, 6, 1025, 30), (20, 2, 5, 5000)])
 def test_planned_rows_agree_with_the_other_kernels(gpu, oracle, d, depth, B, L):  # noqa: F811
     """The planner's own cut, whole paths side by side in a workgroup included, against the plan's other kernels: no row
-    further apart than two foldings of the same increments can be (assert_parity's bounds, on every row)."""
+    further apart than two foldings of the same increments can be (assert_parity's bounds, on every row).  (At depth 2 the plan
+    comes with rows that need no scan, which are taken off it.)"""
     rc, plan = gpu.sig_plan(gpu.default_ctx(), B, L, d, depth, 1)
     assert rc == gpu.SIG_OK and plan.row_workgroups >= 1, plan.as_dict()
     x = workloads.brownian_paths(B, L, d, seed=9300 + d + L)
-    got = run_gpu(gpu, x, depth, True)
-    assert np.array_equal(got, run_gpu(gpu, x, depth, True, plan))
-    plan.row_workgroups = 0
-    assert_parity(got, run_gpu(gpu, x, depth, True, plan).astype(np.float64), x, depth, True)
+    if plan.split_rows == 0:
+        assert np.array_equal(run_gpu(gpu, x, depth, True), run_gpu(gpu, x, depth, True, plan))
+    rows, other = rows_plan(plan), other_plan(plan)
+    got = run_gpu(gpu, x, depth, True, rows)
+    assert_parity(got, run_gpu(gpu, x, depth, True, other).astype(np.float64), x, depth, True)
 
 
 def test_a_point_that_is_not_a_number_spoils_the_same_coefficients(gpu):  # noqa: F811
@@ -90,14 +110,15 @@ def test_rows_are_not_taken_where_they_do_not_apply(gpu):  # noqa: F811
     assert gpu.sig_plan(None, 64, 256, 4, 4, 0)[1].row_workgroups == 0
 
 
-def _errors(gpu, oracle, x, depth, plan, paths):
-    """Relative error of the planned rows and of the plan's other kernels against the fp64 oracle, over the first `paths` paths."""
+def _errors(gpu, oracle, x, depth, plans, paths):
+    """Relative error of each plan against the fp64 oracle, over the first `paths` paths.  The plans name different kernels."""
     import torch
+    named = {(p.split_rows > 0, p.split_rows == 0 and p.row_workgroups > 0) for p in plans}
+    assert len(named) == len(plans), [p.as_dict() for p in plans]
     want = oracle.signature(x[:paths].astype(np.float64), depth, stream=True)
     xt = torch.from_numpy(x).cuda()
     errs = []
-    for segs in (plan.row_workgroups, 0):
-        plan.row_workgroups = segs
+    for plan in plans:
         out = torch.empty((x.shape[0], x.shape[1] - 1, want.shape[-1]), device="cuda")
         assert gpu.sig_compute(gpu.default_ctx(), xt, depth, True, out, plan=plan) == gpu.SIG_OK
         got = out[:paths].cpu().numpy().astype(np.float64)
@@ -117,7 +138,7 @@ def test_rounding_is_no_larger_than_the_other_kernels(gpu, oracle, d, depth, B, 
     x = workloads.brownian_paths(B, L, d, seed=9400 + d + L)
     if L < 30:   # uniform increments: level 1 is not small against the others
         x = workloads.uniform_paths(B, L, d, seed=9401 + d)
-    rows, other = _errors(gpu, oracle, x, depth, plan, paths)
+    rows, other = _errors(gpu, oracle, x, depth, [rows_plan(plan), other_plan(plan)], paths)
     assert rows <= 1.1 * other, (rows, other)
 
 

@@ -217,8 +217,10 @@ def test_pointers_that_are_only_float_aligned(gpu, oracle):
 
 
 # calls that keep something in context scratch: forward segments joined by a second launch, the level-scan family, the
-# gradient cut into time segments, the general gradient
-SCRATCH = [(128, 2000, 5, 4, 0, False), (48, 200, 12, 3, 1, False), (3, 300, 7, 5, 0, True), (40, 60, 12, 3, 1, True)]
+# gradient cut into time segments, the general gradient, the stretches of rows split across workgroups, the sums of a long path's
+# every-prefix gradient at depth 2, the rows that depth 3 of twelve channels leaves for it
+SCRATCH = [(128, 2000, 5, 4, 0, False), (48, 200, 12, 3, 1, False), (3, 300, 7, 5, 0, True), (40, 60, 13, 3, 1, True),
+           (2, 700, 9, 4, 1, False), (1, 1500, 6, 2, 1, True), (40, 60, 12, 3, 1, True)]
 
 
 def scratch_call(gpu, ctx, i, seed):
@@ -232,6 +234,7 @@ def scratch_call(gpu, ctx, i, seed):
     if not backward:
         rc, plan = gpu.sig_plan(ctx, B, L, d, depth, stream_flag)
         plan.row_workgroups = 0   # (rows written straight from registers keep nothing in scratch)
+        assert (plan.split_rows > 1) == ((d, depth) == (9, 4))
         rc, _, _, scratch = gpu.sig_plan_footprint(B, L, d, depth, stream_flag, plan)
         assert rc == gpu.SIG_OK and scratch > 0
 
@@ -245,6 +248,7 @@ def scratch_call(gpu, ctx, i, seed):
             return out
         return forward
     out, g = torch.empty(rows, device="cuda"), torch.randn(rows, device="cuda", generator=gen)
+    assert (gpu.sig_backward_segments(ctx, B, L, d, depth, stream_flag) > 1) == (d != 13)
     assert gpu.sig_compute(ctx, x, depth, stream_flag, out) == gpu.SIG_OK
     torch.cuda.synchronize()
 
