@@ -118,8 +118,9 @@ enum sig_variant {
  *                 fields only `variant` and row_workgroups are read: they say whether a point that is not a number spoils level 1
  *                 of the rows behind it, as in the mapping without split_rows, and at depth 2 which cuts lead.  Compiled for (10,3), 8-10 channels at
  *                 depth 4, 5 and 6 at depth 5, 4 at depth 6; and for 2-20 channels at depth 2, where n is the workgroups of a path (1:
- *                 or several paths in one) and nothing below applies.  Context scratch for the stretches' signatures, (n - 1) D floats a path;
- *                 where it cannot be had (or exceeds 8 GiB) a stretch folds what lies before it again.  Final mode ignores
+ *                 or several paths in one) and nothing below applies.  Context scratch for the stretches' signatures, (n - 1) D floats a path
+ *                 (so that such calls on several streams are ordered, as above); where it cannot be had or exceeds 8 GiB, and in a
+ *                 captured call whose other fields name a mapping without scratch, a stretch folds what lies before it again.  Final mode ignores
  *                 it; a negative value is invalid in both
  */
 typedef struct sig_plan_t {

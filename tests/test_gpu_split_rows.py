@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2501_08455_amd import workloads
+from test_gpu_backward import launches
 from test_gpu_parity import assert_parity, check, gpu, run_gpu  # noqa: F401
 from test_gpu_stream_rows import _errors, assert_level1_is_added_up, copy_plan, infinite_points  # noqa: F401
 
@@ -105,3 +106,33 @@ def test_without_scratch_what_lies_before_is_folded_again(gpu):  # noqa: F811
     out.fill_(float("nan"))
     assert gpu.sig_compute_noalloc(gpu.default_ctx(), xt, 4, 1, out) == gpu.SIG_OK   # 1.7 MB of the fixed scratch
     assert np.array_equal(out.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("d,depth,B,L,most", [(4, 6, 20, 300, 1), (6, 5, 20, 300, 1), (9, 4, 2, 700, 2)])
+def test_captured_calls_keep_off_scratch_that_their_plan_would_not_use(gpu, d, depth, B, L, most):  # noqa: F811
+    """A graph of a call whose kernels without split rows take no scratch may run beside other calls: it holds one launch, on a context that
+    has the scratch too.  (9,4), which goes launch by launch without split rows, holds two."""
+    import torch
+    ctx = gpu.sig_create()
+    x = workloads.brownian_paths(B, L, d, seed=91)
+    xt = torch.from_numpy(x).cuda()
+    rc, plan = gpu.sig_plan(ctx, B, L, d, depth, 1)
+    assert rc == gpu.SIG_OK and plan.split_rows > 1 and (plan.variant == gpu.SIG_VARIANT_LEVEL_SCAN and plan.row_workgroups == 0) == (most == 2)
+    out = torch.empty((B, L - 1, gpu.sig_size(d, depth)), device="cuda")
+    call = lambda: gpu.sig_compute(ctx, xt, depth, True, out)   # noqa: E731
+    try:
+        assert call() == gpu.SIG_OK            # the scratch grows here
+        torch.cuda.synchronize()
+        want = out.cpu().numpy()
+        assert launches(gpu, call) == most
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            assert call() == gpu.SIG_OK
+        for _ in range(3):
+            out.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert_parity(out.cpu().numpy(), want.astype(np.float64), x, depth, True)
+    finally:
+        torch.cuda.synchronize()
+        gpu.sig_destroy(ctx)
