@@ -253,8 +253,9 @@ int sig_combine(sig_ctx *ctx, const float *a, const float *b, int64_t B, int d, 
  * points or so (fewer than d at depth 2, up to 78 at (4,6); the batch moves this) and every other shape are swept on the
  * signature itself, as below.
  * Stream mode at depth 2, two to twenty channels: one launch over sums of the rows behind each step (two for a few long paths,
- * with context scratch of a row of d (d + 1) floats for each of up to 32 workgroups a path; where scratch cannot be had a path
- * stays in one workgroup); `out` is not read.  Depth 3, eleven and twelve channels: first a sweep over the rows' third level that
+ * with context scratch of a row of d (d + 1) floats for each of up to 32 workgroups a path; where scratch cannot be had, and in
+ * captured calls of up to ten channels but for at most 32 paths of more than 512 points, a path stays in one
+ * workgroup); `out` is not read.  Depth 3, eleven and twelve channels: first a sweep over the rows' third level that
  * leaves rows of d (d + 2) floats in context scratch, then the same over those (without that scratch, or where it would exceed
  * 8 GiB, the general sweep).  Paths of 2^30 points, and rows of 2^31 floats where scratch cannot be had, take the general sweep.
  * The other sweeps start from the signature at the end and undo one increment at a time.  Shapes with a compiled register

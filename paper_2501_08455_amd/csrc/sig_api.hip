@@ -1414,11 +1414,13 @@ int sig_backward(sig_ctx *ctx, const float *path, int64_t B, int64_t L, int d, i
         return eb == hipSuccess ? SIG_OK : SIG_ERR_HIP;
     }
     if (stream_flag && depth == 2) {
-        // sums over the rows behind a step; where scratch cannot be had a path stays in one workgroup
+        // Sums over the rows behind a step; where scratch cannot be had a path stays in one workgroup.  In a captured call too, but for few
+        // long paths and many channels, which any sweep cuts with scratch: its graph may run beside other calls of the context.
         const int64_t floats = stream_gradient_scratch_floats(d, B, L, ctx->num_cu);
         if (floats >= 0) {
             const size_t bytes = (size_t)floats * sizeof(float);
-            if (floats > 0 && Scratch::within_reach(ctx, bytes, st)) {
+            const bool shared = d > 10 || (L > 512 && B <= 32);
+            if (floats > 0 && Scratch::within_reach(ctx, bytes, st) && (shared || !Scratch::captured(st))) {
                 rc = scratch.get(ctx, bytes, st, &work);
                 if (rc == SIG_ERR_ALLOC) work = nullptr;
                 else if (rc != SIG_OK) return rc;

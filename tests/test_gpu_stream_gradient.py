@@ -103,6 +103,36 @@ def test_a_capture_that_cannot_grow_scratch_keeps_a_path_in_one_workgroup(gpu, o
         gpu.sig_destroy(fresh)
 
 
+@pytest.mark.parametrize("d,B,L,most", [(6, 3, 400, 1), (10, 60, 700, 1), (6, 3, 900, 2), (15, 3, 200, 2)])
+def test_captured_calls_share_scratch_only_for_few_long_paths(gpu, oracle, d, B, L, most):
+    """A graph may run beside other calls of the context: it holds one launch also where the scratch is there, but for calls that any sweep
+    cuts with scratch."""
+    import torch
+    x = workloads.brownian_paths(B, L, d, seed=9905 + d)
+    xt = torch.from_numpy(x).cuda()
+    out = gpu.signature(xt, 2, stream=True)
+    g = torch.from_numpy(np.random.default_rng(6).normal(size=tuple(out.shape)).astype(np.float32)).cuda()
+    ctx, gx = gpu.sig_create(), torch.empty_like(xt)
+    call = lambda: gpu.sig_backward(ctx, xt, 2, 1, out, g, gx)   # noqa: E731
+    try:
+        assert gpu.sig_backward_segments(ctx, B, L, d, 2, 1) > 1 and call() == gpu.SIG_OK      # the scratch grows here
+        assert launches(gpu, call) == most
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            assert call() == gpu.SIG_OK
+        pick = sorted({0, B - 1})
+        want = oracle.signature_backward(x[pick], 2, g[pick].cpu().numpy(), stream=True)
+        for _ in range(3):
+            gx.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.linalg.norm(gx[pick].cpu().numpy() - want) <= 1e-5 * np.linalg.norm(want)
+    finally:
+        torch.cuda.synchronize()
+        gpu.sig_destroy(ctx)
+
+
 def test_depth_three_without_enough_scratch_takes_the_general_sweep(gpu, oracle):
     """A capture on a context whose scratch holds what the general sweep needs, but not the reduced rows."""
     import torch
