@@ -122,11 +122,11 @@ int split_rows_wanted(int d, int depth, int64_t B, int64_t L, int cus, int held_
     if (!s || B < 1 || L < 2) return 0;
     const int64_t K = L - 1;
     if (d == 10 && depth == 3 && (!registers || 2 * B < 5 * (int64_t)cus)) return 0;
-    if (d == 8 && (registers ? B > 60000 / K : K < 160)) return 0;
+    if (d == 8 && (registers ? B > 60000 * (int64_t)cus / 256 / K : K < 160)) return 0;
     int best = 0;
     double least = 0.0;
     for (int W = 1; W <= split::kMostSegments; W *= 2) {
-        if (W > 1 && (K / W < split::kTile || B > 1500 / W || B * (W - 1) * s->D > split::kMostPieces)) break;
+        if (W > 1 && (K / W < split::kTile || B > 1500 * (int64_t)cus / 256 / W || B * (W - 1) * s->D > split::kMostPieces)) break;
         split::Cut c;
         double us = 0.0;
         if (!split::best_cut(*s, B, L, W, cus, &c, &us) || (best && us >= least)) continue;

@@ -582,12 +582,14 @@ struct Cut {
     int mode;               // UNCUT or CUT
     int chunks, segs, groups, steps, rows;
     int tile;               // rows of a slot that a wavefront stages at a time
+    int threads;
     size_t lds;             // bytes of a workgroup
     int64_t grid;
 };
 
-template <int d, bool GIVEN>
-hipError_t launch(const Args &A0, const Cut &c, hipStream_t st)
+// The launches of a cut: whole paths, or (several workgroups a path) their sums first
+using Kernel = void (*)(Args);
+hipError_t launch_cut(Kernel uncut, Kernel totals, Kernel cut, const Args &A0, const Cut &c, hipStream_t st)
 {
     Args A = A0;
     A.chunks = c.chunks;
@@ -595,39 +597,36 @@ hipError_t launch(const Args &A0, const Cut &c, hipStream_t st)
     A.groups = c.groups;
     A.steps = c.steps;
     A.rows = c.rows;
-    const dim3 grid((unsigned)c.grid);
-    if (c.mode == UNCUT) {
-        constexpr size_t lds = (size_t)lds_floats(d, GIVEN, UNCUT) * sizeof(float);
-        static_assert(lds <= (size_t)kMaxLdsBytes, "a wavefront's tile fits its workgroup's LDS");
-        hipLaunchKernelGGL((sig_stream_depth2_kernel<d, UNCUT, GIVEN>), grid, dim3(threads_of(UNCUT)), lds, st, A);
-        return hipGetLastError();
-    }
-    constexpr size_t lds = (size_t)lds_floats(d, GIVEN, CUT) * sizeof(float);
-    static_assert(lds <= (size_t)kMaxLdsBytes, "the tiles and sums of a workgroup's slots fit its LDS");
+    const dim3 grid((unsigned)c.grid), threads((unsigned)c.threads);
     if (c.segs > 1) {
-        hipLaunchKernelGGL((sig_stream_depth2_kernel<d, TOTALS, GIVEN>), grid, dim3(threads_of(TOTALS)), lds, st, A);
+        hipLaunchKernelGGL(totals, grid, threads, c.lds, st, A);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((sig_stream_depth2_kernel<d, CUT, GIVEN>), grid, dim3(threads_of(CUT)), lds, st, A);
+    hipLaunchKernelGGL(c.mode == UNCUT ? uncut : cut, grid, threads, c.lds, st, A);
     return hipGetLastError();
 }
 
-// UNCUT (W == 0) or CUT with W workgroups a path and at most `most_chunks` stretches side by side; false where a launch would hold 2^32
-// threads, a path 2^30 points, or a workgroup's rows 2^31 floats.
-bool cut(int d, bool given, int64_t B, int64_t L, int64_t W, int most_chunks, Cut *c)
+template <int d, bool GIVEN>
+hipError_t launch(const Args &A, const Cut &c, hipStream_t st)
 {
-    const int64_t K = L - 1, D = row_floats(d, given), slots = slots_of(W > 0 ? CUT : UNCUT, d);
-    if (L > INT32_MAX / 2) return false;
+    static_assert(lds_floats(d, GIVEN, UNCUT) * sizeof(float) <= (size_t)kMaxLdsBytes, "a wavefront's tile fits its workgroup's LDS");
+    static_assert(lds_floats(d, GIVEN, CUT) * sizeof(float) <= (size_t)kMaxLdsBytes, "the tiles and sums of a workgroup's slots fit its LDS");
+    return launch_cut(&sig_stream_depth2_kernel<d, UNCUT, GIVEN>, &sig_stream_depth2_kernel<d, TOTALS, GIVEN>, &sig_stream_depth2_kernel<d, CUT, GIVEN>, A, c, st);
+}
+
+// Whole paths of K rows of D floats side by side in the slots of a workgroup (W == 0), or W workgroups a path and at most `most_chunks` stretches
+// side by side in each.  False where the launch would hold 2^32 threads.
+bool cut_rows(int64_t B, int64_t K, int64_t D, int64_t slots, int threads, int64_t W, int64_t most_chunks, Cut *c)
+{
+    c->threads = threads;
     c->chunks = c->segs = 1;
-    c->tile = tile_rows(d, given);
-    c->lds = (size_t)lds_floats(d, given, W > 0 ? CUT : UNCUT) * sizeof(float);
     c->steps = c->rows = (int)K;
+    c->groups = (int)slots;
     if (W == 0) {
         c->mode = UNCUT;
-        c->groups = (int)slots;
         c->grid = (B + slots - 1) / slots;
-        return slots * L <= INT32_MAX / D && c->grid * threads_of(UNCUT) < (int64_t)1 << 32;
+        return c->grid * threads < (int64_t)1 << 32;
     }
     c->mode = CUT;
     int64_t rows = (K + W - 1) / W;                       // of a workgroup
@@ -649,7 +648,18 @@ bool cut(int d, bool given, int64_t B, int64_t L, int64_t W, int most_chunks, Cu
     c->segs = (int)W;
     c->groups = W > 1 || C * T < K ? 1 : (int)(slots / C);
     c->grid = W > 1 ? B * W : (B + c->groups - 1) / c->groups;
-    return c->groups * (W > 1 ? rows + c->tile : K) <= INT32_MAX / D && c->grid * threads_of(CUT) < (int64_t)1 << 32;
+    return c->grid * threads < (int64_t)1 << 32;
+}
+
+// UNCUT (W == 0) or CUT; false also where a path has 2^30 points, or a workgroup's rows 2^31 floats
+bool cut(int d, bool given, int64_t B, int64_t L, int64_t W, int most_chunks, Cut *c)
+{
+    const int64_t K = L - 1, D = row_floats(d, given);
+    const int mode = W == 0 ? UNCUT : CUT;
+    if (L > INT32_MAX / 2 || !cut_rows(B, K, D, slots_of(mode, d), threads_of(mode), W, most_chunks, c)) return false;
+    c->tile = tile_rows(d, given);
+    c->lds = (size_t)lds_floats(d, given, mode) * sizeof(float);
+    return c->groups * (c->segs > 1 ? (int64_t)c->rows + c->tile : mode == UNCUT ? L : K) <= INT32_MAX / D;
 }
 
 // Microseconds of a launch, fitted to 16,500 calls (2 to 20 channels, 4 to 2,000 points, 1 to 60,000 paths) with all their cuts, 99,000
@@ -704,65 +714,23 @@ bool choose(int d, bool given, int64_t B, int64_t L, int cus, bool scratch, Cut 
     return found;
 }
 
-// The same for depth 3: UNCUT (W == 0), or CUT with W workgroups a path
+// The same for depth 3
 template <int d>
-hipError_t launch3(const Args &A0, const Cut &c, hipStream_t st)
+hipError_t launch3(const Args &A, const Cut &c, hipStream_t st)
 {
-    using Tl = Tile3<d>;
-    Args A = A0;
-    A.chunks = c.chunks;
-    A.segs = c.segs;
-    A.groups = c.groups;
-    A.steps = c.steps;
-    A.rows = c.rows;
-    const dim3 grid((unsigned)c.grid);
-    constexpr size_t lds = (size_t)Tl::lds_floats(CUT) * sizeof(float), uncut = (size_t)Tl::lds_floats(UNCUT) * sizeof(float);
-    static_assert(lds <= (size_t)kMaxLdsBytes, "the tiles, parked sums and sums of a workgroup's slots fit its LDS");
-    if (c.mode == UNCUT) {
-        hipLaunchKernelGGL((sig_stream_depth3_kernel<d, UNCUT>), grid, dim3(Tl::NT), uncut, st, A);
-        return hipGetLastError();
-    }
-    if (c.segs > 1) {
-        hipLaunchKernelGGL((sig_stream_depth3_kernel<d, TOTALS>), grid, dim3(Tl::NT), lds, st, A);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL((sig_stream_depth3_kernel<d, CUT>), grid, dim3(Tl::NT), lds, st, A);
-    return hipGetLastError();
+    static_assert(Tile3<d>::lds_floats(CUT) * sizeof(float) <= (size_t)kMaxLdsBytes, "the tiles, parked sums and sums of a workgroup's slots fit its LDS");
+    return launch_cut(&sig_stream_depth3_kernel<d, UNCUT>, &sig_stream_depth3_kernel<d, TOTALS>, &sig_stream_depth3_kernel<d, CUT>, A, c, st);
 }
 
 int threads3(int d) { return d == 11 ? Tile3<11>::NT : Tile3<12>::NT; }
 
 bool cut3(int d, int64_t B, int64_t L, int64_t W, Cut *c)
 {
-    const int64_t K = L - 1, D = d + d * d + (int64_t)d * d * d, threads = threads3(d), slots = threads / (d * d);
-    if (slots * L > INT32_MAX / D) return false;          // (offsets in the rows of a workgroup's paths)
-    c->mode = W == 0 ? UNCUT : CUT;
-    c->chunks = c->segs = 1;
-    c->steps = c->rows = (int)K;
-    c->groups = (int)slots;
-    if (W == 0) {
-        c->grid = (B + slots - 1) / slots;
-        return c->grid * threads < (int64_t)1 << 32;
-    }
-    int64_t rows = (K + W - 1) / W;
-    const int64_t C = rows < slots ? rows : slots;
-    int64_t T = (rows + C - 1) / C;
-    int64_t most = kBlockBytes / (C * D * (int64_t)sizeof(float));
-    if (most < 8) most = 8;
-    const int64_t blocks = (T + most - 1) / most;
-    T = (T + blocks - 1) / blocks;
-    if (W > 1) {
-        rows = (rows + C * T - 1) / (C * T) * (C * T);
-        W = (K + rows - 1) / rows;
-    }
-    c->chunks = (int)C;
-    c->steps = (int)T;
-    c->rows = (int)rows;
-    c->segs = (int)W;
-    c->groups = W > 1 || C * T < K ? 1 : (int)(slots / C);
-    c->grid = W > 1 ? B * W : (B + c->groups - 1) / c->groups;
-    return c->grid * threads < (int64_t)1 << 32;
+    const int64_t D = d + d * d + (int64_t)d * d * d, slots = threads3(d) / (d * d);
+    const int mode = W == 0 ? UNCUT : CUT;
+    c->lds = (size_t)(d == 11 ? Tile3<11>::lds_floats(mode) : Tile3<12>::lds_floats(mode)) * sizeof(float);
+    return L <= INT32_MAX / D / slots &&                  // (offsets in the rows of a workgroup's paths)
+           cut_rows(B, L - 1, D, slots, threads3(d), W, slots, c);
 }
 
 // Workgroups of a path: as many as give every unit one, four rows a workgroup at least ((12,3), 46 paths of 71 points: one 107 us, four 60,
