@@ -116,7 +116,7 @@ struct Geo {
 // Wavefronts per SIMD the kernels are built for: what a lane's words and some fifty more registers allow.  Without the bound
 // the compiler spends registers on the sums over the rows, before the words exist, and halves the residency.
 // The words of (5,4) to (7,4) fit four wavefronts, which takes a spare register off (5,4) (134 otherwise; 65,536 paths of 100
-// points 186 -> 177 us); at depth 5 and 6 it would spill ((4,5) 113 -> 126 us).
+// points 186 -> 177 us on one card); at depth 5 and 6 it would spill ((4,5) 113 -> 126 us).
 constexpr int min_waves(int depth, int state) { return state > 100 ? 2 : state > 57 ? 3 : depth == 4 && state > 24 ? 4 : 1; }
 
 // Summands that `threads` threads split one of cnt sums per path into
@@ -552,12 +552,13 @@ extern __shared__ __align__(16) float sig_bracket_smem[];
 // Several whole paths per wavefront (one wavefront per workgroup, so no barrier costs anything), each walked uncut.
 // Per step and wavefront some 50 vector instructions for the walk, 20 for the outputs and 8 for the loads, after some 700 per
 // path for the bracket values.  Bound by waiting, mostly for LDS: (5,4), 100 points, 65,536 paths issue 81,000 vector
-// instructions per SIMD in 414,000 cycles (5.1 cycles each, against 2.2 where the pipe is full), the LDS is busy 70 % of
-// the time (28 % of that bank conflicts), and 531 MB move where 507 must (205 us under the counters).  Registers decide
+// instructions per SIMD in 372,000 cycles (4.6 cycles each, against 2.2 where the pipe is full), the LDS is busy 78 % of
+// the time (28 % of that bank conflicts), and 537 MB move where 507 must (184 to 211 us under the counters).  Registers decide
 // the residency (128 there: four wavefronts per SIMD; two to seven over the shapes); keeping the paths' bracket values in
 // registers as they are formed, instead of all paths' in LDS, and having the next path's rows in flight took a quarter
-// off (246 -> 188 us on one card).  The counters are from three wavefronts; places of the tile in 32 bits, loaded without a
-// condition, and the fourth wavefront: 195 -> 175 us (82 of them the bracket values), (2,6) with 700 points 365 -> 280.
+// off (246 -> 188 us on one card).  Places of the tile in 32 bits, loaded without a condition, and the fourth wavefront took 6 to 8 % more:
+// 190 to 199 us and 179 to 186 in turn on each of two cards (82 of them the bracket values; calls behind an idle card take 200 to 215 on
+// both sides, so that single calls show less); (2,6) with 700 points 365 -> 280.
 template <class G>
 constexpr int packed_lds_floats()
 {

@@ -10,10 +10,12 @@
 // twice costs next to nothing beside its rows.  Few paths also span W workgroups, each of which sums all that lies before its own
 // rows; no workgroup waits for another.
 //
-// Bound by the stores where the batch fills the chip (3.6 MB a us whole, 3.0 cut: the streams of a cut path lie further apart),
-// else by one wave's steps.  Tiles: 6,400 floats a wavefront whole (longer runs; six wavefronts a unit hold the rows
-// of the others' stores), 1,600 cut (sixteen wavefronts, whose scans overlap; twelve with more points in LDS, see cut()).  Before and now, us: (20,2) 1,177 paths of 1,386 points
-// 1,315 and 708, (2,2) 20,000 of 500 180 and 117, (12,2) 1,024 of 100 26.8 and 20.8.
+// Bound by the stores where the batch fills the chip: the rows are written once (1.00 to 1.05 times their bytes by the counters) at 4.1 to 4.5 MB a
+// us of all that moves, the wavefronts wait for memory half of their time and more, the LDS is busy a third (a third of that conflicts).  Else by
+// one wave's steps.  Tiles: 6,400 floats a wavefront whole (longer runs; five or six wavefronts a unit hold the rows
+// of the others' stores), 1,600 cut (sixteen wavefronts, whose scans overlap; twelve with more points in LDS, see cut()).  Before (one launch
+// per level, or register kernels) and now, us, one MI355X, both in turn: (20,2) 1,177 paths of 1,386 points 1,315 and 708, (2,2) 20,000
+// of 500 180 and 117, (12,2) 1,024 of 100 26.8 and 20.8.
 //
 // Rounding: the steps of a tile are summed from zero and what their addition to the sum rounds off goes into the next tile's; level 1
 // is the distance between two points.  Error against 64 bits 0.2 to 1.0 times that of the kernels that took these calls (14,300 calls;

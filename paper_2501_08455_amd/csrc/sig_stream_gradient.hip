@@ -14,8 +14,10 @@
 // memory, 4 bytes a lane and d apart, the address unit took 40 cycles a load).  Whole paths side by side in wavefronts, walked
 // from their last row (UNCUT), or stretches of a path side by side in a workgroup (CUT): each slot sums its own rows, a scan in
 // LDS adds what lies behind it, and it walks its rows once more.  Few paths also span W workgroups, whose sums a first launch
-// (TOTALS) leaves in scratch.  Bound by the rows' bytes where uncut wavefronts fill the chip, by a row's 0.2 to 0.7 us of LDS
-// and dependent multiply-adds elsewhere.  Measured, the sweep on signatures against this: 128 paths of 150 points of 16 channels
+// (TOTALS) leaves in scratch.  Bound by the rows' bytes where the batch fills the chip (uncut they are read once, at 3.0 to 3.7 TB/s of all
+// that moves; cut twice, from memory where the blocks that run together exceed the caches: (9,2) 2,040 paths of 1,777 points read 3.1 GB, 1.3
+// of them rows, at 6.3 TB/s), by a row's 0.2 to 0.7 us of LDS and dependent multiply-adds elsewhere.  Measured, the sweep on
+// signatures against this, one MI355X, both in turn: 128 paths of 150 points of 16 channels
 // (the general sweep) 577 -> 19.5 us, one of 100 of 12 358 -> 9; 20,591 of 79 of 9 248 -> 168 (126 at the rate of a copy), 2,040
 // of 1,777 of 9 5,440 -> 493, 55,774 of 446 of 2 786 -> 386, one of 1,445 of 10 55 -> 16; over 4,013 calls 2.9 times as fast in
 // the mean.  Rounding against 64 bits: 3e-8 to 1.7e-6 of the gradient's norm, 0.1 to 1.0 times the sweep's (its A is undone
@@ -633,7 +635,7 @@ bool cut_rows(int64_t B, int64_t K, int64_t D, int64_t slots, int threads, int64
     int64_t C = rows < slots ? rows : slots;
     if (C > most_chunks) C = most_chunks;
     int64_t T = (rows + C - 1) / C;
-    // a block's rows are read twice, the second time from the caches
+    // a block's rows are read twice, the second time from the caches while few workgroups run together
     int64_t most = kBlockBytes / (C * D * (int64_t)sizeof(float));
     if (most < 8) most = 8;
     const int64_t blocks = (T + most - 1) / most;
