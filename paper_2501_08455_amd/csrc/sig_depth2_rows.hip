@@ -384,17 +384,22 @@ bool leads(int d, int64_t K, const Cut &c)
 }
 
 // The fastest launch with `segs` workgroups a path (1: or less than one).  registers: of those that lead on the register kernels, where any do.
-bool choose(int d, int64_t B, int64_t L, int segs, int cus, bool registers, Cut *best, double *least)
+// of_all: is lowered to the least time of all of them.
+bool choose(int d, int64_t B, int64_t L, int segs, int cus, bool registers, Cut *best, double *least, double *of_all = nullptr)
 {
     const int64_t K = L - 1;
     const bool leading = registers && d <= 10 && K >= kLeastSteps;
-    bool found = false;
+    bool found = false, behind = true;      // behind: none that leads so far
     auto take = [&](int W, int most_chunks) {
         Cut c;
-        if (!cut(d, B, L, W, most_chunks, cus, &c) || (leading && !leads(d, K, c))) return;
+        if (!cut(d, B, L, W, most_chunks, cus, &c)) return;
+        const bool leads_here = !leading || leads(d, K, c);
+        if (!leads_here && !behind && !of_all) return;
         const double us = microseconds(d, B, L, cus, c);
-        if (found && us >= *least) return;
+        if (of_all && us < *of_all) *of_all = us;
+        if (leads_here ? !behind && us >= *least : !behind || (found && us >= *least)) return;
         found = true;
+        behind = !leads_here;
         *best = c;
         *least = us;
     };
@@ -408,7 +413,7 @@ bool choose(int d, int64_t B, int64_t L, int segs, int cus, bool registers, Cut 
                 if (C < slots) take(1, C);
         }
     }
-    return found || (leading && choose(d, B, L, segs, cus, false, best, least));
+    return found;
 }
 
 }  // namespace depth2_rows
@@ -433,14 +438,13 @@ int depth2_rows_wanted(int d, int64_t B, int64_t L, int cus, int chunks)
     const bool narrow = registers && (d <= 4 || d == 7);
     Cut best;
     int W = 0;
-    double least = 0.0, least_of_all = 0.0;
+    double least = 0.0, least_of_all = HUGE_VAL;
     for (int segs = 1; segs <= kMostSegments; segs *= 2) {
         if (segs > 1 && (K < kShortSteps || K / segs < 2 || B > 600 * (int64_t)cus / 256 / segs)) break;
         Cut c;
         double us = 0.0;
-        if (narrow && choose(d, B, L, segs, cus, false, &c, &us) && (least_of_all == 0.0 || us < least_of_all)) least_of_all = us;
+        if (!choose(d, B, L, segs, cus, registers, &c, &us, narrow ? &least_of_all : nullptr) || (W && us >= least)) continue;
         if (narrow && segs > 1 && (d <= 3 || (d == 4 && K < (B > cus / 4 ? 1000 : 600)))) continue;
-        if (!choose(d, B, L, segs, cus, registers, &c, &us) || (W && us >= least)) continue;
         best = c;
         W = segs;
         least = us;
